@@ -128,9 +128,11 @@ def _network(case, g, side_streams=0):
     for layer in range(case["layers"]):
         w = torch.zeros(dims[layer + 1], in_dims[layer] + 1, device="cuda")
         body = torch.randn(dims[layer + 1], in_dims[layer], generator=g, device="cuda") / math.sqrt(in_dims[layer])
-        # the softmax layer starts small instead of at zero: the derivatives of the first minibatch, from which the
-        # factors are built, then have a spectrum of their own
-        w[:, :-1] = body * 0.1 if layer == case["layers"] - 1 else body
+        # Not zero in the softmax layer: its first derivatives, one-hot minus nearly uniform, would have many equal singular
+        # values, and the factors built from them would not be unique.  Behind wide tanh layers full size makes the first
+        # steps unstable.
+        small = layer == case["layers"] - 1 and case["nonlin"] == "tanh"
+        w[:, :-1] = body * 0.1 if small else body
         net.set_params(layer, w)
     return net
 
@@ -303,13 +305,11 @@ def work(case):
 def tolerance(case):
     """About four times the largest difference from the same passes in 64 bits (warm-up included), over the listed and drawn cases."""
     if case["kind"] == "simple":
-        return {"rel": 1e-5}      # 1.6e-6
+        return {"rel": 1e-5, "max": 2.2e-3}      # 1.6e-6, 5.4e-4
     if case["kind"] == "precondition":
-        return {"rel": 5e-5}      # 1.3e-5: 12 calls before the pass, each updating the factor the next one uses
+        return {"rel": 5e-5, "max": 7e-3}        # 1.2e-5, 1.7e-3: 12 calls before the pass, each updating the factor the next one uses
     if case.get("method") == "simple":
-        return {"rel": 1e-4}      # 8e-6 .. 2.3e-5
+        return {"rel": 4e-5, "max": 6e-4}        # 8e-6, 1.6e-4
     if case["nonlin"] == "tanh":
-        return {"rel": 4e-4}      # 1e-4
-    # 2.4e-3 (3e-3 over replicas), in the softmax layer of the speech-shaped network: its first derivatives (one-hot minus nearly uniform)
-    # have many equal singular values across the rank cut, so the initial factor is not unique
-    return {"rel": 1e-2}
+        return {"rel": 1e-3, "max": 0.18}        # 2.7e-4, 4.7e-2: one row of the softmax layer, a class seen once
+    return {"rel": 4e-3, "max": 9e-2}            # 9.8e-4, 2.2e-2
