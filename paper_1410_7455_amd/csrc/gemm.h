@@ -1,10 +1,9 @@
 // Grouped fp32 MFMA GEMM for gfx950 (CDNA4).
 //
-// One launch runs a list of independent problems C = alpha * op(A) * op(B) [+ beta * C]; every
-// workgroup owns one (problem, split, tile_m, tile_n) unit.  All matrix products of the NG-SGD step
-// go through this kernel: the layer GEMMs (forward A B^T, backward A B, update A^T B) and the
-// skinny products of the online preconditioner (H = X W^T, J = H^T X, Xhat = X - H W, K = J J^T,
-// L = H^T H, W_{t+1} = A_t B_t; App. B.3 of the paper).
+// One launch runs a list of independent problems C = alpha * op(A) * op(B); every workgroup owns one
+// (problem, split, tile_m, tile_n) unit.  The skinny products of the online preconditioner go through
+// this kernel (H = X W^T, J = H^T X, Xhat = X - H W, K = J J^T, L = H^T H, W_{t+1} = A_t B_t; App. B.3
+// of the paper), and the Gram matrix of the simple method; the layer GEMMs have their own (split_gemm.h).
 //
 // Tiling: 64-lane wavefronts, v_mfma_f32_16x16x4_f32.  A workgroup of WGM x WGN waves computes a
 // BM x BN tile; a wave owns (BM/WGM) x (BN/WGN) as TM x TN MFMA tiles.  Operand tiles are staged
@@ -24,7 +23,7 @@ constexpr int kPrefetch = 2;   // K-blocks in flight from memory per workgroup
 constexpr int kXcds = 8;   // accelerator dies (XCDs) of the MI355X, each with a private L2
 
 enum Epilogue : int {
-  EPI_STORE = 0,        // C = alpha*acc + beta*C
+  EPI_STORE = 0,        // C = alpha*acc
   EPI_ATOMIC_F32 = 1,   // C += alpha*acc            (split-K, float atomics)
   EPI_ATOMIC_F64 = 2,   // (double)C += alpha*acc    (split-K, double atomics)
   EPI_SUB_ROWNORM = 3,  // C = C - acc; aux[tile_n][row] = sum over the tile's columns of C^2
@@ -37,12 +36,12 @@ struct GemmProblem {
   int M, N, K;
   int lda, ldb, ldc;
   float alpha, beta;
-  const double* alpha_dev[3];  // optional device scalars multiplied into alpha
+  const double* alpha_dev[3];  // optional device scalars multiplied into alpha (split_gemm_kernel, as beta)
   int tiles_m, tiles_n, splits, k_per_split;
   int tile_begin;              // first workgroup index of this problem
   float* aux;                  // EPI_SUB_ROWNORM: [tiles_n][M] row-norm partials
   double* sumsq;               // SUMSQ_A: [splits*tiles_m] partial sums of squares of A
-  long long c_split_stride;    // EPI_STORE with splits > 1: split s writes its partial product to C + s*stride
+  long long c_split_stride;    // split_gemm_kernel with splits > 1: split s writes its partial product to C + s*stride
   const int* gate;             // optional: the problem is skipped unless (*gate & gate_mask) != 0
   int gate_mask;
 };
@@ -512,10 +511,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_kernel(const GemmGroup g) 
     }
   }
 
-  float alpha = P.alpha;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-    if (P.alpha_dev[i] != nullptr) alpha *= (float)(*P.alpha_dev[i]);
+  const float alpha = P.alpha;
 
   if (EPI == EPI_SUB_ROWNORM) {
     float* C = static_cast<float*>(P.C);
@@ -561,9 +557,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_kernel(const GemmGroup g) 
     return;
   }
 
-  if (EPI == EPI_STORE && !B_KC && (TN == 2 || TN == 4)) {
-    // a lane owns TN adjacent columns of each of its rows: one vector store where the row allows it
-    float* const C = static_cast<float*>(P.C) + (size_t)split * P.c_split_stride;
+  if (EPI == EPI_STORE && !B_KC && TN == 2) {
+    // a lane owns two adjacent columns of each of its rows: one vector store where the row allows it
+    float* const C = static_cast<float*>(P.C);
     const int col0 = n0 + local_col(0);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -576,26 +572,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_kernel(const GemmGroup g) 
         for (int j = 0; j < TN; ++j)
           v[j] = ACC64 ? (float)((double)alpha * (double)acc[i][j][r]) : alpha * (float)acc[i][j][r];
         float* c = C + (size_t)row * P.ldc + col0;
-        if (col0 + TN <= N && (reinterpret_cast<uintptr_t>(c) & (4 * TN - 1)) == 0) {
-          if (TN == 4) {
-            float4 o = make_float4(v[0], v[1], v[2], v[TN - 1]);
-            if (P.beta != 0.f) {
-              const float4 old = *reinterpret_cast<const float4*>(c);
-              o.x += P.beta * old.x; o.y += P.beta * old.y; o.z += P.beta * old.z; o.w += P.beta * old.w;
-            }
-            *reinterpret_cast<float4*>(c) = o;
-          } else {
-            float2 o = make_float2(v[0], v[1]);
-            if (P.beta != 0.f) {
-              const float2 old = *reinterpret_cast<const float2*>(c);
-              o.x += P.beta * old.x; o.y += P.beta * old.y;
-            }
-            *reinterpret_cast<float2*>(c) = o;
-          }
+        if (col0 + 2 <= N && (reinterpret_cast<uintptr_t>(c) & 7) == 0) {
+          *reinterpret_cast<float2*>(c) = make_float2(v[0], v[TN - 1]);
         } else {
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            if (col0 + j < N) c[j] = (P.beta != 0.f) ? v[j] + P.beta * c[j] : v[j];
+            if (col0 + j < N) c[j] = v[j];
         }
       }
     }
@@ -613,8 +595,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_kernel(const GemmGroup g) 
         if (row < M && col < N) {
           const float v = ACC64 ? (float)((double)alpha * (double)acc[i][j][r]) : alpha * (float)acc[i][j][r];
           if (EPI == EPI_STORE) {
-            float* c = static_cast<float*>(P.C) + (size_t)split * P.c_split_stride + (size_t)row * P.ldc + col;
-            *c = (P.beta != 0.f) ? v + P.beta * (*c) : v;
+            static_cast<float*>(P.C)[(size_t)row * P.ldc + col] = v;
           } else if (EPI == EPI_ATOMIC_F32) {
             unsafeAtomicAdd(static_cast<float*>(P.C) + (size_t)row * P.ldc + col, v);
           } else if (EPI == EPI_ATOMIC_F64) {

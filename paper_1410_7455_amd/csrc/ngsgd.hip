@@ -18,6 +18,7 @@
 #include "kernels.h"
 #include "simple_ng.h"
 #include "small_update.h"
+#include "split_gemm.h"
 #include "state.h"
 
 using namespace ngsgd;
@@ -279,40 +280,46 @@ inline int choose_splits(int tiles, int ksteps) {
 constexpr int BK = 16;
 
 enum LayerGemm { GEMM_FWD, GEMM_BWD, GEMM_UPD };
-constexpr int LBK = 32;             // K-block of the layer GEMMs
-constexpr int kBwdAccChunk = 4;     // K-blocks per MFMA chain in the backward GEMM (128 products per chain)
 constexpr int kMaxBwdSplits = 8;    // split-K slabs of the backward GEMM, summed by the nonlinearity's backward kernel
-
-// Tile shapes of the layer GEMMs.  The products of a minibatch step are small next to the chip (a few hundred
-// 64x64 tiles for 256 compute units), so what decides the time is how evenly the tiles fill it: every shape is
-// priced as (rounds of 512 workgroups) x (tile area), and the cheapest is taken (the first listed among equals).
-enum LayerTile { TILE_64x64, TILE_64x48, TILE_64x80, TILE_64x96, TILE_32x96, TILE_128x128, TILE_COUNT };
-constexpr int kTileBM[TILE_COUNT] = {64, 64, 64, 64, 32, 128};
-constexpr int kTileBN[TILE_COUNT] = {64, 48, 80, 96, 96, 128};
 constexpr int kComputeUnits = 256;
 
-// Wavefronts per workgroup of each tile shape (see launch_layer_tile) and what a workgroup of that shape gets done
-// per unit of tile area and time relative to a four-wavefront one when each fills a compute unit's round.
-constexpr int kTileWaves[TILE_COUNT] = {8, 4, 4, 12, 4, 4};
-inline LayerTile pick_layer_tile(const GemmDesc* d, int n) {
+// Tile shapes of the layer GEMMs.  The products of a minibatch step are small next to the chip (a few hundred 64 x 64
+// tiles for 256 compute units), so what decides the time is how evenly the tiles fill it: every shape is priced as
+// launch + rounds x (fill + K-blocks x time per K-block), and the cheapest is taken.
+enum LayerTile { TILE_32x64, TILE_64x64, TILE_64x96, TILE_64x128, TILE_128x128, TILE_64x64_SHALLOW, TILE_COUNT };
+constexpr int kTileBM[TILE_COUNT] = {32, 64, 64, 64, 128, 64};
+constexpr int kTileBN[TILE_COUNT] = {64, 64, 96, 128, 128, 64};
+constexpr int kTileBK[TILE_COUNT] = {64, 64, 64, 64, 32, 32};
+// Microseconds: what a round spends besides its K-blocks (first loads, stores), and what 64 k values add per tile of a
+// compute unit.  The latter by operand layout (forward: both K-contiguous; backward: A; update: neither), measured on
+// 512 x 3000 x 301, 1024 x 2048 x 2049, 600 x 1000 x 1000 (forward), 512 x 300 x 3000 in 8 slabs, 1024 x 2048 x 2048
+// (backward) and the grouped update products of both networks.  Three workgroups of the shallow 64 x 64 tile share a
+// compute unit: their time per block is per tile all the same, but they are filled together.
+constexpr double kTileLaunch = 1.5;
+constexpr double kTileFill[TILE_COUNT] = {1.7, 2.1, 2.5, 2.8, 3.5, 2.1};
+constexpr int kTileResident[TILE_COUNT] = {1, 1, 1, 1, 1, 3};
+constexpr double kTileBlock[3][TILE_COUNT] = {{0.58, 0.90, 1.05, 1.40, 2.15, 0.90},
+                                              {0.75, 1.10, 1.30, 1.55, 2.40, 1.06},
+                                              {1.00, 1.55, 1.90, 2.10, 2.90, 1.20}};
+LayerTile pick_layer_tile(LayerGemm layout, const GemmDesc* d, int n) {
   LayerTile best = TILE_64x64;
   double best_cost = 0.0;
   for (int t = 0; t < TILE_COUNT; ++t) {
     long long tiles = 0;
-    for (int i = 0; i < n; ++i)
-      tiles += (long long)((d[i].M + kTileBM[t] - 1) / kTileBM[t]) * ((d[i].N + kTileBN[t] - 1) / kTileBN[t]) *
-               std::max(1, d[i].splits);
-    // eight wavefronts per compute unit make a round (two workgroups of four, or one of eight or twelve): one
-    // four-wavefront workgroup alone leaves the matrix unit idle while it waits on LDS and memory
-    const int per_cu = std::max(1, 8 / kTileWaves[t]);
-    const double rounds = (double)((tiles + per_cu * kComputeUnits - 1) / (per_cu * kComputeUnits));
-    const double area = (double)kTileBM[t] * kTileBN[t] * per_cu;
-    // a large tile does more work per byte staged: it wins once the rounds are many; twelve wavefronts on one
-    // 64 x 96 tile get through a round faster than two four-wavefront workgroups on 64 x 48 tiles each (measured
-    // on the 512 x 3000 x 301 product: 14.5 against 15.8 us)
-    const double speed = t == TILE_128x128 ? 1.25 : (kTileWaves[t] == 12 ? 1.09 : 1.0);
-    const double cost = rounds * area / speed;
-    if (t == 0 || cost < best_cost) {
+    double depth = 0.0;   // k values per tile, averaged over the tiles
+    for (int i = 0; i < n; ++i) {
+      const int splits = std::max(1, d[i].splits);
+      const long long here = (long long)((d[i].M + kTileBM[t] - 1) / kTileBM[t]) *
+                             ((d[i].N + kTileBN[t] - 1) / kTileBN[t]) * splits;
+      tiles += here;
+      depth += (double)here * ((d[i].K + splits - 1) / splits);
+    }
+    if (tiles == 0) continue;
+    const double blocks = std::ceil(depth / (double)tiles / 64.0);
+    const double rounds = (double)((tiles + kComputeUnits - 1) / kComputeUnits);
+    const double fills = std::ceil(rounds / kTileResident[t]);
+    const double cost = kTileLaunch + fills * kTileFill[t] + rounds * blocks * kTileBlock[layout][t];
+    if (best_cost == 0.0 || cost < best_cost) {
       best_cost = cost;
       best = (LayerTile)t;
     }
@@ -320,29 +327,27 @@ inline LayerTile pick_layer_tile(const GemmDesc* d, int n) {
   return best;
 }
 
-template <bool A_KC, bool B_KC, int CHUNK>
+template <bool A_KC, bool B_KC>
 hipError_t launch_layer_tile(LayerTile t, const GemmDesc* d, int n, hipStream_t s) {
   switch (t) {
-    case TILE_64x48: return launch_gemm_group<64, 48, LBK, 4, 1, A_KC, B_KC, EPI_STORE, false, CHUNK>(d, n, s);
-    case TILE_64x80: return launch_gemm_group<64, 80, LBK, 4, 1, A_KC, B_KC, EPI_STORE, false, CHUNK>(d, n, s);
-    case TILE_64x96: return launch_gemm_group<64, 96, LBK, 4, 3, A_KC, B_KC, EPI_STORE, false, CHUNK>(d, n, s);
-    case TILE_32x96: return launch_gemm_group<32, 96, LBK, 2, 2, A_KC, B_KC, EPI_STORE, false, CHUNK>(d, n, s);
-    case TILE_128x128: return launch_gemm_group<128, 128, LBK, 2, 2, A_KC, B_KC, EPI_STORE, false, CHUNK>(d, n, s);
-    default: return launch_gemm_group<64, 64, LBK, 4, 2, A_KC, B_KC, EPI_STORE, false, CHUNK>(d, n, s);
+    case TILE_32x64: return launch_split_gemm<32, 64, 64, 2, 2, 2, 8, A_KC, B_KC>(d, n, s);
+    case TILE_64x96: return launch_split_gemm<64, 96, 64, 2, 2, 2, 8, A_KC, B_KC>(d, n, s);
+    case TILE_64x128: return launch_split_gemm<64, 128, 64, 2, 2, 2, 8, A_KC, B_KC>(d, n, s);
+    case TILE_128x128: return launch_split_gemm<128, 128, 32, 2, 2, 1, 4, A_KC, B_KC>(d, n, s);
+    case TILE_64x64_SHALLOW: return launch_split_gemm<64, 64, 32, 2, 2, 1, 4, A_KC, B_KC>(d, n, s);
+    default: return launch_split_gemm<64, 64, 64, 2, 2, 2, 8, A_KC, B_KC>(d, n, s);
   }
 }
 
-int launch_layer_gemms(LayerGemm kind, const GemmDesc* d, int n, hipStream_t s) {
-  ProfScope prof(kind == GEMM_FWD ? NGSGD_PROF_GEMM_FWD : (kind == GEMM_BWD ? NGSGD_PROF_GEMM_BWD : NGSGD_PROF_GEMM_UPD),
-                 s);
-  const LayerTile t = pick_layer_tile(d, n);
-  hipError_t e = hipSuccess;
-  switch (kind) {
-    case GEMM_FWD: e = launch_layer_tile<true, true, 0>(t, d, n, s); break;
-    case GEMM_BWD: e = launch_layer_tile<true, false, kBwdAccChunk>(t, d, n, s); break;   // long K: two-level sums
-    case GEMM_UPD: e = launch_layer_tile<false, false, 0>(t, d, n, s); break;
+// `slabs` (optional): how many split-K slabs of the first problem are written.
+int launch_layer_gemms(LayerGemm layout, const GemmDesc* d, int n, hipStream_t s, int* slabs = nullptr) {
+  const LayerTile t = pick_layer_tile(layout, d, n);
+  if (slabs != nullptr) *slabs = kTileBK[t] == 64 ? planned_splits<64, 64, 64>(d[0]) : planned_splits<64, 64, 32>(d[0]);
+  switch (layout) {
+    case GEMM_FWD: HIP_TRY((launch_layer_tile<true, true>(t, d, n, s))); break;
+    case GEMM_BWD: HIP_TRY((launch_layer_tile<true, false>(t, d, n, s))); break;
+    case GEMM_UPD: HIP_TRY((launch_layer_tile<false, false>(t, d, n, s))); break;
   }
-  HIP_TRY(e);
   return NGSGD_OK;
 }
 
@@ -1114,12 +1119,8 @@ int simple_many(const std::vector<SimpleCall>& calls, bool scale_output, hipStre
           rows.push_back(d);
         }
       }
-      if (!rows.empty())
-        HIP_TRY((launch_layer_tile<true, false, kBwdAccChunk>(pick_layer_tile(rows.data(), (int)rows.size()),
-                                                             rows.data(), (int)rows.size(), s)));
-      if (!cols.empty())
-        HIP_TRY((launch_layer_tile<true, true, 0>(pick_layer_tile(cols.data(), (int)cols.size()), cols.data(),
-                                                  (int)cols.size(), s)));
+      if (!rows.empty()) NG_TRY(launch_layer_gemms(GEMM_BWD, rows.data(), (int)rows.size(), s));
+      if (!cols.empty()) NG_TRY(launch_layer_gemms(GEMM_FWD, cols.data(), (int)cols.size(), s));
       hipLaunchKernelGGL(simple_rows_kernel, dim3(n_max, cnt), dim3(256), 0, s, g);
       LAUNCH_CHECK();
       hipLaunchKernelGGL(simple_gamma_kernel, dim3(cnt), dim3(256), 0, s, g);
@@ -1608,7 +1609,10 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
     g.B = L.W; g.ldb = L.ldw;
     g.C = L.A; g.ldc = L.lda;
     g.M = N; g.N = L.dout; g.K = L.in1;
-    NG_TRY(launch_layer_gemms(GEMM_FWD, &g, 1, s));
+    {
+      ProfScope prof(NGSGD_PROF_GEMM_FWD, s);
+      NG_TRY(launch_layer_gemms(GEMM_FWD, &g, 1, s));
+    }
     if (l < nl - 1) {
       ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);
       ngsgd_layer& Nx = Ls[l + 1];
@@ -1688,9 +1692,12 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
     const size_t slab = (size_t)net->max_batch * net->lddx;
     g.c_split_stride = (long long)slab;
     const int tiles = ((N + 63) / 64) * ((L.din + 63) / 64);
-    g.splits = std::min(kMaxBwdSplits, choose_splits(tiles, (L.dout + LBK - 1) / LBK));
-    const int n_slabs = planned_splits<64, 64, LBK>(g);   // depends on the K-block only, not on the tile shape
-    NG_TRY(launch_layer_gemms(GEMM_BWD, &g, 1, s));
+    g.splits = std::min(kMaxBwdSplits, choose_splits(tiles, (L.dout + 31) / 32));
+    int n_slabs = 1;
+    {
+      ProfScope prof(NGSGD_PROF_GEMM_BWD, s);
+      NG_TRY(launch_layer_gemms(GEMM_BWD, &g, 1, s, &n_slabs));
+    }
     ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);
     if (P.nonlin == NGSGD_TANH) {
       hipLaunchKernelGGL(tanh_backward_kernel, dim3((P.dout + 1023) / 1024, N), dim3(256), 0, s, net->dX, net->lddx,
@@ -1735,6 +1742,7 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
     }
     std::vector<GemmDesc> upd;
     for (const int l : layers) upd.push_back(update_desc(Ls[l], N, lr, 1.f, Ls[l].W, Ls[l].ldw));
+    ProfScope prof(NGSGD_PROF_GEMM_UPD, s);
     return launch_layer_gemms(GEMM_UPD, upd.data(), (int)upd.size(), s);
   };
   std::vector<int> all_layers;
