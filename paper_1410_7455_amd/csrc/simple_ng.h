@@ -17,13 +17,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm.h"
 #include "kernels.h"
 #include "state.h"
 
 namespace ngsgd {
 
 constexpr int kSimpleBlock = 32;      // pivot block of the inversion
-constexpr int kSimpleGramTile = 128;  // the Gram matrix is computed in tiles of this size, upper triangle only
+constexpr int kSimpleGramTile = kSymGramTile;   // the Gram matrix is computed in tiles of this size, upper triangle only
 constexpr int kSimpleMaxGroup = 16;   // matrices per grouped launch (the argument block stays within 4 KB)
 
 struct SimpleArgs {

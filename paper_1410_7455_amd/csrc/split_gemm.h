@@ -228,9 +228,8 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
     if (unit >= g.p[i].tile_begin) pi = i;
   const GemmProblem& P = g.p[pi];
   int local = unit - P.tile_begin;
-  const int per_split = P.tiles_m * P.tiles_n;
-  const int split = local / per_split;
-  local -= split * per_split;
+  const int split = local / P.per_split;
+  local -= split * P.per_split;
   int tm, tn;
   if (P.tiles_m <= P.tiles_n) {
     tm = local % P.tiles_m;
@@ -408,7 +407,7 @@ inline hipError_t launch_split_gemm(const GemmDesc* descs, int count, hipStream_
     for (int i = 0; i < n; ++i) {
       plan_tiles<BM, BN, BK>(descs[done + i], grp.p[i]);
       grp.p[i].tile_begin = total;
-      total += grp.p[i].tiles_m * grp.p[i].tiles_n * grp.p[i].splits;
+      total += grp.p[i].per_split * grp.p[i].splits;
     }
     grp.total_tiles = total;
     if (total > 0) {

@@ -72,6 +72,20 @@ def test_medium_shapes_and_reuse(ngsgd, N, D):
         assert rel(rn_g, rn_o) < 2e-4
 
 
+@pytest.mark.parametrize("N,D", [(64, 64), (64, 131), (65, 129), (63, 128), (128, 192), (129, 640), (191, 193), (130, 64), (300, 129), (400, 256)])
+def test_gram_tiles_and_splits(ngsgd, N, D):
+    """Gram matrices at the edges of their 64 x 64 tiles (one to six tile rows), both layouts, with K ranges of one and
+    of several splits, the last of them ragged."""
+    import torch
+    rng = np.random.default_rng(3000 + 31 * N + D)
+    M = data(rng, N, D)
+    got, g_g, rn_g = gpu_call(torch, ngsgd.SimplePreconditioner(N, D), M)
+    want, g_o, rn_o = simple_ng(M.astype(np.float64))
+    assert rel(got, want) < TOL
+    assert g_g == pytest.approx(g_o, rel=1e-4)
+    assert rel(rn_g, rn_o) < 2e-4
+
+
 def test_degenerate_inputs(ngsgd):
     """Zero matrix (gamma = 1, output 0), identical rows (output = input), rows on distinct axes (output = input)."""
     import torch
