@@ -2,18 +2,23 @@
 // top-R eigenpairs of S_0 = X_0^T X_0 / N, rho_0, D_0, then W_0 = E_0^{1/2} R_0.
 //
 // The eigenproblem is solved on the smaller of the D x D covariance and the N x N Gram matrix (same
-// non-zero spectrum; an eigenvector u of the Gram matrix gives X_0^T u / sqrt(N lambda)).  The n x n
-// symmetric matrix (n <= 1024..) is diagonalised in fp64 by a two-sided block Jacobi method: the indices are
-// cut into blocks of 32; in a round every workgroup holds two blocks, applies that round's rotations to their
-// 64 x 64 sub-matrix in LDS and keeps the accumulated rotation Q; a second launch applies A <- Q^T A Q,
-// V <- V Q tile by tile on the fp64 matrix unit.  A sweep over n = 512 is 16 rounds of two launches that touch
-// the matrix once each (the element-wise method it replaces took 511 launches per sweep, each a pass over the
-// whole matrix) and rotates every index pair once.  This runs once per process (and after each
-// parameter-averaging round), never inside the steady-state step.
+// non-zero spectrum; an eigenvector u of the Gram matrix gives X_0^T u / sqrt(N lambda)), in fp64 throughout:
+//   1. Householder reduction to a tridiagonal matrix, Q^T A Q = T: one launch per column, each a pass over the
+//      trailing matrix by many workgroups; the last 128 columns in one launch with the matrix in LDS;
+//   2. the R largest eigenvalues of T by multisection with Sturm counts, a wavefront each;
+//   3. their eigenvectors by inverse iteration from random vectors, a thread each, then orthonormalised together
+//      (twice, through the inverse Cholesky factor of their Gram matrix): vectors of equal eigenvalues start out
+//      independent and any orthonormal basis of their space serves;
+//   4. back with the reflections, four vectors per wavefront.
+// The error is a few eps |A| whatever the spectrum.  Bound: the chain of n - 128 launches (n = 512, ten instances of
+// the speech-shaped network: 384 x 5 us of 2.6 ms); a reduction needs no iteration, where the block Jacobi method this
+// replaces took 11 to 18 sweeps of 32 launches and did not settle on softmax derivatives within them (12.8 ms).
+// This runs once per process (and after each parameter-averaging round), never inside the steady-state step.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
+#include "gemm.h"
 #include "kernels.h"
 #include "small_update.h"
 #include "state.h"
@@ -22,13 +27,8 @@ namespace ngsgd {
 
 constexpr double kNullEigRatio = 1.0e-12;          // eigenvalues of S_0 at or below this ratio carry no direction
 constexpr double kCompletionMinResidual = 0.1;     // Gram-Schmidt completion threshold
-constexpr int kInitBlock = 32;                     // index block of the block Jacobi method
-constexpr int kInitPair = 2 * kInitBlock;          // two blocks: the sub-problem a workgroup holds in a round
-constexpr int kInitMaxSweeps = 18;                 // block sweeps enqueued; the kernels return at once after convergence
-constexpr double kInitRotateTol = 1.0e-8;          // entries below this, relative to their diagonal pair, are not rotated ...
-constexpr double kInitCountFloor = 3.0e-14;        // ... nor those below this fraction of the trace (the rounding noise
-                                                   // that applying a round's rotations leaves in every entry)
-constexpr int kInitSolveLds = 4 * kInitPair * (kInitPair + 1) * (int)sizeof(double);   // two copies of A_sub and Q
+constexpr int kInitPad = 64;                       // the matrix is padded with zeros to a multiple of this
+constexpr double kInitEps = 2.220446049250313e-16;
 
 struct InitArgs {
   PrecondScalars* st;
@@ -36,17 +36,26 @@ struct InitArgs {
   int ld;
   int N, D, R;
   int n;               // min(N, D): size of the eigenproblem
-  int np;              // n rounded up to a multiple of 64 (zero padding, decoupled from the rest)
-  int use_cov;         // 1: n = D, matrix X^T X / N; 0: n = N, matrix X X^T / N
-  double* A;           // np x np, diagonalised in place
-  double* V;           // np x np eigenvector accumulator (columns)
-  double* Q;           // (np / 64) x 64 x 64: the rotation of every workgroup of the current round
-  double* stat;        // [0] trace of the matrix, [1] block sweeps run
-  int* cnt;            // [3]: rotations of block sweep s in cnt[s % 3]
-  int* idx;            // R: column of V for each kept eigenpair, -1 if the direction is null
+  int np;              // n rounded up to a multiple of kInitPad
+  int rq;              // R rounded up to a multiple of 16
+  int use_cov;         // 1: n = D, matrix X^T X; 0: n = N, matrix X X^T
+  double* A;           // np x np matrix, reduced in place; then scratch of the inverse iteration (4 np rq), at last the
+                       // eigenvectors, rq x np
+  double* V;           // reflection j in row j (np x np), zero up to column j
+  double* X;           // np x rq: eigenvectors of T
+  double* T;           // 8 np: vectors of the tridiagonal form
+  int* idx;            // R: row of the eigenvector matrix for each kept eigenpair, -1 if the direction is null
   float* W;            // R x ldw
   int ldw;
-  double* vwork;       // D doubles
+  double* vwork;       // kMaxRank + D doubles
+
+  __device__ double* G() const { return X + (size_t)np * rq; }   // rq x rq: Gram matrix of X, then the inverse of its Cholesky factor
+  __device__ double* lam() const { return G() + (size_t)rq * rq; }   // R eigenvalues, descending
+  __device__ double* diag() const { return T; }                  // T / N
+  __device__ double* off() const { return T + np; }
+  __device__ double* tau() const { return T + 2 * np; }          // the reflections' factors
+  __device__ double* y(const int parity) const { return T + (3 + parity) * (size_t)np; }   // A v of the last two columns
+  __device__ double* vec() const { return T + 5 * (size_t)np; }  // 3 np: used instead of LDS where that is too small
 };
 struct InitGroup {
   int count;
@@ -55,405 +64,697 @@ struct InitGroup {
 };
 
 // The initialisation is some hundreds of small launches: the instance list is stored in device memory once and the
-// kernels take a pointer to it (a launch that carries the 3.6 KB list by value costs the host three times as much).
+// kernels take a pointer to it (a launch that carries the list by value costs the host three times as much).
 __global__ void init_store_group_kernel(const InitGroup g, InitGroup* __restrict__ dst) {
   const uint32_t* src = reinterpret_cast<const uint32_t*>(&g);
   uint32_t* out = reinterpret_cast<uint32_t*>(dst);
   for (int i = threadIdx.x; i < (int)(sizeof(InitGroup) / sizeof(uint32_t)); i += blockDim.x) out[i] = src[i];
 }
 
-// C = (1/N) X^T X (use_cov) or (1/N) X X^T, fp64 accumulation of fp32 data; V = I.  Grid (tiles, tiles, instance).
-__global__ __launch_bounds__(256) void init_gram_kernel(const InitGroup* __restrict__ gp) {
+// The Gram product fills the 64 x 64 tiles on and above the diagonal; this copies them below it.
+// Grid (np/32, np/32, instance), 256 threads.
+__global__ __launch_bounds__(256) void init_mirror_kernel(const InitGroup* __restrict__ gp) {
   const InitArgs& a = gp->a[blockIdx.z];
-  const int n = a.n, np = a.np;
-  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
-  if (i0 >= np || j0 >= np) return;
-  __shared__ float sa[32][33], sb[32][33];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;   // 16 x 16 threads, 2 x 2 outputs each
-  double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-  const int K = a.use_cov ? a.N : a.D;
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    for (int t = threadIdx.x; t < 32 * 32; t += 256) {
-      const int r = t >> 5, c = t & 31;
-      float va = 0.f, vb = 0.f;
-      if (a.use_cov) {   // element (i, k) = X[k][i]: r indexes k, c indexes i
-        const int k = k0 + r;
-        if (k < K) {
-          if (i0 + c < n) va = a.M[(size_t)k * a.ld + i0 + c];
-          if (j0 + c < n) vb = a.M[(size_t)k * a.ld + j0 + c];
-        }
-        sa[r][c] = va;   // [k][i]
-        sb[r][c] = vb;
-      } else {           // element (i, k) = X[i][k]: r indexes i, c indexes k
-        const int k = k0 + c;
-        if (k < K) {
-          if (i0 + r < n) va = a.M[(size_t)(i0 + r) * a.ld + k];
-          if (j0 + r < n) vb = a.M[(size_t)(j0 + r) * a.ld + k];
-        }
-        sa[c][r] = va;   // stored [k][i] as well
-        sb[c][r] = vb;
-      }
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int k = 0; k < 32; ++k) {
-      const double a0 = sa[k][ty], a1 = sa[k][ty + 16];
-      const double b0 = sb[k][tx], b1 = sb[k][tx + 16];
-      acc[0][0] += a0 * b0;
-      acc[0][1] += a0 * b1;
-      acc[1][0] += a1 * b0;
-      acc[1][1] += a1 * b1;
-    }
-    __syncthreads();
-  }
-  const double inv_n = 1.0 / (double)a.N;
-  for (int u = 0; u < 2; ++u)
-    for (int v = 0; v < 2; ++v) {
-      const int i = i0 + ty + 16 * u, j = j0 + tx + 16 * v;
-      if (i < np && j < np) {
-        a.A[(size_t)i * np + j] = (i < n && j < n) ? acc[u][v] * inv_n : 0.0;
-        a.V[(size_t)i * np + j] = i == j ? 1.0 : 0.0;
-      }
-    }
-}
-
-// Trace of the matrix (the scale of the convergence test) and cleared rotation counters.  One workgroup per instance.
-__global__ __launch_bounds__(256) void init_scale_kernel(const InitGroup* __restrict__ gp) {
-  const InitArgs& a = gp->a[blockIdx.x];
-  __shared__ double scratch[16];
-  double t = 0.0;
-  for (int i = threadIdx.x; i < a.n; i += 256) t += a.A[(size_t)i * a.np + i];
-  t = block_sum(t, scratch);
-  if (threadIdx.x == 0) {
-    a.stat[0] = t;
-    a.stat[1] = 0.0;
-    a.cnt[0] = a.cnt[1] = a.cnt[2] = 0;
-  }
-}
-
-// A block sweep is one "inside" round, in which every block rotates the index pairs it contains, followed by the
-// nb - 1 rounds of a round-robin over the blocks, in which a block pair (I, J) rotates the pairs (i in I, j in J):
-// every index pair once per sweep, as in the element-wise cyclic method.  An instance keeps iterating while the
-// previous sweep made at least one rotation.
-struct InitRound {
-  int nb, npairs, sweep, r;   // r = 0: inside round; r >= 1: round-robin round r - 1
-  bool active;
-};
-__device__ __forceinline__ InitRound init_round(const InitArgs& a, int ground) {
-  InitRound o;
-  o.nb = a.np / kInitBlock;
-  o.npairs = o.nb / 2;
-  const int per_sweep = o.nb;
-  o.sweep = ground / per_sweep;
-  o.r = ground % per_sweep;
-  o.active = o.sweep == 0 || a.cnt[(o.sweep + 2) % 3] != 0;
-  return o;
-}
-// the two blocks that workgroup `pair` holds in this round
-__device__ __forceinline__ void init_block_pair(const InitRound& rd, int pair, int& I, int& J) {
-  if (rd.r == 0) {
-    I = 2 * pair;
-    J = 2 * pair + 1;
-  } else {
-    round_robin_pair(rd.nb, rd.r - 1, pair, I, J);
-  }
-}
-// global index of local index l (0..63) of the blocks (I, J)
-__device__ __forceinline__ int init_pair_index(int I, int J, int l) {
-  return (l < kInitBlock ? I : J) * kInitBlock + (l & (kInitBlock - 1));
-}
-// index pair k (0..31) of inner round ir, as local indices (0..63) of the two blocks: inside round (31 inner
-// rounds): pairs within the first block for k < 16, within the second otherwise; cross round (32 inner rounds):
-// (k, 32 + (k + ir) % 32)
-__device__ __forceinline__ void init_inner_pair(bool inside, int ir, int k, int& p, int& q) {
-  if (inside) {
-    const int off = k < kInitBlock / 2 ? 0 : kInitBlock;
-    round_robin_pair(kInitBlock, ir, k & (kInitBlock / 2 - 1), p, q);
-    p += off;
-    q += off;
-  } else {
-    p = k;
-    q = kInitBlock + ((k + ir) & (kInitBlock - 1));
-  }
-}
-
-// The rotations of one round for the two blocks of a workgroup (31 or 32 inner rounds of 32 disjoint rotations) on
-// their 64 x 64 sub-matrix, in LDS; the accumulated rotation goes to Q.  The first 32 threads compute an inner
-// round's rotations (division-free); then thread t updates the 2 x 2 block (pair t / 32, pair t % 32) of the
-// sub-matrix and two rows of Q's column pair t % 32; both are double-buffered, two barriers per inner round.
-// Grid (pairs, count), 1024 threads, kInitSolveLds bytes of dynamic LDS.
-__global__ __launch_bounds__(1024) void init_block_solve_kernel(const InitGroup* __restrict__ gp, const int ground) {
-  const InitArgs& a = gp->a[blockIdx.y];
-  const InitRound rd = init_round(a, ground);
-  const int pair = blockIdx.x;
-  // the counter of the next sweep is cleared whether or not this instance still iterates (nobody reads or adds to
-  // it during this sweep), so that an instance that has converged stays so
-  if (pair == 0 && rd.r == 0 && threadIdx.x == 0) a.cnt[(rd.sweep + 1) % 3] = 0;
-  if (pair >= rd.npairs || !rd.active) return;   // uniform over the workgroup
-  constexpr int P = kInitPair, LD = kInitPair + 1;
-  extern __shared__ double dyn_init[];
-  double* sA = dyn_init;                 // [2][P][LD]
-  double* sQ = dyn_init + 2 * P * LD;    // [2][P][LD]
-  __shared__ double scratch[16];
-  __shared__ double s_c[kInitBlock], s_s[kInitBlock];
-  const int tid = threadIdx.x, np = a.np;
-  int I, J;
-  init_block_pair(rd, pair, I, J);
-  const bool inside = rd.r == 0;
-  const int inner_rounds = inside ? kInitBlock - 1 : kInitBlock;
-  for (int e = tid; e < P * P; e += 1024) {
-    const int li = e >> 6, lj = e & 63;
-    sA[li * LD + lj] = a.A[(size_t)init_pair_index(I, J, li) * np + init_pair_index(I, J, lj)];
-    sQ[li * LD + lj] = li == lj ? 1.0 : 0.0;
-  }
+  const int np = a.np, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+  if (i0 >= np || j0 >= np || i0 / kSymGramTile <= j0 / kSymGramTile) return;
+  __shared__ double t[32][33];
+  const int c = threadIdx.x & 31, r = threadIdx.x >> 5;
+#pragma unroll
+  for (int q = 0; q < 32; q += 8) t[r + q][c] = a.A[(size_t)(j0 + r + q) * np + i0 + c];
   __syncthreads();
-  const double floor_abs = kInitCountFloor * a.stat[0];
-  if (pair == 0 && rd.r == 0 && tid == 0) a.stat[1] = (double)(rd.sweep + 1);   // block sweeps this instance has run
-  const int bi = tid >> 5, bj = tid & 31;
-  int significant = 0;
-  for (int ir = 0; ir < inner_rounds; ++ir) {
-    const double* Ain = sA + (ir & 1) * P * LD;
-    double* Aout = sA + ((ir & 1) ^ 1) * P * LD;
-    const double* Qin = sQ + (ir & 1) * P * LD;
-    double* Qout = sQ + ((ir & 1) ^ 1) * P * LD;
-    if (tid < kInitBlock) {
-      int p, q;
-      init_inner_pair(inside, ir, tid, p, q);
-      const double app = Ain[p * LD + p], aqq = Ain[q * LD + q], apq = Ain[p * LD + q];
-      // Entries below the relative threshold are left: inside a cluster of (nearly) equal eigenvalues any
-      // orthonormal basis serves, and rotating its small entries would only diagonalise the cluster's own
-      // perturbation, sweep after sweep; across separated eigenvalues such an entry moves an eigenvector by less
-      // than the threshold.  Entries at the level of the rounding noise are left as well.
-      double c = 1.0, s = 0.0;
-      if (fabs(apq) > kInitRotateTol * sqrt(fabs(app * aqq)) && fabs(apq) > floor_abs) {
-        bool large;
-        jacobi_rotation(app, aqq, apq, 0.0, c, s, large);
-        ++significant;
-      }
-      s_c[tid] = c;
-      s_s[tid] = s;
-    }
-    __syncthreads();
-    int pi, qi, pj, qj;
-    init_inner_pair(inside, ir, bi, pi, qi);
-    init_inner_pair(inside, ir, bj, pj, qj);
-    const double ci = s_c[bi], si = s_s[bi], cj = s_c[bj], sj = s_s[bj];
-    const double x00 = Ain[pi * LD + pj], x01 = Ain[pi * LD + qj], x10 = Ain[qi * LD + pj], x11 = Ain[qi * LD + qj];
-    const double y00 = ci * x00 - si * x10, y01 = ci * x01 - si * x11;
-    const double y10 = si * x00 + ci * x10, y11 = si * x01 + ci * x11;
-    double b00 = y00 * cj - y01 * sj, b01 = y00 * sj + y01 * cj;
-    double b10 = y10 * cj - y11 * sj, b11 = y10 * sj + y11 * cj;
-    if (bi == bj) b01 = b10 = 0.0;
-    Aout[pi * LD + pj] = b00;
-    Aout[pi * LD + qj] = b01;
-    Aout[qi * LD + pj] = b10;
-    Aout[qi * LD + qj] = b11;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int row = bi + 32 * h;
-      const double u0 = Qin[row * LD + pj], u1 = Qin[row * LD + qj];
-      Qout[row * LD + pj] = u0 * cj - u1 * sj;
-      Qout[row * LD + qj] = u0 * sj + u1 * cj;
-    }
-    __syncthreads();
-  }
-  const double* Qfin = sQ + (inner_rounds & 1) * P * LD;
-  double* Qg = a.Q + (size_t)pair * P * P;
-  for (int e = tid; e < P * P; e += 1024) Qg[e] = Qfin[(e >> 6) * LD + (e & 63)];
-  const double total = block_sum((double)significant, scratch);
-  if (tid == 0 && total > 0.0) atomicAdd(&a.cnt[rd.sweep % 3], (int)total);
+  for (int q = 0; q < 32; q += 8) a.A[(size_t)(i0 + r + q) * np + j0 + c] = t[c][r + q];
 }
 
-// Applies the round's rotations: A <- Q^T A Q on the 64 x 64 tile (workgroup x's blocks, workgroup y's blocks), or
-// V <- V Q on the tile (64 rows, workgroup y's blocks), in place (a tile depends on itself only).
-// Grid (pairs + row chunks, pairs, count), 256 threads: wavefront w owns the 32 x 32 quadrant (w / 2, w % 2).
-// v_mfma_f64_16x16x4_f64: lane l supplies A[l%16][l/16] and B[l/16][l%16]; register r holds row 4r + l/16, column l%16.
-__global__ __launch_bounds__(256) void init_block_apply_kernel(const InitGroup* __restrict__ gp, const int ground, const int pairs_max) {
-  const InitArgs& a = gp->a[blockIdx.z];
-  const InitRound rd = init_round(a, ground);
-  const int pb = blockIdx.y;
-  const bool is_v = (int)blockIdx.x >= pairs_max;
-  const int pa = is_v ? 0 : blockIdx.x, chunk = is_v ? (int)blockIdx.x - pairs_max : 0;
-  if (!rd.active || pb >= rd.npairs) return;                                   // uniform over the workgroup
-  if (is_v ? chunk * kInitPair >= a.np : pa >= rd.npairs) return;
-  constexpr int P = kInitPair, LD = kInitPair + 1;
-  __shared__ double sT[P][LD];
-  typedef double doublex4 __attribute__((ext_vector_type(4)));
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l16 = lane & 15, g4 = lane >> 4;
-  const int qi = wave >> 1, qj = wave & 1;
-  const int np = a.np;
-  int Ia = 0, Ja = 0, Ib, Jb;
-  init_block_pair(rd, pb, Ib, Jb);
-  if (!is_v) init_block_pair(rd, pa, Ia, Ja);
-  double* __restrict__ X = is_v ? a.V : a.A;
-  const double* __restrict__ Qb = a.Q + (size_t)pb * P * P;
-  auto grow = [&](const int l) { return is_v ? chunk * P + l : init_pair_index(Ia, Ja, l); };   // row of the tile's row l
-  int gcol[2];
-#pragma unroll
-  for (int nj = 0; nj < 2; ++nj) gcol[nj] = init_pair_index(Ib, Jb, qj * 32 + nj * 16 + l16);
+// Sum over the 64 lanes without LDS: the 16 lanes of a row through the vector ALU's cross-lane path, the four rows
+// through scalar registers.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add_f64(const double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double read_lane_f64(const double v, const int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double row16_sum_f64(double v) {
+  v = dpp_add_f64<0xB1>(v);    // quad_perm [1,0,3,2]
+  v = dpp_add_f64<0x4E>(v);    // quad_perm [2,3,0,1]
+  v = dpp_add_f64<0x141>(v);   // row_half_mirror
+  return dpp_add_f64<0x140>(v);   // row_mirror
+}
+__device__ __forceinline__ double wave_sum_uniform(double v) {
+  v = row16_sum_f64(v);
+  return (read_lane_f64(v, 0) + read_lane_f64(v, 16)) + (read_lane_f64(v, 32) + read_lane_f64(v, 48));
+}
+// all 256 threads; `red` holds 4 doubles, and another call with the same array is a barrier away
+__device__ __forceinline__ double block256_sum_f64(double v, double* red) {
+  v = wave_sum_uniform(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
+}
 
-  if (is_v) {
-    // the tile itself is the left factor
-    for (int e = tid; e < P * P; e += 256) {
-      const int lr = e >> 6, lc = e & 63;
-      sT[lr][lc] = X[(size_t)grow(lr) * np + init_pair_index(Ib, Jb, lc)];
-    }
-  } else {
-    // T = Q_a^T (tile): this wavefront's quadrant, K = 64
-    const double* __restrict__ Qa = a.Q + (size_t)pa * P * P;
-    doublex4 t[2][2];
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-      for (int nj = 0; nj < 2; ++nj) t[mi][nj] = doublex4{0, 0, 0, 0};
-#pragma unroll 4
-    for (int ks = 0; ks < P / 4; ++ks) {
-      const int k = ks * 4 + g4;
-      double af[2], bf[2];
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi) af[mi] = Qa[k * P + qi * 32 + mi * 16 + l16];
-      const size_t xrow = (size_t)grow(k) * np;
-#pragma unroll
-      for (int nj = 0; nj < 2; ++nj) bf[nj] = X[xrow + gcol[nj]];
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int nj = 0; nj < 2; ++nj)
-          t[mi][nj] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[mi], bf[nj], t[mi][nj], 0, 0, 0);
-    }
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-      for (int nj = 0; nj < 2; ++nj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sT[qi * 32 + mi * 16 + 4 * r + g4][qj * 32 + nj * 16 + l16] = t[mi][nj][r];
+// Reflection that maps (x0, tail) to (beta, 0), sigma the sum of squares of the tail: I - tau v v^T with v = (1, scale tail).
+struct Reflection {
+  double beta, tau, scale;
+};
+__device__ __forceinline__ Reflection reflection(const double x0, const double sigma) {
+  Reflection h;
+  h.beta = x0;
+  h.tau = h.scale = 0.0;
+  if (sigma > 0.0) {
+    h.beta = x0 > 0.0 ? -sqrt(x0 * x0 + sigma) : sqrt(x0 * x0 + sigma);
+    h.tau = (h.beta - x0) / h.beta;
+    h.scale = 1.0 / (x0 - h.beta);
   }
-  __syncthreads();   // every wavefront has read what it needs of the tile: it may be overwritten now
-  // (left factor) Q_b
-  doublex4 acc[2][2];
+  return h;
+}
+
+// Column j of the reduction.  Every workgroup forms the vectors for itself: w from the last column's product y = A v
+// (w = tau y - (tau^2 / 2)(y.v) v), row j of the matrix as that column's update A - v w^T - w v^T leaves it, and from it
+// the next reflection.  Then it updates its rows of the trailing matrix and multiplies them with the new vector in the
+// same pass.  Row j itself is only read.  Grid (16-row groups, instance), 256 threads, four rows per wavefront; the
+// first 512 columns of its rows are requested before anything else.
+// phases: 3 both; where three vectors do not fit into LDS (n > kTriLdsCols) 1, the vectors, to a.vec() by one workgroup
+// per instance, then 2.
+constexpr int kTriTail = 128;                 // columns left to the kernel that keeps the matrix in LDS
+constexpr int kTriRows = 4;                   // rows per wavefront
+constexpr int kTriChunks = 8;                 // 64-column chunks held in registers
+constexpr int kTriLdsCols = 2048;
+__global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __restrict__ gp, const int j, const int phases) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  const int n = a.n, np = a.np;
+  if (j >= n - kTriTail) return;   // uniform over the workgroup, as below
+  const int wg_row = j + 1 + (int)blockIdx.x * 4 * kTriRows;
+  if (phases == 1 ? blockIdx.x != 0 : wg_row >= n) return;
+  extern __shared__ double dyn_tri[];
+  __shared__ double red[2][4];
+  double* const vo = phases == 3 ? dyn_tri : a.vec();   // the last column's v and w, and the new v
+  double* const wo = vo + np;
+  double* const vn = wo + np;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c0 = (j + 1) & ~63, chunks = (np - c0) / 64;
+  const int row0 = wg_row + wave * kTriRows;
+  double buf[kTriRows][kTriChunks];
+  double* rowp[kTriRows];
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
+  for (int q = 0; q < kTriRows; ++q) rowp[q] = a.A + (size_t)min(row0 + q, n - 1) * np + c0 + lane;
+  auto load = [&](const int k0) {
 #pragma unroll
-    for (int nj = 0; nj < 2; ++nj) acc[mi][nj] = doublex4{0, 0, 0, 0};
-#pragma unroll 4
-  for (int ks = 0; ks < P / 4; ++ks) {
-    const int k = ks * 4 + g4;
-    double af[2], bf[2];
+    for (int q = 0; q < kTriRows; ++q)
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi) af[mi] = sT[qi * 32 + mi * 16 + l16][k];
+      for (int k = 0; k < kTriChunks; ++k)
+        if (k0 + k < chunks) buf[q][k] = rowp[q][(size_t)(k0 + k) * 64];
+  };
+  if (phases & 2) load(0);
+  if (phases & 1) {
+    const double* const v = a.V + (size_t)(j > 0 ? j - 1 : 0) * np;
+    const double* const y = a.y((j & 1) ^ 1);
+    const double* const rowj = a.A + (size_t)j * np;
+    double tau = 0.0, half = 0.0, vj = 0.0, wj = 0.0;
+    if (j > 0) {
+      double s = 0.0;
+      for (int c = j + tid; c < n; c += 256) s += y[c] * v[c];
+      tau = a.tau()[j - 1];
+      half = 0.5 * tau * tau * block256_sum_f64(s, red[0]);
+      vj = v[j];
+      wj = tau * y[j] - half * vj;
+    }
+    double sigma = 0.0;
+    for (int c = (j & ~63) + tid; c < np; c += 256) {
+      const bool in = c >= j && c < n;
+      const double vc = in && j > 0 ? v[c] : 0.0;
+      const double wc = in && j > 0 ? tau * y[c] - half * vc : 0.0;
+      const double x = in ? rowj[c] - vj * wc - wj * vc : 0.0;
+      vo[c] = vc;
+      wo[c] = wc;
+      vn[c] = x;
+      if (c > j + 1) sigma += x * x;
+    }
+    sigma = block256_sum_f64(sigma, red[1]);   // also makes vn visible to all
+    const Reflection h = reflection(vn[j + 1], sigma);
+    const double dj = vn[j];
+    __syncthreads();
+    for (int c = (j & ~63) + tid; c < np; c += 256) vn[c] = c > j + 1 ? vn[c] * h.scale : (c == j + 1 ? 1.0 : 0.0);
+    if (blockIdx.x == 0 && tid == 0) {
+      a.diag()[j] = dj;
+      a.off()[j] = h.beta;
+      a.tau()[j] = h.tau;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0)
+      for (int c = tid; c < np; c += 256) a.V[(size_t)j * np + c] = c > j ? vn[c] : 0.0;
+  }
+  if (!(phases & 2)) return;
+  double acc[kTriRows], vr[kTriRows], wr[kTriRows];
 #pragma unroll
-    for (int nj = 0; nj < 2; ++nj) bf[nj] = Qb[k * P + qj * 32 + nj * 16 + l16];
+  for (int q = 0; q < kTriRows; ++q) {
+    acc[q] = 0.0;
+    vr[q] = vo[min(row0 + q, n - 1)];
+    wr[q] = wo[min(row0 + q, n - 1)];
+  }
+  for (int k0 = 0; k0 < chunks; k0 += kTriChunks) {
+    if (k0 > 0) load(k0);
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
+    for (int k = 0; k < kTriChunks; ++k) {
+      if (k0 + k >= chunks) break;
+      const int c = c0 + (k0 + k) * 64 + lane;
+      const double vc = vo[c], wc = wo[c], xc = vn[c];
 #pragma unroll
-      for (int nj = 0; nj < 2; ++nj)
-        acc[mi][nj] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[mi], bf[nj], acc[mi][nj], 0, 0, 0);
+      for (int q = 0; q < kTriRows; ++q) {
+        const double t = buf[q][k] - vr[q] * wc - wr[q] * vc;
+        acc[q] += t * xc;
+        if (row0 + q < n) rowp[q][(size_t)(k0 + k) * 64] = t;
+      }
+    }
   }
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
+  for (int q = 0; q < kTriRows; ++q) {
+    acc[q] = wave_sum_uniform(acc[q]);
+    if (lane == 0 && row0 + q < n) a.y(j & 1)[row0 + q] = acc[q];
+  }
+}
+
+// The last (at most 128) columns, the matrix in LDS: eight threads per row, 16 columns each.  Also divides T by N.
+// One workgroup of 1024 threads per instance.
+constexpr int kTriTailLd = kTriTail + 8;   // eight rows by eight columns touch every bank once
+constexpr int kTriTailLds = (kTriTail * kTriTailLd + 3 * kTriTail) * (int)sizeof(double);
+__global__ __launch_bounds__(1024) void init_tri_tail_kernel(const InitGroup* __restrict__ gp) {
+  const InitArgs& a = gp->a[blockIdx.x];
+  constexpr int T = kTriTail, LD = kTriTailLd;
+  extern __shared__ double dyn_tri[];
+  double* const S = dyn_tri;
+  double* const sv = S + T * LD;
+  double* const sy = sv + T;
+  double* const sw = sy + T;
+  __shared__ double s_tau;
+  const int n = a.n, np = a.np, j0 = max(0, n - T), m = n - j0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = tid >> 3, q8 = tid & 7;
+  const double inv_n = 1.0 / (double)a.N;
+  for (int e = tid; e < T * T; e += 1024) {
+    const int i = e >> 7, c = e & (T - 1);
+    S[i * LD + c] = i < m && c < m ? a.A[(size_t)(j0 + i) * np + j0 + c] : 0.0;
+  }
+  if (tid < T) {
+    const bool in = j0 > 0 && tid < m;
+    sv[tid] = in ? a.V[(size_t)(j0 - 1) * np + j0 + tid] : 0.0;
+    sy[tid] = in ? a.y((j0 - 1) & 1)[j0 + tid] : 0.0;
+  }
+  for (int i = tid; i < j0; i += 1024) {
+    a.diag()[i] *= inv_n;
+    a.off()[i] *= inv_n;
+  }
+  double tau = j0 > 0 ? a.tau()[j0 - 1] : 0.0;
+  __syncthreads();
+  for (int jj = -1; jj < m - 1; ++jj) {
+    // sv, sy and tau belong to column jj (before the first: to the last column of the other kernel)
+    const double dot = wave_sum_uniform(sy[lane] * sv[lane] + sy[lane + 64] * sv[lane + 64]);
+    const double half = 0.5 * tau * tau * dot;
+    if (tid < T) sw[tid] = tau * sy[tid] - half * sv[tid];
+    __syncthreads();
+    const int k_lo = (jj + 1) >> 3;   // columns below jj + 1 are done
+    {
+      const double vr = sv[r], wr = sw[r];
+#pragma unroll 4
+      for (int k = k_lo; k < T / 8; ++k) {
+        const int c = 8 * k + q8;
+        S[r * LD + c] -= vr * sw[c] + wr * sv[c];
+      }
+    }
+    __syncthreads();
+    const int j = jj + 1;
+    if (j >= m - 1) break;
+    if (wave == 0) {   // row j is final: the next reflection
+      const double x0 = lane > j ? S[j * LD + lane] : 0.0, x1 = lane + 64 > j ? S[j * LD + lane + 64] : 0.0;
+      const double sigma = wave_sum_uniform((lane > j + 1 ? x0 * x0 : 0.0) + (lane + 64 > j + 1 ? x1 * x1 : 0.0));
+      const Reflection h = reflection(S[j * LD + j + 1], sigma);
+      sv[lane] = lane == j + 1 ? 1.0 : x0 * h.scale;
+      sv[lane + 64] = lane + 64 == j + 1 ? 1.0 : x1 * h.scale;
+      if (lane == 0) {
+        s_tau = h.tau;
+        a.diag()[j0 + j] = S[j * LD + j] * inv_n;
+        a.off()[j0 + j] = h.beta * inv_n;
+        a.tau()[j0 + j] = h.tau;
+      }
+    }
+    __syncthreads();
+    tau = s_tau;
+    double acc = 0.0;
+    const int k_new = (j + 1) >> 3;
+#pragma unroll 4
+    for (int k = k_new; k < T / 8; ++k) acc += S[r * LD + 8 * k + q8] * sv[8 * k + q8];
+    acc = dpp_add_f64<0xB1>(acc);
+    acc = dpp_add_f64<0x4E>(acc);
+    acc = dpp_add_f64<0x141>(acc);   // eight lanes
+    if (q8 == 0) sy[r] = r > j ? acc : 0.0;
+    for (int c = tid; c < np; c += 1024) {
+      const int l = c - j0;
+      a.V[(size_t)(j0 + j) * np + c] = l > j && l < m ? sv[l] : 0.0;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    a.diag()[n - 1] = S[(m - 1) * LD + m - 1] * inv_n;
+    a.off()[n - 1] = 0.0;
+  }
+}
+
+__device__ __forceinline__ double reciprocal_f64(const double x) {   // hardware estimate, two Newton steps
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+// interval that holds the eigenvalues of T (Gershgorin), all lanes of a wavefront together
+__device__ __forceinline__ void tri_bounds(const InitArgs& a, const int lane, double& lo, double& hi) {
+  lo = 1.0e300;
+  hi = -1.0e300;
+  for (int i = lane; i < a.n; i += 64) {
+    const double radius = (i > 0 ? fabs(a.off()[i - 1]) : 0.0) + fabs(a.off()[i]), d = a.diag()[i];
+    lo = fmin(lo, d - radius);
+    hi = fmax(hi, d + radius);
+  }
+  hi = wave_max_d(hi);
+  lo = -wave_max_d(-lo);
+}
+
+// Eigenvalue k (descending) of T: a wavefront counts the eigenvalues below 64 points of the interval at once, six bits
+// a pass.  Bound: the serial recurrence, n divisions a pass.  Grid (R, instance), 64 threads.
+constexpr int kSectionPasses = 12;
+__global__ __launch_bounds__(64) void init_eigenvalue_kernel(const InitGroup* __restrict__ gp) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  const int k = blockIdx.x, lane = threadIdx.x, n = a.n;
+  if (k >= a.R) return;
+  double lo, hi;
+  tri_bounds(a, lane, lo, hi);
+  const double norm = fmax(fabs(lo), fabs(hi));
+  const double margin = 2.0 * kInitEps * (double)n * norm;
+  const double piv_min = fmax(1.0e-290, 1.0e-290 * norm * norm);
+  lo -= margin;
+  hi += margin;
+  const double* __restrict__ d = a.diag();
+  const double* __restrict__ e = a.off();
+  for (int pass = 0; pass < kSectionPasses; ++pass) {
+    const double width = hi - lo;
+    if (!(width > 0.5 * kInitEps * norm)) break;
+    const double step = width / 65.0, x = lo + step * (double)(lane + 1);
+    double q = d[0] - x;
+    int below = q < 0.0 ? 1 : 0;
+#pragma unroll 8
+    for (int i = 1; i < n; ++i) {
+      if (fabs(q) < piv_min) q = -piv_min;
+      q = fma(-(e[i - 1] * e[i - 1]), reciprocal_f64(q), d[i] - x);
+      below += q < 0.0 ? 1 : 0;
+    }
+    const int m = __popcll(__ballot(below <= n - 1 - k));   // points at or below the eigenvalue
+    const double base = lo;
+    if (m > 0) lo = base + step * (double)m;
+    if (m < 64) hi = base + step * (double)(m + 1);
+  }
+  if (lane == 0) a.lam()[k] = 0.5 * (lo + hi);
+}
+
+// Eigenvectors of T by inverse iteration: T - lambda = P L U with row exchanges once, then three solves from a random
+// vector.  A thread per vector; everything is laid out with the vector index running fastest.
+// Bound: the serial chains of n steps.  What they read does not depend on them, so every solve goes in blocks of eight
+// steps whose operands are requested a block ahead (900 us without, the loads being ordered behind the stores).
+// Grid (ceil(rq / 64), instance), 64 threads.
+constexpr int kInverseSolves = 3;
+constexpr int kInverseBlock = 8;
+__device__ __forceinline__ double inverse_start(const int i, const int k) {   // integer hash, uniform in [-1, 1)
+  uint32_t h = (uint32_t)i * 0x9E3779B9u ^ (uint32_t)(k + 1) * 0x85EBCA6Bu;
+  h = (h ^ (h >> 16)) * 0x7FEB352Du;
+  h = (h ^ (h >> 15)) * 0x846CA68Bu;
+  h ^= h >> 16;
+  return (double)(int32_t)h * (1.0 / 2147483648.0);
+}
+__global__ __launch_bounds__(64) void init_eigenvector_kernel(const InitGroup* __restrict__ gp) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  constexpr int B = kInverseBlock;
+  const int k = blockIdx.x * 64 + threadIdx.x, n = a.n, rq = a.rq;
+  if ((int)blockIdx.x * 64 >= rq) return;
+  double lo, hi;
+  tri_bounds(a, threadIdx.x, lo, hi);
+  const double norm = fmax(fabs(lo), fabs(hi));
+  if (k >= rq) return;
+  double* const __restrict__ X = a.X + k;
+  const double lambda = k < a.R ? a.lam()[k] : 0.0;
+  if (!(k < a.R && lambda > kNullEigRatio * a.lam()[0] && norm > 0.0)) {
+    for (int i = 0; i < n; ++i) X[(size_t)i * rq] = 0.0;
+    return;
+  }
+  const size_t plane = (size_t)a.np * rq;
+  double* const __restrict__ r0 = a.A + k;   // 1 / diagonal of U, its two superdiagonals, multipliers of L (lowest bit: rows exchanged)
+  double* const __restrict__ u1 = a.A + k + plane;
+  double* const __restrict__ u2 = a.A + k + 2 * plane;
+  double* const __restrict__ ml = a.A + k + 3 * plane;
+  const double* __restrict__ d = a.diag();
+  const double* __restrict__ e = a.off();
+  const double tiny = kInitEps * norm;
+  {
+    double p = d[0] - lambda, b = e[0];
+#pragma unroll 4
+    for (int i = 0; i < n - 1; ++i) {
+      const double s = e[i], dn = d[i + 1] - lambda, en = e[i + 1];
+      const bool swap = fabs(p) < fabs(s);
+      double piv = swap ? s : p;
+      if (fabs(piv) < tiny) piv = piv < 0.0 ? -tiny : tiny;
+      const double inv = reciprocal_f64(piv);
+      const double l = (swap ? p : s) * inv;
+      const double x1 = swap ? dn : b, x2 = swap ? en : 0.0;
+      const size_t at = (size_t)i * rq;
+      r0[at] = inv;
+      u1[at] = x1;
+      u2[at] = x2;
+      ml[at] = __builtin_bit_cast(double, (__builtin_bit_cast(uint64_t, l) & ~1ull) | (swap ? 1ull : 0ull));
+      p = swap ? fma(-l, dn, b) : fma(-l, b, dn);
+      b = swap ? -l * en : en;
+    }
+    if (fabs(p) < tiny) p = p < 0.0 ? -tiny : tiny;
+    r0[(size_t)(n - 1) * rq] = reciprocal_f64(p);
+    u1[(size_t)(n - 1) * rq] = u2[(size_t)(n - 1) * rq] = 0.0;
+  }
+  double scale = 1.0;
+  for (int it = 0; it < kInverseSolves; ++it) {
+    if (it > 0) {   // L y = P x, in place: step i takes x_{i+1} and leaves y_i
+      double bl[2][B], bx[2][B];
+      auto fetch = [&](const int i0, const int set) {   // steps beyond n - 2 are read from it and not taken
+#pragma unroll
+        for (int t = 0; t < B; ++t) {
+          const size_t at = (size_t)min(i0 + t, n - 2) * rq;
+          bl[set][t] = ml[at];
+          bx[set][t] = X[at + rq];
+        }
+      };
+      double cur = X[0] * scale;
+      auto steps = [&](const int i0, const int set) {
+#pragma unroll
+        for (int t = 0; t < B; ++t) {
+          if (i0 + t >= n - 1) break;
+          const double l = bl[set][t], nxt = bx[set][t] * scale;
+          const bool swap = (__builtin_bit_cast(uint64_t, l) & 1ull) != 0;
+          X[(size_t)(i0 + t) * rq] = swap ? nxt : cur;
+          cur = swap ? fma(-l, nxt, cur) : fma(-l, cur, nxt);
+        }
+      };
+      fetch(0, 0);
+      for (int i0 = 0; i0 < n - 1; i0 += 2 * B) {   // a block writes elements below those that the next one reads
+        fetch(i0 + B, 1);
+        steps(i0, 0);
+        fetch(i0 + 2 * B, 0);
+        steps(i0 + B, 1);
+      }
+      X[(size_t)(n - 1) * rq] = cur;
+    }
+    double x1 = 0.0, x2 = 0.0, ss = 0.0;
+    double b0[2][B], b1[2][B], b2[2][B], by[2][B];
+    auto fetch = [&](const int i0, const int set) {   // rows i0, i0 - 1, ...; those below 0 are read from row 0 and not taken
+#pragma unroll
+      for (int t = 0; t < B; ++t) {
+        const int i = max(i0 - t, 0);
+        const size_t at = (size_t)i * rq;
+        b0[set][t] = r0[at];
+        b1[set][t] = u1[at];
+        b2[set][t] = u2[at];
+        by[set][t] = it > 0 ? X[at] : inverse_start(i, k);
+      }
+    };
+    auto steps = [&](const int i0, const int set) {   // U x = y
+#pragma unroll
+      for (int t = 0; t < B; ++t) {
+        if (i0 - t < 0) break;
+        const double x = fma(-b1[set][t], x1, fma(-b2[set][t], x2, by[set][t])) * b0[set][t];
+        X[(size_t)(i0 - t) * rq] = x;
+        ss = fma(x, x, ss);
+        x2 = x1;
+        x1 = x;
+      }
+    };
+    fetch(n - 1, 0);
+    for (int i0 = n - 1; i0 >= 0; i0 -= 2 * B) {
+      fetch(i0 - B, 1);
+      steps(i0, 0);
+      fetch(i0 - 2 * B, 0);
+      steps(i0 - B, 1);
+    }
+    scale = 1.0 / sqrt(ss);
+  }
+#pragma unroll 8
+  for (int i = 0; i < n; ++i) X[(size_t)i * rq] *= scale;
+}
+
+// G = X^T X, a 16 x 16 tile per workgroup of four wavefronts.  Grid (rq/16, rq/16, instance).
+// v_mfma_f64_16x16x4_f64: lane l supplies A[l%16][l/16] and B[l/16][l%16]; register r holds row 4r + l/16, column l%16.
+// `second`: X is what the first orthonormalisation left.
+__device__ __forceinline__ double* init_ortho_input(const InitArgs& a, const int second) {
+  return second ? a.A + (size_t)a.np * a.rq : a.X;   // behind the place of the final vectors
+}
+__global__ __launch_bounds__(256) void init_ortho_gram_kernel(const InitGroup* __restrict__ gp, const int second) {
+  const InitArgs& a = gp->a[blockIdx.z];
+  const int rq = a.rq, a0 = blockIdx.y * 16, b0 = blockIdx.x * 16;
+  if (a0 >= rq || b0 >= rq) return;
+  typedef double doublex4 __attribute__((ext_vector_type(4)));
+  __shared__ double part[4][256];
+  const double* __restrict__ X = init_ortho_input(a, second);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
+  doublex4 acc = {0, 0, 0, 0};
+  for (int i0 = wave * 4; i0 < a.n; i0 += 16) {
+    const int i = i0 + g4;
+    const double x = i < a.n ? X[(size_t)i * rq + a0 + l16] : 0.0, y = i < a.n ? X[(size_t)i * rq + b0 + l16] : 0.0;
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) part[wave][(4 * r + g4) * 16 + l16] = acc[r];
+  __syncthreads();
+  const int t = threadIdx.x;
+  a.G()[(size_t)(a0 + (t >> 4)) * rq + b0 + (t & 15)] = (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]);
+}
+
+// G = L L^T replaced by L^-1: elimination without pivoting of [G | I], the right half growing in the columns that become
+// zero, one barrier per pivot.  A null vector (zero row) is left out.  One workgroup of 1024 threads per instance.
+__global__ __launch_bounds__(1024) void init_ortho_factor_kernel(const InitGroup* __restrict__ gp) {
+  const InitArgs& a = gp->a[blockIdx.x];
+  __shared__ double S[kMaxRank][kMaxRank + 8];
+  __shared__ double s_piv[kMaxRank];
+  const int rq = a.rq, tid = threadIdx.x, r = tid >> 3, q8 = tid & 7;   // eight threads per row (all in one wavefront)
+  for (int e = tid; e < rq * rq; e += 1024) S[e / rq][e % rq] = a.G()[e];
+  __syncthreads();
+  for (int k = 0; k < rq; ++k) {
+    const double piv = S[k][k];
+    const double inv = piv > 1.0e-30 ? reciprocal_f64(piv) : 0.0;
+    if (tid == 0) s_piv[k] = inv;
+    if (r > k && r < rq) {
+      const double f = S[r][k] * inv;
+#pragma unroll 4
+      for (int c = q8; c < rq; c += 8) {
+        const double s = S[r][c] - f * S[k][c];
+        S[r][c] = c == k ? -f : s;
+      }
+    }
+    __syncthreads();
+  }
+  for (int e = tid; e < rq * rq; e += 1024) {
+    const int i = e / rq, c = e % rq;
+    a.G()[e] = sqrt(s_piv[i]) * (c < i ? S[i][c] : (c == i ? 1.0 : 0.0));
+  }
+}
+
+// X L^-T: first to the input of the second pass, then transposed to its place (rq x np, zero beyond n).
+// Grid (np/64, instance), 256 threads: a wavefront owns 16 rows of X.
+__global__ __launch_bounds__(256) void init_ortho_apply_kernel(const InitGroup* __restrict__ gp, const int second) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  const int rq = a.rq, n = a.n, np = a.np;
+  if ((int)blockIdx.x * 64 >= np) return;
+  typedef double doublex4 __attribute__((ext_vector_type(4)));
+  const double* __restrict__ X = init_ortho_input(a, second);
+  double* __restrict__ out = second ? a.A : init_ortho_input(a, 1);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int i0 = blockIdx.x * 64 + wave * 16;
+  for (int b0 = 0; b0 < rq; b0 += 16) {
+    doublex4 acc = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int k0 = 0; k0 < b0 + 16; k0 += 4) {   // L^-1 is lower triangular
+      const double x = i0 + l16 < n ? X[(size_t)(i0 + l16) * rq + k0 + g4] : 0.0;
+      const double l = a.G()[(size_t)(b0 + l16) * rq + k0 + g4];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, l, acc, 0, 0, 0);
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const size_t xrow = (size_t)grow(qi * 32 + mi * 16 + 4 * r + g4) * np;
-#pragma unroll
-      for (int nj = 0; nj < 2; ++nj) X[xrow + gcol[nj]] = acc[mi][nj][r];
-    }
-}
-
-// Top-R eigenvalues, rho_0, D_0, E_0 (App. B.3.2 with eq. beta2, etii).  One workgroup per instance.
-__global__ __launch_bounds__(1024) void init_select_kernel(const InitGroup* __restrict__ gp) {
-  __shared__ double scratch[16];
-  __shared__ double s_lam[kMaxRank];
-  __shared__ int s_idx[kMaxRank];
-  const InitArgs& a = gp->a[blockIdx.x];
-  const int n = a.n, R = a.R, D = a.D;
-  const size_t lda = a.np;
-  const double* A = a.A;
-  PrecondScalars* st = a.st;
-  double tr = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) tr += A[i * lda + i];
-  tr = block_sum(tr, scratch);
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const double li = A[i * lda + i];
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      const double lj = A[j * lda + j];
-      rank += (lj > li || (lj == li && j < i)) ? 1 : 0;
-    }
-    if (rank < R) {
-      s_lam[rank] = li;
-      s_idx[rank] = i;
+      const int i = i0 + 4 * r + g4, k = b0 + l16;
+      out[second ? (size_t)k * np + i : (size_t)i * rq + k] = acc[r];
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double lmax = s_lam[0];
-    double sum_l = 0.0;
-    for (int k = 0; k < R; ++k) {
-      const bool keep = lmax > 0.0 && s_lam[k] > kNullEigRatio * lmax;
-      if (!keep) {
-        s_lam[k] = 0.0;
-        s_idx[k] = -1;
-      }
-      sum_l += s_lam[k];
+}
+
+// Eigenvectors of T -> of A: the reflections, last to first, on a vector per wavefront, which it holds in registers
+// (NC 64-element chunks).  Bound: the latency of n dependent inner products (four vectors per wavefront: 255 us for
+// n = 512 and ten instances).  Grid (ceil(R/4), instance), 256 threads.
+template <int NC>
+__device__ __forceinline__ void init_back_registers(const InitArgs& a, double* __restrict__ xk, const int lane) {
+  const int n = a.n, np = a.np;
+  const double* __restrict__ V = a.V + lane;
+  const double* __restrict__ tau = a.tau();
+  double x[NC], v[2][NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) x[c] = 64 * c < np ? xk[64 * c + lane] : 0.0;
+  auto fetch = [&](const int j, const int set) {   // requested two steps ahead
+#pragma unroll
+    for (int c = 0; c < NC; ++c) v[set][c] = 64 * c < np ? V[(size_t)max(j, 0) * np + 64 * c] : 0.0;
+  };
+  auto step = [&](const int j, const int set) {
+    if (j < 0) return;
+    double dot[2] = {0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) dot[c & 1] = fma(v[set][c], x[c], dot[c & 1]);
+    const double f = tau[j] * wave_sum_uniform(dot[0] + dot[1]);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) x[c] = fma(-f, v[set][c], x[c]);
+  };
+  fetch(n - 2, 0);
+  fetch(n - 3, 1);
+  for (int j = n - 2; j >= 0; j -= 2) {
+    step(j, 0);
+    fetch(j - 2, 0);
+    step(j - 1, 1);
+    fetch(j - 3, 1);
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    if (64 * c < np) xk[64 * c + lane] = x[c];
+}
+__global__ __launch_bounds__(256) void init_back_kernel(const InitGroup* __restrict__ gp) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, n = a.n, np = a.np;
+  if (k >= a.R) return;
+  double* const x = a.A + (size_t)k * np;
+  if (np <= 128) {
+    init_back_registers<2>(a, x, lane);
+  } else if (np <= 512) {
+    init_back_registers<8>(a, x, lane);
+  } else if (np <= 1024) {
+    init_back_registers<16>(a, x, lane);
+  } else {
+    for (int j = n - 2; j >= 0; --j) {   // a lane reads and writes only its own elements of x
+      const double* const v = a.V + (size_t)j * np;
+      double dot = 0.0;
+      for (int c = (j & ~63) + lane; c < np; c += 64) dot = fma(v[c], x[c], dot);
+      dot = a.tau()[j] * wave_sum_uniform(dot);
+      for (int c = (j & ~63) + lane; c < np; c += 64) x[c] = fma(-dot, v[c], x[c]);
     }
-    const double rho0 = fmax((tr - sum_l) / (double)(D - R), gp->epsilon);
-    double sum_d = 0.0;
-    for (int k = 0; k < R; ++k) {
-      const double d = fmax(gp->epsilon, s_lam[k] - rho0);
-      st->d[k] = d;
-      sum_d += d;
-    }
-    const double beta = rho0 * (1.0 + gp->alpha) + gp->alpha / (double)D * sum_d;
-    for (int k = 0; k < R; ++k) st->e[k] = 1.0 / (beta / st->d[k] + 1.0);
+  }
+}
+
+// rho_0, D_0, E_0 from the top-R eigenvalues (App. B.3.2 with eq. beta2, etii).  One workgroup per instance.
+__global__ __launch_bounds__(256) void init_select_kernel(const InitGroup* __restrict__ gp) {
+  __shared__ double scratch[16];
+  const InitArgs& a = gp->a[blockIdx.x];
+  const int n = a.n, R = a.R, D = a.D, k = threadIdx.x;
+  static_assert(kMaxRank <= 256, "a thread per eigenvalue");
+  PrecondScalars* st = a.st;
+  double tr = 0.0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) tr += a.diag()[i];
+  tr = block_sum(tr, scratch);
+  const double lmax = a.lam()[0];
+  const double l = k < R ? a.lam()[k] : 0.0;
+  const bool keep = lmax > 0.0 && l > kNullEigRatio * lmax;
+  const double sum_l = block_sum(keep ? l : 0.0, scratch);
+  const double rho0 = fmax((tr - sum_l) / (double)(D - R), gp->epsilon);
+  const double d = fmax(gp->epsilon, (keep ? l : 0.0) - rho0);
+  const double sum_d = block_sum(k < R ? d : 0.0, scratch);
+  const double beta = rho0 * (1.0 + gp->alpha) + gp->alpha / (double)D * sum_d;
+  if (k < R) {
+    a.idx[k] = keep ? k : -1;
+    a.vwork[k] = keep ? l : 0.0;   // for the Gram route's 1 / sqrt(N lambda)
+    st->d[k] = d;
+    st->e[k] = 1.0 / (beta / d + 1.0);
+  }
+  if (k == 0) {
     st->rho = rho0;
     st->beta = beta;
     st->trace_S0 = tr;
-    st->flags = a.cnt[((int)a.stat[1] + 2) % 3] != 0 ? kFlagNoConverge : 0;   // the last sweep run still rotated
-    st->sweeps = (int)a.stat[1];   // block sweeps of the initial eigen-decomposition
-    // eigenvalue kept for the Gram route's 1/sqrt(N lambda); parked in gamma/tr fields is not possible: use vwork
-    for (int k = 0; k < R; ++k) {
-      a.idx[k] = s_idx[k];
-      a.vwork[k] = s_lam[k];
-    }
+    st->flags = 0;
+    st->sweeps = 0;   // nothing iterates here
   }
 }
 
-// W_0 rows of the kept eigenpairs: sqrt(e_i) v_i with v_i a column of V (covariance route) or
-// X_0^T u_i / sqrt(N lambda_i) (Gram route); zero for null directions.  Grid (col blocks of 64, R, instance).
-__global__ __launch_bounds__(256) void init_rows_kernel(const InitGroup* __restrict__ gp) {
-  const InitArgs& a = gp->a[blockIdx.z];
-  const int i = blockIdx.y;
-  if (i >= a.R) return;
-  const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int part = threadIdx.x >> 6;   // 4 slices of the row range
-  if ((int)blockIdx.x * 64 >= a.ldw) return;
-  __shared__ double s_acc[4][64];
-  const int src_col = a.idx[i];
-  const double* V = a.V;
-  const int n = a.np;   // leading dimension of V
-  double acc = 0.0;
-  if (src_col >= 0 && col < a.D) {
-    if (a.use_cov) {
-      if (part == 0) acc = V[(size_t)col * n + src_col];
-    } else {
-      const int rows_per = (a.N + 3) / 4;
-      const int r0 = part * rows_per, r1 = min(a.N, r0 + rows_per);
-      for (int r = r0; r < r1; ++r) acc += (double)a.M[(size_t)r * a.ld + col] * V[(size_t)r * n + src_col];
+// W_0 rows of the kept eigenpairs: sqrt(e_i) v_i with v_i an eigenvector (covariance route) or X_0^T u_i / sqrt(N lambda_i)
+// (Gram route, on the fp64 matrix unit); zero for null directions.  A workgroup forms all rows for 64 columns, 16 per
+// wavefront, so that X_0 is read once; the vectors go through LDS in blocks of 32 elements.
+// Grid (64-column blocks, instance), 256 threads.
+constexpr int kInitRowsK = 32;
+template <int TR>   // 16-row tiles
+__device__ __forceinline__ void init_rows_block(const InitArgs& a, double* sU) {
+  typedef double doublex4 __attribute__((ext_vector_type(4)));
+  constexpr int LD = kInitRowsK + 2;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+  const int col = blockIdx.x * 64 + (tid >> 6) * 16 + l16;
+  const int np = a.np, R = a.R;
+  doublex4 acc[TR];   // register r: row 4 r + lane / 16 of a tile, column lane % 16
+#pragma unroll
+  for (int t = 0; t < TR; ++t) acc[t] = doublex4{0, 0, 0, 0};
+  if (a.use_cov) {
+#pragma unroll
+    for (int t = 0; t < TR; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * t + 4 * r + g4;
+        if (i < R && col < a.D) acc[t][r] = a.A[(size_t)i * np + col];
+      }
+  } else {
+    const float* __restrict__ m = a.M + min(col, a.D - 1);   // columns beyond D reach no row that is stored
+    float x[kInitRowsK / 4];
+    auto fetch = [&](const int r0) {
+#pragma unroll
+      for (int ks = 0; ks < kInitRowsK / 4; ++ks) x[ks] = m[(size_t)min(r0 + 4 * ks + g4, a.N - 1) * a.ld];
+    };
+    fetch(0);
+    for (int r0 = 0; r0 < a.N; r0 += kInitRowsK) {
+      __syncthreads();
+      for (int e = tid; e < 16 * TR * kInitRowsK; e += 256) {
+        const int r = e % kInitRowsK, i = e / kInitRowsK;
+        sU[i * LD + r] = i < R && r0 + r < a.N ? a.A[(size_t)i * np + r0 + r] : 0.0;
+      }
+      __syncthreads();
+      float cur[kInitRowsK / 4];
+#pragma unroll
+      for (int ks = 0; ks < kInitRowsK / 4; ++ks) cur[ks] = x[ks];
+      if (r0 + kInitRowsK < a.N) fetch(r0 + kInitRowsK);
+#pragma unroll
+      for (int ks = 0; ks < kInitRowsK / 4; ++ks)
+#pragma unroll
+        for (int t = 0; t < TR; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(sU[(16 * t + l16) * LD + 4 * ks + g4], (double)cur[ks], acc[t], 0, 0, 0);
     }
   }
-  s_acc[part][threadIdx.x & 63] = acc;
-  __syncthreads();
-  if (part == 0 && col < a.ldw) {
-    double v = s_acc[0][threadIdx.x] + s_acc[1][threadIdx.x] + s_acc[2][threadIdx.x] + s_acc[3][threadIdx.x];
-    if (src_col >= 0 && col < a.D) {
-      double scale = sqrt(a.st->e[i]);
-      if (!a.use_cov) scale /= sqrt((double)a.N * a.vwork[i]);
-      v *= scale;
-    } else {
-      v = 0.0;
+  if (col >= a.ldw) return;
+#pragma unroll
+  for (int t = 0; t < TR; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * t + 4 * r + g4;
+      if (i >= R) continue;
+      double v = 0.0;
+      if (a.idx[i] >= 0 && col < a.D) {
+        double scale = sqrt(a.st->e[i]);
+        if (!a.use_cov) scale /= sqrt((double)a.N * a.vwork[i]);
+        v = acc[t][r] * scale;
+      }
+      a.W[(size_t)i * a.ldw + col] = (float)v;
     }
-    a.W[(size_t)i * a.ldw + col] = (float)v;
+}
+__global__ __launch_bounds__(256) void init_rows_kernel(const InitGroup* __restrict__ gp) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  if ((int)blockIdx.x * 64 >= a.ldw) return;
+  __shared__ double sU[kMaxRank * (kInitRowsK + 2)];
+  if (a.R <= 32) {
+    init_rows_block<2>(a, sU);
+  } else {
+    init_rows_block<kMaxRank / 16>(a, sU);
   }
 }
 

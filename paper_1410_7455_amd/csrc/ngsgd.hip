@@ -159,9 +159,8 @@ struct ngsgd_precond {
   int n_init_max = 0;
   double* Ai = nullptr;
   double* Vi = nullptr;
-  double* Qi = nullptr;
-  double* init_stat = nullptr;
-  int* init_cnt = nullptr;
+  double* Xi = nullptr;
+  double* ti = nullptr;
   InitGroup* init_group = nullptr;   // device copy of the instance list of an initialisation this instance leads
   int* idx = nullptr;
   double* vwork = nullptr;
@@ -200,12 +199,11 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.sumsq_part = c.take<double>(kSumsqMax);
   p.deferred = c.take<int>(kSumsqMax);
   p.n_init_max = NB < D ? NB : D;
-  const size_t np_init = (size_t)(p.n_init_max + kInitPair - 1) / kInitPair * kInitPair;
-  p.Ai = c.take<double>(np_init * np_init);
+  const size_t np_init = align_up(p.n_init_max, kInitPad), rq = align_up(R, 16);
+  p.Ai = c.take<double>(std::max(np_init * np_init, 4 * np_init * rq));
   p.Vi = c.take<double>(np_init * np_init);
-  p.Qi = c.take<double>(np_init / kInitPair * kInitPair * kInitPair);
-  p.init_stat = c.take<double>(2);
-  p.init_cnt = c.take<int>(4);
+  p.Xi = c.take<double>(np_init * rq + rq * rq + rq);
+  p.ti = c.take<double>(8 * np_init);
   p.init_group = c.take<InitGroup>(1);
   p.idx = c.take<int>(kMaxRank);
   p.vwork = c.take<double>((size_t)kMaxRank + D);
@@ -263,8 +261,10 @@ int ensure_kernel_attributes() {
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(orth_fix_kernel<6>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, orth_dyn));
   }
-  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(init_block_solve_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kInitSolveLds));
+  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(init_tri_step_kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 3 * kTriLdsCols * (int)sizeof(double)));
+  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(init_tri_tail_kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kTriTailLds));
   g_attr_done = true;
   return NGSGD_OK;
 }
@@ -422,12 +422,12 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
       a.R = p.rank;
       a.use_cov = p.dim <= c.N ? 1 : 0;
       a.n = a.use_cov ? p.dim : c.N;
-      a.np = (a.n + kInitPair - 1) / kInitPair * kInitPair;
+      a.np = (int)align_up(a.n, kInitPad);
+      a.rq = (int)align_up(a.R, 16);
       a.A = p.Ai;
       a.V = p.Vi;
-      a.Q = p.Qi;
-      a.stat = p.init_stat;
-      a.cnt = p.init_cnt;
+      a.X = p.Xi;
+      a.T = p.ti;
       a.idx = p.idx;
       a.W = p.W;
       a.ldw = p.ldw;
@@ -438,27 +438,60 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
       g.alpha = p.alpha;       // one configuration per group (instances of one net share it)
       g.epsilon = p.epsilon;
     }
-    const int np_max = (n_max + kInitPair - 1) / kInitPair * kInitPair;
-    const int tiles = np_max / 32;
+    const int np_max = (int)align_up(n_max, kInitPad), rq_max = (int)align_up(r_max, 16);
     InitGroup* gd = calls[done].p->init_group;
-    static_assert(sizeof(InitGroup) % sizeof(uint32_t) == 0, "copied word by word");
+    static_assert(sizeof(InitGroup) % sizeof(uint32_t) == 0 && sizeof(InitGroup) <= 4096, "copied word by word");
     hipLaunchKernelGGL(init_store_group_kernel, dim3(1), dim3(256), 0, s, g, gd);
     LAUNCH_CHECK();
-    hipLaunchKernelGGL(init_gram_kernel, dim3(tiles, tiles, n), dim3(256), 0, s, gd);
+    {
+      FillGroup fg;
+      fg.count = n;
+      std::vector<GemmDesc> rows, cols;
+      for (int i = 0; i < n; ++i) {
+        const InitArgs& a = g.a[i];
+        fg.ptr[i] = reinterpret_cast<uint32_t*>(a.A);
+        fg.n[i] = (size_t)a.np * a.np * 2;
+        GemmDesc d;
+        d.A = a.M; d.lda = a.ld;
+        d.C = a.A; d.ldc = a.np;
+        d.M = a.n;
+        d.K = a.use_cov ? a.N : a.D;
+        (a.use_cov ? cols : rows).push_back(d);
+      }
+      hipLaunchKernelGGL(fill_zero_group_kernel, dim3((unsigned)std::min<size_t>(((size_t)np_max * np_max * 2 + 2047) / 2048, 256), n),
+                         dim3(256), 0, s, fg);
+      LAUNCH_CHECK();
+      if (!rows.empty()) HIP_TRY(launch_sym_gram<true>(rows.data(), (int)rows.size(), s));
+      if (!cols.empty()) HIP_TRY(launch_sym_gram<false>(cols.data(), (int)cols.size(), s));
+      hipLaunchKernelGGL(init_mirror_kernel, dim3(np_max / 32, np_max / 32, n), dim3(256), 0, s, gd);
+      LAUNCH_CHECK();
+    }
+    for (int j = 0; j < n_max - kTriTail; ++j) {
+      const int groups = (n_max - j - 1 + 4 * kTriRows - 1) / (4 * kTriRows);
+      if (np_max <= kTriLdsCols) {
+        hipLaunchKernelGGL(init_tri_step_kernel, dim3(groups, n), dim3(256), 3 * np_max * sizeof(double), s, gd, j, 3);
+      } else {
+        hipLaunchKernelGGL(init_tri_step_kernel, dim3(1, n), dim3(256), 0, s, gd, j, 1);
+        hipLaunchKernelGGL(init_tri_step_kernel, dim3(groups, n), dim3(256), 0, s, gd, j, 2);
+      }
+    }
+    hipLaunchKernelGGL(init_tri_tail_kernel, dim3(n), dim3(1024), kTriTailLds, s, gd);
     LAUNCH_CHECK();
-    hipLaunchKernelGGL(init_scale_kernel, dim3(n), dim3(256), 0, s, gd);
+    hipLaunchKernelGGL(init_eigenvalue_kernel, dim3(r_max, n), dim3(64), 0, s, gd);
     LAUNCH_CHECK();
-    // block Jacobi: every instance runs its own sweeps of (blocks) rounds inside the common launches and
-    // drops out (its workgroups return at once) after a sweep without a rotation
-    const int pairs_max = np_max / kInitPair, rounds_per_sweep = 2 * pairs_max;   // inside round + round-robin
-    for (int r = 0; r < kInitMaxSweeps * rounds_per_sweep; ++r) {
-      hipLaunchKernelGGL(init_block_solve_kernel, dim3(pairs_max, n), dim3(1024), kInitSolveLds, s, gd, r);
-      hipLaunchKernelGGL(init_block_apply_kernel, dim3(2 * pairs_max, pairs_max, n), dim3(256), 0, s, gd, r, pairs_max);
+    hipLaunchKernelGGL(init_eigenvector_kernel, dim3((rq_max + 63) / 64, n), dim3(64), 0, s, gd);
+    LAUNCH_CHECK();
+    for (int second = 0; second < 2; ++second) {
+      hipLaunchKernelGGL(init_ortho_gram_kernel, dim3(rq_max / 16, rq_max / 16, n), dim3(256), 0, s, gd, second);
+      hipLaunchKernelGGL(init_ortho_factor_kernel, dim3(n), dim3(1024), 0, s, gd);
+      hipLaunchKernelGGL(init_ortho_apply_kernel, dim3(np_max / 64, n), dim3(256), 0, s, gd, second);
     }
     LAUNCH_CHECK();
-    hipLaunchKernelGGL(init_select_kernel, dim3(n), dim3(1024), 0, s, gd);
+    hipLaunchKernelGGL(init_back_kernel, dim3((r_max + 3) / 4, n), dim3(256), 0, s, gd);
     LAUNCH_CHECK();
-    hipLaunchKernelGGL(init_rows_kernel, dim3((ldw_max + 63) / 64, r_max, n), dim3(256), 0, s, gd);
+    hipLaunchKernelGGL(init_select_kernel, dim3(n), dim3(256), 0, s, gd);
+    LAUNCH_CHECK();
+    hipLaunchKernelGGL(init_rows_kernel, dim3((ldw_max + 63) / 64, n), dim3(256), 0, s, gd);
     LAUNCH_CHECK();
     hipLaunchKernelGGL(init_complete_kernel, dim3(n), dim3(1024), 0, s, gd);
     LAUNCH_CHECK();

@@ -109,6 +109,44 @@ def test_free_running_from_device_initialisation(ngsgd, N, D, R):
             compare_states(torch, pre, ora, rng)
 
 
+@pytest.mark.parametrize("N,D,R", [(9, 12, 1), (40, 9, 8), (64, 65, 16), (65, 64, 17), (127, 300, 33), (128, 128, 32), (129, 140, 48), (140, 129, 3),
+                                   (192, 500, 80), (193, 193, 96), (300, 257, 20), (520, 700, 64), (700, 600, 90), (1030, 1100, 31),
+                                   (2113, 2180, 12)])
+def test_initial_factor(ngsgd, N, D, R):
+    """The factor built from the first minibatch, which the first call applies: both routes (matrix of rows, matrix of
+    columns) at the edges of the column blocks, below and above the size whose tridiagonal reduction fits into LDS,
+    and beyond what the back transformation holds in registers and the reduction's vectors in LDS."""
+    import torch
+    rng = np.random.default_rng(77 + N + 3 * D)
+    ora = OnlineNaturalGradient(D, R, num_samples_history=500.0, update_period=1)
+    pre = ngsgd.Preconditioner(D, R, max_batch=N + 3, num_samples_history=500.0, update_period=1)
+    M = data(rng, N, D, decay=0.985)
+    expect, g_o, rn_o = ora.precondition(M)
+    got, g_g, rn_g = gpu_call(torch, pre, M)
+    assert rel(got, expect) < 1e-5      # fp32 products of a matrix and its factor
+    assert g_g == pytest.approx(g_o, rel=1e-5)
+    assert rel(rn_g, rn_o) < 2e-5
+
+
+@pytest.mark.parametrize("N,D,R,groups", [(96, 300, 20, 3), (200, 150, 40, 7), (260, 400, 24, 24), (512, 600, 80, 41)])
+def test_initial_factor_of_equal_eigenvalues(ngsgd, N, D, R, groups):
+    """Orthogonal directions in groups of equal strength, the cut between two groups: the eigenvectors of a group are any
+    basis of its space, the factor's action is unique."""
+    import torch
+    rng = np.random.default_rng(5 + N)
+    n = min(N, D)
+    q1, _ = np.linalg.qr(rng.standard_normal((N, n)))
+    q2, _ = np.linalg.qr(rng.standard_normal((D, n)))
+    level = np.minimum(np.arange(n) * groups // R, groups)      # R values in `groups` levels, the rest on one below them
+    M = ((q1 * (3.0 * 0.7 ** (level * 8.0 / groups))[None, :]) @ q2.T).astype(np.float32)
+    ora = OnlineNaturalGradient(D, R, num_samples_history=500.0, update_period=1)
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, num_samples_history=500.0, update_period=1)
+    expect, g_o, _ = ora.precondition(M)
+    got, g_g, _ = gpu_call(torch, pre, M)
+    assert rel(got, expect) < TOL
+    assert g_g == pytest.approx(g_o, rel=1e-4)
+
+
 def test_degenerate_first_minibatches(ngsgd):
     """Zero and rank-deficient first inputs: floors, gamma = 1 on a zero matrix, completion of R_0."""
     import torch
