@@ -4,15 +4,17 @@
 // The eigenproblem is solved on the smaller of the D x D covariance and the N x N Gram matrix (same
 // non-zero spectrum; an eigenvector u of the Gram matrix gives X_0^T u / sqrt(N lambda)), in fp64 throughout:
 //   1. Householder reduction to a tridiagonal matrix, Q^T A Q = T: one launch per column, each a pass over the
-//      trailing matrix by many workgroups; the last 128 columns in one launch with the matrix in LDS;
+//      trailing matrix by many workgroups; the last 160 columns in one launch with the matrix in registers;
 //   2. the R largest eigenvalues of T by multisection with Sturm counts, a wavefront each;
 //   3. their eigenvectors by inverse iteration from random vectors, a thread each, then orthonormalised together
 //      (twice, through the inverse Cholesky factor of their Gram matrix): vectors of equal eigenvalues start out
 //      independent and any orthonormal basis of their space serves;
 //   4. back with the reflections, four vectors per wavefront.
-// The error is a few eps |A| whatever the spectrum.  Bound: the chain of n - 128 launches (n = 512, ten instances of
-// the speech-shaped network: 384 x 5 us of 2.6 ms); a reduction needs no iteration, where the block Jacobi method this
-// replaces took 11 to 18 sweeps of 32 launches and did not settle on softmax derivatives within them (12.8 ms).
+// The error is a few eps |A| whatever the spectrum.  Bound: the chain of n - 160 launches.  Ten instances of the
+// speech-shaped network, five of them with n = 512: 3.6 ms, of it 352 launches of 14 us (reading and writing 2 MB per
+// instance) falling to 6 us (latency), the last 160 columns 0.38 ms, eigenvalues 0.14, inverse iteration 0.27,
+// orthonormalisation 0.2, back transformation 0.28, rows of W 0.11.  A reduction needs no iteration; block Jacobi took
+// 11 to 18 sweeps of 32 launches and did not settle on softmax derivatives within them (12.8 ms).
 // This runs once per process (and after each parameter-averaging round), never inside the steady-state step.
 #pragma once
 
@@ -43,7 +45,7 @@ struct InitArgs {
                        // eigenvectors, rq x np
   double* V;           // reflection j in row j (np x np), zero up to column j
   double* X;           // np x rq: eigenvectors of T
-  double* T;           // 8 np: vectors of the tridiagonal form
+  double* T;           // 11 np: vectors of the tridiagonal form
   int* idx;            // R: row of the eigenvector matrix for each kept eigenpair, -1 if the direction is null
   float* W;            // R x ldw
   int ldw;
@@ -55,7 +57,10 @@ struct InitArgs {
   __device__ double* off() const { return T + np; }
   __device__ double* tau() const { return T + 2 * np; }          // the reflections' factors
   __device__ double* y(const int parity) const { return T + (3 + parity) * (size_t)np; }   // A v of the last two columns
-  __device__ double* vec() const { return T + 5 * (size_t)np; }  // 3 np: used instead of LDS where that is too small
+  __device__ double* bounds() const { return T + 5 * (size_t)np; }   // interval that holds T's eigenvalues, largest magnitude in it
+  __device__ double* sdiag() const { return T + 6 * (size_t)np; }    // T scaled to unit norm: diagonal, squared off-diagonal
+  __device__ double* soff2() const { return T + 7 * (size_t)np; }
+  __device__ double* vec() const { return T + 8 * (size_t)np; }  // 3 np: used instead of LDS where that is too small
 };
 struct InitGroup {
   int count;
@@ -119,6 +124,11 @@ __device__ __forceinline__ double block256_sum_f64(double v, double* red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+__device__ __forceinline__ double reciprocal_f64(const double x) {   // hardware estimate, two Newton steps
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
 // Reflection that maps (x0, tail) to (beta, 0), sigma the sum of squares of the tail: I - tau v v^T with v = (1, scale tail).
 struct Reflection {
   double beta, tau, scale;
@@ -127,10 +137,15 @@ __device__ __forceinline__ Reflection reflection(const double x0, const double s
   Reflection h;
   h.beta = x0;
   h.tau = h.scale = 0.0;
-  if (sigma > 0.0) {
-    h.beta = x0 > 0.0 ? -sqrt(x0 * x0 + sigma) : sqrt(x0 * x0 + sigma);
-    h.tau = (h.beta - x0) / h.beta;
-    h.scale = 1.0 / (x0 - h.beta);
+  const double nn = fma(x0, x0, sigma);
+  if (sigma > 0.0 && nn > 1.0e-290) {   // (below: the column is zero)
+    double r = __builtin_amdgcn_rsq(nn);   // hardware estimate, two Newton steps
+    r = fma(0.5 * r, fma(-nn * r, r, 1.0), r);
+    r = fma(0.5 * r, fma(-nn * r, r, 1.0), r);
+    const double norm = nn * r, size = fabs(x0) + norm;
+    h.beta = x0 > 0.0 ? -norm : norm;
+    h.tau = fma(fabs(x0), r, 1.0);
+    h.scale = reciprocal_f64(x0 > 0.0 ? size : -size);
   }
   return h;
 }
@@ -142,9 +157,10 @@ __device__ __forceinline__ Reflection reflection(const double x0, const double s
 // first 512 columns of its rows are requested before anything else.
 // phases: 3 both; where three vectors do not fit into LDS (n > kTriLdsCols) 1, the vectors, to a.vec() by one workgroup
 // per instance, then 2.
-constexpr int kTriTail = 128;                 // columns left to the kernel that keeps the matrix in LDS
+constexpr int kTriTail = 160;                 // columns left to the kernel that keeps the matrix in registers
 constexpr int kTriRows = 4;                   // rows per wavefront
 constexpr int kTriChunks = 8;                 // 64-column chunks held in registers
+constexpr int kTriCols = 2;                   // columns per thread requested together in the vector phase
 constexpr int kTriLdsCols = 2048;
 __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __restrict__ gp, const int j, const int phases) {
   const InitArgs& a = gp->a[blockIdx.y];
@@ -176,31 +192,53 @@ __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __r
     const double* const v = a.V + (size_t)(j > 0 ? j - 1 : 0) * np;
     const double* const y = a.y((j & 1) ^ 1);
     const double* const rowj = a.A + (size_t)j * np;
-    double tau = 0.0, half = 0.0, vj = 0.0, wj = 0.0;
+    const int b0 = j & ~63;
+    double tau = 0.0, vj = 0.0, yj = 0.0;
+    if (j > 0) {
+      tau = a.tau()[j - 1];
+      vj = v[j];
+      yj = y[j];
+    }
+    // this thread's columns: the first kTriCols of them are requested together
+    double pv[kTriCols], py[kTriCols], px[kTriCols];
+#pragma unroll
+    for (int t = 0; t < kTriCols; ++t) {
+      const int c = b0 + tid + 256 * t;
+      const bool in = c >= j && c < n;
+      pv[t] = in && j > 0 ? v[c] : 0.0;
+      py[t] = in && j > 0 ? y[c] : 0.0;
+      px[t] = in ? rowj[c] : 0.0;
+    }
+    double half = 0.0;
     if (j > 0) {
       double s = 0.0;
-      for (int c = j + tid; c < n; c += 256) s += y[c] * v[c];
-      tau = a.tau()[j - 1];
+#pragma unroll
+      for (int t = 0; t < kTriCols; ++t) s += py[t] * pv[t];
+      for (int c = b0 + tid + 256 * kTriCols; c < n; c += 256) s += y[c] * v[c];
       half = 0.5 * tau * tau * block256_sum_f64(s, red[0]);
-      vj = v[j];
-      wj = tau * y[j] - half * vj;
     }
+    const double wj = tau * yj - half * vj;
     double sigma = 0.0;
-    for (int c = (j & ~63) + tid; c < np; c += 256) {
-      const bool in = c >= j && c < n;
-      const double vc = in && j > 0 ? v[c] : 0.0;
-      const double wc = in && j > 0 ? tau * y[c] - half * vc : 0.0;
-      const double x = in ? rowj[c] - vj * wc - wj * vc : 0.0;
+    auto column = [&](const int c, const double vc, const double yc, const double xc) {
+      const double wc = tau * yc - half * vc;
+      const double x = xc - vj * wc - wj * vc;
       vo[c] = vc;
       wo[c] = wc;
       vn[c] = x;
       if (c > j + 1) sigma += x * x;
+    };
+#pragma unroll
+    for (int t = 0; t < kTriCols; ++t)
+      if (b0 + tid + 256 * t < np) column(b0 + tid + 256 * t, pv[t], py[t], px[t]);
+    for (int c = b0 + tid + 256 * kTriCols; c < np; c += 256) {
+      const bool in = c < n;
+      column(c, in && j > 0 ? v[c] : 0.0, in && j > 0 ? y[c] : 0.0, in ? rowj[c] : 0.0);
     }
     sigma = block256_sum_f64(sigma, red[1]);   // also makes vn visible to all
     const Reflection h = reflection(vn[j + 1], sigma);
     const double dj = vn[j];
     __syncthreads();
-    for (int c = (j & ~63) + tid; c < np; c += 256) vn[c] = c > j + 1 ? vn[c] * h.scale : (c == j + 1 ? 1.0 : 0.0);
+    for (int c = b0 + tid; c < np; c += 256) vn[c] = c > j + 1 ? vn[c] * h.scale : (c == j + 1 ? 1.0 : 0.0);
     if (blockIdx.x == 0 && tid == 0) {
       a.diag()[j] = dj;
       a.off()[j] = h.beta;
@@ -240,152 +278,203 @@ __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __r
   }
 }
 
-// The last (at most 128) columns, the matrix in LDS: eight threads per row, 16 columns each.  Also divides T by N.
-// One workgroup of 1024 threads per instance.
-constexpr int kTriTailLd = kTriTail + 8;   // eight rows by eight columns touch every bank once
-constexpr int kTriTailLds = (kTriTail * kTriTailLd + 3 * kTriTail) * (int)sizeof(double);
-__global__ __launch_bounds__(1024) void init_tri_tail_kernel(const InitGroup* __restrict__ gp) {
+// The last (at most 160) columns, the matrix in registers: 16 x 16 threads, thread (ti, tj) holds rows ti + 16 a and columns
+// tj + 16 b as a 10 x 10 tile.  Two barriers per column: row j is
+// published, every wavefront forms the reflection for itself; the products are published, every wavefront forms w for
+// itself.  Row blocks that are done are skipped (a branch per element costs more than the finished columns).  Bound: fp64 multiply-adds, then the chain of two sums over
+// the workgroup per column.  (1024 threads spend their time on the parts that every wavefront repeats: 2.7 us a column
+// with 4 x 4 tiles of 128 columns, 3.9 us with 6 x 6 of 192; a 12 x 12 tile no longer fits into 256 registers: 2.8 us.)  Also divides T by N and scales it for the kernels that
+// follow.  One workgroup of 256 threads per instance.
+constexpr int kTriTile = kTriTail / 16;
+__global__ __launch_bounds__(256) void init_tri_tail_kernel(const InitGroup* __restrict__ gp) {
   const InitArgs& a = gp->a[blockIdx.x];
-  constexpr int T = kTriTail, LD = kTriTailLd;
-  extern __shared__ double dyn_tri[];
-  double* const S = dyn_tri;
-  double* const sv = S + T * LD;
-  double* const sy = sv + T;
-  double* const sw = sy + T;
-  __shared__ double s_tau;
+  constexpr int T = kTriTail, K = kTriTile;
+  constexpr int TP = (T + 63) / 64 * 64;   // the vectors are padded with zeros for a wavefront's lanes
+  static_assert(T % 16 == 0 && T <= 256, "tile and lane counts");
+  __shared__ double srow[TP], sy[TP], scratch[16];
+  __shared__ double sv[4][TP], sw[4][TP];   // every wavefront's own copy of v and w
   const int n = a.n, np = a.np, j0 = max(0, n - T), m = n - j0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = tid >> 3, q8 = tid & 7;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ti = tid >> 4, tj = tid & 15;
   const double inv_n = 1.0 / (double)a.N;
-  for (int e = tid; e < T * T; e += 1024) {
-    const int i = e >> 7, c = e & (T - 1);
-    S[i * LD + c] = i < m && c < m ? a.A[(size_t)(j0 + i) * np + j0 + c] : 0.0;
-  }
-  if (tid < T) {
-    const bool in = j0 > 0 && tid < m;
-    sv[tid] = in ? a.V[(size_t)(j0 - 1) * np + j0 + tid] : 0.0;
-    sy[tid] = in ? a.y((j0 - 1) & 1)[j0 + tid] : 0.0;
-  }
-  for (int i = tid; i < j0; i += 1024) {
+  double* const v = sv[wave];
+  double* const w = sw[wave];
+  double S[K][K];
+#pragma unroll
+  for (int x = 0; x < K; ++x)
+#pragma unroll
+    for (int b = 0; b < K; ++b) {
+      const int i = ti + 16 * x, c = tj + 16 * b;
+      S[x][b] = i < m && c < m ? a.A[(size_t)(j0 + i) * np + j0 + c] : 0.0;
+    }
+  // the last column that the other kernel took (none: a reflection with tau = 0)
+  double tau = j0 > 0 ? a.tau()[j0 - 1] : 0.0;
+  for (int c = lane; c < TP; c += 64) v[c] = j0 > 0 && c < T ? a.V[(size_t)(j0 - 1) * np + j0 + c] : 0.0;   // j0 > 0: all T columns exist
+  if (tid < TP) srow[tid] = 0.0;
+  if (tid < TP) sy[tid] = j0 > 0 && tid < T ? a.y((j0 - 1) & 1)[j0 + tid] : 0.0;
+  for (int i = tid; i < j0; i += 256) {
     a.diag()[i] *= inv_n;
     a.off()[i] *= inv_n;
   }
-  double tau = j0 > 0 ? a.tau()[j0 - 1] : 0.0;
   __syncthreads();
-  for (int jj = -1; jj < m - 1; ++jj) {
-    // sv, sy and tau belong to column jj (before the first: to the last column of the other kernel)
-    const double dot = wave_sum_uniform(sy[lane] * sv[lane] + sy[lane + 64] * sv[lane + 64]);
-    const double half = 0.5 * tau * tau * dot;
-    if (tid < T) sw[tid] = tau * sy[tid] - half * sv[tid];
-    __syncthreads();
-    const int k_lo = (jj + 1) >> 3;   // columns below jj + 1 are done
+  for (int j = 0;; ++j) {
+    // A <- A - v w^T - w v^T with the reflection of column j - 1, whose product A v is in sy
     {
-      const double vr = sv[r], wr = sw[r];
-#pragma unroll 4
-      for (int k = k_lo; k < T / 8; ++k) {
-        const int c = 8 * k + q8;
-        S[r * LD + c] -= vr * sw[c] + wr * sv[c];
+      double yl[TP / 64], vl[TP / 64], dot = 0.0;
+#pragma unroll
+      for (int t = 0; t < TP / 64; ++t) {
+        yl[t] = sy[lane + 64 * t];
+        vl[t] = v[lane + 64 * t];
+        dot = fma(yl[t], vl[t], dot);
+      }
+      const double half = 0.5 * tau * tau * wave_sum_uniform(dot);
+#pragma unroll
+      for (int t = 0; t < TP / 64; ++t) w[lane + 64 * t] = fma(tau, yl[t], -half * vl[t]);
+    }
+    __builtin_amdgcn_wave_barrier();   // LDS operations of a wavefront are performed in order
+    {
+      double vc[K], wc[K];
+#pragma unroll
+      for (int b = 0; b < K; ++b) {
+        vc[b] = v[tj + 16 * b];
+        wc[b] = w[tj + 16 * b];
+      }
+#pragma unroll
+      for (int x = 0; x < K; ++x) {
+        if (16 * x + 15 < j) continue;   // uniform
+        const double vr = v[ti + 16 * x], wr = w[ti + 16 * x];
+#pragma unroll
+        for (int b = 0; b < K; ++b) S[x][b] = fma(-vr, wc[b], fma(-wr, vc[b], S[x][b]));
+        if (x == j >> 4 && ti == (j & 15)) {
+#pragma unroll
+          for (int b = 0; b < K; ++b) srow[tj + 16 * b] = S[x][b];
+        }
       }
     }
     __syncthreads();
-    const int j = jj + 1;
-    if (j >= m - 1) break;
-    if (wave == 0) {   // row j is final: the next reflection
-      const double x0 = lane > j ? S[j * LD + lane] : 0.0, x1 = lane + 64 > j ? S[j * LD + lane + 64] : 0.0;
-      const double sigma = wave_sum_uniform((lane > j + 1 ? x0 * x0 : 0.0) + (lane + 64 > j + 1 ? x1 * x1 : 0.0));
-      const Reflection h = reflection(S[j * LD + j + 1], sigma);
-      sv[lane] = lane == j + 1 ? 1.0 : x0 * h.scale;
-      sv[lane + 64] = lane + 64 == j + 1 ? 1.0 : x1 * h.scale;
-      if (lane == 0) {
-        s_tau = h.tau;
-        a.diag()[j0 + j] = S[j * LD + j] * inv_n;
-        a.off()[j0 + j] = h.beta * inv_n;
-        a.tau()[j0 + j] = h.tau;
-      }
+    if (tid == 0) a.diag()[j0 + j] = srow[j] * inv_n;
+    if (j == m - 1) break;
+    double xl[TP / 64], sigma = 0.0;
+#pragma unroll
+    for (int t = 0; t < TP / 64; ++t) {
+      xl[t] = lane + 64 * t > j + 1 ? srow[lane + 64 * t] : 0.0;
+      sigma = fma(xl[t], xl[t], sigma);
     }
-    __syncthreads();
-    tau = s_tau;
-    double acc = 0.0;
-    const int k_new = (j + 1) >> 3;
-#pragma unroll 4
-    for (int k = k_new; k < T / 8; ++k) acc += S[r * LD + 8 * k + q8] * sv[8 * k + q8];
-    acc = dpp_add_f64<0xB1>(acc);
-    acc = dpp_add_f64<0x4E>(acc);
-    acc = dpp_add_f64<0x141>(acc);   // eight lanes
-    if (q8 == 0) sy[r] = r > j ? acc : 0.0;
-    for (int c = tid; c < np; c += 1024) {
-      const int l = c - j0;
-      a.V[(size_t)(j0 + j) * np + c] = l > j && l < m ? sv[l] : 0.0;
+    const Reflection h = reflection(srow[j + 1], wave_sum_uniform(sigma));
+    tau = h.tau;
+    if (tid == 0) {
+      a.off()[j0 + j] = h.beta * inv_n;
+      a.tau()[j0 + j] = h.tau;
+    }
+    double* const Vj = a.V + (size_t)(j0 + j) * np;
+#pragma unroll
+    for (int t = 0; t < TP / 64; ++t) {
+      const int c = lane + 64 * t;
+      xl[t] = c == j + 1 ? 1.0 : xl[t] * h.scale;
+      v[c] = xl[t];
+      if (wave == 0 && j0 + c < n) Vj[j0 + c] = xl[t];
+    }
+    for (int c = tid; c < np; c += 256)
+      if (c < j0 || c >= n) Vj[c] = 0.0;
+    __builtin_amdgcn_wave_barrier();
+    double vc[K], acc[K];
+#pragma unroll
+    for (int b = 0; b < K; ++b) vc[b] = v[tj + 16 * b];
+#pragma unroll
+    for (int x = 0; x < K; ++x) {
+      acc[x] = 0.0;
+      if (16 * x + 15 <= j) continue;
+#pragma unroll
+      for (int b = 0; b < K; ++b) acc[x] = fma(S[x][b], vc[b], acc[x]);
+      acc[x] = row16_sum_f64(acc[x]);
+    }
+    if (tj == 0) {
+#pragma unroll
+      for (int x = 0; x < K; ++x) sy[ti + 16 * x] = ti + 16 * x > j ? acc[x] : 0.0;
     }
     __syncthreads();
   }
-  if (tid == 0) {
-    a.diag()[n - 1] = S[(m - 1) * LD + m - 1] * inv_n;
-    a.off()[n - 1] = 0.0;
-  }
-}
-
-__device__ __forceinline__ double reciprocal_f64(const double x) {   // hardware estimate, two Newton steps
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
-}
-// interval that holds the eigenvalues of T (Gershgorin), all lanes of a wavefront together
-__device__ __forceinline__ void tri_bounds(const InitArgs& a, const int lane, double& lo, double& hi) {
-  lo = 1.0e300;
-  hi = -1.0e300;
-  for (int i = lane; i < a.n; i += 64) {
+  if (tid == 0) a.off()[n - 1] = 0.0;
+  __threadfence_block();
+  __syncthreads();
+  // interval that holds the eigenvalues (Gershgorin), and T scaled to unit norm; a squared off-diagonal of zero becomes
+  // negligibly small instead, so that the Sturm sequences never stop at a zero
+  double lo = 1.0e300, hi = -1.0e300;
+  for (int i = tid; i < n; i += 256) {
     const double radius = (i > 0 ? fabs(a.off()[i - 1]) : 0.0) + fabs(a.off()[i]), d = a.diag()[i];
     lo = fmin(lo, d - radius);
     hi = fmax(hi, d + radius);
   }
-  hi = wave_max_d(hi);
-  lo = -wave_max_d(-lo);
+  hi = block_max(hi, scratch);
+  lo = -block_max(-lo, scratch);
+  const double norm = fmax(fabs(lo), fabs(hi)), inv = norm > 0.0 ? 1.0 / norm : 0.0;
+  for (int i = tid; i < n; i += 256) {
+    const double e = a.off()[i] * inv;
+    a.sdiag()[i] = a.diag()[i] * inv;
+    a.soff2()[i] = fmax(e * e, 1.0e-60);
+  }
+  if (tid == 0) {
+    a.bounds()[0] = lo;
+    a.bounds()[1] = hi;
+    a.bounds()[2] = norm;
+  }
 }
 
 // Eigenvalue k (descending) of T: a wavefront counts the eigenvalues below 64 points of the interval at once, six bits
-// a pass.  Bound: the serial recurrence, n divisions a pass.  Grid (R, instance), 64 threads.
+// a pass.  The count is the number of sign changes of the leading minors of T - x, by their three-term recurrence (one
+// multiply-add on the critical path; with quotients instead, a reciprocal per step, 306 us for n = 512), rescaled every
+// eight steps: a step changes their size by at most a factor of four upwards and far less than 2^-128 downwards.
+// Grid (R, instance), 64 threads.
 constexpr int kSectionPasses = 12;
 __global__ __launch_bounds__(64) void init_eigenvalue_kernel(const InitGroup* __restrict__ gp) {
   const InitArgs& a = gp->a[blockIdx.y];
   const int k = blockIdx.x, lane = threadIdx.x, n = a.n;
   if (k >= a.R) return;
-  double lo, hi;
-  tri_bounds(a, lane, lo, hi);
-  const double norm = fmax(fabs(lo), fabs(hi));
-  const double margin = 2.0 * kInitEps * (double)n * norm;
-  const double piv_min = fmax(1.0e-290, 1.0e-290 * norm * norm);
-  lo -= margin;
-  hi += margin;
-  const double* __restrict__ d = a.diag();
-  const double* __restrict__ e = a.off();
+  const double norm = a.bounds()[2], inv = norm > 0.0 ? 1.0 / norm : 0.0;
+  const double margin = 2.0 * kInitEps * (double)n;
+  double lo = a.bounds()[0] * inv - margin, hi = a.bounds()[1] * inv + margin;
+  const double* __restrict__ d = a.sdiag();
+  const double* __restrict__ e2 = a.soff2();
   for (int pass = 0; pass < kSectionPasses; ++pass) {
     const double width = hi - lo;
-    if (!(width > 0.5 * kInitEps * norm)) break;
+    if (!(width > 0.5 * kInitEps)) break;
     const double step = width / 65.0, x = lo + step * (double)(lane + 1);
-    double q = d[0] - x;
-    int below = q < 0.0 ? 1 : 0;
-#pragma unroll 8
-    for (int i = 1; i < n; ++i) {
-      if (fabs(q) < piv_min) q = -piv_min;
-      q = fma(-(e[i - 1] * e[i - 1]), reciprocal_f64(q), d[i] - x);
-      below += q < 0.0 ? 1 : 0;
+    double p = d[0] - x, p1 = 1.0;
+    uint32_t below = (uint32_t)(__builtin_bit_cast(uint64_t, p) >> 63);
+    auto advance = [&](const int i) {
+      const double q = fma(d[i] - x, p, -(e2[i - 1] * p1));
+      below += (uint32_t)((__builtin_bit_cast(uint64_t, q) ^ __builtin_bit_cast(uint64_t, p)) >> 63);
+      p1 = p;
+      p = q;
+    };
+    int i = 1;
+    for (; i + 8 <= n; i += 8) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) advance(i + t);
+      const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(p1)));
+      p = __builtin_amdgcn_ldexp(p, ex);
+      p1 = __builtin_amdgcn_ldexp(p1, ex);
     }
-    const int m = __popcll(__ballot(below <= n - 1 - k));   // points at or below the eigenvalue
+    for (; i < n; ++i) advance(i);
+    const int m = __popcll(__ballot((int)below <= n - 1 - k));   // points at or below the eigenvalue
     const double base = lo;
     if (m > 0) lo = base + step * (double)m;
     if (m < 64) hi = base + step * (double)(m + 1);
   }
-  if (lane == 0) a.lam()[k] = 0.5 * (lo + hi);
+  if (lane == 0) a.lam()[k] = 0.5 * (lo + hi) * norm;
 }
 
 // Eigenvectors of T by inverse iteration: T - lambda = P L U with row exchanges once, then three solves from a random
 // vector.  A thread per vector; everything is laid out with the vector index running fastest.
 // Bound: the serial chains of n steps.  What they read does not depend on them, so every solve goes in blocks of eight
-// steps whose operands are requested a block ahead (900 us without, the loads being ordered behind the stores).
-// Grid (ceil(rq / 64), instance), 64 threads.
+// steps whose operands are requested a block ahead (n = 512, ten instances: 900 us with plain loops in device memory,
+// where every load waits behind the stores, 546 us in blocks, 270 us in blocks and LDS).
+// Where a few vectors' factors fit into LDS (40 bytes per element) a workgroup takes `count` vectors there, otherwise 64 in
+// device memory.  Grid (ceil(rq / count), instance), 64 threads.
 constexpr int kInverseSolves = 3;
+constexpr int kInverseLds = 150 * 1024, kInverseLdsMin = 4, kInverseLdsMax = 16;   // bytes; vectors of a workgroup
 constexpr int kInverseBlock = 8;
+constexpr int kInversePad = 3 * kInverseBlock;   // blocks are requested whole, and one ahead
+__host__ __device__ constexpr size_t inverse_lds_bytes(const int np) { return (5 * (size_t)(np + 2 * kInversePad) + 1) * sizeof(double); }
 __device__ __forceinline__ double inverse_start(const int i, const int k) {   // integer hash, uniform in [-1, 1)
   uint32_t h = (uint32_t)i * 0x9E3779B9u ^ (uint32_t)(k + 1) * 0x85EBCA6Bu;
   h = (h ^ (h >> 16)) * 0x7FEB352Du;
@@ -393,26 +482,28 @@ __device__ __forceinline__ double inverse_start(const int i, const int k) {   //
   h ^= h >> 16;
   return (double)(int32_t)h * (1.0 / 2147483648.0);
 }
-__global__ __launch_bounds__(64) void init_eigenvector_kernel(const InitGroup* __restrict__ gp) {
+template <bool LDS>
+__global__ __launch_bounds__(64) void init_eigenvector_kernel(const InitGroup* __restrict__ gp, const int count) {
   const InitArgs& a = gp->a[blockIdx.y];
   constexpr int B = kInverseBlock;
-  const int k = blockIdx.x * 64 + threadIdx.x, n = a.n, rq = a.rq;
-  if ((int)blockIdx.x * 64 >= rq) return;
-  double lo, hi;
-  tri_bounds(a, threadIdx.x, lo, hi);
-  const double norm = fmax(fabs(lo), fabs(hi));
-  if (k >= rq) return;
-  double* const __restrict__ X = a.X + k;
+  extern __shared__ double dyn_inv[];
+  const int k = blockIdx.x * count + threadIdx.x, n = a.n;
+  if ((int)threadIdx.x >= count || k >= a.rq) return;
+  const double norm = a.bounds()[2];
   const double lambda = k < a.R ? a.lam()[k] : 0.0;
   if (!(k < a.R && lambda > kNullEigRatio * a.lam()[0] && norm > 0.0)) {
-    for (int i = 0; i < n; ++i) X[(size_t)i * rq] = 0.0;
+    for (int i = 0; i < n; ++i) a.X[(size_t)i * a.rq + k] = 0.0;
     return;
   }
-  const size_t plane = (size_t)a.np * rq;
-  double* const __restrict__ r0 = a.A + k;   // 1 / diagonal of U, its two superdiagonals, multipliers of L (lowest bit: rows exchanged)
-  double* const __restrict__ u1 = a.A + k + plane;
-  double* const __restrict__ u2 = a.A + k + 2 * plane;
-  double* const __restrict__ ml = a.A + k + 3 * plane;
+  // In LDS a vector's factors are contiguous, kInversePad elements around each of the five rows, and the vectors an odd
+  // number of doubles apart; in device memory the vector index runs fastest.
+  const int rq = LDS ? 1 : a.rq;   // stride of an element
+  const size_t plane = LDS ? (size_t)(a.np + 2 * kInversePad) : (size_t)a.np * rq;
+  double* const __restrict__ r0 = LDS ? dyn_inv + threadIdx.x * (5 * plane + 1) + kInversePad : a.A + k;   // 1 / diagonal of U, its two superdiagonals,
+  double* const __restrict__ u1 = r0 + plane;                               // multipliers of L (lowest bit: rows exchanged)
+  double* const __restrict__ u2 = r0 + 2 * plane;
+  double* const __restrict__ ml = r0 + 3 * plane;
+  double* const __restrict__ X = LDS ? r0 + 4 * plane : a.X + k;
   const double* __restrict__ d = a.diag();
   const double* __restrict__ e = a.off();
   const double tiny = kInitEps * norm;
@@ -446,7 +537,7 @@ __global__ __launch_bounds__(64) void init_eigenvector_kernel(const InitGroup* _
       auto fetch = [&](const int i0, const int set) {   // steps beyond n - 2 are read from it and not taken
 #pragma unroll
         for (int t = 0; t < B; ++t) {
-          const size_t at = (size_t)min(i0 + t, n - 2) * rq;
+          const size_t at = (size_t)(LDS ? i0 + t : min(i0 + t, n - 2)) * rq;
           bl[set][t] = ml[at];
           bx[set][t] = X[at + rq];
         }
@@ -476,8 +567,8 @@ __global__ __launch_bounds__(64) void init_eigenvector_kernel(const InitGroup* _
     auto fetch = [&](const int i0, const int set) {   // rows i0, i0 - 1, ...; those below 0 are read from row 0 and not taken
 #pragma unroll
       for (int t = 0; t < B; ++t) {
-        const int i = max(i0 - t, 0);
-        const size_t at = (size_t)i * rq;
+        const int i = LDS ? i0 - t : max(i0 - t, 0);
+        const ptrdiff_t at = (ptrdiff_t)i * rq;
         b0[set][t] = r0[at];
         b1[set][t] = u1[at];
         b2[set][t] = u2[at];
@@ -505,7 +596,7 @@ __global__ __launch_bounds__(64) void init_eigenvector_kernel(const InitGroup* _
     scale = 1.0 / sqrt(ss);
   }
 #pragma unroll 8
-  for (int i = 0; i < n; ++i) X[(size_t)i * rq] *= scale;
+  for (int i = 0; i < n; ++i) a.X[(size_t)i * a.rq + k] = X[(size_t)i * rq] * scale;
 }
 
 // G = X^T X, a 16 x 16 tile per workgroup of four wavefronts.  Grid (rq/16, rq/16, instance).
@@ -592,36 +683,47 @@ __global__ __launch_bounds__(256) void init_ortho_apply_kernel(const InitGroup* 
 }
 
 // Eigenvectors of T -> of A: the reflections, last to first, on a vector per wavefront, which it holds in registers
-// (NC 64-element chunks).  Bound: the latency of n dependent inner products (four vectors per wavefront: 255 us for
-// n = 512 and ten instances).  Grid (ceil(R/4), instance), 256 threads.
+// (NC 64-element chunks; chunks where the reflection is zero are neither read nor touched).  Bound: the latency of n
+// dependent inner products, with the reflections requested four steps ahead.  Grid (ceil(R/4), instance), 256 threads.
+constexpr int kBackAhead = 4;
 template <int NC>
 __device__ __forceinline__ void init_back_registers(const InitArgs& a, double* __restrict__ xk, const int lane) {
   const int n = a.n, np = a.np;
   const double* __restrict__ V = a.V + lane;
   const double* __restrict__ tau = a.tau();
-  double x[NC], v[2][NC];
+  double x[NC], v[kBackAhead][NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) x[c] = 64 * c < np ? xk[64 * c + lane] : 0.0;
-  auto fetch = [&](const int j, const int set) {   // requested two steps ahead
+  auto live = [&](const int c, const int j) { return 64 * c < np && 64 * c + 63 > j; };
+  auto fetch = [&](const int j, const int set) {
+    if (j < 0) return;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) v[set][c] = 64 * c < np ? V[(size_t)max(j, 0) * np + 64 * c] : 0.0;
+    for (int c = 0; c < NC; ++c)
+      if (live(c, j)) v[set][c] = V[(size_t)j * np + 64 * c];
   };
   auto step = [&](const int j, const int set) {
     if (j < 0) return;
     double dot[2] = {0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < NC; ++c) dot[c & 1] = fma(v[set][c], x[c], dot[c & 1]);
+    for (int c = 0; c < NC; ++c)
+      if (live(c, j)) dot[c & 1] = fma(v[set][c], x[c], dot[c & 1]);
     const double f = tau[j] * wave_sum_uniform(dot[0] + dot[1]);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) x[c] = fma(-f, v[set][c], x[c]);
+    for (int c = 0; c < NC; ++c)
+      if (live(c, j)) x[c] = fma(-f, v[set][c], x[c]);
   };
-  fetch(n - 2, 0);
-  fetch(n - 3, 1);
-  for (int j = n - 2; j >= 0; j -= 2) {
-    step(j, 0);
-    fetch(j - 2, 0);
-    step(j - 1, 1);
-    fetch(j - 3, 1);
+#pragma unroll
+  for (int t = 0; t < kBackAhead; ++t) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) v[t][c] = 0.0;
+    fetch(n - 2 - t, t);
+  }
+  for (int j = n - 2; j >= 0; j -= kBackAhead) {
+#pragma unroll
+    for (int t = 0; t < kBackAhead; ++t) {
+      step(j - t, t);
+      fetch(j - t - kBackAhead, t);
+    }
   }
 #pragma unroll
   for (int c = 0; c < NC; ++c)

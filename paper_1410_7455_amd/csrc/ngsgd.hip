@@ -203,7 +203,7 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.Ai = c.take<double>(std::max(np_init * np_init, 4 * np_init * rq));
   p.Vi = c.take<double>(np_init * np_init);
   p.Xi = c.take<double>(np_init * rq + rq * rq + rq);
-  p.ti = c.take<double>(8 * np_init);
+  p.ti = c.take<double>(11 * np_init);
   p.init_group = c.take<InitGroup>(1);
   p.idx = c.take<int>(kMaxRank);
   p.vwork = c.take<double>((size_t)kMaxRank + D);
@@ -263,8 +263,8 @@ int ensure_kernel_attributes() {
   }
   HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(init_tri_step_kernel),
                               hipFuncAttributeMaxDynamicSharedMemorySize, 3 * kTriLdsCols * (int)sizeof(double)));
-  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(init_tri_tail_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kTriTailLds));
+  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(init_eigenvector_kernel<true>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kInverseLds));
   g_attr_done = true;
   return NGSGD_OK;
 }
@@ -475,11 +475,17 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
         hipLaunchKernelGGL(init_tri_step_kernel, dim3(groups, n), dim3(256), 0, s, gd, j, 2);
       }
     }
-    hipLaunchKernelGGL(init_tri_tail_kernel, dim3(n), dim3(1024), kTriTailLds, s, gd);
+    hipLaunchKernelGGL(init_tri_tail_kernel, dim3(n), dim3(256), 0, s, gd);
     LAUNCH_CHECK();
     hipLaunchKernelGGL(init_eigenvalue_kernel, dim3(r_max, n), dim3(64), 0, s, gd);
     LAUNCH_CHECK();
-    hipLaunchKernelGGL(init_eigenvector_kernel, dim3((rq_max + 63) / 64, n), dim3(64), 0, s, gd);
+    const int lds_vectors = std::min(kInverseLdsMax, (int)(kInverseLds / inverse_lds_bytes(np_max)));
+    if (lds_vectors >= kInverseLdsMin) {
+      hipLaunchKernelGGL(init_eigenvector_kernel<true>, dim3((rq_max + lds_vectors - 1) / lds_vectors, n), dim3(64),
+                         inverse_lds_bytes(np_max) * lds_vectors, s, gd, lds_vectors);
+    } else {
+      hipLaunchKernelGGL(init_eigenvector_kernel<false>, dim3((rq_max + 63) / 64, n), dim3(64), 0, s, gd, 64);
+    }
     LAUNCH_CHECK();
     for (int second = 0; second < 2; ++second) {
       hipLaunchKernelGGL(init_ortho_gram_kernel, dim3(rq_max / 16, rq_max / 16, n), dim3(256), 0, s, gd, second);

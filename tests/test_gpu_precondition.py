@@ -109,8 +109,8 @@ def test_free_running_from_device_initialisation(ngsgd, N, D, R):
             compare_states(torch, pre, ora, rng)
 
 
-@pytest.mark.parametrize("N,D,R", [(9, 12, 1), (40, 9, 8), (64, 65, 16), (65, 64, 17), (127, 300, 33), (128, 128, 32), (129, 140, 48), (140, 129, 3),
-                                   (192, 500, 80), (193, 193, 96), (300, 257, 20), (520, 700, 64), (700, 600, 90), (1030, 1100, 31),
+@pytest.mark.parametrize("N,D,R", [(9, 12, 1), (40, 9, 8), (64, 65, 16), (65, 64, 17), (127, 300, 33), (128, 128, 32), (129, 140, 48), (140, 129, 3), (160, 161, 20), (161, 160, 33), (162, 170, 9),
+                                   (191, 400, 20), (192, 500, 80), (193, 193, 96), (300, 257, 20), (520, 700, 64), (700, 600, 90), (960, 1000, 16), (1030, 1100, 31),
                                    (2113, 2180, 12)])
 def test_initial_factor(ngsgd, N, D, R):
     """The factor built from the first minibatch, which the first call applies: both routes (matrix of rows, matrix of
@@ -126,6 +126,22 @@ def test_initial_factor(ngsgd, N, D, R):
     assert rel(got, expect) < 1e-5      # fp32 products of a matrix and its factor
     assert g_g == pytest.approx(g_o, rel=1e-5)
     assert rel(rn_g, rn_o) < 2e-5
+
+
+@pytest.mark.parametrize("first,second", [(300, 201), (201, 300), (130, 70), (161, 159)])
+def test_initial_factor_after_a_reset(ngsgd, first, second):
+    """A second initialisation in the same workspace with another number of rows."""
+    import torch
+    D, R = 340, 24
+    rng = np.random.default_rng(first)
+    pre = ngsgd.Preconditioner(D, R, max_batch=300, num_samples_history=500.0, update_period=1)
+    for N in (first, second):
+        ora = OnlineNaturalGradient(D, R, num_samples_history=500.0, update_period=1)
+        M = data(rng, N, D, decay=0.985)
+        expect, _, _ = ora.precondition(M)
+        pre.reset()
+        got, _, _ = gpu_call(torch, pre, M)
+        assert rel(got, expect) < 1e-5
 
 
 @pytest.mark.parametrize("N,D,R,groups", [(96, 300, 20, 3), (200, 150, 40, 7), (260, 400, 24, 24), (512, 600, 80, 41)])
