@@ -1108,7 +1108,7 @@ int simple_many(const std::vector<SimpleCall>& calls, bool scale_output, hipStre
       LAUNCH_CHECK();
       const int wg = (nblk_max + 1) / 2;
       for (int k = 0; k < nblk_max; ++k) {
-        hipLaunchKernelGGL(simple_sweep_kernel, dim3(wg + 1, wg, cnt), dim3(256), 0, s, g, k);   // + look-ahead column
+        hipLaunchKernelGGL(simple_sweep_kernel, dim3(wg + 1, wg, cnt), dim3(256), 0, s, g, k);   // look-ahead column first
         LAUNCH_CHECK();
       }
     }

@@ -48,47 +48,56 @@ struct SimpleGroup {
   SimpleArgs a[kSimpleMaxGroup];
 };
 
-// Gauss-Jordan inversion of a 32 x 32 positive-definite block by a workgroup of 256 threads, without pivoting.
+// Gauss-Jordan inversion of a 32 x 32 positive-definite block by a workgroup of 256 threads, without pivoting, two
+// pivots at a time (their 2 x 2 block is positive definite as well: one reciprocal, of its determinant).
 // Thread (c = tid % 32, r0 = tid / 32) holds column c of rows r0, r0+8, r0+16, r0+24 in cur[] on entry (the
-// block) and on exit (its inverse).  A step only needs the pivot row and the pivot column, which their owners
+// block) and on exit (its inverse).  A step only needs the two pivot rows and pivot columns, which their owners
 // publish (for the next step, into the other pair of arrays) as soon as they have them: one barrier and a few
-// LDS words per step, and the arithmetic is branch-free.  sRow, sCol: LDS, [2][32] each.
-__device__ __forceinline__ void invert_block_32(double (&cur)[4], double (*sRow)[kSimpleBlock],
-                                                double (*sCol)[kSimpleBlock]) {
+// LDS words per step, and the arithmetic is branch-free.  Bound: the latency of 16 such steps (32 with one pivot each:
+// the elimination launch below, which waits for this chain, took 12.4 us, now 8.2).
+struct PivotPair {
+  double row[2][kSimpleBlock];      // rows p and p + 1
+  double col[kSimpleBlock][2];      // columns p and p + 1
+};
+__device__ __forceinline__ void invert_block_32(double (&cur)[4], PivotPair (&pub)[2]) {
   constexpr int B = kSimpleBlock;
   const int tid = threadIdx.x, c = tid & 31, r0 = tid >> 5;
+  auto publish = [&](PivotPair& to, const int p, const double row_value) {   // row_value: cur[p / 8]
+    if (r0 == (p & 7)) to.row[0][c] = row_value;
+    if (r0 == ((p + 1) & 7)) to.row[1][c] = row_value;
+    if ((c & ~1) == p) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (r0 + 8 * q == 0) sRow[0][c] = cur[q];
-    if (c == 0) sCol[0][r0 + 8 * q] = cur[q];
-  }
+      for (int q = 0; q < 4; ++q) to.col[r0 + 8 * q][c & 1] = cur[q];
+    }
+  };
+  publish(pub[0], 0, cur[0]);
   __syncthreads();
-  for (int p = 0; p < B; ++p) {
-    const int par = p & 1;
-    const double piv = sRow[par][p];
-    const double rv = sRow[par][c];
-    double colv[4];
+  for (int p = 0; p < B; p += 2) {
+    const PivotPair& in = pub[(p >> 1) & 1];
+    const double aa = in.row[0][p], ab = in.row[0][p + 1], ba = in.row[1][p], bb = in.row[1][p + 1];
+    const double v0 = in.row[0][c], v1 = in.row[1][c];
+    double x0[4], x1[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) colv[q] = sCol[par][r0 + 8 * q];
-    double inv = __builtin_amdgcn_rcp(piv);        // hardware estimate, two Newton steps
-    inv = fma(fma(-piv, inv, 1.0), inv, inv);
-    inv = fma(fma(-piv, inv, 1.0), inv, inv);
-    const double rowv = rv * inv;
-    const double on_row = c == p ? inv : rowv;
+    for (int q = 0; q < 4; ++q) {
+      x0[q] = in.col[r0 + 8 * q][0];
+      x1[q] = in.col[r0 + 8 * q][1];
+    }
+    const double det = fma(aa, bb, -(ab * ba));
+    double inv = __builtin_amdgcn_rcp(det);        // hardware estimate, two Newton steps
+    inv = fma(fma(-det, inv, 1.0), inv, inv);
+    inv = fma(fma(-det, inv, 1.0), inv, inv);
+    // inverse of the pivot block times the pivot rows; in the pivot columns the inverse itself
+    const double u0 = c == p ? 1.0 : (c == p + 1 ? 0.0 : v0), u1 = c == p ? 0.0 : (c == p + 1 ? 1.0 : v1);
+    const double e0 = inv * fma(bb, u0, -(ab * u1)), e1 = inv * fma(aa, u1, -(ba * u0));
+    const bool pivot_col = (c & ~1) == p;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int r = r0 + 8 * q;
-      const double off_row = c == p ? -colv[q] * inv : fma(-colv[q], rowv, cur[q]);
-      cur[q] = r == p ? on_row : off_row;
+      const double off_row = fma(-x0[q], e0, fma(-x1[q], e1, pivot_col ? 0.0 : cur[q]));
+      cur[q] = r == p ? e0 : (r == p + 1 ? e1 : off_row);
     }
-    // row p+1 is register (p+1)/8 of the threads with r0 = (p+1) % 8; column p+1 is all four registers of two lanes
-    const int qn = (p + 1) >> 3;
-    const double next_row = qn == 0 ? cur[0] : (qn == 1 ? cur[1] : (qn == 2 ? cur[2] : cur[3]));
-    if (r0 == ((p + 1) & 7)) sRow[par ^ 1][c] = next_row;
-    if (c == p + 1) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sCol[par ^ 1][r0 + 8 * q] = cur[q];
-    }
+    const int qn = (p + 2) >> 3;   // rows p + 2 and p + 3 are the same register
+    publish(pub[((p >> 1) & 1) ^ 1], p + 2, qn == 0 ? cur[0] : (qn == 1 ? cur[1] : (qn == 2 ? cur[2] : cur[3])));
     __syncthreads();
   }
 }
@@ -101,7 +110,7 @@ __global__ __launch_bounds__(256) void simple_prepare_kernel(const SimpleGroup g
   const SimpleArgs& a = g.a[blockIdx.z];
   if ((int)blockIdx.x >= a.nblk || (int)blockIdx.y >= a.nblk) return;
   __shared__ double scratch[16];
-  __shared__ double sRow[2][kSimpleBlock], sCol[2][kSimpleBlock];
+  __shared__ PivotPair pub[2];
   const int tid = threadIdx.x, np = a.np, n = a.n;
   const double* __restrict__ S = a.buf[1];
   double t = 0.0;
@@ -130,7 +139,7 @@ __global__ __launch_bounds__(256) void simple_prepare_kernel(const SimpleGroup g
     blk[q] = v;
   }
   if (blockIdx.x == 0 && blockIdx.y == 0) {
-    invert_block_32(blk, sRow, sCol);
+    invert_block_32(blk, pub);
 #pragma unroll
     for (int q = 0; q < 4; ++q) a.pinv[0][tid + 256 * q] = blk[q];
   }
@@ -138,21 +147,23 @@ __global__ __launch_bounds__(256) void simple_prepare_kernel(const SimpleGroup g
 
 // One pivot block k of the blocked Gauss-Jordan inversion.  Grid (ceil(nblk_max/2) + 1, ceil(nblk_max/2), count),
 // 256 threads: wavefront w of workgroup (x, y) owns block (2y + w/2, 2x + w%2) and replaces it, using the inverse
-// P_k of the pivot block that the previous launch left in pinv[k % 2].  The one workgroup of the extra grid column
-// looks ahead: it forms the next pivot block (k+1, k+1) as this step leaves it and inverts it into pinv[(k+1) % 2],
-// so the 32-step elimination is done once per matrix and step, beside the block updates and not before them.
+// P_k of the pivot block that the previous launch left in pinv[k % 2].  The one workgroup of the extra first grid column
+// looks ahead: it forms the next pivot block (k+1, k+1) as this step leaves it (a 16 x 16 quadrant per wavefront) and
+// inverts it into pinv[(k+1) % 2], so the elimination is done once per matrix and step, beside the block updates and
+// not before them.  Its chain is the launch's time, so it is started first.
 // v_mfma_f64_16x16x4_f64: lane l supplies A[l%16][l/16] and B[l/16][l%16]; register r of lane l holds
 // row 4r + l/16, column l%16 of the 16 x 16 result.
 __global__ __launch_bounds__(256) void simple_sweep_kernel(const SimpleGroup g, const int k) {
   const SimpleArgs& a = g.a[blockIdx.z];
   const int nblk = a.nblk;
-  const bool ahead = blockIdx.x == gridDim.x - 1;
+  const bool ahead = blockIdx.x == 0;
+  const int bx = (int)blockIdx.x - 1;
   if (k >= nblk) return;                                                                  // uniform per workgroup
   if (ahead && (blockIdx.y != 0 || k + 1 >= nblk)) return;
-  if (!ahead && (2 * (int)blockIdx.x >= nblk || 2 * (int)blockIdx.y >= nblk)) return;
+  if (!ahead && (2 * bx >= nblk || 2 * (int)blockIdx.y >= nblk)) return;
   constexpr int B = kSimpleBlock;
   __shared__ double sP[B][B + 1];      // P_k
-  __shared__ double sRow[2][B], sCol[2][B];
+  __shared__ PivotPair pub[2];
   __shared__ double sT[4][B][B + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int np = a.np;
@@ -160,11 +171,51 @@ __global__ __launch_bounds__(256) void simple_sweep_kernel(const SimpleGroup g, 
   double* __restrict__ dst = a.buf[(k & 1) ^ 1];
   const size_t k0 = (size_t)k * B;
 
-  const int bi = ahead ? k + 1 : 2 * blockIdx.y + (wave >> 1), bj = ahead ? k + 1 : 2 * blockIdx.x + (wave & 1);
-  const bool active = ahead ? wave == 0 : (bi < nblk && bj < nblk);
   const int l16 = lane & 15, g4 = lane >> 4;
-  const size_t i0 = (size_t)bi * B, j0 = (size_t)bj * B;
   typedef double doublex4 __attribute__((ext_vector_type(4)));
+  if (ahead) {
+    const size_t d0 = k0 + B;
+    const int hi = (wave >> 1) * 16, hj = (wave & 1) * 16;
+    double bf[B / 4], af[B / 4];
+    doublex4 acc, t = {0, 0, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = tid + 256 * q;
+      sP[e >> 5][e & 31] = a.pinv[k & 1][e];
+      sT[0][e >> 5][e & 31] = src[(d0 + (e >> 5)) * np + k0 + (e & 31)];
+    }
+#pragma unroll
+    for (int ks = 0; ks < B / 4; ++ks) bf[ks] = src[(k0 + ks * 4 + g4) * np + d0 + hj + l16];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[r] = src[(d0 + hi + 4 * r + g4) * np + d0 + hj + l16];
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < B / 4; ++ks)
+      t = __builtin_amdgcn_mfma_f64_16x16x4f64(sT[0][hi + l16][ks * 4 + g4], sP[ks * 4 + g4][hj + l16], t, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sT[1][hi + 4 * r + g4][hj + l16] = t[r];
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < B / 4; ++ks) af[ks] = -sT[1][hi + l16][ks * 4 + g4];
+#pragma unroll
+    for (int ks = 0; ks < B / 4; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(af[ks], bf[ks], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sT[2][hi + 4 * r + g4][hj + l16] = acc[r];
+    __syncthreads();
+    double blk[4];   // the elimination's layout
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = tid + 256 * q;
+      blk[q] = sT[2][e >> 5][e & 31];
+    }
+    invert_block_32(blk, pub);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a.pinv[(k + 1) & 1][tid + 256 * q] = blk[q];
+    return;
+  }
+  const int bi = 2 * blockIdx.y + (wave >> 1), bj = 2 * bx + (wave & 1);
+  const bool active = bi < nblk && bj < nblk;
+  const size_t i0 = (size_t)bi * B, j0 = (size_t)bj * B;
 
   // everything this wavefront needs is requested up front: P_k, A_ik by rows (it goes to LDS), A_kj as B-operand
   // fragments, A_ij as accumulators
@@ -247,12 +298,10 @@ __global__ __launch_bounds__(256) void simple_sweep_kernel(const SimpleGroup g, 
     for (int e = lane; e < B * B; e += 64) sT[wave][e >> 5][e & 31] = -P[e >> 5][e & 31];
   }
   __syncthreads();
-  if (!active && !ahead) return;
+  if (!active) return;
 
   // new block: (bj != k)  C0 - T A_kj with C0 = A_ij (bi != k) or 0;   (bj == k)  -T
-  if (!active) {
-    // look-ahead workgroup, wavefronts 1..3: nothing to multiply
-  } else if (bj != k) {
+  if (bj != k) {
 #pragma unroll
     for (int ks = 0; ks < B / 4; ++ks) {
       double af[2];
@@ -271,28 +320,6 @@ __global__ __launch_bounds__(256) void simple_sweep_kernel(const SimpleGroup g, 
       for (int nj = 0; nj < 2; ++nj)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[mi][nj][r] = -sT[wave][mi * 16 + 4 * r + g4][nj * 16 + l16];
-  }
-  if (ahead) {
-    // the next pivot block is in wavefront 0's accumulators: through LDS to the elimination's layout, invert, publish
-    if (active) {
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int nj = 0; nj < 2; ++nj)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) sT[1][mi * 16 + 4 * r + g4][nj * 16 + l16] = acc[mi][nj][r];
-    }
-    __syncthreads();
-    double blk[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + 256 * q;
-      blk[q] = sT[1][e >> 5][e & 31];
-    }
-    invert_block_32(blk, sRow, sCol);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) a.pinv[(k + 1) & 1][tid + 256 * q] = blk[q];
-    return;
   }
   const bool last = k == nblk - 1;
 #pragma unroll
