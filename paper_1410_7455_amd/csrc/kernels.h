@@ -457,12 +457,16 @@ __global__ __launch_bounds__(1024) void finish_apply_kernel(const FinishGroup g)
   auto row_sum = [&](int r) -> double {
     float p0 = 0.f, p1 = 0.f;
     if (r < N) {
-      int c = part;
-      for (; c + 4 < nct; c += 8) {
-        p0 += a.rownorm_part[(size_t)c * N + r];
-        p1 += a.rownorm_part[(size_t)(c + 4) * N + r];
+      for (int c = part; c < nct; c += 32) {   // eight loads at a time: the latency of each batch is what this costs
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = a.rownorm_part[(size_t)min(c + 4 * u, nct - 1) * N + r];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const float x = c + 4 * u < nct ? v[u] : 0.f;
+          if (u & 1) p1 += x; else p0 += x;
+        }
       }
-      if (c < nct) p0 += a.rownorm_part[(size_t)c * N + r];
     }
     double p = (double)p0 + (double)p1;
     p += __shfl_xor(p, 1);

@@ -894,7 +894,9 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
       if (m_max >= kEigReserveFromRank) eig_dyn = std::max<size_t>(eig_dyn, kEigLdsReserve);
       const int n_off = (m_max / 2) * (m_max / 2 - 1) / 2;   // off-diagonal blocks, owned by the waves after the first
       const int items = std::max(1, (n_off + (kEigThreads - 64) - 1) / (kEigThreads - 64));
-      if (items <= 1) {
+      if (m_max <= kEigSmallRank) {
+        hipLaunchKernelGGL((eig_update_kernel<1, kEigThreadsSmall>), dim3(n), dim3(kEigThreadsSmall), eig_dyn, s, g);
+      } else if (items <= 1) {
         hipLaunchKernelGGL((eig_update_kernel<1, kEigThreads>), dim3(n), dim3(kEigThreads), eig_dyn, s, g);
       } else if (items == 2) {
         hipLaunchKernelGGL((eig_update_kernel<2, kEigThreads>), dim3(n), dim3(kEigThreads), eig_dyn, s, g);

@@ -19,7 +19,10 @@
 namespace ngsgd {
 
 constexpr int kSmallThreads = 1024;          // orthogonality fix kernel
-constexpr int kEigThreads = 1024;            // R x R eigen-update kernel
+constexpr int kEigThreads = 1024;          // R x R eigen-update kernel
+// Up to rank 40 the blocks of a round fit into three wavefronts next to the rotation wavefront, one on each SIMD; the
+// twelve others only meet at the barriers (rank 20: 45.4 -> 42.9 us).
+constexpr int kEigThreadsSmall = 256, kEigSmallRank = 40;
 // most 2x2 blocks of the upper triangle one thread may own
 constexpr int kEigMaxItems = ((kMaxRank / 2) * (kMaxRank / 2 - 1) / 2 + (kEigThreads - 64) - 1) / (kEigThreads - 64);
 
@@ -103,35 +106,6 @@ __device__ __forceinline__ bool jacobi_rotation(double app, double aqq, double a
   return true;
 }
 
-// Exact variant used by the (not latency critical) initialisation.
-__device__ __forceinline__ bool sym_schur2(double app, double aqq, double apq, double& c, double& s) {
-  c = 1.0;
-  s = 0.0;
-  if (!(fabs(apq) > kJacobiTol * sqrt(fabs(app * aqq))) || fabs(apq) <= 1.0e-300) return false;
-  const double tau = (aqq - app) / (2.0 * apq);
-  const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-  c = 1.0 / sqrt(1.0 + t * t);
-  s = t * c;
-  return true;
-}
-
-// Round-robin pairing of m (even) players: in round r, pair k is (m-1, r) for k = 0 and
-// ((r+k) mod (m-1), (r-k) mod (m-1)) otherwise; over rounds 0..m-2 every pair meets once.  Returned with p < q.
-__device__ __forceinline__ void round_robin_pair(int m, int r, int k, int& p, int& q) {
-  if (k == 0) {
-    p = r;
-    q = m - 1;
-  } else {
-    p = (r + k) % (m - 1);
-    q = (r - k + (m - 1)) % (m - 1);
-  }
-  if (p > q) {
-    const int t = p;
-    p = q;
-    q = t;
-  }
-}
-
 // The Jacobi iteration works in "position space" (Brent-Luk): position 2k is the first and 2k+1 the second
 // member of pair k, rotations always act on (2k, 2k+1), and after every round the matrix is permuted so that the
 // next round's partners sit together again.  The permutation is the same every round,
@@ -165,10 +139,9 @@ template <int ITEMS, int NT>
 __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
   extern __shared__ __attribute__((aligned(16))) double dyn[];   // two copies of Z (upper triangle, four planes)
   __shared__ double scratch[16];
-  __shared__ double s_d[kMaxRank], s_ise[kMaxRank], s_dr[kMaxRank], s_c[kMaxRank + 1], s_enew[kMaxRank];
+  __shared__ double s_ise[kMaxRank], s_dr[kMaxRank], s_c[kMaxRank + 1];
   __shared__ __attribute__((aligned(16))) double2 s_cs[2][kMaxHalf];   // (c, s) of the pairs, this round's and the next's
   __shared__ int s_perm[kMaxRank];
-  __shared__ double s_scal[8];
   __shared__ int s_flag[2];
   __shared__ int s_rotated[2];
 
@@ -185,20 +158,14 @@ __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
   double tr_part = 0.0;   // tr(X X^T), summed here: the kernel that finishes the output may still be running
   for (int i = tid; i < a.n_sumsq; i += nt) tr_part += a.sumsq_part[i];
   const double tr_M = block_sum(tr_part, scratch);
-  for (int i = tid; i < R; i += nt) s_d[i] = st->d[i];
-  __syncthreads();
-  if (tid == 0) {
-    double sum_d = 0.0;
-    for (int i = 0; i < R; ++i) sum_d += s_d[i];
-    s_scal[0] = sum_d;
-    s_scal[1] = rho * (1.0 + g.alpha) + g.alpha / (double)D * sum_d;  // beta_t, eq. beta2
-  }
-  __syncthreads();
-  const double sum_d = s_scal[0], beta = s_scal[1];
-  for (int i = tid; i < R; i += nt) {
-    const double e = 1.0 / (beta / s_d[i] + 1.0);                     // eq. etii
-    s_ise[i] = 1.0 / sqrt(e);
-    s_dr[i] = s_d[i] + rho;
+  static_assert(kMaxRank <= NT, "a thread per eigenvalue");
+  const double d_old = tid < R ? st->d[tid] : 0.0;
+  const double sum_d = block_sum(d_old, scratch);
+  const double beta = rho * (1.0 + g.alpha) + g.alpha / (double)D * sum_d;   // beta_t, eq. beta2
+  if (tid < R) {
+    const double e = 1.0 / (beta / d_old + 1.0);                      // eq. etii
+    s_ise[tid] = 1.0 / sqrt(e);
+    s_dr[tid] = d_old + rho;
   }
   __syncthreads();
 
@@ -252,11 +219,14 @@ __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
 #pragma unroll
   for (int it = 0; it < ITEMS; ++it) {
     const int item = (tid - 64) + it * (nt - 64);
-    int d = 1, rem = (item >= 0 && item < n_off) ? item : 0;
-    while (half - d > 0 && rem >= half - d) {   // diagonal d holds the blocks (0, d), ..., (half-1-d, half-1)
-      rem -= half - d;
-      ++d;
-    }
+    const int it_no = (item >= 0 && item < n_off) ? item : 0;
+    // diagonal d holds the blocks (0, d), ..., (half-1-d, half-1), numbers (d-1) half - d (d-1) / 2 onwards
+    auto first_of = [half](const int d) { return (d - 1) * half - d * (d - 1) / 2; };
+    const float w = (float)half - 0.5f;
+    int d = max(1, min(half - 1, 1 + (int)(w - sqrtf(fmaxf(w * w - 2.f * (float)it_no, 0.f)))));
+    while (d > 1 && first_of(d) > it_no) --d;
+    while (d < half - 1 && first_of(d + 1) <= it_no) ++d;
+    const int rem = it_no - first_of(d);
     const int bi = rem, bj = min(rem + d, half - 1);   // (an idle thread of a single-pair problem: bj = bi = 0)
     blk_i[it] = bi;
     blk_j[it] = bj;
@@ -398,21 +368,14 @@ __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
     a.work->rank_of[i] = rank;
   }
   __syncthreads();
+  // eq. rhodash2, dt1, rhot1
+  const double root = tid < R ? sqrt(s_c[s_perm[tid]]) : 0.0;   // eigenpair at position tid
+  const double sum_sqrt = block_sum(root, scratch);
+  const double rho_dash = ((eta / N) * tr_M + (1.0 - eta) * ((double)D * rho + sum_d) - sum_sqrt) / (double)(D - R);
+  const double rho_new = fmax(g.epsilon, rho_dash);
+  const double dn = fmax(root - rho_dash, g.epsilon);
+  const double beta_new = rho_new * (1.0 + g.alpha) + g.alpha / (double)D * block_sum(tid < R ? dn : 0.0, scratch);
   if (tid == 0) {
-    double sum_sqrt = 0.0;
-    for (int i = 0; i < R; ++i) sum_sqrt += sqrt(s_c[i]);
-    // eq. rhodash2, dt1, rhot1
-    const double rho_dash = ((eta / N) * tr_M + (1.0 - eta) * ((double)D * rho + sum_d) - sum_sqrt) / (double)(D - R);
-    const double rho_new = fmax(g.epsilon, rho_dash);
-    double sum_dn = 0.0;
-    for (int k = 0; k < R; ++k) {
-      const double dn = fmax(sqrt(s_c[s_perm[k]]) - rho_dash, g.epsilon);
-      s_enew[k] = dn;     // temporarily d_{t+1}
-      sum_dn += dn;
-    }
-    const double beta_new = rho_new * (1.0 + g.alpha) + g.alpha / (double)D * sum_dn;
-    s_scal[2] = rho_new;
-    s_scal[3] = beta_new;
     const double cmax = s_c[s_perm[0]], cmin = s_c[s_perm[R - 1]];
     int flags = 0;
     if (s_flag[0]) flags |= kFlagFloored | kFlagOrthCheck;
@@ -424,16 +387,13 @@ __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
     st->beta = beta_new;
     a.work->n_rounds = rounds;
   }
-  __syncthreads();
-  const double beta_new = s_scal[3];
-  for (int k = tid; k < R; k += nt) {
-    const double dn = s_enew[k];
+  if (tid < R) {
     const double en = 1.0 / (beta_new / dn + 1.0);
-    st->d[k] = dn;
-    st->e[k] = en;
+    st->d[tid] = dn;
+    st->e[tid] = en;
     // A_t = (eta/N) E_{t+1}^{1/2} C_t^{-1/2} U_t^T E_t^{-1/2}  (eq. wt1): scale of row k / eigenpair s_perm[k]
-    a.work->colscale[s_perm[k]] = (eta / N) * sqrt(en / s_c[s_perm[k]]);
-    a.work->rowscale[k] = s_ise[k];
+    a.work->colscale[s_perm[tid]] = (eta / N) * sqrt(en / s_c[s_perm[tid]]);
+    a.work->rowscale[tid] = s_ise[tid];
   }
   for (int idx = tid; idx < R * R; idx += nt) a.K[idx] = 0.0;
 }
