@@ -463,8 +463,12 @@ __global__ __launch_bounds__(64) void init_eigenvalue_kernel(const InitGroup* __
   if (lane == 0) a.lam()[k] = 0.5 * (lo + hi) * norm;
 }
 
-// Eigenvectors of T by inverse iteration: T - lambda = P L U with row exchanges once, then three solves from a random
-// vector.  A thread per vector; everything is laid out with the vector index running fastest.
+// Eigenvectors of T by inverse iteration: T - sigma = P L U with row exchanges once, then three solves from a random
+// vector.  sigma lies 64 eps |T| above the eigenvalue: within a cluster of equal eigenvalues, which rounding spreads over
+// a few eps |T|, every direction is then amplified alike and the vectors stay as independent as they started.  (With
+// sigma on the eigenvalue itself those nearest to it win: of 80 vectors from the spectrum of one-hot rows the smallest
+// eigenvalue of the Gram matrix came down to 1e-12 and at times to nothing; with the shift it is 1e-6 to 1e-3.)
+// A thread per vector; everything is laid out with the vector index running fastest.
 // Bound: the serial chains of n steps.  What they read does not depend on them, so every solve goes in blocks of eight
 // steps whose operands are requested a block ahead (n = 512, ten instances: 900 us with plain loops in device memory,
 // where every load waits behind the stores, 546 us in blocks, 270 us in blocks and LDS).
@@ -472,6 +476,7 @@ __global__ __launch_bounds__(64) void init_eigenvalue_kernel(const InitGroup* __
 // device memory.  Grid (ceil(rq / count), instance), 64 threads.
 constexpr int kInverseSolves = 3;
 constexpr int kInverseLds = 150 * 1024, kInverseLdsMin = 4, kInverseLdsMax = 16;   // bytes; vectors of a workgroup
+constexpr double kInverseShift = 64.0 * kInitEps;
 constexpr int kInverseBlock = 8;
 constexpr int kInversePad = 3 * kInverseBlock;   // blocks are requested whole, and one ahead
 __host__ __device__ constexpr size_t inverse_lds_bytes(const int np) { return (5 * (size_t)(np + 2 * kInversePad) + 1) * sizeof(double); }
@@ -506,12 +511,12 @@ __global__ __launch_bounds__(64) void init_eigenvector_kernel(const InitGroup* _
   double* const __restrict__ X = LDS ? r0 + 4 * plane : a.X + k;
   const double* __restrict__ d = a.diag();
   const double* __restrict__ e = a.off();
-  const double tiny = kInitEps * norm;
+  const double tiny = kInitEps * norm, sigma = lambda + kInverseShift * norm;
   {
-    double p = d[0] - lambda, b = e[0];
+    double p = d[0] - sigma, b = e[0];
 #pragma unroll 4
     for (int i = 0; i < n - 1; ++i) {
-      const double s = e[i], dn = d[i + 1] - lambda, en = e[i + 1];
+      const double s = e[i], dn = d[i + 1] - sigma, en = e[i + 1];
       const bool swap = fabs(p) < fabs(s);
       double piv = swap ? s : p;
       if (fabs(piv) < tiny) piv = piv < 0.0 ? -tiny : tiny;

@@ -163,6 +163,25 @@ def test_initial_factor_of_equal_eigenvalues(ngsgd, N, D, R, groups):
     assert g_g == pytest.approx(g_o, rel=1e-4)
 
 
+@pytest.mark.parametrize("seed", range(8))
+@pytest.mark.parametrize("N,D,R", [(512, 5000, 80), (300, 400, 90), (150, 1000, 40)])
+def test_initial_factor_of_one_hot_rows(ngsgd, N, D, R, seed):
+    """First derivatives under a zero softmax layer: one-hot minus uniform rows.  Classes seen once give hundreds of equal
+    eigenvalues and the cut goes through them; the output's singular values do not depend on the choice."""
+    import torch
+    rng = np.random.default_rng(seed)
+    law = np.arange(1, D + 1) ** -1.1
+    M = np.full((N, D), -1.0 / D, dtype=np.float32)
+    M[np.arange(N), rng.choice(D, N, p=law / law.sum())] += 1.0
+    ora = OnlineNaturalGradient(D, R, num_samples_history=500.0, update_period=1)
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, num_samples_history=500.0, update_period=1)
+    expect, g_o, _ = ora.precondition(M)
+    got, g_g, _ = gpu_call(torch, pre, M)
+    sg, sw = (np.sqrt(np.maximum(np.linalg.eigvalsh(x @ x.T), 0.0)) for x in (got.astype(np.float64), expect))
+    assert np.max(np.abs(sg - sw)) < TOL * sw[-1]
+    assert g_g == pytest.approx(g_o, rel=1e-4)
+
+
 def test_degenerate_first_minibatches(ngsgd):
     """Zero and rank-deficient first inputs: floors, gamma = 1 on a zero matrix, completion of R_0."""
     import torch
