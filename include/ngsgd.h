@@ -89,14 +89,16 @@ typedef struct {
   float max_change_per_sample;    /* App. C.3; 0 disables the limit (paper: 0.075)     */
   int32_t method;                 /* NGSGD_METHOD_ONLINE (App. B) or _SIMPLE (App. A)  */
   float simple_epsilon;           /* floor on tr(X^T X) in beta, App. A.2 (1e-20)      */
-  int32_t side_streams;           /* internal streams for the factor updates: 0 = default
-                                   * (2), else 1..3.  Two: the last layer's derivatives and
-                                   * the layer inputs start after the forward pass, the
-                                   * other derivatives after the backward pass (shortest
-                                   * single-network step); three start the upper hidden
-                                   * layers in the middle of the backward pass; one is
-                                   * better when many networks share the GPU, which has
-                                   * few hardware queues per process                      */
+  int32_t side_streams;           /* internal streams for the factor updates: 0 = chosen
+                                   * by the sizes (1 or 2), else 1..3.  One: all updates
+                                   * start after the backward pass; two: the last layer's
+                                   * derivatives and the layer inputs start after the
+                                   * forward pass, the other derivatives after the backward
+                                   * pass (shorter for deep networks with a large rank);
+                                   * three start the upper hidden layers in the middle of
+                                   * the backward pass.  One is better when many networks
+                                   * share the GPU, which has few hardware queues per
+                                   * process                                              */
 } ngsgd_config;
 
 /* ---- one preconditioner instance (App. B) ------------------------------------------------- */

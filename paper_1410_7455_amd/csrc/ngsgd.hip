@@ -112,13 +112,22 @@ inline int rank_class(int rank) { return rank <= 32 ? 32 : (rank <= 80 ? 80 : 96
 // the next step's forward / backward pass; the new factor is first needed by the next preconditioning.  The
 // instances are split over kSideStreams streams by the moment their matrix exists (the last layer's derivatives
 // and all layer inputs after the forward pass, the other derivatives as the backward pass produces them), so that
-// each group's products H, J and its R x R work start as early as possible.  Two streams are the default (the last
-// layer's derivatives and the layer inputs; the other derivatives after the backward pass): a third, which starts the
-// upper hidden layers' derivatives in the middle of the backward pass, measured 1 - 2 % slower on the speech-shaped
-// network (its small launches share the chip with the backward pass, and every further hardware queue in use
-// lengthens the gaps between dependent kernels on all of them, plain steps included).
+// each group's products H, J and its R x R work start as early as possible.
 constexpr int kSideStreams = 3;          // most
-constexpr int kDefaultSideStreams = 2;
+// Without the caller's choice: one stream, or two (the last layer's derivatives and the layer inputs; the other
+// derivatives after the backward pass).  The second one takes the early group out of the chain that the next step waits
+// for, and costs a dozen launches and some events per update, and longer gaps on every queue.  It pays where the chain
+// (rank) is long, most of the factors are in the early group's way (layers) and the products of a step do not cover the
+// chain anyway.  Two streams against one, time per step: 3 layers, 130 - 2000 wide, rank 24 - 90: 1.02 - 1.25 times;
+// 5 and 6 layers, rank up to 60: 0.99 - 1.08; rank 70 - 90: 500 wide 0.97 - 0.99, 5 x 3000 (300) with 512 rows 0.99, with
+// 256 rows and 600 inputs 0.98 - 1.04, 512 rows 1.00 - 1.04, 6 x 2000 1.01 - 1.03.
+// A third stream, which starts the upper hidden layers' derivatives in the middle of the backward pass, measured 1 - 2 %
+// slower than two on the speech-shaped network.
+constexpr int kTwoStreamsFromRank = 64, kTwoStreamsFromLayers = 5;
+constexpr double kTwoStreamsMostWork = 3.0e9;   // rows x parameters
+inline int default_side_streams(const int rank, const int n_layers, const double rows_by_params) {
+  return rank >= kTwoStreamsFromRank && n_layers >= kTwoStreamsFromLayers && rows_by_params <= kTwoStreamsMostWork ? 2 : 1;
+}
 struct SideSync {
   hipStream_t stream = nullptr;
   hipEvent_t inputs_ready = nullptr;   // recorded on the caller's stream: the group's matrices exist
@@ -883,8 +892,8 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
       r_max = std::max(r_max, p.rank);
     }
     g.count = n;
-    ProfScope prof(NGSGD_PROF_PRECOND_SMALL, s);
     {
+      ProfScope prof(NGSGD_PROF_PRECOND_SMALL, s);
       const int m_max = (r_max + 1) & ~1;
       const int n_blocks = (m_max / 2) * (m_max / 2 + 1) / 2;   // 2x2 blocks of the upper triangle
       size_t eig_dyn = (size_t)2 * 4 * n_blocks * sizeof(double);   // two copies of four planes
@@ -905,6 +914,7 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
       }
       LAUNCH_CHECK();
     }
+    ProfScope prof(NGSGD_PROF_PRECOND_SMALL, s);
     const int rows_per_block = kEigvecThreads / 64;
     hipLaunchKernelGGL(eigvec_kernel, dim3(n, (r_max + rows_per_block - 1) / rows_per_block), dim3(kEigvecThreads),
                        r_max >= kEigReserveFromRank ? kEigvecLdsReserve : 0, s, g);
@@ -1440,7 +1450,6 @@ void net_layout(ngsgd_net& net, const ngsgd_config* cfg, Carver& c) {
   net.method = cfg->method;
   net.alpha = cfg->alpha;
   net.simple_epsilon = cfg->simple_epsilon;
-  net.n_side = cfg->side_streams > 0 ? cfg->side_streams : kDefaultSideStreams;
   const bool simple = cfg->method == NGSGD_METHOD_SIMPLE;
   net.layers.assign(cfg->n_layers, ngsgd_layer());
   int din = cfg->dims[0];
@@ -1461,6 +1470,9 @@ void net_layout(ngsgd_net& net, const ngsgd_config* cfg, Carver& c) {
     din = L.groups;
   }
   net.n_params_padded = n_params;
+  net.n_side = cfg->side_streams > 0 ? cfg->side_streams
+                                     : default_side_streams(std::max(cfg->rank_in, cfg->rank_out), cfg->n_layers,
+                                                            (double)cfg->max_batch * (double)n_params);
   net.params = c.take<float>(n_params);
   size_t off = 0;
   for (auto& L : net.layers) {

@@ -380,3 +380,11 @@ def test_back_to_back_steps_equal_synchronised_steps(ngsgd):
     np.testing.assert_allclose(o_free, o_sync, rtol=1e-5)
     for a, b in zip(w_free, w_sync):
         assert rel(a, b) < 1e-5
+
+
+def test_small_pnorm_net_with_two_side_streams(ngsgd):
+    """As test_small_pnorm_net_past_the_always_update_phase with two internal streams, which the library chooses by
+    itself for deep networks with a large rank only."""
+    spec = workloads.small_pnorm()
+    ora, gpu = make_pair(ngsgd, spec, renorm=True, max_change=0.075, side_streams=2)
+    run_and_compare(ngsgd, spec, ora, gpu, 16)
