@@ -39,6 +39,7 @@ struct GemmProblem {
   const double* alpha_dev[3];  // optional device scalars multiplied into alpha (split_gemm_kernel, as beta)
   int tiles_m, tiles_n, splits, k_per_split;
   int per_split;               // tiles of one split
+  int kc;                      // gram_kernel: the operands' K index is the contiguous one
   int sym;                     // C is symmetric (A = B): only the tiles on and above the diagonal are computed
   int tile_begin;              // first workgroup index of this problem
   float* aux;                  // EPI_SUB_ROWNORM: [tiles_n][M] row-norm partials
@@ -48,11 +49,16 @@ struct GemmProblem {
   int gate_mask;
 };
 
-struct GemmGroup {
+template <int CAPACITY>
+struct GemmGroupOf {
+  static constexpr int kCapacity = CAPACITY;
   int count;
   int total_tiles;
-  GemmProblem p[kMaxGroup];
+  GemmProblem p[CAPACITY];
 };
+using GemmGroup = GemmGroupOf<kMaxGroup>;
+using GramGroup = GemmGroupOf<24>;   // two problems per instance: the argument block stays within 4 KB
+static_assert(sizeof(GramGroup) <= 4096, "kernel arguments");
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
@@ -304,9 +310,10 @@ __device__ __forceinline__ float group16_sum(float v) {
 // ACC64 accumulates in fp64 on the fp64 matrix unit (half the fp32 rate).  The factor update needs it: J, K and
 // L hold nearly parallel rows while the factor is still turning towards the data, and the weak directions then
 // sit in differences that fp32 accumulation wipes out.
-template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, bool SUMSQ_A, int ACC_CHUNK = 0,
-          bool ACC64 = false, int PF = kPrefetch>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_kernel(const GemmGroup g) {
+template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, bool SUMSQ_A, int ACC_CHUNK, bool ACC64, int PF,
+          typename Group>
+__device__ __forceinline__ void gemm_unit(const Group& g, const int pi, const int unit) {
+  const GemmProblem& P = g.p[pi];   // (a pointer to it would make the compiler copy the argument to scratch memory)
   using acc_t = typename AccType<ACC64>::type;
   constexpr int NT = WGM * WGN * 64;
   constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -329,16 +336,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_kernel(const GemmGroup g) 
   const int wm = wave / WGN, wn = wave % WGN;
   const int r16 = lane & 15, g4 = lane >> 4;
 
-  // Workgroups go to the eight accelerator dies round-robin by their index, and each die has its own L2: give
-  // every die one contiguous eighth of the unit list, so that the workgroups sharing an L2 share operand panels.
-  const int per_xcd = (g.total_tiles + kXcds - 1) / kXcds;
-  const int unit = ((int)blockIdx.x % kXcds) * per_xcd + (int)blockIdx.x / kXcds;
-  if (unit >= g.total_tiles) return;   // the grid is rounded up to a multiple of the die count
-  int pi = 0;
-  for (int i = 1; i < g.count; ++i)
-    if (unit >= g.p[i].tile_begin) pi = i;
-  const GemmProblem& P = g.p[pi];
-  if (P.gate != nullptr && ((*P.gate) & P.gate_mask) == 0) return;   // uniform over the workgroup
   // Within a split the tiles are numbered along the shorter side of the tile grid first: a die's contiguous run of
   // units then covers a compact patch, all of the small operand's panels but only its own share of the large one's.
   int local = unit - P.tile_begin;
@@ -614,6 +611,45 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_kernel(const GemmGroup g) 
   }
 }
 
+// The unit (problem, split, tile) of a workgroup; returns the problem's index, -1: none.
+template <typename Group>
+__device__ __forceinline__ int find_unit(const Group& g, int& unit) {
+  // Workgroups go to the eight accelerator dies round-robin by their index, and each die has its own L2: give
+  // every die one contiguous eighth of the unit list, so that the workgroups sharing an L2 share operand panels.
+  const int per_xcd = (g.total_tiles + kXcds - 1) / kXcds;
+  unit = ((int)blockIdx.x % kXcds) * per_xcd + (int)blockIdx.x / kXcds;
+  if (unit >= g.total_tiles) return -1;   // the grid is rounded up to a multiple of the die count
+  int pi = 0;
+  for (int i = 1; i < g.count; ++i)
+    if (unit >= g.p[i].tile_begin) pi = i;
+  const GemmProblem& P = g.p[pi];
+  if (P.gate != nullptr && ((*P.gate) & P.gate_mask) == 0) return -1;   // uniform over the workgroup
+  return pi;
+}
+
+template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, bool SUMSQ_A, int ACC_CHUNK = 0,
+          bool ACC64 = false, int PF = kPrefetch>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_kernel(const GemmGroup g) {
+  int unit;
+  const int pi = find_unit(g, unit);
+  if (pi >= 0) gemm_unit<BM, BN, BK, WGM, WGN, A_KC, B_KC, EPI, SUMSQ_A, ACC_CHUNK, ACC64, PF>(g, pi, unit);
+}
+
+// R x R Gram products of both layouts in one launch, fp64 accumulation, double atomics.  They are short (a few
+// microseconds for any size), so what counts is the number of launches: K = J J^T and L = H^T H apart took 9.4 us each
+// at rank 80 (512 x 5000) and 4.7 us at rank 20.
+template <int BM, int BN, int BK, int WGM, int WGN>
+__global__ __launch_bounds__(WGM* WGN * 64) void gram_kernel(const GramGroup g) {
+  int unit;
+  const int pi = find_unit(g, unit);
+  if (pi < 0) return;
+  if (g.p[pi].kc) {
+    gemm_unit<BM, BN, BK, WGM, WGN, true, true, EPI_ATOMIC_F64, false, 0, true, kPrefetch>(g, pi, unit);
+  } else {
+    gemm_unit<BM, BN, BK, WGM, WGN, false, false, EPI_ATOMIC_F64, false, 0, true, kPrefetch>(g, pi, unit);
+  }
+}
+
 // ---- host side -------------------------------------------------------------------------------
 struct GemmDesc {  // what a caller states; tiling is filled in by the launcher
   const float* A = nullptr;
@@ -628,6 +664,7 @@ struct GemmDesc {  // what a caller states; tiling is filled in by the launcher
   int splits = 1;  // requested split-K factor (atomic epilogues, or EPI_STORE with c_split_stride)
   long long c_split_stride = 0;
   int sym = 0;     // EPI_ATOMIC_F64 with M = N and square tiles
+  int kc = 0;      // launch_gram_group
   const int* gate = nullptr;
   int gate_mask = 0;
 };
@@ -651,16 +688,16 @@ inline void plan_tiles(const GemmDesc& d, GemmProblem& p) {
   p.k_per_split = (steps_per > 0 ? steps_per : 1) * BK;
   p.splits = ksteps > 0 ? (ksteps + steps_per - 1) / steps_per : 1;
   p.sym = d.sym;
+  p.kc = d.kc;
   p.per_split = d.sym ? p.tiles_n * (p.tiles_n + 1) / 2 : p.tiles_m * p.tiles_n;
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, bool SUMSQ_A, int ACC_CHUNK = 0,
-          bool ACC64 = false, int PF = kPrefetch>
-inline hipError_t launch_gemm_group(const GemmDesc* descs, int count, hipStream_t stream) {
+template <int BM, int BN, int BK, typename Group>
+inline hipError_t launch_unit_kernel(void (*kernel)(const Group), const int threads, const GemmDesc* descs, int count, hipStream_t stream) {
   int done = 0;
   while (done < count) {
-    GemmGroup grp;
-    const int n = (count - done) < kMaxGroup ? (count - done) : kMaxGroup;
+    Group grp;
+    const int n = (count - done) < Group::kCapacity ? (count - done) : Group::kCapacity;
     grp.count = n;
     int total = 0;
     for (int i = 0; i < n; ++i) {
@@ -670,15 +707,23 @@ inline hipError_t launch_gemm_group(const GemmDesc* descs, int count, hipStream_
     }
     grp.total_tiles = total;
     if (total > 0) {
-      hipLaunchKernelGGL((gemm_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, EPI, SUMSQ_A, ACC_CHUNK, ACC64, PF>),
-                         dim3((total + kXcds - 1) / kXcds * kXcds),
-                         dim3(WGM * WGN * 64), 0, stream, grp);
+      hipLaunchKernelGGL(kernel, dim3((total + kXcds - 1) / kXcds * kXcds), dim3(threads), 0, stream, grp);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
     done += n;
   }
   return hipSuccess;
+}
+template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, bool SUMSQ_A, int ACC_CHUNK = 0,
+          bool ACC64 = false, int PF = kPrefetch>
+inline hipError_t launch_gemm_group(const GemmDesc* descs, int count, hipStream_t stream) {
+  return launch_unit_kernel<BM, BN, BK>(gemm_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, EPI, SUMSQ_A, ACC_CHUNK, ACC64, PF>,
+                                        WGM * WGN * 64, descs, count, stream);
+}
+template <int BM, int BN, int BK, int WGM, int WGN>
+inline hipError_t launch_gram_group(const GemmDesc* descs, int count, hipStream_t stream) {
+  return launch_unit_kernel<BM, BN, BK>(gram_kernel<BM, BN, BK, WGM, WGN>, WGM * WGN * 64, descs, count, stream);
 }
 
 // number of K splits a problem is actually planned with

@@ -148,6 +148,7 @@ struct ngsgd_precond {
   int ldh = 0;   // leading dimension of H and A_t (= rank class)
   PrecondScalars* st = nullptr;
   float* zero_region = nullptr;   // [arrival counters, deferred count | H | K | L], cleared before each call
+  bool kl_clean = false;          // K and L are known to be clear
   int clean_rows = 0;             // the counters and this many rows of H are known to be clear (left so by the
                                   // finishing kernel of a call that went through the fused apply kernel)
   size_t zero_floats_all = 0;
@@ -389,10 +390,9 @@ hipError_t by_rank_class(int rc, F32 f32, F80 f80, F96 f96) {
 // long dimension.  Ranks up to 32: one 32 x 32 tile per instance; above: 64 x 64 tiles (a single 80 x 80 tile with one
 // row of MFMA tiles per wavefront was measured slower at rank 80: 399 instead of 387 us for the 512 x 5000 call,
 // fewer and longer workgroups)
-template <bool KC>
 hipError_t launch_small_gram(int rc, const GemmDesc* d, int n, hipStream_t s) {
-  if (rc == 32) return launch_gemm_group<32, 32, BK, 2, 1, KC, KC, EPI_ATOMIC_F64, false, 0, true>(d, n, s);
-  return launch_gemm_group<64, 64, BK, 2, 2, KC, KC, EPI_ATOMIC_F64, false, 0, true>(d, n, s);
+  if (rc == 32) return launch_gram_group<32, 32, BK, 2, 1>(d, n, s);
+  return launch_gram_group<64, 64, BK, 2, 2>(d, n, s);
 }
 constexpr int kGramMinSplitSteps = 4;   // K-blocks per split of a 32 x 32 tile at least: below that the atomic epilogue dominates
 inline int gram_splits(int rc, int rank, int instances, int k) {
@@ -558,10 +558,10 @@ int precond_validate(const std::vector<PrecondCall>& calls) {
 
 inline bool factor_due(const ngsgd_precond& p) { return p.t < p.always_update_first || p.t % p.update_period == 0; }
 
-// Clears the accumulation buffers of the listed instances (H always; K, L when the factor is updated).  With
-// `keep_clean` (the fused apply path, whose finishing kernel clears what it used) an instance whose counters and
-// H rows are still clear is skipped, and no kernel is launched when that holds for all of them.
-int clear_accumulators(const std::vector<PrecondCall>& list, hipStream_t s, bool keep_clean = false) {
+// Clears the accumulation buffers of the listed instances (H always; K, L when the factor is updated) as far as they
+// are not still clear from the kernel that ended their last use (the finishing kernel of the fused path, the
+// orthogonality check of an update); no kernel is launched when that holds for all of them.
+int clear_accumulators(const std::vector<PrecondCall>& list, hipStream_t s) {
   for (size_t done = 0; done < list.size();) {
     FillGroup fg;
     const int n = (int)std::min<size_t>(kMaxInstances, list.size() - done);
@@ -572,8 +572,9 @@ int clear_accumulators(const std::vector<PrecondCall>& list, hipStream_t s, bool
       ngsgd_precond& p = *c.p;
       fg.ptr[i] = reinterpret_cast<uint32_t*>(p.zero_region);
       fg.n[i] = factor_due(p) ? p.zero_floats_all : p.arrive_slots + (size_t)c.N * p.ldh;
-      if (keep_clean && p.clean_rows >= c.N) fg.n[i] = 0;
-      if (!keep_clean) p.clean_rows = 0;   // the caller is about to accumulate into H and leaves it that way
+      if (p.clean_rows >= c.N && (!factor_due(p) || p.kl_clean)) fg.n[i] = 0;
+      p.clean_rows = 0;   // until the kernel that clears them again has been enqueued
+      if (factor_due(p)) p.kl_clean = false;
       n_max = std::max(n_max, fg.n[i]);
     }
     done += n;
@@ -736,8 +737,7 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
   if (!do_products) {
     // the caller has issued the products already
   } else if (fused) {
-    NG_TRY(clear_accumulators(full, s, true));
-    for (auto& c : full) c.p->clean_rows = 0;   // until the finishing kernel below has been enqueued
+    NG_TRY(clear_accumulators(full, s));
     NG_TRY(launch_fused_apply(full, s));
   } else if (!hj_ready) {
     if (!to_init.empty()) NG_TRY(run_init(to_init, s));
@@ -828,7 +828,7 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
   if (to_update.empty()) return NGSGD_OK;
   {
     // K = J J^T, L = H^T H, fp64 accumulation across the splits
-    std::vector<GemmDesc> dk, dl;
+    std::vector<GemmDesc> d;   // one launch for both
     int rc = 0;
     for (auto& c : to_update) rc = std::max(rc, c.p->ldh);
     for (auto& c : to_update) {
@@ -839,18 +839,18 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
       g.C = p.K; g.ldc = p.rank;
       g.M = p.rank; g.N = p.rank; g.K = p.dim;
       g.splits = gram_splits(rc, p.rank, (int)to_update.size(), p.dim);
-      dk.push_back(g);
+      g.kc = 1;
+      d.push_back(g);
       GemmDesc h;
       h.A = p.H; h.lda = p.ldh;
       h.B = p.H; h.ldb = p.ldh;
       h.C = p.L; h.ldc = p.rank;
       h.M = p.rank; h.N = p.rank; h.K = p.last_N;
       h.splits = gram_splits(rc, p.rank, (int)to_update.size(), p.last_N);
-      dl.push_back(h);
+      d.push_back(h);
     }
     ProfScope prof(NGSGD_PROF_PRECOND_KL, s);
-    HIP_TRY(launch_small_gram<true>(rc, dk.data(), (int)dk.size(), s));
-    HIP_TRY(launch_small_gram<false>(rc, dl.data(), (int)dl.size(), s));
+    HIP_TRY(launch_small_gram(rc, d.data(), (int)d.size(), s));
   }
   // B_t over J (needs D_t, rho_t: before the R x R update)
   for (size_t done = 0; done < to_update.size();) {
@@ -935,9 +935,12 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s) {
       const ngsgd_precond& p = *to_update[done + i].p;
       OrthArgs& o = og.a[i];
       o.st = p.st; o.G = p.K; o.At = p.At; o.ldat = p.ldh; o.R = p.rank;
+      o.clear_ptr = p.zero_region; o.L = p.L;
+      o.clear_floats = (int)(p.arrive_slots + (size_t)p.last_N * p.ldh);
       r_max = std::max(r_max, p.rank);
     }
     og.count = n;
+    const bool clears = n == 1 || r_max <= kOrthClearRank;
     auto launch_new_factor = [&](const bool only_if_reorthogonalised) -> int {
       for (int rc : {32, 80, 96}) {
         std::vector<GemmDesc> d;
@@ -967,7 +970,6 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s) {
     {
       // App. B.3.1: W W^T of the new factor, accumulated into K (cleared by the R x R kernel) only for the
       // instances whose update asked for the check, then the check itself and, if needed, the Cholesky fix
-      ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
       std::vector<GemmDesc> dg;
       for (int i = 0; i < n; ++i) {
         ngsgd_precond& p = *to_update[done + i].p;
@@ -977,26 +979,37 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s) {
         w.C = p.K; w.ldc = p.rank;
         w.M = p.rank; w.N = p.rank; w.K = p.dim;
         w.splits = gram_splits(rank_class(r_max), p.rank, n, p.dim);
+        w.kc = 1;
         w.gate = &p.st->flags;
         w.gate_mask = kFlagOrthCheck;
         dg.push_back(w);
       }
-      HIP_TRY(launch_small_gram<true>(rank_class(r_max), dg.data(), (int)dg.size(), s));
+      {
+        ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
+        HIP_TRY(launch_small_gram(rank_class(r_max), dg.data(), (int)dg.size(), s));
+      }
+      ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
       const size_t dyn = (size_t)r_max * (r_max + 1) * sizeof(double);   // W W^T of an instance
       const int ct = orth_columns_per_thread(r_max);   // 2 R / 32 rounded up: 1 .. 6
       if (ct <= 2) {
-        hipLaunchKernelGGL(orth_fix_kernel<2>, dim3(n), dim3(kSmallThreads), dyn, s, og);
+        hipLaunchKernelGGL(orth_fix_kernel<2>, dim3(n, clears ? kOrthClearBlocks : 1), dim3(kSmallThreads), dyn, s, og);
       } else if (ct <= 3) {
-        hipLaunchKernelGGL(orth_fix_kernel<3>, dim3(n), dim3(kSmallThreads), dyn, s, og);
+        hipLaunchKernelGGL(orth_fix_kernel<3>, dim3(n, clears ? kOrthClearBlocks : 1), dim3(kSmallThreads), dyn, s, og);
       } else if (ct <= 5) {
-        hipLaunchKernelGGL(orth_fix_kernel<5>, dim3(n), dim3(kSmallThreads), dyn, s, og);
+        hipLaunchKernelGGL(orth_fix_kernel<5>, dim3(n, clears ? kOrthClearBlocks : 1), dim3(kSmallThreads), dyn, s, og);
       } else {
-        hipLaunchKernelGGL(orth_fix_kernel<6>, dim3(n), dim3(kSmallThreads), dyn, s, og);
+        hipLaunchKernelGGL(orth_fix_kernel<6>, dim3(n, clears ? kOrthClearBlocks : 1), dim3(kSmallThreads), dyn, s, og);
       }
       LAUNCH_CHECK();
     }
     // where the check failed the kernel has folded the fix into A_t: W_{t+1} = A_t B_t once more for those
     NG_TRY(launch_new_factor(true));
+    for (int i = 0; i < n; ++i) {
+      ngsgd_precond& p = *to_update[done + i].p;
+      if (!clears) continue;
+      p.clean_rows = p.last_N;
+      p.kl_clean = true;
+    }
     done += n;
   }
   return NGSGD_OK;

@@ -500,11 +500,21 @@ __global__ __launch_bounds__(kEigvecThreads) void eigvec_kernel(const SmallGroup
 // 1e-3, W <- E^{1/2} L^{-1} E^{-1/2} W with O = L L^T.  Runs only when the update asked for the check.
 struct OrthArgs {
   PrecondScalars* st;
-  const double* G;   // R x R, W W^T of the new factor (accumulated only when the check was requested)
+  double* G;         // R x R, W W^T of the new factor (accumulated only when the check was requested); cleared on exit
   float* At;         // R x R (ldat): A_t on entry; when the fix is needed, E^{1/2} L^{-1} E^{-1/2} A_t on return
   int ldat;
   int R;
+  // what the update accumulated into besides G (arrival counters and H, contiguous; L): cleared here, behind their last
+  // readers, so that the next call needs no clearing launch in front of it
+  float* clear_ptr;
+  double* L;
+  int clear_floats;   // a multiple of 4
 };
+constexpr int kOrthClearBlocks = 8;   // workgroups per instance, the first one checks and the others clear
+// Several instances of a larger rank are left to a launch of small workgroups in front of the next update: 1024 threads and
+// 50 KB of LDS each wait for a compute unit behind the layer products (eight replicas of the speech-shaped network: 9.23
+// instead of 9.0 ms per period).
+constexpr int kOrthClearRank = 32;
 struct OrthGroup {
   int count;
   OrthArgs a[kMaxInstances];
@@ -536,9 +546,16 @@ __global__ __launch_bounds__(kSmallThreads) void orth_fix_kernel(const OrthGroup
   __shared__ double s_dinv[kMaxRank];                      // D_ii^{-1/2}
   const OrthArgs& a = g.a[blockIdx.x];
   PrecondScalars* st = a.st;
-  if (!(st->flags & kFlagOrthCheck)) return;   // uniform over the workgroup
   const int R = a.R;
   const int tid = threadIdx.x, nt = blockDim.x;
+  if (blockIdx.y > 0) {
+    const int at = ((int)blockIdx.y - 1) * nt + tid, step = (kOrthClearBlocks - 1) * nt;
+    float4* const z = reinterpret_cast<float4*>(a.clear_ptr);
+    for (int i = at; i < a.clear_floats / 4; i += step) z[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = at; i < R * R; i += step) a.L[i] = 0.0;
+    return;
+  }
+  if (!(st->flags & kFlagOrthCheck)) return;   // uniform over the workgroup; G was cleared by the R x R update
   // the check: G and E through LDS (coalesced reads), O symmetrised from there
   double* const Gs = dyn;   // R x (R + 1)
   const int SG = R + 1;
@@ -548,6 +565,7 @@ __global__ __launch_bounds__(kSmallThreads) void orth_fix_kernel(const OrthGroup
   double dev = 0.0;
   for (int idx = tid; idx < R * R; idx += nt) {
     const int r = idx / R, c = idx % R;
+    a.G[idx] = 0.0;   // its content is in LDS
     if (c < r) continue;
     const double o = 0.5 * (Gs[r * SG + c] + Gs[c * SG + r]) * s_ise[r] * s_ise[c];
     dev = fmax(dev, fabs(o - (r == c ? 1.0 : 0.0)));

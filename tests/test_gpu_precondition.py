@@ -404,3 +404,22 @@ def test_eigenvalues_under_the_floor(ngsgd):
         expect, _, _ = eff.precondition(M)
         got, _, _ = gpu_call(torch, pre, M)
         assert rel(got, expect) < TOL
+
+
+@pytest.mark.parametrize("R", [6, 40, 90])
+def test_accumulators_stay_clear_between_calls(ngsgd, R):
+    """Calls with and without a factor update, with fewer and with more rows than the call before: what an update or
+    an apply accumulates into is cleared by the kernel that ends it, and by a launch of its own only where that
+    kernel did not reach (more rows than before)."""
+    import torch
+    D = 260
+    rng = np.random.default_rng(900 + R)
+    kw = dict(num_samples_history=500.0, update_period=3, always_update_first=2)
+    ora = OnlineNaturalGradient(D, R, **kw)
+    pre = ngsgd.Preconditioner(D, R, max_batch=230, **kw)
+    for step, N in enumerate((130, 200, 111, 111, 230, 150, 210, 140, 140, 230)):
+        M = data(rng, N, D, decay=0.985)
+        expect, g_o, _ = ora.precondition(M)
+        got, g_g, _ = gpu_call(torch, pre, M)
+        assert rel(got, expect) < TOL, f"step {step}"
+        assert g_g == pytest.approx(g_o, rel=1e-4)
