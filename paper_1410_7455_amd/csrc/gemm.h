@@ -694,10 +694,10 @@ inline void plan_tiles(const GemmDesc& d, GemmProblem& p) {
 
 template <int BM, int BN, int BK, typename Group>
 inline hipError_t launch_unit_kernel(void (*kernel)(const Group), const int threads, const GemmDesc* descs, int count, hipStream_t stream) {
-  int done = 0;
-  while (done < count) {
+  const int launches = (count + Group::kCapacity - 1) / Group::kCapacity;   // of equal shares: none is left with a few tiles
+  for (int done = 0, part = 0; part < launches; ++part) {
     Group grp;
-    const int n = (count - done) < Group::kCapacity ? (count - done) : Group::kCapacity;
+    const int n = (count - done + launches - part - 1) / (launches - part);
     grp.count = n;
     int total = 0;
     for (int i = 0; i < n; ++i) {
