@@ -2,7 +2,8 @@
 //
 // Every fp32 operand is written as the sum of three bf16 numbers, x = h + m + l, each the round-to-nearest bf16 of
 // what the ones before left over.  bf16 has the exponent range of fp32 and 8 significant bits, so the three together
-// hold all 24 bits of x exactly (as long as l, about 2^-17 x, stays above the subnormal range).  A product of two
+// hold all 24 bits of x exactly (as long as l, about 2^-17 x, stays above the subnormal range; an infinity, and a value
+// within 0.4 % of the largest fp32 number, whose h would be one, gives NaN).  A product of two
 // bf16 numbers is exact in fp32, and of the nine partial products
 //     a b = hh + (hm + mh) + (hl + mm + lh) + (ml + lm) + ll
 // the last three are below 2^-24 |a b| together, half a unit in the last place of an fp32 product: the kernel adds
