@@ -2,13 +2,16 @@
 //
 // Every fp32 operand is written as the sum of three bf16 numbers, x = h + m + l, each the round-to-nearest bf16 of
 // what the ones before left over.  bf16 has the exponent range of fp32 and 8 significant bits, so the three together
-// hold all 24 bits of x exactly (as long as l, about 2^-17 x, stays above the subnormal range; an infinity, and a value
-// within 0.4 % of the largest fp32 number, whose h would be one, gives NaN).  A product of two
+// hold all 24 bits of x exactly (as long as l, about 2^-17 x, stays above the subnormal range).  A product of two
 // bf16 numbers is exact in fp32, and of the nine partial products
 //     a b = hh + (hm + mh) + (hl + mm + lh) + (ml + lm) + ll
 // the last three are below 2^-24 |a b| together, half a unit in the last place of an fp32 product: the kernel adds
 // the other six.  The matrix unit does them 16 times faster than fp32 products (2.5 PFLOP/s against 157 TFLOP/s), so
 // six of them cost 3/8 of one fp32 product.
+// Infinities do not split, nor do the numbers within 0.4 % of the largest, whose h is one, and partial products of
+// different signs may overflow where their sum is an infinity.  All of that ends as an infinity or a NaN in the sum: a
+// wavefront that finds one among its elements forms them again on the fp32 matrix unit (redo_tile), and that result
+// stands: a product is infinite, NaN or large exactly where the fp32 product is.
 // Accumulation is fp32 as before.  An instruction adds 32 products instead of 4 (v_mfma_f32_16x16x4_f32), and the matrix
 // unit does not round its accumulator additions to nearest, so the shorter chains make long sums more accurate, not less.
 #pragma once
@@ -197,6 +200,38 @@ struct SplitStageSelect<false, ROWS, BK, NT> {
 
 constexpr int kSplitFold = 4;   // K-blocks per MFMA chain
 
+// Four elements (row, k), ..., (row, k + 3) of an operand; those from k_end on are zero.
+template <bool KC>
+__device__ __forceinline__ floatx4 load_k4(const float* __restrict__ base, const int ld, const int row, const int k, const int k_end) {
+  floatx4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int at = min(k + e, k_end - 1);
+    const float x = KC ? base[(size_t)row * ld + at] : base[(size_t)at * ld + row];
+    v[e] = k + e < k_end ? x : 0.f;
+  }
+  return v;
+}
+
+// The 16 x 16 tile of A B at row m0 and column n0 on the fp32 matrix unit, from memory, laid out as in the kernel below
+// (a lane owns four adjacent columns of one row).  For tiles that the split cannot form: nothing here is fast.
+template <bool A_KC, bool B_KC>
+__device__ __forceinline__ floatx4 redo_tile(const GemmProblem& P, const int m0, const int n0, const int k_begin, const int k_end, const int lane) {
+  const int m = min(m0 + (lane & 15), P.M - 1), n = min(n0 + (lane & 15), P.N - 1), g4 = lane >> 4;
+  floatx4 total = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = k_begin; k0 < k_end; k0 += 128) {
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int k = k0; k < min(k0 + 128, k_end); k += 16) {
+      const floatx4 a = load_k4<A_KC>(P.A, P.lda, m, k + 4 * g4, k_end), b = load_k4<B_KC>(P.B, P.ldb, n, k + 4 * g4, k_end);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc, 0, 0, 0);
+    }
+    total += acc;
+  }
+  return total;
+}
+
 // C = alpha A B [+ beta C] (slab `split` of it at C + split * c_split_stride), see gemm_kernel for the operands.
 // WGM x WGN wavefronts cover the BM x BN tile, WGK of them share the k values of a K-block (their sums are added
 // through LDS at the end).  Another PW wavefronts only stage: they load the next K-block, split it and write it to the
@@ -376,26 +411,40 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
     if (P.alpha_dev[i] != nullptr) alpha *= (float)(*P.alpha_dev[i]);
   const float beta = P.beta;
   float* const C = static_cast<float*>(P.C) + (size_t)split * P.c_split_stride;
+  auto store = [&](const int i, const int j, const floatx4 sum) {
+    const int row = m0 + wm * WM + i * 16 + r16, col = n0 + wn * WN + j * 16 + 4 * g4;
+    if (row >= M || col >= N) return;
+    float* c = C + (size_t)row * P.ldc + col;
+    floatx4 v = alpha * sum;
+    if (col + 4 <= N && (reinterpret_cast<uintptr_t>(c) & 15) == 0) {
+      if (beta != 0.f) v += beta * *reinterpret_cast<const floatx4*>(c);
+      *reinterpret_cast<floatx4*>(c) = v;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (col + q < N) c[q] = beta != 0.f ? v[q] + beta * c[q] : v[q];
+    }
+  };
+  bool lost = false;   // an element of C is an infinity or a NaN (rows and columns beyond C hold whatever lies there)
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-    const int row = m0 + wm * WM + i * 16 + r16;
-    if (row >= M) continue;
+    float nan_if = 0.f;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = n0 + wn * WN + j * 16 + 4 * g4;
-      if (col >= N) continue;
-      float* c = C + (size_t)row * P.ldc + col;
-      floatx4 v = alpha * total[i][j];
-      if (col + 4 <= N && (reinterpret_cast<uintptr_t>(c) & 15) == 0) {
-        if (beta != 0.f) v += beta * *reinterpret_cast<const floatx4*>(c);
-        *reinterpret_cast<floatx4*>(c) = v;
-      } else {
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (col + q < N) c[q] = beta != 0.f ? v[q] + beta * c[q] : v[q];
-      }
-    }
+      for (int q = 0; q < 4; ++q) nan_if = fmaf(n0 + wn * WN + j * 16 + 4 * g4 + q < N ? total[i][j][q] : 0.f, 0.f, nan_if);
+    lost |= m0 + wm * WM + i * 16 + r16 < M && nan_if != 0.f;
   }
+  if (__any(lost)) {
+#pragma unroll 1
+    for (int t = 0; t < TM * TN; ++t)
+      store(t / TN, t % TN, redo_tile<A_KC, B_KC>(P, m0 + wm * WM + t / TN * 16, n0 + wn * WN + t % TN * 16, k_begin, k_end, lane));
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) store(i, j, total[i][j]);
 }
 
 template <int BM, int BN, int BK, int WGM, int WGN, int WGK, int PW, bool A_KC, bool B_KC>

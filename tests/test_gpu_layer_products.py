@@ -45,3 +45,75 @@ def test_gradients_of_a_plain_network(ngsgd, n, din, hidden, classes):
     for l in range(2):
         assert rel(gpu.last_gradient(l).cpu().numpy(), ora.last["delta"][l]) < TOL, l
         assert rel(gpu.get_params(l).cpu().numpy(), ora.W[l]) < TOL, l
+
+
+def plain_pair(ngsgd, dims, weights, n):
+    import torch
+    nonlin = [workloads.TANH] * (len(dims) - 2)
+    ora = NGSGDNetwork(dims, nonlin, weights, rank_in=0, rank_out=0)
+    gpu = ngsgd.Network(dims, nonlin, n, rank_in=0, rank_out=0)
+    for l, w in enumerate(weights):
+        gpu.set_params(l, torch.from_numpy(w).cuda())
+    return ora, gpu
+
+
+def gradients(ora, gpu, x, y):
+    """(oracle, GPU) mean log-probability and gradients of one step."""
+    import torch
+    with np.errstate(over="ignore", under="ignore"):
+        obj = ora.step(x, y, 0.01)
+    out = gpu.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.01)
+    grads = [gpu.last_gradient(l).cpu().numpy() for l in range(len(ora.W))]
+    return (obj, ora.last["delta"]), (float(out.item()), grads)
+
+
+def test_largest_finite_feature(ngsgd):
+    """A feature within 0.4 % of the largest fp32 number and a weight of zero: only the gradient sees it."""
+    rng = np.random.default_rng(6)
+    n, din, classes = 90, 36, 40
+    x = rng.standard_normal((n, din)).astype(np.float32)
+    x[17, 5] = 3.4e38
+    y = rng.integers(0, classes, n).astype(np.int32)
+    ora, gpu = plain_pair(ngsgd, [din, classes], [np.zeros((classes, din + 1), np.float32)], n)
+    (_, want), (_, got) = gradients(ora, gpu, x, y)
+    others = [c for c in range(din + 1) if c != 5]
+    assert rel(got[0][:, 5], want[0][:, 5]) < TOL
+    assert rel(got[0][:, others], want[0][:, others]) < TOL
+
+
+@pytest.mark.parametrize("din,hidden,classes", [(36, 40, 50), (128, 300, 259)])
+def test_class_with_an_infinite_bias(ngsgd, din, hidden, classes):
+    """A class switched off by a bias of minus infinity: it has probability zero, the others share the rest, and it gives
+    no derivative."""
+    rng = np.random.default_rng(7)
+    n, off = 130, 33
+    weights = [rng.standard_normal((o, i + 1)).astype(np.float32) / np.float32(np.sqrt(i + 1)) for i, o in ((din, hidden), (hidden, classes))]
+    weights[1][off, -1] = -np.inf
+    x = rng.standard_normal((n, din)).astype(np.float32)
+    y = rng.integers(0, 30, n).astype(np.int32)
+    ora, gpu = plain_pair(ngsgd, [din, hidden, classes], weights, n)
+    (obj_o, want), (obj_g, got) = gradients(ora, gpu, x, y)
+    assert abs(obj_g - obj_o) < 2e-6 * abs(obj_o)
+    for l in range(2):
+        assert rel(got[l], want[l]) < TOL, l
+    assert not got[1][off].any()
+
+
+@pytest.mark.parametrize("din,classes", [(36, 50), (360, 259)])
+def test_product_beyond_the_largest_number(ngsgd, din, classes):
+    """A class whose logit is a finite number times a finite number of the other sign, -1.4e50: minus infinity."""
+    rng = np.random.default_rng(8)
+    n, off = 130, 33
+    weights = [rng.standard_normal((classes, din + 1)).astype(np.float32) / np.float32(np.sqrt(din + 1))]
+    weights[0][:, 3] = 0.0
+    weights[0][off, 3] = -1.3e25
+    x = rng.standard_normal((n, din)).astype(np.float32)
+    x[:, 3] = rng.uniform(1.0e25, 1.2e25, n).astype(np.float32)
+    y = rng.integers(0, 30, n).astype(np.int32)
+    ora, gpu = plain_pair(ngsgd, [din, classes], weights, n)
+    (obj_o, want), (obj_g, got) = gradients(ora, gpu, x, y)
+    assert abs(obj_g - obj_o) < 2e-6 * abs(obj_o)
+    others = [c for c in range(din + 1) if c != 3]
+    assert rel(got[0][:, 3], want[0][:, 3]) < TOL
+    assert rel(got[0][:, others], want[0][:, others]) < TOL
+    assert not got[0][off].any()
