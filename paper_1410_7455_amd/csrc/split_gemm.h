@@ -1,17 +1,18 @@
 // fp32 matrix products on the bf16 matrix unit of gfx950, without giving up fp32 precision.
 //
-// Every fp32 operand is written as the sum of three bf16 numbers, x = h + m + l, each the round-to-nearest bf16 of
-// what the ones before left over.  bf16 has the exponent range of fp32 and 8 significant bits, so the three together
-// hold all 24 bits of x exactly (as long as l, about 2^-17 x, stays above the subnormal range).  A product of two
-// bf16 numbers is exact in fp32, and of the nine partial products
+// Every fp32 operand, times 2^23, is written as the sum of three bf16 numbers, x = h + m + l, each the round-to-nearest
+// bf16 of what the ones before left over.  bf16 has the exponent range of fp32 and 8 significant bits, so the three
+// together hold all 24 bits of x exactly; with the factor that is so down to the smallest subnormal number, whose last bit
+// becomes the smallest normal bf16 number (without it l is subnormal from 2^-109 on, and operands of 2^-118 give results
+// with errors of 1e-5 to 1e-4).  A product of two bf16 numbers is exact in fp32, and of the nine partial products
 //     a b = hh + (hm + mh) + (hl + mm + lh) + (ml + lm) + ll
 // the last three are below 2^-24 |a b| together, half a unit in the last place of an fp32 product: the kernel adds
 // the other six.  The matrix unit does them 16 times faster than fp32 products (2.5 PFLOP/s against 157 TFLOP/s), so
 // six of them cost 3/8 of one fp32 product.
-// Infinities do not split, nor do the numbers within 0.4 % of the largest, whose h is one, and partial products of
-// different signs may overflow where their sum is an infinity.  All of that ends as an infinity or a NaN in the sum: a
-// wavefront that finds one among its elements forms them again on the fp32 matrix unit (redo_tile), and that result
-// stands: a product is infinite, NaN or large exactly where the fp32 product is.
+// At the other end the factor leaves room for operands up to 2^104 and sums up to 2^81; infinities do not split, and
+// partial products of different signs may overflow where their sum is an infinity.  All of that ends as an infinity or a
+// NaN in the sum: a wavefront that finds one among its elements forms them again on the fp32 matrix unit (redo_tile), and
+// that result stands: a product is infinite, NaN or large exactly where the fp32 product is.
 // Accumulation is fp32 as before.  An instruction adds 32 products instead of 4 (v_mfma_f32_16x16x4_f32), and the matrix
 // unit does not round its accumulator additions to nearest, so the shorter chains make long sums more accurate, not less.
 #pragma once
@@ -29,9 +30,12 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uint32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kSplitPlanes = 3;
+constexpr float kSplitScale = 0x1p23f, kSplitUnscale = 0x1p-46f;   // of an operand; of a product of two
 
 // (x0, x1) -> three words, each holding the two elements' h, m and l.
 __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t (&out)[kSplitPlanes]) {
+  x0 *= kSplitScale;
+  x1 *= kSplitScale;
 #pragma unroll
   for (int p = 0; p < kSplitPlanes; ++p) {
     const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{x0, x1}), bf16x2));
@@ -444,7 +448,7 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) store(i, j, total[i][j]);
+    for (int j = 0; j < TN; ++j) store(i, j, kSplitUnscale * total[i][j]);
 }
 
 template <int BM, int BN, int BK, int WGM, int WGN, int WGK, int PW, bool A_KC, bool B_KC>

@@ -67,6 +67,29 @@ def gradients(ora, gpu, x, y):
     return (obj, ora.last["delta"]), (float(out.item()), grads)
 
 
+@pytest.mark.parametrize("where", ["features", "hidden weights", "output weights"])
+def test_operands_near_the_smallest_normal_number(ngsgd, where):
+    """Features and weights of about 2^-118: their products keep the precision of any other.  The last layer's gradient
+    holds the features (hidden activations) themselves, the first layer's the derivatives behind the output weights."""
+    rng = np.random.default_rng(5)
+    tiny = np.float32(2.0 ** -118)
+    dims = [36, 50] if where == "features" else [36, 40, 50]
+    n = 70
+    weights = [rng.standard_normal((dims[l + 1], dims[l] + 1)).astype(np.float32) / np.float32(np.sqrt(dims[l] + 1)) for l in range(len(dims) - 1)]
+    x = rng.standard_normal((n, 36)).astype(np.float32)
+    y = rng.integers(0, 50, n).astype(np.int32)
+    if where == "features":
+        x *= tiny
+    else:
+        weights[0 if where == "hidden weights" else 1] *= tiny
+    ora, gpu = plain_pair(ngsgd, dims, weights, n)
+    (_, want), (_, got) = gradients(ora, gpu, x, y)
+    at = 0 if where == "output weights" else len(dims) - 2
+    cols = slice(None) if where == "output weights" else slice(0, -1)      # (the bias input is one)
+    assert 0.0 < np.linalg.norm(want[at][:, cols]) < 1e-30
+    assert rel(got[at][:, cols], want[at][:, cols]) < TOL
+
+
 def test_largest_finite_feature(ngsgd):
     """A feature within 0.4 % of the largest fp32 number and a weight of zero: only the gradient sees it."""
     rng = np.random.default_rng(6)

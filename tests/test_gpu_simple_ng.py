@@ -86,6 +86,19 @@ def test_gram_tiles_and_splits(ngsgd, N, D):
     assert rel(rn_g, rn_o) < 2e-4
 
 
+@pytest.mark.parametrize("N,D", [(96, 200), (200, 96)])
+def test_large_inputs(ngsgd, N, D):
+    """Rows of about 2^60: the inverse, about 2^-122, enters the last product with the precision of any other operand
+    (the method does not change with the scale of its input)."""
+    import torch
+    rng = np.random.default_rng(60)
+    M = data(rng, N, D) * np.float32(2.0 ** 60 / np.sqrt(np.mean(data(rng, N, D) ** 2)))
+    got, g_g, _ = gpu_call(torch, ngsgd.SimplePreconditioner(N, D), M)
+    want, g_o, _ = simple_ng(M.astype(np.float64))
+    assert rel(got, want) < 1e-5
+    assert g_g == pytest.approx(g_o, rel=1e-5)
+
+
 def test_degenerate_inputs(ngsgd):
     """Zero matrix (gamma = 1, output 0), identical rows (output = input), rows on distinct axes (output = input)."""
     import torch
