@@ -124,6 +124,15 @@ __device__ __forceinline__ double block256_sum_f64(double v, double* red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// What a wavefront's lanes wrote to LDS before is what its lanes read behind it.  The hardware performs a wavefront's LDS
+// operations in order; the fences keep the compiler to that order too (the barrier alone does not order memory for it).
+// Costs no instruction.
+__device__ __forceinline__ void wave_lds_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ double reciprocal_f64(const double x) {   // hardware estimate, two Newton steps
   double r = __builtin_amdgcn_rcp(x);
   r = fma(fma(-x, r, 1.0), r, r);
@@ -330,7 +339,7 @@ __global__ __launch_bounds__(256) void init_tri_tail_kernel(const InitGroup* __r
 #pragma unroll
       for (int t = 0; t < TP / 64; ++t) w[lane + 64 * t] = fma(tau, yl[t], -half * vl[t]);
     }
-    __builtin_amdgcn_wave_barrier();   // LDS operations of a wavefront are performed in order
+    wave_lds_exchange();   // w
     {
       double vc[K], wc[K];
 #pragma unroll
@@ -375,7 +384,7 @@ __global__ __launch_bounds__(256) void init_tri_tail_kernel(const InitGroup* __r
     }
     for (int c = tid; c < np; c += 256)
       if (c < j0 || c >= n) Vj[c] = 0.0;
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_exchange();   // v
     double vc[K], acc[K];
 #pragma unroll
     for (int b = 0; b < K; ++b) vc[b] = v[tj + 16 * b];
