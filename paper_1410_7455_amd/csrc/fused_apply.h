@@ -65,13 +65,14 @@ struct FusedGroup {
   FusedArgs a[kMaxInstances];
 };
 
-// 16-byte load at device scope (sc1): served from where the atomics of all dies are performed, never from a stale
-// line of this die's caches.  The compiler does not track the load: wait_coherent_loads() must follow before use.
-__device__ __forceinline__ void load_coherent_f4(floatx4& dst, const float* p) {
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(dst) : "v"(p) : "memory");
-}
-__device__ __forceinline__ void wait_coherent_loads(floatx4& dst) {
-  asm volatile("s_waitcnt vmcnt(0)" : "+v"(dst) : : "memory");
+// 16 bytes at device scope (sc1): served from where the atomics of all dies are performed, never from a stale
+// line of this die's caches.  Two loads that the compiler knows of, so that it waits for them before the first use.
+__device__ __forceinline__ floatx4 load_coherent_f4(const float* p) {
+  const uint64_t* const q = reinterpret_cast<const uint64_t*>(p);
+  const uint64_t lo = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return floatx4{__builtin_bit_cast(float, (uint32_t)lo), __builtin_bit_cast(float, (uint32_t)(lo >> 32)),
+                 __builtin_bit_cast(float, (uint32_t)hi), __builtin_bit_cast(float, (uint32_t)(hi >> 32))};
 }
 
 // TIMING is for microbenchmarks only (bit 0: no atomics on H, bit 1: no wait); production code uses 0.
@@ -244,12 +245,8 @@ __global__ __launch_bounds__(kFusedThreads, (RC <= 80 ? 3 : 2)) void fused_apply
   {
     const float* hrow = P.H + (size_t)min(row, N - 1) * P.ldh;
     floatx4 hv[TJ];
-    {
 #pragma unroll
-      for (int jj = 0; jj < TJ; ++jj) load_coherent_f4(hv[jj], hrow + min(16 * jj + 4 * g4, P.ldh - 4));
-#pragma unroll
-      for (int jj = 0; jj < TJ; ++jj) wait_coherent_loads(hv[jj]);
-    }
+    for (int jj = 0; jj < TJ; ++jj) hv[jj] = load_coherent_f4(hrow + min(16 * jj + 4 * g4, P.ldh - 4));
 #pragma unroll
     for (int jj = 0; jj < TJ; ++jj) {
       const int left = R - (16 * jj + 4 * g4);

@@ -22,3 +22,10 @@ def test_wavefront_barriers_are_fenced():
         assert all_of_them == len(re.findall(fenced, text)), name
         seen += all_of_them
     assert seen > 0
+
+
+def test_no_load_in_inline_assembly():
+    """The compiler takes the output of an assembly statement as written at once: with the wait in another statement it
+    may use or reuse the register while the load is in flight."""
+    for name, text in sources():
+        assert not re.search(r'asm[^;]*"[^"]*(global|buffer|flat|ds|s)_(load|read)', text), name
