@@ -561,7 +561,13 @@ inline bool factor_due(const ngsgd_precond& p) { return p.t < p.always_update_fi
 // Clears the accumulation buffers of the listed instances (H always; K, L when the factor is updated) as far as they
 // are not still clear from the kernel that ended their last use (the finishing kernel of the fused path, the
 // orthogonality check of an update); no kernel is launched when that holds for all of them.
+// A call that is being captured runs later and any number of times: it always clears, and clears nothing for the others.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusActive;
+}
 int clear_accumulators(const std::vector<PrecondCall>& list, hipStream_t s) {
+  const bool captured = capturing(s);
   for (size_t done = 0; done < list.size();) {
     FillGroup fg;
     const int n = (int)std::min<size_t>(kMaxInstances, list.size() - done);
@@ -572,7 +578,7 @@ int clear_accumulators(const std::vector<PrecondCall>& list, hipStream_t s) {
       ngsgd_precond& p = *c.p;
       fg.ptr[i] = reinterpret_cast<uint32_t*>(p.zero_region);
       fg.n[i] = factor_due(p) ? p.zero_floats_all : p.arrive_slots + (size_t)c.N * p.ldh;
-      if (p.clean_rows >= c.N && (!factor_due(p) || p.kl_clean)) fg.n[i] = 0;
+      if (!captured && p.clean_rows >= c.N && (!factor_due(p) || p.kl_clean)) fg.n[i] = 0;
       p.clean_rows = 0;   // until the kernel that clears them again has been enqueued
       if (factor_due(p)) p.kl_clean = false;
       n_max = std::max(n_max, fg.n[i]);
@@ -792,7 +798,7 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
     }
     hipLaunchKernelGGL(finish_apply_kernel, dim3(n), dim3(1024), 0, s, g);
     LAUNCH_CHECK();
-    if (fused)
+    if (fused && !capturing(s))
       for (int i = 0; i < n; ++i) full[done + i].p->clean_rows = full[done + i].N;
     done += n;
   }
@@ -940,7 +946,7 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s) {
       r_max = std::max(r_max, p.rank);
     }
     og.count = n;
-    const bool clears = n == 1 || r_max <= kOrthClearRank;
+    const bool clears = n == 1 || r_max <= kOrthClearRank, counts = clears && !capturing(s);
     auto launch_new_factor = [&](const bool only_if_reorthogonalised) -> int {
       for (int rc : {32, 80, 96}) {
         std::vector<GemmDesc> d;
@@ -1006,7 +1012,7 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s) {
     NG_TRY(launch_new_factor(true));
     for (int i = 0; i < n; ++i) {
       ngsgd_precond& p = *to_update[done + i].p;
-      if (!clears) continue;
+      if (!counts) continue;
       p.clean_rows = p.last_N;
       p.kl_clean = true;
     }

@@ -423,3 +423,46 @@ def test_accumulators_stay_clear_between_calls(ngsgd, R):
         got, g_g, _ = gpu_call(torch, pre, M)
         assert rel(got, expect) < TOL, f"step {step}"
         assert g_g == pytest.approx(g_o, rel=1e-4)
+
+
+@pytest.mark.parametrize("replayed", [True, False])
+def test_captured_update_between_eager_calls(ngsgd, replayed):
+    """A captured call does not rely on what the calls before its capture left clear, nor the calls behind the capture on
+    what only a replay would clear.  The matrices have too many patches for the fused apply kernel: a call without an
+    update leaves in place what it accumulated."""
+    import torch
+    N, D, R = 1024, 10400, 4
+    rng = np.random.default_rng(31)
+    mats = [torch.from_numpy(np.ascontiguousarray(data(rng, N, D, decay=0.999))).cuda() for _ in range(7)]
+    # the reference runs every call eagerly; a captured call counts, so that the schedules differ
+    kw = dict(max_batch=N, num_samples_history=3000.0)
+    eager = ngsgd.Preconditioner(D, R, update_period=2 if replayed else 3, always_update_first=1, **kw)
+    captured = ngsgd.Preconditioner(D, R, update_period=1 << 30 if replayed else 2, always_update_first=2 if replayed else 1, **kw)
+    static = mats[0].clone()
+    graph = torch.cuda.CUDAGraph()
+
+    def capture():
+        with torch.cuda.graph(graph):
+            captured.precondition(static)
+
+    def both(m, replay=False):
+        other = m.clone()
+        eager.precondition(other)
+        static.copy_(m)
+        if replay:
+            graph.replay()
+        else:
+            captured.precondition(static)
+        torch.cuda.synchronize()
+        assert rel(static.cpu().numpy(), other.cpu().numpy()) < 1e-5
+
+    both(mats[0])                      # an update
+    if replayed:
+        capture()                      # of an update, behind one
+        for i in range(1, 7, 2):
+            both(mats[i])              # without
+            both(mats[i + 1], replay=True)
+    else:
+        both(mats[1])                  # without
+        capture()                      # of an update, behind a call without one, and never replayed
+        both(mats[2])                  # without
