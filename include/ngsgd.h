@@ -90,7 +90,9 @@ typedef struct {
   int32_t method;                 /* NGSGD_METHOD_ONLINE (App. B) or _SIMPLE (App. A)  */
   float simple_epsilon;           /* floor on tr(X^T X) in beta, App. A.2 (1e-20)      */
   int32_t side_streams;           /* internal streams for the factor updates: 0 = chosen
-                                   * by the sizes (1 or 2), else 1..3.  One: all updates
+                                   * by the layers, the ranks and max_batch (1 or 2; a network
+                                   * created for much larger minibatches than it is given may
+                                   * get the slower of the two), else 1..3.  One: all updates
                                    * start after the backward pass; two: the last layer's
                                    * derivatives and the layer inputs start after the
                                    * forward pass, the other derivatives after the backward

@@ -116,17 +116,20 @@ inline int rank_class(int rank) { return rank <= 32 ? 32 : (rank <= 80 ? 80 : 96
 constexpr int kSideStreams = 3;          // most
 // Without the caller's choice: one stream, or two (the last layer's derivatives and the layer inputs; the other
 // derivatives after the backward pass).  The second one takes the early group out of the chain that the next step waits
-// for, and costs a dozen launches and some events per update, and longer gaps on every queue.  It pays where the chain
-// (rank) is long, most of the factors are in the early group's way (layers) and the products of a step do not cover the
-// chain anyway.  Two streams against one, time per step: 3 layers, 130 - 2000 wide, rank 24 - 90: 1.02 - 1.25 times;
-// 5 and 6 layers, rank up to 60: 0.99 - 1.08; rank 70 - 90: 500 wide 0.97 - 0.99, 5 x 3000 (300) with 512 rows 0.99, with
-// 256 rows and 600 inputs 0.98 - 1.04, 512 rows 1.00 - 1.04, 6 x 2000 1.01 - 1.03.
+// for, and costs a dozen launches and some events per update, and longer gaps on every queue.  It pays where that chain is
+// long (a large rank), most of the factors are in the early group's way (layers) and the products of a step do not cover the
+// chain anyway.  Products grow with rows x parameters, the chain about with the rank's third power, and their ratio
+// separates what was measured.  Time per step with two streams over that with one, 57 networks, rank 64 to 96:
+//   5 to 8 layers, ratio up to 4400: 0.94 - 1.01, and 1.04 once (42 networks, 0.978 on average);
+//   ratio above: 1.00 - 1.06, and 0.985 once (5 x 3000 (300) with 512 rows, rank 80: 1.00; tanh layers of 1000 to 2000: 1.01 - 1.06);
+//   3 and 4 layers: 0.99 - 1.02.  Ranks 24 to 60: 0.99 - 1.08 with 5 or 6 layers, 1.02 - 1.25 with 3.
 // A third stream, which starts the upper hidden layers' derivatives in the middle of the backward pass, measured 1 - 2 %
 // slower than two on the speech-shaped network.
 constexpr int kTwoStreamsFromRank = 64, kTwoStreamsFromLayers = 5;
-constexpr double kTwoStreamsMostWork = 3.0e9;   // rows x parameters
+constexpr double kTwoStreamsMostRatio = 4400.0;   // rows x parameters / rank^3
 inline int default_side_streams(const int rank, const int n_layers, const double rows_by_params) {
-  return rank >= kTwoStreamsFromRank && n_layers >= kTwoStreamsFromLayers && rows_by_params <= kTwoStreamsMostWork ? 2 : 1;
+  const double chain = (double)rank * rank * rank;
+  return rank >= kTwoStreamsFromRank && n_layers >= kTwoStreamsFromLayers && rows_by_params <= kTwoStreamsMostRatio * chain ? 2 : 1;
 }
 struct SideSync {
   hipStream_t stream = nullptr;
