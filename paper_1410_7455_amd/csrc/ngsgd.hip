@@ -315,9 +315,10 @@ constexpr double kTileBlock[3][TILE_COUNT] = {{0.58, 0.90, 1.05, 1.40, 2.15, 0.9
                                               {0.75, 1.10, 1.30, 1.55, 2.40, 1.06},
                                               {1.00, 1.55, 1.90, 2.10, 2.90, 1.20}};
 LayerTile pick_layer_tile(LayerGemm layout, const GemmDesc* d, int n) {
-  LayerTile best = TILE_64x64;
+  LayerTile best = TILE_64x64_SHALLOW;
   double best_cost = 0.0;
   for (int t = 0; t < TILE_COUNT; ++t) {
+    if (t == TILE_64x64 && layout != GEMM_FWD) continue;   // the shallow one is cheaper for any size, and the only one built
     long long tiles = 0;
     double depth = 0.0;   // k values per tile, averaged over the tiles
     for (int i = 0; i < n; ++i) {
@@ -347,9 +348,12 @@ hipError_t launch_layer_tile(LayerTile t, const GemmDesc* d, int n, hipStream_t 
     case TILE_64x96: return launch_split_gemm<64, 96, 64, 2, 2, 2, 8, A_KC, B_KC>(d, n, s);
     case TILE_64x128: return launch_split_gemm<64, 128, 64, 2, 2, 2, 8, A_KC, B_KC>(d, n, s);
     case TILE_128x128: return launch_split_gemm<128, 128, 32, 2, 2, 1, 4, A_KC, B_KC>(d, n, s);
-    case TILE_64x64_SHALLOW: return launch_split_gemm<64, 64, 32, 2, 2, 1, 4, A_KC, B_KC>(d, n, s);
-    default: return launch_split_gemm<64, 64, 64, 2, 2, 2, 8, A_KC, B_KC>(d, n, s);
+    case TILE_64x64:
+      if constexpr (A_KC && B_KC) return launch_split_gemm<64, 64, 64, 2, 2, 2, 8, A_KC, B_KC>(d, n, s);
+      break;
+    default: break;
   }
+  return launch_split_gemm<64, 64, 32, 2, 2, 1, 4, A_KC, B_KC>(d, n, s);
 }
 
 // `slabs` (optional): how many split-K slabs of the first problem are written.

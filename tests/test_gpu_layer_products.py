@@ -16,10 +16,10 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-6
 
 # (minibatch, input, hidden, classes): below, at and above the tile sizes 32, 64, 96, 128 and the K-blocks of 32 and 64;
-# then shapes whose tile counts select the larger tiles
+# then shapes whose tile counts select the other tiles (test_kernel_sources.py looks after that)
 SHAPES = [(1, 4, 3, 2), (2, 8, 33, 5), (31, 36, 33, 17), (32, 64, 32, 64), (33, 60, 65, 31), (63, 64, 95, 97), (65, 68, 127, 129),
           (96, 128, 191, 193), (129, 256, 257, 63), (200, 300, 1000, 259), (512, 360, 3001, 1009), (515, 1024, 2051, 333),
-          (1027, 700, 2050, 301), (300, 2048, 2040, 300)]
+          (1027, 700, 2050, 301), (300, 2048, 2040, 300), (257, 100, 70, 4957), (291, 112, 61, 4974), (129, 100, 2545, 392), (92, 584, 133, 4882)]
 
 
 def rel(a, b):

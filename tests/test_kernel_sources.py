@@ -1,4 +1,5 @@
 """Rules of the kernel sources that no run can show to be broken: code that breaks them may pass every test."""
+import math
 import os
 import re
 
@@ -29,3 +30,63 @@ def test_no_load_in_inline_assembly():
     may use or reuse the register while the load is in flight."""
     for name, text in sources():
         assert not re.search(r'asm[^;]*"[^"]*(global|buffer|flat|ds|s)_(load|read)', text), name
+
+
+def tile_tables():
+    """The constants of the layer products' tile choice, as the library is built with them."""
+    with open(os.path.join(CSRC, "ngsgd.hip")) as f:
+        text = f.read()
+
+    def table(name):
+        body = re.search(name + r"\[[^=]*=\s*(\{.*?\});", text, re.S).group(1)
+        return eval(body.replace("{", "[").replace("}", "]"), {"__builtins__": {}})
+
+    def number(name):
+        return float(re.search(name + r" = ([0-9.]+);", text).group(1))
+
+    tiles = re.search(r"enum LayerTile \{([^}]*)\}", text).group(1).replace(" ", "").split(",")[:-1]
+    return dict(tiles=tiles, bm=table("kTileBM"), bn=table("kTileBN"), fill=table("kTileFill"), resident=table("kTileResident"),
+                block=table("kTileBlock"), launch=number("kTileLaunch"), units=int(number("kComputeUnits")),
+                slabs=int(number("kMaxBwdSplits")), target=int(number("kTargetBlocks")))
+
+
+FORWARD, BACKWARD, UPDATE = range(3)
+
+
+def tile_of(t, layout, products):
+    """The choice of pick_layer_tile for products (M, N, K, splits) of one launch."""
+    best = None
+    for i, name in enumerate(t["tiles"]):
+        if name == "TILE_64x64" and layout != FORWARD:
+            continue
+        tiles, depth = 0, 0.0
+        for m, n, k, splits in products:
+            here = -(-m // t["bm"][i]) * -(-n // t["bn"][i]) * splits
+            tiles += here
+            depth += here * -(-k // splits)
+        rounds = -(-tiles // t["units"])
+        cost = (t["launch"] + math.ceil(rounds / t["resident"][i]) * t["fill"][i] +
+                rounds * math.ceil(depth / tiles / 64.0) * t["block"][layout][i])
+        if best is None or cost < best[0]:
+            best = (cost, name)
+    return best[1]
+
+
+def tiles_of_network(t, n, din, hidden, classes):
+    """(layout, tile) of every layer product that test_gradients_of_a_plain_network launches for one of its shapes."""
+    layers = [(din + 1, hidden), (hidden + 1, classes)]
+    out = {(FORWARD, tile_of(t, FORWARD, [(n, o, i, 1)])) for i, o in layers}
+    slabs = t["target"] // (-(-n // 64) * -(-hidden // 64))
+    out.add((BACKWARD, tile_of(t, BACKWARD, [(n, hidden, classes, min(t["slabs"], max(1, min(slabs, -(-classes // 32)))))])))
+    out.add((UPDATE, tile_of(t, UPDATE, [(o, i, n, 1) for i, o in layers])))
+    out |= {(UPDATE, tile_of(t, UPDATE, [(o, i, n, 1)])) for i, o in layers}   # last_gradient: one product a launch
+    return out
+
+
+def test_layer_product_tests_reach_every_tile():
+    """The shapes of the layer products' tests select every tile that is built for a layout."""
+    from test_gpu_layer_products import SHAPES
+    t = tile_tables()
+    reached = set().union(*(tiles_of_network(t, *shape) for shape in SHAPES))
+    built = {(layout, name) for layout in range(3) for name in t["tiles"] if name != "TILE_64x64" or layout == FORWARD}
+    assert built == reached
