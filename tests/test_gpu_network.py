@@ -220,8 +220,8 @@ def test_c1_full_size_first_steps(ngsgd):
 
 def test_wide_layers_ragged_minibatch(ngsgd):
     """Layers as wide as those of configs[1] with a minibatch that is no multiple of any tile (500 rows): the
-    twelve-wavefront 64 x 96 tiles of the forward and backward products with a ragged row tile, ragged column tiles
-    and a K tail, and the last row block of the fused apply kernel (500 = 7 x 64 + 52) at ranks 20 and 80."""
+    64 x 96 tiles of the forward and backward products with a ragged row tile, ragged column tiles and a K tail, and
+    the last row block of the fused apply kernel (500 = 7 x 64 + 52) at ranks 20 and 80."""
     import dataclasses
     base = workloads.c1_pnorm()
     spec = dataclasses.replace(base, name="wide_ragged", index=11, dims=[360, 3000, 3000, 5000], nonlin=base.nonlin[:2],
@@ -354,17 +354,14 @@ def test_average_replicas_on_their_own_streams(ngsgd):
             assert rel(gpu.get_params(l).cpu().numpy(), ora.W[l]) < TOL
 
 
-def test_back_to_back_steps_equal_synchronised_steps(ngsgd):
-    """The factor updates of a step overlap the following steps on internal streams: steps enqueued back to back
-    must give what steps separated by a device synchronisation give.
-    (Both are GPU runs; sums over split products use atomics, so they agree to rounding, not bit for bit.)"""
+def back_to_back_equals_synchronised(ngsgd, side_streams):
     import torch
     spec = workloads.small_pnorm()
     batches = [workloads.minibatch(spec, t) for t in range(14)]
     batches = [(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()) for x, y in batches]
     finals = []
     for synchronise in (False, True):
-        _, gpu = make_pair(ngsgd, spec, renorm=True, max_change=0.075)
+        _, gpu = make_pair(ngsgd, spec, renorm=True, max_change=0.075, side_streams=side_streams)
         out = torch.zeros(1, dtype=torch.float64, device="cuda")
         objs = []
         for t, (x, y) in enumerate(batches):
@@ -380,6 +377,20 @@ def test_back_to_back_steps_equal_synchronised_steps(ngsgd):
     np.testing.assert_allclose(o_free, o_sync, rtol=1e-5)
     for a, b in zip(w_free, w_sync):
         assert rel(a, b) < 1e-5
+
+
+def test_back_to_back_steps_equal_synchronised_steps(ngsgd):
+    """The factor updates of a step overlap the following steps on internal streams: steps enqueued back to back
+    must give what steps separated by a device synchronisation give.
+    (Both are GPU runs; sums over split products use atomics, so they agree to rounding, not bit for bit.)"""
+    back_to_back_equals_synchronised(ngsgd, 0)
+
+
+@pytest.mark.parametrize("side_streams", [1, 2, 3])
+def test_back_to_back_steps_with_each_number_of_side_streams(ngsgd, side_streams):
+    """The same with one stream, and with two and three, whose groups of factor updates start before the backward pass and
+    are waited for in two places of the step behind an update: the default takes one or two by the network's sizes."""
+    back_to_back_equals_synchronised(ngsgd, side_streams)
 
 
 def test_small_pnorm_net_with_two_side_streams(ngsgd):
