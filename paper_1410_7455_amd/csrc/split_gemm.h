@@ -451,28 +451,14 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
     for (int j = 0; j < TN; ++j) store(i, j, kSplitUnscale * total[i][j]);
 }
 
+// Of a GemmDesc the kernel uses the operands, alpha, alpha_dev, beta and the splits; `gate`, `sym`, `aux` and `sumsq` are
+// for gemm_kernel.
 template <int BM, int BN, int BK, int WGM, int WGN, int WGK, int PW, bool A_KC, bool B_KC>
 inline hipError_t launch_split_gemm(const GemmDesc* descs, int count, hipStream_t stream) {
-  for (int done = 0; done < count;) {
-    GemmGroup grp;
-    const int n = (count - done) < kMaxGroup ? (count - done) : kMaxGroup;
-    grp.count = n;
-    int total = 0;
-    for (int i = 0; i < n; ++i) {
-      plan_tiles<BM, BN, BK>(descs[done + i], grp.p[i]);
-      grp.p[i].tile_begin = total;
-      total += grp.p[i].per_split * grp.p[i].splits;
-    }
-    grp.total_tiles = total;
-    if (total > 0) {
-      hipLaunchKernelGGL((split_gemm_kernel<BM, BN, BK, WGM, WGN, WGK, PW, A_KC, B_KC>),
-                         dim3((total + kXcds - 1) / kXcds * kXcds), dim3((WGM * WGN * WGK + PW) * 64), 0, stream, grp);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    done += n;
-  }
-  return hipSuccess;
+  for (int i = 0; i < count; ++i)
+    if (descs[i].gate != nullptr || descs[i].sym || descs[i].aux != nullptr || descs[i].sumsq != nullptr) return hipErrorInvalidValue;
+  return launch_unit_kernel<BM, BN, BK>(split_gemm_kernel<BM, BN, BK, WGM, WGN, WGK, PW, A_KC, B_KC>, (WGM * WGN * WGK + PW) * 64,
+                                        descs, count, stream);
 }
 
 }  // namespace ngsgd
