@@ -573,8 +573,7 @@ bool capturing(hipStream_t s) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusActive;
 }
-int clear_accumulators(const std::vector<PrecondCall>& list, hipStream_t s) {
-  const bool captured = capturing(s);
+int clear_accumulators(const std::vector<PrecondCall>& list, hipStream_t s, const bool captured) {
   for (size_t done = 0; done < list.size();) {
     FillGroup fg;
     const int n = (int)std::min<size_t>(kMaxInstances, list.size() - done);
@@ -726,6 +725,7 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
                   std::vector<PrecondCall>& to_update_out, bool hj_ready = false, bool do_products = true,
                   bool do_finish = true) {
   std::vector<PrecondCall> full, to_init, to_update;
+  const bool captured = capturing(s);
   for (auto& c : calls) {
     ngsgd_precond& p = *c.p;
     if (p.rank == 0) {
@@ -750,11 +750,11 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
   if (!do_products) {
     // the caller has issued the products already
   } else if (fused) {
-    NG_TRY(clear_accumulators(full, s));
+    NG_TRY(clear_accumulators(full, s, captured));
     NG_TRY(launch_fused_apply(full, s));
   } else if (!hj_ready) {
     if (!to_init.empty()) NG_TRY(run_init(to_init, s));
-    NG_TRY(clear_accumulators(full, s));
+    NG_TRY(clear_accumulators(full, s, captured));
     NG_TRY(launch_h_products(full, s));
     NG_TRY(launch_j_products(to_update, s));
   }
@@ -805,7 +805,7 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
     }
     hipLaunchKernelGGL(finish_apply_kernel, dim3(n), dim3(1024), 0, s, g);
     LAUNCH_CHECK();
-    if (fused && !capturing(s))
+    if (fused && !captured)
       for (int i = 0; i < n; ++i) full[done + i].p->clean_rows = full[done + i].N;
     done += n;
   }
@@ -1722,7 +1722,7 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
     SideSync& sd = net->side[k];
     HIP_TRY(hipEventRecord(sd.inputs_ready, s));
     HIP_TRY(hipStreamWaitEvent(sd.stream, sd.inputs_ready, 0));
-    NG_TRY(clear_accumulators(early_calls[k], sd.stream));
+    NG_TRY(clear_accumulators(early_calls[k], sd.stream, capturing(sd.stream)));
     NG_TRY(launch_h_products(early_calls[k], sd.stream));
     NG_TRY(launch_j_products(early_calls[k], sd.stream));
     HIP_TRY(hipEventRecord(sd.hj_done, sd.stream));
