@@ -96,11 +96,12 @@ typedef struct {
                                    * start after the backward pass; two: the last layer's
                                    * derivatives and the layer inputs start after the
                                    * forward pass, the other derivatives after the backward
-                                   * pass (shorter for deep networks with a large rank);
-                                   * three start the upper hidden layers in the middle of
-                                   * the backward pass.  One is better when many networks
-                                   * share the GPU, which has few hardware queues per
-                                   * process                                              */
+                                   * pass (shorter for deep networks with a large rank, also
+                                   * some that get one by default: worth a try for a network
+                                   * alone on its GPU); three start the upper hidden layers
+                                   * in the middle of the backward pass.  One is better when
+                                   * many networks share the GPU, which has few hardware
+                                   * queues per process                                    */
 } ngsgd_config;
 
 /* ---- one preconditioner instance (App. B) ------------------------------------------------- */

@@ -118,11 +118,14 @@ constexpr int kSideStreams = 3;          // most
 // derivatives after the backward pass).  The second one takes the early group out of the chain that the next step waits
 // for, and costs a dozen launches and some events per update, and longer gaps on every queue.  It pays where that chain is
 // long (a large rank), most of the factors are in the early group's way (layers) and the products of a step do not cover the
-// chain anyway.  Products grow with rows x parameters, the chain about with the rank's third power, and their ratio
-// separates what was measured.  Time per step with two streams over that with one, 57 networks, rank 64 to 96:
-//   5 to 8 layers, ratio up to 4400: 0.94 - 1.01, and 1.04 once (42 networks, 0.978 on average);
-//   ratio above: 1.00 - 1.06, and 0.985 once (5 x 3000 (300) with 512 rows, rank 80: 1.00; tanh layers of 1000 to 2000: 1.01 - 1.06);
-//   3 and 4 layers: 0.99 - 1.02.  Ranks 24 to 60: 0.99 - 1.08 with 5 or 6 layers, 1.02 - 1.25 with 3.
+// chain anyway.  Products grow with rows x parameters, the chain about with the rank's third power; where their ratio is
+// small two streams are the better choice whatever the data.  Time per step with two over that with one, rank 64 to 96,
+// fresh minibatches:
+//   5 to 8 layers, ratio up to 4400: 0.93 - 1.00, and 1.01 and 1.02 once (42 networks, 0.975 on average);
+//   ratio above: by the sweeps that the eigen-updates take.  5 x 3000 (300) with 512 rows, rank 80: 0.96 - 0.98 at a learning
+//   rate of 0.01 (8 to 10 sweeps), 1.00 - 1.01 at 0.002 (6 or 7), and 1.06 with three such networks in the process, which
+//   share four hardware queues; 6 layers 0.98 - 0.99 and 1.04; tanh layers of 1000 and 2000: 0.99 - 1.06;
+//   3 and 4 layers: 0.95 - 1.02.  Ranks 24 to 60: 0.99 - 1.08 with 5 or 6 layers, 1.02 - 1.25 with 3.
 // A third stream, which starts the upper hidden layers' derivatives in the middle of the backward pass, measured 1 - 2 %
 // slower than two on the speech-shaped network.
 constexpr int kTwoStreamsFromRank = 64, kTwoStreamsFromLayers = 5;
