@@ -22,7 +22,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_MFMA_F32_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
+PEAK_MFMA_F32_TFLOPS = 157.3      # MI355X dense fp32 matrix peak (the preconditioner's products)
+PEAK_MFMA_BF16_TFLOPS = 2516.6    # MI355X dense bf16 matrix peak
+PEAK_LAYER_TFLOPS = PEAK_MFMA_BF16_TFLOPS / 6   # the layer products: six bf16 products for one of fp32
 PEAK_HBM_GBS = 8000.0             # MI355X HBM3E
 POOL = 16                         # distinct matrices / minibatches resident on the GPU, cycled (side legs)
 REPLICA_POOL = 64                 # distinct minibatches per replica in the interleaving leg, cycled
@@ -68,10 +70,9 @@ def measured_traffic_per_launch(category):
     WRITE_SIZE runs of this file, scaled by a plain copy of known size; see the summary for the commands).
     None when the summary is missing or does not list the kernels."""
     import re
-    # template arguments after the tile shape: A K-contiguous, B K-contiguous, epilogue, sum of squares, chunk, fp64
-    pattern = {"gemm_fwd": r"gemm_kernel<\d+, \d+, 32, \d, \d, true, true, 0, false, 0, false",
-               "gemm_bwd": r"gemm_kernel<\d+, \d+, 32, \d, \d, true, false, 0, false, 4, false",
-               "gemm_upd": r"gemm_kernel<\d+, \d+, 32, \d, \d, false, false, 0, false, 0, false"}.get(category)
+    # template arguments: tile, K-block, wavefronts (M, N, K shares, staging), A K-contiguous, B K-contiguous
+    layout = {"gemm_fwd": "true, true", "gemm_bwd": "true, false", "gemm_upd": "false, false"}.get(category)
+    pattern = layout and r"split_gemm_kernel<\d+, \d+, \d+, \d, \d, \d, \d+, " + layout + ">"
     path = os.path.join(ROOT, "profiles", "step_c1_pnorm_hbm_traffic.txt")
     if pattern is None or not os.path.exists(path):
         return None
@@ -90,20 +91,22 @@ def measured_traffic_per_launch(category):
 
 def machine_peaks():
     """Peaks re-derived on the box that runs the measurement, next to the data-sheet values the fractions use:
-    fp32 matrix peak = compute units x clock x 256 flop / clock / unit (both read from `rocminfo`), and the
+    fp32 and bf16 matrix peak = compute units x clock x 256 and 4096 flop / clock / unit (read from `rocminfo`), and the
     bandwidth of a plain device-to-device copy of 1 GiB (read + write bytes over its HIP-event time)."""
     import re
     import subprocess
 
     import torch
 
-    out = dict(datasheet_mfma_f32_tflops=PEAK_MFMA_F32_TFLOPS, datasheet_hbm_gbs=PEAK_HBM_GBS)
+    out = dict(datasheet_mfma_f32_tflops=PEAK_MFMA_F32_TFLOPS, datasheet_mfma_bf16_tflops=PEAK_MFMA_BF16_TFLOPS,
+               layer_product_peak_tflops=PEAK_LAYER_TFLOPS, datasheet_hbm_gbs=PEAK_HBM_GBS)
     try:
         txt = subprocess.run(["rocminfo"], capture_output=True, text=True, timeout=60).stdout
         gpu = txt[txt.index("gfx9"):] if "gfx9" in txt else txt
         cus = int(re.search(r"Compute Unit:\s+(\d+)", gpu).group(1))
         mhz = int(re.search(r"Max Clock Freq\. \(MHz\):\s+(\d+)", gpu).group(1))
-        out.update(compute_units=cus, max_clock_mhz=mhz, derived_mfma_f32_tflops=cus * mhz * 1e6 * 256 / 1e12)
+        out.update(compute_units=cus, max_clock_mhz=mhz, derived_mfma_f32_tflops=cus * mhz * 1e6 * 256 / 1e12,
+                   derived_mfma_bf16_tflops=cus * mhz * 1e6 * 4096 / 1e12)
     except Exception as e:   # rocminfo missing or its format changed: the data-sheet values still stand
         out["rocminfo_error"] = str(e)[:200]
     src = torch.ones(256 * 1024 * 1024, dtype=torch.float32, device="cuda")
@@ -121,7 +124,7 @@ def machine_peaks():
     del src, dst
     log(f"[bench] machine: {out.get('compute_units')} CUs at {out.get('max_clock_mhz')} MHz -> "
         f"{out.get('derived_mfma_f32_tflops', float('nan')):.1f} TFLOP/s fp32 matrix peak (data sheet "
-        f"{PEAK_MFMA_F32_TFLOPS}); 1 GiB copy {out['measured_copy_gbs']:.0f} GB/s read+write (data sheet HBM "
+        f"{PEAK_MFMA_F32_TFLOPS}), {out.get('derived_mfma_bf16_tflops', float('nan')):.0f} bf16, layer products {PEAK_LAYER_TFLOPS:.0f}; 1 GiB copy {out['measured_copy_gbs']:.0f} GB/s read+write (data sheet HBM "
         f"{PEAK_HBM_GBS:.0f})")
     return out
 
@@ -179,7 +182,7 @@ def run_step_bench(args):
     always_first = 10                    # App. B.4: the factors are updated on each of the first 10 minibatches
     net = ng.Network(spec.dims, spec.nonlin, n, spec.pnorm_group, spec.rank_in, spec.rank_out, spec.alpha,
                      spec.num_samples_history, spec.epsilon, spec.update_period, renorm=True,
-                     max_change_per_sample=0.075)
+                     max_change_per_sample=0.075, side_streams=2)   # one network alone on its GPU (one stream: 2 - 4 % slower)
     for l, w in enumerate(workloads.initial_weights(spec)):
         net.set_params(l, torch.from_numpy(w).cuda())
     # Untimed: at least --warmup steps, and whatever it takes to leave the start-up phase of the schedule (state
@@ -262,18 +265,19 @@ def run_step_bench(args):
     dominant = max((k for k in breakdown if k in flops), key=lambda k: breakdown[k]["ms_per_step"])
     ms, cnt = prof[dominant]
     achieved = flops[dominant] * prof_steps / (ms * 1e-3) / 1e12
-    roofline = dict(bound="mfma", kernel=dominant, achieved=achieved, peak=PEAK_MFMA_F32_TFLOPS, unit="TFLOP/s",
-                    frac=achieved / PEAK_MFMA_F32_TFLOPS, traffic=measured_traffic_per_launch(dominant),
+    roofline = dict(bound="mfma", kernel=dominant, achieved=achieved, peak=PEAK_LAYER_TFLOPS, unit="TFLOP/s",
+                    peak_is="dense bf16 matrix peak / 6 (an fp32 product is formed from six bf16 products)",
+                    frac=achieved / PEAK_LAYER_TFLOPS, traffic=measured_traffic_per_launch(dominant),
                     traffic_unit="bytes of HBM traffic per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE); read from the "
                                  "committed summary under profiles/, not measured in this run",
                     algorithmic_bytes_per_launch=gemm_bytes_per_step(spec, n)[dominant] * prof_steps / cnt,
                     flops_per_launch=flops[dominant] * prof_steps / cnt, avg_launch_us=ms * 1e3 / cnt,
                     all_gemms_tflops=sum(flops.values()) * prof_steps /
                     (sum(prof[k][0] for k in flops) * 1e-3) / 1e12)
-    roofline["all_gemms_frac"] = roofline["all_gemms_tflops"] / PEAK_MFMA_F32_TFLOPS
-    # whole step: frames/s if every flop ran at the fp32 matrix peak and every algorithmic byte at the HBM peak
+    roofline["all_gemms_frac"] = roofline["all_gemms_tflops"] / PEAK_LAYER_TFLOPS
+    # whole step: frames/s if every flop ran at the peak of its matrix unit and every algorithmic byte at the HBM peak
     work = step_work(spec, n, period)
-    t_flops = (work["gemm_flops"] + work["precond_flops"]) / (PEAK_MFMA_F32_TFLOPS * 1e12)
+    t_flops = work["gemm_flops"] / (PEAK_LAYER_TFLOPS * 1e12) + work["precond_flops"] / (PEAK_MFMA_F32_TFLOPS * 1e12)
     t_bytes = (work["gemm_bytes"] + work["precond_bytes"]) / (PEAK_HBM_GBS * 1e9)
     at_peak = n / max(t_flops, t_bytes)
     step_roofline = dict(bound="mfma" if t_flops >= t_bytes else "hbm", flops_per_step=work["gemm_flops"] + work["precond_flops"],
@@ -420,14 +424,14 @@ def run_wide_bench(steps=40, warmup=12):
     gemm = {k: dict(ms_per_step=prof[k][0] / steps, tflops=flops[k] * steps / (prof[k][0] * 1e-3) / 1e12) for k in flops}
     all_tf = sum(flops.values()) * steps / (sum(prof[k][0] for k in flops) * 1e-3) / 1e12
     log(f"[bench] configs[3] wide tanh net: {elapsed * 1e3 / steps:.3f} ms/step, {n * steps / elapsed:,.0f} frames/s, "
-        f"layer GEMMs {all_tf:.1f} TFLOP/s ({all_tf / PEAK_MFMA_F32_TFLOPS * 100:.0f} % of fp32 matrix peak): "
+        f"layer GEMMs {all_tf:.1f} TFLOP/s ({all_tf / PEAK_LAYER_TFLOPS * 100:.0f} % of a sixth of the bf16 matrix peak): "
         + ", ".join(f"{k} {v['tflops']:.1f}" for k, v in gemm.items()) + f"; mean log-prob {final_logp:.4f}")
     del net
     return dict(workload="configs[3] wider tanh DNN: 440 -> 6x tanh 2048 -> 8000, minibatch 1024, ranks 20/80, "
                          "update period 4, max-change 0.075, lr 0.01",
                 value=n * steps / elapsed, unit="frames/s", ms_per_step=elapsed * 1e3 / steps, steps=steps,
                 final_mean_logprob=final_logp, gemm=gemm, all_gemms_tflops=all_tf,
-                all_gemms_mfma_frac=all_tf / PEAK_MFMA_F32_TFLOPS)
+                all_gemms_mfma_frac=all_tf / PEAK_LAYER_TFLOPS)
 
 
 def run_simple_bench(steps=60, warmup=5, calls=40):

@@ -90,3 +90,13 @@ def test_layer_product_tests_reach_every_tile():
     reached = set().union(*(tiles_of_network(t, *shape) for shape in SHAPES))
     built = {(layout, name) for layout in range(3) for name in t["tiles"] if name != "TILE_64x64" or layout == FORWARD}
     assert built == reached
+
+
+def test_traffic_summary_lists_the_layer_products():
+    """bench.py reports the HBM traffic of a layer product from the committed counter summary: the summary has to be of the
+    kernels that are launched."""
+    import bench
+    for category in ("gemm_fwd", "gemm_bwd", "gemm_upd"):
+        traffic = bench.measured_traffic_per_launch(category)
+        assert traffic is not None and 1e6 < traffic < 1e9, category
+    assert bench.measured_traffic_per_launch("elementwise") is None
