@@ -9,7 +9,7 @@
 //   3. their eigenvectors by inverse iteration from random vectors, a thread each, then orthonormalised together
 //      (twice, through the inverse Cholesky factor of their Gram matrix): vectors of equal eigenvalues start out
 //      independent and any orthonormal basis of their space serves;
-//   4. back with the reflections, four vectors per wavefront.
+//   4. back with the reflections, a vector per wavefront.
 // The error is a few eps |A| whatever the spectrum.  Bound: the chain of n - 160 launches.  Ten instances of the
 // speech-shaped network, five of them with n = 512: 3.6 ms, of it 352 launches of 14 us (reading and writing 2 MB per
 // instance) falling to 6 us (latency), the last 160 columns 0.38 ms, eigenvalues 0.14, inverse iteration 0.27,
@@ -489,7 +489,9 @@ constexpr double kInverseShift = 64.0 * kInitEps;
 constexpr int kInverseBlock = 8;
 constexpr int kInversePad = 3 * kInverseBlock;   // blocks are requested whole, and one ahead
 __host__ __device__ constexpr size_t inverse_lds_bytes(const int np) { return (5 * (size_t)(np + 2 * kInversePad) + 1) * sizeof(double); }
-__device__ __forceinline__ double inverse_start(const int i, const int k) {   // integer hash, uniform in [-1, 1)
+// Uniform in [-1, 1): an integer hash whose finisher (shifts and multipliers) is "lowbias32" of C. Wellons, "Prospecting for
+// hash functions", 2018.
+__device__ __forceinline__ double inverse_start(const int i, const int k) {
   uint32_t h = (uint32_t)i * 0x9E3779B9u ^ (uint32_t)(k + 1) * 0x85EBCA6Bu;
   h = (h ^ (h >> 16)) * 0x7FEB352Du;
   h = (h ^ (h >> 15)) * 0x846CA68Bu;

@@ -241,7 +241,10 @@ __device__ __forceinline__ floatx4 redo_tile(const GemmProblem& P, const int m0,
 // through LDS at the end).  Another PW wavefronts only stage: they load the next K-block, split it and write it to the
 // other LDS buffer.  Splitting costs as much vector-ALU time as the products cost matrix-unit time; with both in the
 // same wavefronts, in step with each other through the barrier, the two added up (1024 x 2048 x 2049: 55 us with
-// eight wavefronts that do both, 50 us with eight that multiply and eight that stage; 512 x 3000 x 301: 11.1 and 10.4 us).
+// eight wavefronts that do both, 50 us with eight that multiply and eight that stage; 512 x 3000 x 301: 11.1 and 10.4 us;
+// the factor 2^23 and the look for infinities have since added 6 %).  What bounds it: matrix unit 39 - 52 % busy, LDS 20 - 35 %
+// without conflicts, vector ALU issuing in 39 - 58 % of its slots for products of 1024 rows; the rest is the two roles' wait
+// for each other at the barrier of every K-block.
 template <int BM, int BN, int BK, int WGM, int WGN, int WGK, int PW, bool A_KC, bool B_KC>
 __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel(const GemmGroup g) {
   constexpr int CW = WGM * WGN * WGK;
@@ -342,8 +345,8 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
   // The product is formed transposed (B's rows as the rows of the MFMA tile): a lane then owns four adjacent columns
   // of one row of C, register q of lane (r16, g4) being C[.. + r16][.. + 4 g4 + q].
   // Two-level sums: an MFMA chain runs over kSplitFold K-blocks and is then added to the total with an ordinary fp32
-  // add.  The error stays near 2e-7 of the result's norm for every K (K = 301 / 2049 / 8000: 1.8e-7, 2.0e-7, 2.1e-7;
-  // the fp32 MFMA chains before: 3.1e-7, 8.1e-7 and, restarted every 128 products, 2.8e-7).
+  // add.  The error grows little with K (update products over 301 / 2049 / 8000 rows: 1.1e-7, 1.3e-7, 1.6e-7 of the result's
+  // norm; unbroken chains of fp32 MFMAs: 3.2e-7, 7.8e-7, 1.6e-6).
   floatx4 acc[TM][TN], total[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
