@@ -104,6 +104,29 @@ def test_largest_finite_feature(ngsgd):
     assert rel(got[0][:, others], want[0][:, others]) < TOL
 
 
+@pytest.mark.parametrize("where", ["features", "weights"])
+@pytest.mark.parametrize("n,din,hidden,classes", SHAPES[2:])
+def test_operands_beyond_the_range_of_the_split(ngsgd, n, din, hidden, classes, where):
+    """Features (softmax weights) of about 2^106, beyond what the bf16 terms hold, with hidden (softmax) inputs so small that
+    the logits are ordinary: every tile of the forward products and of the first layer's gradient (and of the backward
+    product) is formed on the fp32 matrix unit, in chains of 128 products: the same error as the split's."""
+    rng = np.random.default_rng(n + classes)
+    weights = [rng.standard_normal((o, i + 1)).astype(np.float32) / np.float32(np.sqrt(i + 1)) for i, o in ((din, hidden), (hidden, classes))]
+    x = rng.standard_normal((n, din)).astype(np.float32)
+    if where == "features":
+        x *= np.float32(2.0 ** 106)
+        weights[0] *= np.float32(2.0 ** -108)
+    else:
+        weights[0] *= np.float32(2.0 ** -106)
+        weights[1][:, :-1] *= np.float32(2.0 ** 106)
+    y = rng.integers(0, classes, n).astype(np.int32)
+    ora, gpu = plain_pair(ngsgd, [din, hidden, classes], weights, n)
+    (obj_o, want), (obj_g, got) = gradients(ora, gpu, x, y)
+    assert abs(obj_g - obj_o) < 2e-6 * abs(obj_o) + 1e-6
+    for l in range(2):
+        assert rel(got[l], want[l]) < TOL, l
+
+
 @pytest.mark.parametrize("din,hidden,classes", [(36, 40, 50), (128, 300, 259)])
 def test_class_with_an_infinite_bias(ngsgd, din, hidden, classes):
     """A class switched off by a bias of minus infinity: it has probability zero, the others share the rest, and it gives
