@@ -11,8 +11,8 @@
 // six of them cost 3/8 of one fp32 product.
 // At the other end the factor leaves room for operands up to 2^104 and sums up to 2^81; infinities do not split, and
 // partial products of different signs may overflow where their sum is an infinity.  All of that ends as an infinity or a
-// NaN in the sum: a wavefront that finds one among its elements forms them again on the fp32 matrix unit (redo_tile), and
-// that result stands: a product is infinite, NaN or large exactly where the fp32 product is.
+// NaN in the sum: a wavefront that finds one forms that 16 x 16 tile again on the fp32 matrix unit (redo_tile), and that
+// result stands: a product is infinite, NaN or large exactly where the fp32 product is.
 // Accumulation is fp32 as before.  An instruction adds 32 products instead of 4 (v_mfma_f32_16x16x4_f32), and the matrix
 // unit does not round its accumulator additions to nearest, so the shorter chains make long sums more accurate, not less.
 #pragma once
@@ -204,36 +204,47 @@ struct SplitStageSelect<false, ROWS, BK, NT> {
 
 constexpr int kSplitFold = 4;   // K-blocks per MFMA chain
 
-// Four elements (row, k), ..., (row, k + 3) of an operand; those from k_end on are zero.
-template <bool KC>
+// Four elements (row, k), ..., (row, k + 3) of an operand; TAIL: those from k_end on are zero.
+template <bool KC, bool TAIL>
 __device__ __forceinline__ floatx4 load_k4(const float* __restrict__ base, const int ld, const int row, const int k, const int k_end) {
+  if (KC && !TAIL) return *reinterpret_cast<const floatx4*>(base + (size_t)row * ld + k);
   floatx4 v;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int at = min(k + e, k_end - 1);
+    const int at = TAIL ? min(k + e, k_end - 1) : k + e;
     const float x = KC ? base[(size_t)row * ld + at] : base[(size_t)at * ld + row];
-    v[e] = k + e < k_end ? x : 0.f;
+    v[e] = !TAIL || k + e < k_end ? x : 0.f;
   }
   return v;
 }
 
 // The 16 x 16 tile of A B at row m0 and column n0 on the fp32 matrix unit, from memory, laid out as in the kernel below
-// (a lane owns four adjacent columns of one row).  For tiles that the split cannot form: nothing here is fast.
+// (a lane owns four adjacent columns of one row), for tiles that the split cannot form.  Bound: the latency of the loads, the
+// operands of up to 64 k values at a time.
 template <bool A_KC, bool B_KC>
 __device__ __forceinline__ floatx4 redo_tile(const GemmProblem& P, const int m0, const int n0, const int k_begin, const int k_end, const int lane) {
-  const int m = min(m0 + (lane & 15), P.M - 1), n = min(n0 + (lane & 15), P.N - 1), g4 = lane >> 4;
-  floatx4 total = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = k_begin; k0 < k_end; k0 += 128) {
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-    for (int k = k0; k < min(k0 + 128, k_end); k += 16) {
-      const floatx4 a = load_k4<A_KC>(P.A, P.lda, m, k + 4 * g4, k_end), b = load_k4<B_KC>(P.B, P.ldb, n, k + 4 * g4, k_end);
+  constexpr int BATCH = A_KC && B_KC ? 4 : (A_KC || B_KC ? 2 : 1);   // (more for row-contiguous operands takes registers from the kernel)
+  const int m = min(m0 + (lane & 15), P.M - 1), n = min(n0 + (lane & 15), P.N - 1), k4 = 4 * (lane >> 4);
+  floatx4 total = {0.f, 0.f, 0.f, 0.f}, acc = total;
+  auto add = [&](const floatx4 a, const floatx4 b) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc, 0, 0, 0);
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc, 0, 0, 0);
+  };
+  int k = k_begin;
+  for (; k + 16 * BATCH <= k_end; k += 16 * BATCH) {
+    floatx4 a[BATCH], b[BATCH];
+#pragma unroll
+    for (int t = 0; t < BATCH; ++t) {
+      a[t] = load_k4<A_KC, false>(P.A, P.lda, m, k + 16 * t + k4, k_end);
+      b[t] = load_k4<B_KC, false>(P.B, P.ldb, n, k + 16 * t + k4, k_end);
     }
-    total += acc;
+#pragma unroll
+    for (int t = 0; t < BATCH; ++t) add(a[t], b[t]);
+    total += acc;   // chains of at most 64 products
+    acc = floatx4{0.f, 0.f, 0.f, 0.f};
   }
-  return total;
+  for (; k < k_end; k += 16) add(load_k4<A_KC, true>(P.A, P.lda, m, k + k4, k_end), load_k4<B_KC, true>(P.B, P.ldb, n, k + k4, k_end));
+  return total + acc;
 }
 
 // C = alpha A B [+ beta C] (slab `split` of it at C + split * c_split_stride), see gemm_kernel for the operands.
@@ -442,16 +453,33 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
       for (int q = 0; q < 4; ++q) nan_if = fmaf(n0 + wn * WN + j * 16 + 4 * g4 + q < N ? total[i][j][q] : 0.f, 0.f, nan_if);
     lost |= m0 + wm * WM + i * 16 + r16 < M && nan_if != 0.f;
   }
-  if (__any(lost)) {
-#pragma unroll 1
-    for (int t = 0; t < TM * TN; ++t)
-      store(t / TN, t % TN, redo_tile<A_KC, B_KC>(P, m0 + wm * WM + t / TN * 16, n0 + wn * WN + t % TN * 16, k_begin, k_end, lane));
+  if (!__any(lost)) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) store(i, j, kSplitUnscale * total[i][j]);
     return;
   }
+  uint32_t redo = 0;   // tiles with such an element
+  static_assert(TM * TN <= 32, "a bit per tile");
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) store(i, j, kSplitUnscale * total[i][j]);
+    for (int j = 0; j < TN; ++j) {
+      float nan_if = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) nan_if = fmaf(total[i][j][q], 0.f, nan_if);
+      if (__any(nan_if != 0.f)) {
+        redo |= 1u << (i * TN + j);
+      } else {
+        store(i, j, kSplitUnscale * total[i][j]);
+      }
+    }
+  while (redo != 0) {   // uniform
+    const int t = __builtin_ctz(redo), i = t / TN, j = t % TN;
+    redo &= redo - 1;
+    store(i, j, redo_tile<A_KC, B_KC>(P, m0 + wm * WM + i * 16, n0 + wn * WN + j * 16, k_begin, k_end, lane));
+  }
 }
 
 // Of a GemmDesc the kernel uses the operands, alpha, alpha_dev, beta and the splits; `gate`, `sym`, `aux` and `sumsq` are
