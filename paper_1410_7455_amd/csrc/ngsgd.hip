@@ -574,7 +574,11 @@ inline bool factor_due(const ngsgd_precond& p) { return p.t < p.always_update_fi
 // A call that is being captured runs later and any number of times: it always clears, and clears nothing for the others.
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusActive;
+  if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+    (void)hipGetLastError();   // (the NULL stream beside a capture: a launch there reports that itself)
+    return false;
+  }
+  return status == hipStreamCaptureStatusActive;
 }
 int clear_accumulators(const std::vector<PrecondCall>& list, hipStream_t s, const bool captured) {
   for (size_t done = 0; done < list.size();) {
