@@ -138,7 +138,8 @@ int ngsgd_precond_get_state(const ngsgd_precond* p, float* dev_W, double* dev_d,
 
 /* Diagnostics of the latest factor update, copied to HOST memory after waiting for the stream:
  * flags (bit 0: orthogonality check still pending, 1: an eigenvalue of Z_t was floored, 2: the factor was
- * re-orthogonalised (App. B.3.1), 3: the eigen-solver hit its sweep limit) and the Jacobi sweeps it used. */
+ * re-orthogonalised (App. B.3.1), 3: the eigen-solver hit its sweep limit) and the Jacobi sweeps it used (1 where the
+ * direct solver served). */
 int ngsgd_precond_diagnostics(const ngsgd_precond* p, int32_t* flags_host, int32_t* sweeps_host,
                               void* hip_stream);
 

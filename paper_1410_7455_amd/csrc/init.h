@@ -22,7 +22,7 @@
 
 #include "gemm.h"
 #include "kernels.h"
-#include "small_update.h"
+#include "wave_f64.h"
 #include "state.h"
 
 namespace ngsgd {
@@ -89,74 +89,6 @@ __global__ __launch_bounds__(256) void init_mirror_kernel(const InitGroup* __res
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < 32; q += 8) a.A[(size_t)(i0 + r + q) * np + j0 + c] = t[c][r + q];
-}
-
-// Sum over the 64 lanes without LDS: the 16 lanes of a row through the vector ALU's cross-lane path, the four rows
-// through scalar registers.
-template <int CTRL>
-__device__ __forceinline__ double dpp_add_f64(const double v) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
-  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double read_lane_f64(const double v, const int lane) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double row16_sum_f64(double v) {
-  v = dpp_add_f64<0xB1>(v);    // quad_perm [1,0,3,2]
-  v = dpp_add_f64<0x4E>(v);    // quad_perm [2,3,0,1]
-  v = dpp_add_f64<0x141>(v);   // row_half_mirror
-  return dpp_add_f64<0x140>(v);   // row_mirror
-}
-__device__ __forceinline__ double wave_sum_uniform(double v) {
-  v = row16_sum_f64(v);
-  return (read_lane_f64(v, 0) + read_lane_f64(v, 16)) + (read_lane_f64(v, 32) + read_lane_f64(v, 48));
-}
-// all 256 threads; `red` holds 4 doubles, and another call with the same array is a barrier away
-__device__ __forceinline__ double block256_sum_f64(double v, double* red) {
-  v = wave_sum_uniform(v);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-// What a wavefront's lanes wrote to LDS before is what its lanes read behind it.  The hardware performs a wavefront's LDS
-// operations in order; the fences keep the compiler to that order too (the barrier alone does not order memory for it).
-// Costs no instruction.
-__device__ __forceinline__ void wave_lds_exchange() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ double reciprocal_f64(const double x) {   // hardware estimate, two Newton steps
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
-}
-// Reflection that maps (x0, tail) to (beta, 0), sigma the sum of squares of the tail: I - tau v v^T with v = (1, scale tail).
-struct Reflection {
-  double beta, tau, scale;
-};
-__device__ __forceinline__ Reflection reflection(const double x0, const double sigma) {
-  Reflection h;
-  h.beta = x0;
-  h.tau = h.scale = 0.0;
-  const double nn = fma(x0, x0, sigma);
-  if (sigma > 0.0 && nn > 1.0e-290) {   // (below: the column is zero)
-    double r = __builtin_amdgcn_rsq(nn);   // hardware estimate, two Newton steps
-    r = fma(0.5 * r, fma(-nn * r, r, 1.0), r);
-    r = fma(0.5 * r, fma(-nn * r, r, 1.0), r);
-    const double norm = nn * r, size = fabs(x0) + norm;
-    h.beta = x0 > 0.0 ? -norm : norm;
-    h.tau = fma(fabs(x0), r, 1.0);
-    h.scale = reciprocal_f64(x0 > 0.0 ? size : -size);
-  }
-  return h;
 }
 
 // Column j of the reduction.  Every workgroup forms the vectors for itself: w from the last column's product y = A v

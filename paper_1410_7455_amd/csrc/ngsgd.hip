@@ -180,8 +180,8 @@ struct ngsgd_precond {
   InitGroup* init_group = nullptr;   // device copy of the instance list of an initialisation this instance leads
   int* idx = nullptr;
   double* vwork = nullptr;
-  double2* rotlog = nullptr;      // Jacobi rotation log of the latest factor update
-  EigWork* eigwork = nullptr;
+  double2* rotlog = nullptr;      // scratch of a factor update's eigen-problem: Jacobi's rotation log,
+  double* direct = nullptr;       // what the kernels of the direct method hand on
   bool owned_by_net = false;
   SideSync* sync = nullptr;   // set for instances of a network
   int last_N = 0;             // rows of the latest call
@@ -225,9 +225,9 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.vwork = c.take<double>((size_t)kMaxRank + D);
   {
     const int m = (R + 1) & ~1;
-    const size_t rounds = ((size_t)kMaxSweeps * (m - 1 > 0 ? m - 1 : 1) + kEigvecChunk - 1) / kEigvecChunk * kEigvecChunk;
-    p.rotlog = c.take<double2>((rounds + kEigvecChunk) * (m / 2));   // padded: the log is read in whole chunks
-    p.eigwork = c.take<EigWork>(1);
+    const size_t rounds = ((size_t)kMaxSweeps * (m - 1) + 31) / 32 * 32;
+    p.rotlog = c.take<double2>((rounds + kEigLogPad) * (m / 2));
+    p.direct = c.take<double>(direct_scratch_doubles(R));
   }
 }
 
@@ -253,19 +253,39 @@ void precond_configure(ngsgd_precond& p, int dim, int rank, int max_batch, float
 bool g_attr_done = false;
 constexpr int kEigLdsReserve = 126 * 1024;   // dynamic LDS of a large eigen-update workgroup (of 160 KB per compute unit)
 constexpr int kEigReserveFromRank = 48;
-constexpr int kEigvecLdsReserve = 76 * 1024;   // on top of the 48 KB of the staged rotation log
+
+// Of the first kernel's LDS the reflections take a part already.
+template <int K>
+constexpr int kEigReduceReserve = kEigLdsReserve - DirectShape<K>::T * DirectShape<K>::T * (int)sizeof(double);
+template <int K, int ITEMS>
+hipError_t eig_attributes() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(eig_reduce_kernel<K>), hipFuncAttributeMaxDynamicSharedMemorySize, kEigReduceReserve<K>);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(eig_finish_kernel<K, ITEMS, kEigThreads, false>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                             kEigLdsReserve);
+}
+// The three kernels of an R x R update above rank 32.  A large eigen-problem is a long sequential chain bound by latency, on which
+// the next step waits: its single workgroups ask for most of the compute unit's LDS, so that no workgroup of the layer
+// products (which live on LDS bandwidth) is placed next to them.  That costs the products one compute unit in 256 per instance.
+template <int K, int ITEMS>
+hipError_t launch_eig(const SmallGroup& g, const int n, const int r_max, hipStream_t s) {
+  const size_t reserve = r_max >= kEigReserveFromRank ? kEigReduceReserve<K> : 0;
+  hipLaunchKernelGGL(eig_reduce_kernel<K>, dim3(n), dim3(kEigReduceThreads), reserve, s, g);
+  hipLaunchKernelGGL(eig_pairs_kernel<K>, dim3(n, (r_max + 3) / 4), dim3(256), 0, s, g);
+  const int half = (r_max + 1) / 2;
+  const size_t jacobi = (size_t)2 * 4 * (half * (half + 1) / 2) * sizeof(double);   // two copies of four planes of 2 x 2 blocks
+  const size_t direct = (size_t)(DirectShape<K>::T + 16) * DirectShape<K>::STRIDE * sizeof(double);
+  hipLaunchKernelGGL((eig_finish_kernel<K, ITEMS, kEigThreads, false>), dim3(n, (r_max + 15) / 16), dim3(kEigThreads), std::max(jacobi, direct), s, g);
+  return hipGetLastError();
+}
+static_assert((kMaxRank / 2) * (kMaxRank / 2 - 1) / 2 <= 2 * (kEigThreads - 64), "2 x 2 blocks of Jacobi's off-diagonal per thread: two");
 
 int ensure_kernel_attributes() {
   if (g_attr_done) return NGSGD_OK;
-  const int max_dyn = std::max(kEigLdsReserve, 2 * kMaxRank * (kMaxRank | 1) * (int)sizeof(double));
-  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(eig_update_kernel<1, kEigThreads>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, max_dyn));
-  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(eig_update_kernel<2, kEigThreads>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, max_dyn));
-  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(eig_update_kernel<kEigMaxItems, kEigThreads>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, max_dyn));
-  HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(eigvec_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kEigvecLdsReserve));
+  HIP_TRY((eig_attributes<3, 1>()));
+  HIP_TRY((eig_attributes<5, 1>()));
+  HIP_TRY((eig_attributes<6, 2>()));
   {
     const int orth_dyn = kMaxRank * (kMaxRank + 1) * (int)sizeof(double);
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(orth_fix_kernel<2>),
@@ -906,39 +926,24 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
       SmallArgs& a = g.a[i];
       a.st = p.st; a.K = p.K; a.L = p.L; a.At = p.At; a.ldat = p.ldh;
       a.R = p.rank; a.D = p.dim; a.N = p.last_N;
-      a.rotlog = p.rotlog; a.work = p.eigwork;
+      a.rotlog = p.rotlog; a.direct = p.direct;
       a.sumsq_part = p.sumsq_part;
       a.n_sumsq = p.n_sumsq;
       r_max = std::max(r_max, p.rank);
     }
     g.count = n;
-    {
-      ProfScope prof(NGSGD_PROF_PRECOND_SMALL, s);
-      const int m_max = (r_max + 1) & ~1;
-      const int n_blocks = (m_max / 2) * (m_max / 2 + 1) / 2;   // 2x2 blocks of the upper triangle
-      size_t eig_dyn = (size_t)2 * 4 * n_blocks * sizeof(double);   // two copies of four planes
-      // A large eigen-problem is a long sequential chain bound by LDS latency, on which the next step waits: it asks for
-      // most of the compute unit's LDS, so that no workgroup of the layer products (which live on LDS bandwidth) is
-      // placed next to it.  That costs the products one compute unit in 256 per instance.
-      if (m_max >= kEigReserveFromRank) eig_dyn = std::max<size_t>(eig_dyn, kEigLdsReserve);
-      const int n_off = (m_max / 2) * (m_max / 2 - 1) / 2;   // off-diagonal blocks, owned by the waves after the first
-      const int items = std::max(1, (n_off + (kEigThreads - 64) - 1) / (kEigThreads - 64));
-      if (m_max <= kEigSmallRank) {
-        hipLaunchKernelGGL((eig_update_kernel<1, kEigThreadsSmall>), dim3(n), dim3(kEigThreadsSmall), eig_dyn, s, g);
-      } else if (items <= 1) {
-        hipLaunchKernelGGL((eig_update_kernel<1, kEigThreads>), dim3(n), dim3(kEigThreads), eig_dyn, s, g);
-      } else if (items == 2) {
-        hipLaunchKernelGGL((eig_update_kernel<2, kEigThreads>), dim3(n), dim3(kEigThreads), eig_dyn, s, g);
-      } else {
-        hipLaunchKernelGGL((eig_update_kernel<kEigMaxItems, kEigThreads>), dim3(n), dim3(kEigThreads), eig_dyn, s, g);
-      }
-      LAUNCH_CHECK();
-    }
     ProfScope prof(NGSGD_PROF_PRECOND_SMALL, s);
-    const int rows_per_block = kEigvecThreads / 64;
-    hipLaunchKernelGGL(eigvec_kernel, dim3(n, (r_max + rows_per_block - 1) / rows_per_block), dim3(kEigvecThreads),
-                       r_max >= kEigReserveFromRank ? kEigvecLdsReserve : 0, s, g);
-    LAUNCH_CHECK();
+    if (r_max <= kEigSmallRank) {
+      using Shape = DirectShape<kEigSmallRank / 16>;
+      hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true>), dim3(n), dim3(kEigSmallThreads), 2 * Shape::T * Shape::STRIDE * sizeof(double), s, g);
+      LAUNCH_CHECK();
+    } else if (r_max <= 48) {
+      HIP_TRY((launch_eig<3, 1>(g, n, r_max, s)));
+    } else if (r_max <= 80) {
+      HIP_TRY((launch_eig<5, 1>(g, n, r_max, s)));
+    } else {
+      HIP_TRY((launch_eig<6, 2>(g, n, r_max, s)));
+    }
     done += n;
   }
   return NGSGD_OK;

@@ -1,34 +1,34 @@
 // The R x R part of the online natural-gradient update, entirely on the device (App. B.3, B.3.1).
 //
-// eig_update_kernel: one workgroup per instance forms Z_t from K_t and L_t (eq. zt:compute) and finds its
-// eigenvalues by cyclic Jacobi in fp64.  Only Z is rotated: its upper triangle lives in LDS in "position space"
-// (Brent-Luk: the members of pair k stand at positions 2k and 2k+1, and a fixed permutation between rounds brings
-// the next partners together), in two copies used alternately, so a round costs one barrier.  The first wavefront
-// computes the next round's rotations while the others rotate the 2x2 blocks; every rotation is written to a log.
-// The kernel then floors and orders the eigenvalues and produces rho_{t+1}, D_{t+1}, E_{t+1} and the scales of A_t.
-// eigvec_kernel: replays the rotation log on the rows of the identity (one wavefront per row of U_t, the two
-// columns of a pair in one lane, moved between lanes as the players move) and writes A_t (eq. wt1).
+// Z_t is formed from K_t and L_t (eq. zt:compute) and its eigenpairs come from the direct method of eig_direct.h, in one
+// kernel up to rank 32 and in three above (reduction, a workgroup per instance; eigenpairs, sixteen per workgroup; the rest).
+// The finishing kernel floors the eigenvalues and produces rho_{t+1}, D_{t+1}, E_{t+1} and A_t (eq. wt1).  Where the direct
+// method's checks fail it runs cyclic Jacobi first: only Z is rotated, its upper triangle in LDS in "position space"
+// (Brent-Luk: the members of pair k stand at positions 2k and 2k+1, and a fixed permutation between rounds brings the
+// next partners together), in two copies used alternately, so a round costs one barrier; every rotation is written to
+// a log, which is replayed on the rows of the identity.
 // orth_fix_kernel: the orthogonality check of App. B.3.1 and, when it fails, the Cholesky fix folded into A_t.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
+#include "eig_direct.h"
+#include "gemm.h"
 #include "kernels.h"
 #include "state.h"
+#include "wave_f64.h"
 
 namespace ngsgd {
 
 constexpr int kSmallThreads = 1024;          // orthogonality fix kernel
-constexpr int kEigThreads = 1024;          // R x R eigen-update kernel
-// Up to rank 40 the blocks of a round fit into three wavefronts next to the rotation wavefront, one on each SIMD; the
-// twelve others only meet at the barriers (rank 20: 45.4 -> 42.9 us).
-constexpr int kEigThreadsSmall = 256, kEigSmallRank = 40;
-// most 2x2 blocks of the upper triangle one thread may own
-constexpr int kEigMaxItems = ((kMaxRank / 2) * (kMaxRank / 2 - 1) / 2 + (kEigThreads - 64) - 1) / (kEigThreads - 64);
-
-constexpr int kEigvecThreads = 256;          // eigenvector kernel: 4 wavefronts, one row of U each
-constexpr int kEigvecChunk = 32;             // rounds of the rotation log staged in LDS at a time
+constexpr int kEigThreads = 1024;            // finishing kernel of the R x R update above rank 32
+constexpr int kEigReduceThreads = 256;
+// Up to here one kernel does it all: its 32 rows of lanes take all eigenpairs at once.  Update of a 512 x 3001 matrix: rank 20
+// 94 us with one kernel, 100 with three; rank 32 106 and 113.  (Above, the pairs of one workgroup would come in turns.)
+constexpr int kEigSmallRank = 32;
+constexpr int kEigSmallThreads = 512;
 constexpr int kMaxSweeps = 20;
+constexpr int kEigLogPad = 32;               // rounds that the log has room for beyond the last
 constexpr int kMaxHalf = kMaxRank / 2;
 constexpr int kMaxRounds = kMaxSweeps * (kMaxRank - 1);
 constexpr double kJacobiTol = 1.0e-13;       // a pair is left alone once |z_pq| <= tol * sqrt(z_pp z_qq)
@@ -38,26 +38,28 @@ constexpr double kJacobiLargeAbs = 1.0e3;    // ... and above this many absolute
 constexpr double kOrthoCondLimit = 1.0e6;    // App. B.3.1
 constexpr double kOrthoTolerance = 1.0e-3;   // App. B.3.1
 
-// What the eigen-update kernel leaves for the eigenvector kernel (device memory, per instance).
-struct EigWork {
-  int n_rounds;                  // Jacobi rounds executed (rotation log length / half)
-  int pad;
-  int rank_of[kMaxRank];         // position of eigenpair i in decreasing-eigenvalue order
-  double colscale[kMaxRank];     // (eta/N) sqrt(e_{t+1,k} / c_i) for eigenpair i at position k
-  double rowscale[kMaxRank];     // e_{t,j}^{-1/2}
-};
-
+constexpr size_t direct_scratch_doubles(const int R) { return (size_t)R * (2 * kMaxRank + 6) + 1; }
 struct SmallArgs {
   PrecondScalars* st;
   double* K;         // R x R, J J^T; cleared on exit (the orthogonality check accumulates W W^T into it)
   const double* L;   // R x R, H^T H
-  float* At;         // out: A_t (eq. wt1), R x ldat (written by the eigenvector kernel)
+  float* At;         // out: A_t (eq. wt1), R x ldat
   int ldat;
   int R, D, N;
   const double* sumsq_part;   // partial sums of tr(X X^T) left by the H product
   int n_sumsq;
-  double2* rotlog;   // [kMaxRounds][half] (c, s) of every pair of every round
-  EigWork* work;
+  double2* rotlog;   // [kMaxRounds][half] (c, s) of every pair of every round of Jacobi
+  // What the kernels of the direct method hand on: R rows of `ldv` doubles of reflections and of eigenvectors, six vectors, rho_t.
+  double* direct;
+  __device__ double* V() const { return direct; }
+  __device__ double* U(const int ldv) const { return direct + (size_t)R * ldv; }
+  __device__ double* vec(const int ldv, const int which) const { return direct + (size_t)R * (2 * ldv + which); }
+  __device__ double* tau(const int ldv) const { return vec(ldv, 0); }
+  __device__ double* diag(const int ldv) const { return vec(ldv, 1); }
+  __device__ double* off(const int ldv) const { return vec(ldv, 2); }
+  __device__ double* lambda(const int ldv) const { return vec(ldv, 3); }
+  __device__ double* residual(const int ldv) const { return vec(ldv, 4); }
+  __device__ double* d_rho(const int ldv) const { return vec(ldv, 5); }   // diag(D_t), then rho_t
 };
 struct SmallGroup {
   int count;
@@ -130,45 +132,59 @@ __device__ __forceinline__ int player_at(int pos, int rounds, int m) {
   return k == 0 ? m - 1 : (r - k + (m - 1)) % (m - 1);
 }
 
-// Z_t (eq. zt:compute), its eigenvalues by cyclic Jacobi, then rho_{t+1}, D_{t+1}, E_{t+1} (eq. rhodash2, dt1,
-// rhot1, beta2, etii).  One workgroup per instance.  Only Z is rotated here (upper triangle in position space,
-// two LDS copies used alternately); every rotation is logged, and the eigenvector kernel replays the log on the
-// rows of the identity.  A round is: wave 0 computes the half rotations | barrier | every thread rotates its
-// 2x2 blocks from one copy into their next positions in the other copy | barrier.
-template <int ITEMS, int NT>
-__global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
-  extern __shared__ __attribute__((aligned(16))) double dyn[];   // two copies of Z (upper triangle, four planes)
-  __shared__ double scratch[16];
-  __shared__ double s_ise[kMaxRank], s_dr[kMaxRank], s_c[kMaxRank + 1];
-  __shared__ __attribute__((aligned(16))) double2 s_cs[2][kMaxHalf];   // (c, s) of the pairs, this round's and the next's
-  __shared__ int s_perm[kMaxRank];
-  __shared__ int s_flag[2];
-  __shared__ int s_rotated[2];
+// Factors of Z_t and the scalars around it (eq. eta:ns, beta2, etii).
+struct UpdateFactors {
+  double eta, rho, sum_d;
+  double ck, cl, cd;   // of K, of L (with D_ii + rho + D_jj + rho), of the diagonal
+};
+// Every wavefront forms the sums for itself (two elements per lane: no barrier); s_ise and s_dr (beyond the rank 1 and 0) are
+// written by the first one and visible to all on return.
+static_assert(kMaxRank <= 128, "two elements per lane");
+__device__ __forceinline__ UpdateFactors update_factors(const SmallArgs& a, const SmallGroup& g, const double* d_t, const double rho, double* s_ise,
+                                                        double* s_dr, const int padded) {
+  const int lane = threadIdx.x & 63, R = a.R;
+  UpdateFactors f;
+  f.rho = rho;
+  double d[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) d[u] = lane + 64 * u < R ? d_t[lane + 64 * u] : 0.0;
+  f.eta = 1.0 - exp(-(double)a.N / g.num_samples_history);
+  f.sum_d = wave_sum_uniform(d[0] + d[1]);
+  const double beta = f.rho * (1.0 + g.alpha) + g.alpha / (double)a.D * f.sum_d;
+  if (threadIdx.x < 64) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = lane + 64 * u;
+      if (i >= padded) continue;
+      s_ise[i] = i < R ? 1.0 / sqrt(1.0 / (beta / d[u] + 1.0)) : 1.0;   // E_ii^{-1/2}
+      s_dr[i] = i < R ? d[u] + f.rho : 0.0;
+    }
+  }
+  f.ck = (f.eta / a.N) * (f.eta / a.N);
+  f.cl = f.eta * (1.0 - f.eta) / a.N;
+  f.cd = (1.0 - f.eta) * (1.0 - f.eta);
+  __syncthreads();
+  return f;
+}
+// Entry (i, j) of Z_t (eq. zt:compute), from the elements of K_t and L_t.
+__device__ __forceinline__ double z_entry(const UpdateFactors& f, const int i, const int j, const double k, const double l, const double* s_ise,
+                                          const double* s_dr) {
+  const double z = (f.ck * k + f.cl * l * (s_dr[i] + s_dr[j])) * s_ise[i] * s_ise[j];
+  return i == j ? fma(f.cd * s_dr[i], s_dr[i], z) : z;
+}
 
-  const SmallArgs& a = g.a[blockIdx.x];
-  const int R = a.R, D = a.D, N = a.N;
-  const int tid = threadIdx.x;
+// Eigenvalues of Z_t by cyclic Jacobi (upper triangle in position space, two LDS copies used alternately); every rotation is
+// logged.  A round: the first wavefront computes the next round's rotations from the old copy while the others rotate
+// the 2x2 blocks into their next positions in the other copy | barrier.
+// On return s_c[i] is the eigenvalue that player i carries.  All threads of the workgroup.
+template <int ITEMS, int NT>
+__device__ __forceinline__ void jacobi_eigenvalues(const SmallArgs& a, const UpdateFactors& f, const double* s_ise, const double* s_dr, double* dyn,
+                                                   double* scratch, double2 (*s_cs)[kMaxHalf], int* s_rotated, double* s_c, int& sweeps_out,
+                                                   int& rounds_out, bool& converged_out) {
+  const int R = a.R, tid = threadIdx.x;
   constexpr int nt = NT;
   const int m = (R + 1) & ~1;
   const int half = m / 2;
-  PrecondScalars* st = a.st;
-
-  const double eta = 1.0 - exp(-(double)N / g.num_samples_history);   // eq. eta:ns
-  const double rho = st->rho;
-  double tr_part = 0.0;   // tr(X X^T), summed here: the kernel that finishes the output may still be running
-  for (int i = tid; i < a.n_sumsq; i += nt) tr_part += a.sumsq_part[i];
-  const double tr_M = block_sum(tr_part, scratch);
-  static_assert(kMaxRank <= NT, "a thread per eigenvalue");
-  const double d_old = tid < R ? st->d[tid] : 0.0;
-  const double sum_d = block_sum(d_old, scratch);
-  const double beta = rho * (1.0 + g.alpha) + g.alpha / (double)D * sum_d;   // beta_t, eq. beta2
-  if (tid < R) {
-    const double e = 1.0 / (beta / d_old + 1.0);                      // eq. etii
-    s_ise[tid] = 1.0 / sqrt(e);
-    s_dr[tid] = d_old + rho;
-  }
-  __syncthreads();
-
   // Z_t from K_t and L_t (eq. zt:compute), symmetrised, laid out by position in four planes: plane 2a+b holds the
   // entry (2 bi + a, 2 bj + b) of every 2x2 block bi <= bj.  Blocks are numbered diagonal by diagonal (first the
   // blocks (k, k), then (k, k+1), ...): the permutation between rounds moves a block along its diagonal or to
@@ -188,7 +204,6 @@ __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
   };
   for (int idx = tid; idx < 2 * zcopy; idx += nt) dyn[idx] = 0.0;
   __syncthreads();
-  const double ck = (eta / N) * (eta / N), cl = eta * (1.0 - eta) / N;
   double zmax = 0.0;
   for (int idx = tid; idx < m * m; idx += nt) {
     const int pa = idx / m, pb = idx % m;
@@ -196,13 +211,8 @@ __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
     const int i = player_at(pa, 0, m), j = player_at(pb, 0, m);
     double z = 0.0;
     if (i < R && j < R) {
-      const double kij = 0.5 * (a.K[i * R + j] + a.K[j * R + i]);
-      const double lij = 0.5 * (a.L[i * R + j] + a.L[j * R + i]);
-      z = (ck * kij + cl * lij * (s_dr[i] + s_dr[j])) * s_ise[i] * s_ise[j];
-      if (i == j) {
-        z += (1.0 - eta) * (1.0 - eta) * s_dr[i] * s_dr[i];
-        zmax = fmax(zmax, z);
-      }
+      z = z_entry(f, i, j, 0.5 * (a.K[i * R + j] + a.K[j * R + i]), 0.5 * (a.L[i * R + j] + a.L[j * R + i]), s_ise, s_dr);
+      if (i == j) zmax = fmax(zmax, z);
     }
     dyn[place(pa, pb)] = z;
   }
@@ -268,7 +278,7 @@ __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
     rz_da = slot(pa, pa);
     rz_db = slot(pb, pb);
   }
-  double2* __restrict__ rotlog = a.rotlog;
+  double2* __restrict__ rotlog = a.rotlog;   // (what the direct method left there has been read)
   if (tid < 64) __builtin_amdgcn_s_setprio(3);   // the rotation wave's dependent chain bounds the round
   if (tid < 2) s_rotated[tid] = 0;
   __syncthreads();
@@ -344,58 +354,15 @@ __global__ __launch_bounds__(NT) void eig_update_kernel(const SmallGroup g) {
     if (tid == 0) s_rotated[sweeps & 1] = 0;
   }
 
-  // eigenvalues (by player), floor (after eq. zt:eig:repeat), decreasing order
   const int fo = cur ? zcopy : 0;
-  const double floor_c = (1.0 - eta) * (1.0 - eta) * rho * rho;
-  if (tid == 0) s_flag[0] = 0;
-  __syncthreads();
   for (int pos = tid; pos < m; pos += nt) {
     const int i = player_at(pos, rounds, m);
-    if (i >= R) continue;
-    double c = dyn[fo + place(pos, pos)];
-    if (!(c >= floor_c)) {
-      c = floor_c;
-      s_flag[0] = 1;
-    }
-    s_c[i] = c;
+    if (i < R) s_c[i] = dyn[fo + place(pos, pos)];
   }
-  __syncthreads();
-  for (int i = tid; i < R; i += nt) {
-    int rank = 0;
-    const double c = s_c[i];
-    for (int j = 0; j < R; ++j) rank += (s_c[j] > c || (s_c[j] == c && j < i)) ? 1 : 0;
-    s_perm[rank] = i;   // s_perm[k] = index of the k-th largest eigenvalue
-    a.work->rank_of[i] = rank;
-  }
-  __syncthreads();
-  // eq. rhodash2, dt1, rhot1
-  const double root = tid < R ? sqrt(s_c[s_perm[tid]]) : 0.0;   // eigenpair at position tid
-  const double sum_sqrt = block_sum(root, scratch);
-  const double rho_dash = ((eta / N) * tr_M + (1.0 - eta) * ((double)D * rho + sum_d) - sum_sqrt) / (double)(D - R);
-  const double rho_new = fmax(g.epsilon, rho_dash);
-  const double dn = fmax(root - rho_dash, g.epsilon);
-  const double beta_new = rho_new * (1.0 + g.alpha) + g.alpha / (double)D * block_sum(tid < R ? dn : 0.0, scratch);
-  if (tid == 0) {
-    const double cmax = s_c[s_perm[0]], cmin = s_c[s_perm[R - 1]];
-    int flags = 0;
-    if (s_flag[0]) flags |= kFlagFloored | kFlagOrthCheck;
-    if (cmax > kOrthoCondLimit * cmin) flags |= kFlagOrthCheck;
-    if (!converged) flags |= kFlagNoConverge;
-    st->flags = flags;
-    st->sweeps = sweeps;
-    st->rho = rho_new;
-    st->beta = beta_new;
-    a.work->n_rounds = rounds;
-  }
-  if (tid < R) {
-    const double en = 1.0 / (beta_new / dn + 1.0);
-    st->d[tid] = dn;
-    st->e[tid] = en;
-    // A_t = (eta/N) E_{t+1}^{1/2} C_t^{-1/2} U_t^T E_t^{-1/2}  (eq. wt1): scale of row k / eigenpair s_perm[k]
-    a.work->colscale[s_perm[tid]] = (eta / N) * sqrt(en / s_c[s_perm[tid]]);
-    a.work->rowscale[tid] = s_ise[tid];
-  }
-  for (int idx = tid; idx < R * R; idx += nt) a.K[idx] = 0.0;
+  if (tid < 64) __builtin_amdgcn_s_setprio(0);
+  sweeps_out = sweeps;
+  rounds_out = rounds;
+  converged_out = converged;
 }
 
 // Whole-wavefront shifts by one lane through the DPP path of the vector ALU (no LDS traffic): lane i receives the
@@ -413,87 +380,421 @@ __device__ __forceinline__ double wave_shift_down(double x) {
   return __hiloint2double(hi, lo);
 }
 
-// U_t by replaying the rotation log on rows of the identity, then A_t (eq. wt1).  U <- U J only mixes two
-// columns, so rows are independent: each wavefront owns one row and keeps it in registers.  Lane k holds the two
+// U_t by replaying the rotation log on rows of the identity, written as A_t (eq. wt1).  U <- U J only mixes two
+// columns, so rows are independent: a wavefront owns ROWS rows and keeps them in registers.  Lane k holds the two
 // columns that pair k rotates; between rounds the columns move to the neighbouring lanes exactly as the players
-// of the round-robin schedule do (the first lane's second player never moves).  The log is staged through LDS
-// in chunks of kEigvecChunk rounds, the next chunk being fetched while the current one is replayed.
-__global__ __launch_bounds__(kEigvecThreads) void eigvec_kernel(const SmallGroup g) {
-  __shared__ double2 s_log[2][kEigvecChunk * kMaxHalf];
-  extern __shared__ double eigvec_reserved[];   // not used: see the launch
-  const SmallArgs& a = g.a[blockIdx.x];
+// of the round-robin schedule do (the first lane's second player never moves).
+template <int ROWS, int NT>
+__device__ __forceinline__ void replay_rotations(const SmallArgs& a, const int n_rounds, const int* s_rank, const double* s_col, const double* s_ise) {
   const int R = a.R;
   const int m = (R + 1) & ~1, half = m / 2;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row = blockIdx.y * (kEigvecThreads / 64) + wave;   // rows >= R idle along (they share the barriers)
-  const int n_rounds = a.work->n_rounds;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int NW = NT / 64;
   const bool active = lane < half;
   // Lanes beyond the last pair replay the last pair's rotations on zeros: nothing of theirs reaches an active
   // lane (a lane takes from its lower neighbour, and the last active lane takes its own second member).
-  const int ll = active ? lane : half - 1;
+  const double2* lg = a.rotlog + (active ? lane : half - 1);
   // players held by this lane in round 0: first k, second m-1-k (lane 0: the fixed player m-1)
-  double top = (active && lane == row) ? 1.0 : 0.0;
-  double bot = (active && m - 1 - lane == row) ? 1.0 : 0.0;
+  double top[ROWS], bot[ROWS];
+#pragma unroll
+  for (int q = 0; q < ROWS; ++q) {
+    top[q] = active && lane == wave + NW * q ? 1.0 : 0.0;
+    bot[q] = active && m - 1 - lane == wave + NW * q ? 1.0 : 0.0;
+  }
   const bool last_lane = lane == half - 1, lane0 = lane == 0, lane1 = lane == 1;
   const bool single = m == 2;   // one pair: nothing moves
-
-  // the log is padded to whole chunks, and one chunk beyond the last round is allocated: staging needs no guards
-  constexpr int kLoads = (kEigvecChunk * kMaxHalf + kEigvecThreads - 1) / kEigvecThreads;
-  const int chunk_elems = kEigvecChunk * half;
-  const double2* __restrict__ rotlog = a.rotlog;
-  int src[kLoads];
+  auto replay = [&](const double2 cs) {
 #pragma unroll
-  for (int u = 0; u < kLoads; ++u) src[u] = min(tid + u * kEigvecThreads, chunk_elems - 1);
-  double stage_c[kLoads], stage_s[kLoads];   // plain scalars: they must stay in registers
-#pragma unroll
-  for (int u = 0; u < kLoads; ++u) s_log[0][src[u]] = rotlog[src[u]];
-  __syncthreads();
-  for (int base = 0, buf = 0; base < n_rounds; base += kEigvecChunk, buf ^= 1) {
-    const bool more = base + kEigvecChunk < n_rounds;
-    if (more) {   // in flight while this chunk is replayed
-#pragma unroll
-      for (int u = 0; u < kLoads; ++u) {
-        const double2 v = rotlog[(size_t)(base + kEigvecChunk) * half + src[u]];
-        stage_c[u] = v.x;
-        stage_s[u] = v.y;
-      }
-    }
-    const int len = min(kEigvecChunk, n_rounds - base);
-    const double2* lg = s_log[buf] + ll;
-    auto replay = [&](double2 cs) {
+    for (int q = 0; q < ROWS; ++q) {
       // the logged rotation acts on (first, second) of the pair
-      const double nt_ = top * cs.x - bot * cs.y, nb_ = top * cs.y + bot * cs.x;
+      const double nt_ = top[q] * cs.x - bot[q] * cs.y, nb_ = top[q] * cs.y + bot[q] * cs.x;
       // players move: firsts shift one lane down (the last lane takes its own second), seconds shift one lane
       // up (lane 1 takes lane 0's first); lane 0's second is fixed.  With a single pair (m = 2) lane 0 is the
       // last lane as well and both members stay.
       const double t_dn = wave_shift_down(nt_);
       const double b_up = wave_shift_up(nb_);
       const double t_up = wave_shift_up(nt_);
-      top = last_lane ? (single ? nt_ : nb_) : t_dn;
-      bot = lane0 ? nb_ : (lane1 ? t_up : b_up);
-    };
-    int rr = 0;
-    for (; rr + 4 <= len; rr += 4) {   // four rotations fetched ahead of their use
-      const double2 c0 = lg[(rr + 0) * half], c1 = lg[(rr + 1) * half], c2 = lg[(rr + 2) * half], c3 = lg[(rr + 3) * half];
-      replay(c0);
-      replay(c1);
-      replay(c2);
-      replay(c3);
+      top[q] = last_lane ? (single ? nt_ : nb_) : t_dn;
+      bot[q] = lane0 ? nb_ : (lane1 ? t_up : b_up);
     }
-    for (; rr < len; ++rr) replay(lg[rr * half]);
-    if (more) {
+  };
+  constexpr int AHEAD = 8;   // rounds requested ahead; the log is longer than the last round by more than that
+  double2 cs[AHEAD];
 #pragma unroll
-      for (int u = 0; u < kLoads; ++u) s_log[buf ^ 1][src[u]] = make_double2(stage_c[u], stage_s[u]);
+  for (int u = 0; u < AHEAD; ++u) cs[u] = lg[u * half];
+  for (int rr = 0; rr < n_rounds; rr += AHEAD) {
+    double2 next[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) next[u] = lg[(size_t)(rr + AHEAD + u) * half];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      if (rr + u < n_rounds) replay(cs[u]);
     }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) cs[u] = next[u];
   }
-  if (!active || row >= R) return;
+  if (!active) return;
   // the players standing at this lane's two positions after n_rounds rounds
   const int tp = player_at(2 * lane, n_rounds, m), bp = player_at(2 * lane + 1, n_rounds, m);
-  const int j = row;   // row of U = column of A_t
-  const double rs = a.work->rowscale[j];
-  if (tp < R) a.At[(size_t)a.work->rank_of[tp] * a.ldat + j] = (float)(a.work->colscale[tp] * top * rs);
-  if (bp < R) a.At[(size_t)a.work->rank_of[bp] * a.ldat + j] = (float)(a.work->colscale[bp] * bot * rs);
+#pragma unroll
+  for (int q = 0; q < ROWS; ++q) {
+    const int j = wave + NW * q;   // row of U = column of A_t
+    if (j >= R) continue;
+    if (tp < R) a.At[(size_t)s_rank[tp] * a.ldat + j] = (float)(s_col[s_rank[tp]] * top[q] * s_ise[j]);
+    if (bp < R) a.At[(size_t)s_rank[bp] * a.ldat + j] = (float)(s_col[s_rank[bp]] * bot[q] * s_ise[j]);
+  }
+}
+
+// K_t and L_t, all elements requested together, in the registers of NT threads, see eig_direct.h; then Z_t from them.
+template <int K, int NT>
+struct ZLoad {
+  static constexpr int A = DirectTile<K, NT>::A, ROWS = DirectTile<K, NT>::ROWS;
+  double k[A][K], l[A][K];
+  __device__ __forceinline__ void request(const SmallArgs& a) {
+    const int ti = DirectTile<K, NT>::ti(), tj = DirectTile<K, NT>::tj(), last = a.R - 1;
+#pragma unroll
+    for (int x = 0; x < A; ++x)
+#pragma unroll
+      for (int b = 0; b < K; ++b) {
+        const int at = min(ti + ROWS * x, last) * a.R + min(tj + 16 * b, last);
+        k[x][b] = a.K[at];
+        l[x][b] = a.L[at];
+      }
+  }
+  __device__ __forceinline__ void form(const SmallArgs& a, const UpdateFactors& f, const double* s_ise, const double* s_dr, double (&S)[A][K]) const {
+    const int ti = DirectTile<K, NT>::ti(), tj = DirectTile<K, NT>::tj();
+#pragma unroll
+    for (int x = 0; x < A; ++x)
+#pragma unroll
+      for (int b = 0; b < K; ++b) {
+        const int i = ti + ROWS * x, j = tj + 16 * b;
+        S[x][b] = i < a.R && j < a.R ? z_entry(f, i, j, k[x][b], l[x][b], s_ise, s_dr) : 0.0;
+      }
+  }
+};
+
+// Above rank 32, first kernel: Z_t and its reduction.  A workgroup per instance.
+template <int K>
+__global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const SmallGroup g) {
+  using Shape = DirectShape<K>;
+  constexpr int NT = kEigReduceThreads;
+  constexpr int T = Shape::T;
+  extern __shared__ double eig_reserved[];   // not used: see the launch
+  __shared__ double s_ise[T], s_dr[T], s_tau[T], s_diag[T], s_off[T];
+  __shared__ DirectLds<K, NT> lds;
+  __shared__ __attribute__((aligned(16))) double s_V[T * T];
+  const SmallArgs& a = g.a[blockIdx.x];
+  const int R = a.R, tid = threadIdx.x;
+  ZLoad<K, NT> load;
+  load.request(a);
+  const double rho = a.st->rho;
+  const UpdateFactors f = update_factors(a, g, a.st->d, rho, s_ise, s_dr, T);
+  // handed on: the last kernel's workgroups cannot read what one of them replaces
+  for (int i = tid; i <= R; i += NT) a.d_rho(T)[i] = i < R ? a.st->d[i] : rho;
+  typename DirectTile<K, NT>::Regs S;
+  load.form(a, f, s_ise, s_dr, S);
+  direct_reduce<K, NT>(S, R, lds, s_V, s_tau, s_off);
+  direct_store_tridiagonal<K, NT>(S, R, s_diag, s_off);
+  __syncthreads();
+  for (int e = tid; e < (R - 2) * T / 2; e += NT) reinterpret_cast<double2*>(a.V())[e] = reinterpret_cast<const double2*>(s_V)[e];
+  if (tid < R) {
+    a.diag(T)[tid] = s_diag[tid];
+    if (tid < R - 1) a.off(T)[tid] = s_off[tid];
+    if (tid < R - 2) a.tau(T)[tid] = s_tau[tid];
+  }
+}
+
+// Second kernel: four eigenpairs per workgroup of 256 threads.  Grid (instance, ceil(R / 4)).
+template <int K>
+__global__ __launch_bounds__(256) void eig_pairs_kernel(const SmallGroup g) {
+  using Shape = DirectShape<K>;
+  constexpr int T = Shape::T;
+  __shared__ DirectTridiagonal<K> t;
+  __shared__ double s_tau[T], s_work[4][kDirectWork<K>], s_g[T / 4][6];
+  __shared__ __attribute__((aligned(16))) double s_V[T * T];
+  const SmallArgs& a = g.a[blockIdx.x];
+  const int R = a.R, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if ((int)blockIdx.y * 4 >= R) return;
+  if (tid < T) {
+    t.diag[tid] = tid < R ? a.diag(T)[tid] : 0.0;
+    t.off[tid] = tid < R - 1 ? a.off(T)[tid] : 0.0;
+    s_tau[tid] = tid < R - 2 ? a.tau(T)[tid] : 0.0;
+  }
+  const double2* const v_in = reinterpret_cast<const double2*>(a.V());
+#pragma unroll 4
+  for (int e = tid; e < T * T / 2; e += 256)
+    reinterpret_cast<double2*>(s_V)[e] = e < (R - 2) * T / 2 ? v_in[e] : make_double2(0.0, 0.0);
+  __syncthreads();
+  direct_block_products<K, 256>(s_V, T, R, s_g);
+  double lo, hi, norm, x[K], lambda, residual;
+  direct_scale<K>(t, R, lo, hi, norm);   // ends with a barrier
+  const int k = blockIdx.y * 4 + wave;
+  if (k >= R) return;   // uniform over the wavefront
+  direct_pair<K, 64>(t, R, k, lo, hi, s_V, T, s_tau, s_g, s_work[wave], x, lambda, residual);
+  if (group16_index() == 0) {
+#pragma unroll
+    for (int b = 0; b < K; ++b) a.U(T)[(size_t)k * T + group16_member() + 16 * b] = x[b];
+  }
+  if (lane == 0) {
+    a.lambda(T)[k] = lambda * norm;
+    a.residual(T)[k] = residual;
+  }
+}
+
+// What only the one-kernel form keeps in LDS.
+template <int K, int NT, bool FUSED>
+struct FusedLds {
+  DirectLds<K, 256> reduce;
+  double s_tau[16 * K], s_res[16 * K], s_work[NT / 16][kDirectWork<K>], s_g[4 * K][6];
+  double V[16 * K * 16 * K];
+  DirectTridiagonal<K> t;
+};
+template <int K, int NT>
+struct FusedLds<K, NT, false> {};
+
+// The last kernel, and with FUSED the only one: checks the eigenvectors U (rows) and makes them orthogonal to working
+// precision, U <- (3/2 - U U^T / 2) U on the fp64 matrix unit, or has Jacobi find them; then the floors, rho_{t+1}, D_{t+1}, E_{t+1}
+// (eq. rhodash2, dt1, rhot1, beta2, etii) and A_t (eq. wt1).  Above rank 32 a workgroup per 16 rows of A_t: each checks all
+// vectors (so that they agree) and takes its rows' share of the second product; the first one does what is left.
+// Grid (instance, FUSED ? 1 : ceil(R / 16)).
+template <int K, int ITEMS, int NT, bool FUSED>
+__global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
+  using Shape = DirectShape<K>;
+  constexpr int T = Shape::T, SU = Shape::STRIDE, NW = NT / 64;
+  typedef double doublex4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __attribute__((aligned(16))) double dyn[];   // U, then 3/2 - U U^T / 2; or Jacobi's two copies of Z
+  __shared__ double scratch[16];
+  __shared__ double s_ise[T], s_dr[T], s_col[T], s_c[kMaxRank + 1];
+  __shared__ __attribute__((aligned(16))) double2 s_cs[2][kMaxHalf];
+  __shared__ int s_perm[kMaxRank], s_rank[kMaxRank];
+  __shared__ int s_rotated[2];
+  __shared__ FusedLds<K, NT, FUSED> s_fused;
+  static_assert(kMaxRank <= NT && T <= NT, "a thread per eigenvalue");
+  const SmallArgs& a = g.a[blockIdx.x];
+  const int R = a.R, D = a.D, N = a.N;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
+  if (16 * (int)blockIdx.y >= R) return;
+  const bool lead = blockIdx.y == 0;
+  PrecondScalars* st = a.st;
+  double* const U = dyn;
+  double* const M = dyn + T * SU;
+  double lambda = 0.0, residual = 0.0;   // of pair tid
+  double tr_part = 0.0;   // tr(X X^T), summed here: the kernel that finishes the output may still be running
+  for (int i = tid; i < a.n_sumsq; i += NT) tr_part += a.sumsq_part[i];
+  if constexpr (!FUSED) {
+    for (int e = tid; e < T * (T / 2); e += NT) {
+      const int k = e / (T / 2), c = e % (T / 2);
+      const double2 v = k < R ? reinterpret_cast<const double2*>(a.U(T))[(size_t)k * (T / 2) + c] : make_double2(0.0, 0.0);
+      U[k * SU + 2 * c] = v.x;
+      U[k * SU + 2 * c + 1] = v.y;
+    }
+    if (tid < R) {
+      lambda = a.lambda(T)[tid];
+      residual = a.residual(T)[tid];
+    }
+  }
+  ZLoad<K, 256> load;
+  if constexpr (FUSED) load.request(a);   // (the upper half of the threads as well, and drops it)
+  const UpdateFactors f = update_factors(a, g, FUSED ? st->d : a.d_rho(T), FUSED ? st->rho : a.d_rho(T)[R], s_ise, s_dr, T);
+  if constexpr (FUSED) {
+    static_assert(NT >= 256 && NT >= 16 * T, "all pairs at once");
+    if (tid < 256) {
+      typename DirectTile<K, 256>::Regs S;
+      load.form(a, f, s_ise, s_dr, S);
+      direct_reduce<K, 256>(S, R, s_fused.reduce, s_fused.V, s_fused.s_tau, s_fused.t.off);
+      direct_store_tridiagonal<K, 256>(S, R, s_fused.t.diag, s_fused.t.off);
+    } else {
+      for (int e = max(R - 2, 0) * T + tid - 256; e < T * T; e += NT - 256) s_fused.V[e] = 0.0;
+      for (int e = max(R - 2, 0) + tid - 256; e < T; e += NT - 256) s_fused.s_tau[e] = 0.0;
+      direct_reduce_idle(R);
+    }
+    __syncthreads();
+    direct_block_products<K, NT>(s_fused.V, T, R, s_fused.s_g);
+    double lo, hi, norm;
+    direct_scale<K>(s_fused.t, R, lo, hi, norm);
+    const int k = tid >> 4;
+    double x[K], l, r;
+    if ((k & ~3) < R) {   // (uniform over a wavefront)
+      direct_pair<K, 16>(s_fused.t, R, min(k, R - 1), lo, hi, s_fused.V, T, s_fused.s_tau, s_fused.s_g, s_fused.s_work[k], x, l, r);
+      if (l16 == 0 && k < R) {
+        s_c[k] = l * norm;
+        s_fused.s_res[k] = r;
+      }
+    }
+    const int kx = 4 * wave + group16_index();   // whose vector this lane has
+#pragma unroll
+    for (int b = 0; b < K; ++b) U[kx * SU + group16_member() + 16 * b] = kx < R ? x[b] : 0.0;
+    __syncthreads();
+    if (tid < R) {
+      lambda = s_c[tid];
+      residual = s_fused.s_res[tid];
+    }
+  }
+  if (tid < R) s_c[tid] = lambda;
+  tr_part = wave_sum_uniform(tr_part);
+  if (lane == 0) scratch[wave] = tr_part;
+  __syncthreads();
+  double tr_M = 0.0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) tr_M += scratch[w];
+
+  // U U^T, tiles on and above the diagonal.  v_mfma_f64_16x16x4_f64: lane l supplies A[l%16][l/16] and B[l/16][l%16]; register r
+  // holds row 4r + l/16, column l%16 (v_mfma_f32_16x16x4_f32 row 4 (l/16) + r).  M has the rows that this workgroup needs (all with
+  // FUSED): those are formed in fp64, five tiles of 20 matrix instructions by as many wavefronts; the others are only
+  // checked, against a limit that fp32 products (a quarter of the time) resolve.
+  const int first_row = FUSED ? 0 : 16 * (int)blockIdx.y;
+  bool bad = false;
+  for (int tile = wave; tile < K * (K + 1) / 2; tile += NW) {
+    int ti = 0, tj = tile;
+    while (tj >= K - ti) {
+      tj -= K - ti;
+      ++ti;
+    }
+    tj += ti;
+    if (16 * tj >= R) continue;   // uniform
+    const double* const ui = U + (16 * ti + l16) * SU + g4;
+    const double* const uj = U + (16 * tj + l16) * SU + g4;
+    if (FUSED || 16 * ti == first_row || 16 * tj == first_row) {
+      doublex4 part[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+      for (int s0 = 0; s0 < R; s0 += 16) {
+#pragma unroll
+        for (int s = 0; s < 16; s += 4) part[(s >> 2) & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ui[s0 + s], uj[s0 + s], part[(s >> 2) & 1], 0, 0, 0);
+      }
+      const doublex4 acc = part[0] + part[1];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + 4 * r + g4, j = 16 * tj + l16;
+        const double one = i == j ? 1.0 : 0.0;
+        if (i < R && j < R) bad |= !(fabs(acc[r] - one) <= kDirectOrthoLimit);   // (NaN fails)
+        const double v = fma(-0.5, acc[r], 1.5 * one);
+        if (FUSED || 16 * ti == first_row) M[(i - first_row) * SU + j] = v;
+        if (FUSED || 16 * tj == first_row) M[(j - first_row) * SU + i] = v;
+      }
+    } else {
+      floatx4 part[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+      for (int s0 = 0; s0 < R; s0 += 16) {
+#pragma unroll
+        for (int s = 0; s < 16; s += 4)
+          part[(s >> 2) & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)ui[s0 + s], (float)uj[s0 + s], part[(s >> 2) & 1], 0, 0, 0);
+      }
+      const floatx4 acc = part[0] + part[1];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * ti + 4 * g4 + r, j = 16 * tj + l16;
+        if (i < R && j < R) bad |= !(fabsf(acc[r] - (i == j ? 1.f : 0.f)) <= (float)kDirectOrthoLimit);
+      }
+    }
+  }
+  if (tid < R) bad |= !(residual <= kDirectResidual) || !(lambda <= s_c[0] && s_c[R - 1] > 0.0 && s_c[0] <= kDirectCondLimit * s_c[R - 1]);
+  const bool direct = __syncthreads_or(bad ? 1 : 0) == 0;   // (M is complete behind it)
+  if (!direct && !lead) return;
+
+  int sweeps = 1, rounds = 0;
+  bool converged = true;
+  if (!direct) {
+    jacobi_eigenvalues<ITEMS, NT>(a, f, s_ise, s_dr, dyn, scratch, s_cs, s_rotated, s_c, sweeps, rounds, converged);
+    __syncthreads();
+  }
+
+  // Every wavefront handles all eigenvalues, two per lane.  Floor (after eq. zt:eig:repeat), decreasing order:
+  const double floor_c = (1.0 - f.eta) * (1.0 - f.eta) * f.rho * f.rho;
+  bool floored = false;
+  double c[2];
+  int rank[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = lane + 64 * u;
+    rank[u] = i;
+    c[u] = i < R ? s_c[i] : 1.0;
+    if (i < R && !(c[u] >= floor_c)) {
+      c[u] = floor_c;
+      floored = true;
+    }
+  }
+  if (!direct) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = lane + 64 * u;
+      if (wave == 0 && i < R) s_c[i] = c[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = lane + 64 * u;
+      if (i >= R) continue;
+      rank[u] = 0;
+      for (int j = 0; j < R; ++j) rank[u] += (s_c[j] > c[u] || (s_c[j] == c[u] && j < i)) ? 1 : 0;
+      if (wave == 0) {
+        s_perm[rank[u]] = i;   // s_perm[k] = index of the k-th largest eigenvalue
+        s_rank[i] = rank[u];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (lane + 64 * u < R) c[u] = s_c[s_perm[lane + 64 * u]];   // eigenpair at position lane + 64 u
+  }
+  // eq. rhodash2, dt1, rhot1
+  double root[2], dn[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) root[u] = lane + 64 * u < R ? sqrt(c[u]) : 0.0;
+  const double sum_sqrt = wave_sum_uniform(root[0] + root[1]);
+  const double rho_dash = ((f.eta / N) * tr_M + (1.0 - f.eta) * ((double)D * f.rho + f.sum_d) - sum_sqrt) / (double)(D - R);
+  const double rho_new = fmax(g.epsilon, rho_dash);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) dn[u] = lane + 64 * u < R ? fmax(root[u] - rho_dash, g.epsilon) : 0.0;
+  const double beta_new = rho_new * (1.0 + g.alpha) + g.alpha / (double)D * wave_sum_uniform(dn[0] + dn[1]);
+  const bool any_floored = __any(floored);
+  if (wave == 0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int k = lane + 64 * u;
+      if (k >= R) continue;
+      const double en = 1.0 / (beta_new / dn[u] + 1.0);
+      s_col[k] = (f.eta / N) * sqrt(en / c[u]);   // A_t = (eta/N) E_{t+1}^{1/2} C_t^{-1/2} U_t^T E_t^{-1/2}  (eq. wt1)
+      if (lead) {
+        st->d[k] = dn[u];
+        st->e[k] = en;
+      }
+      if (k == R - 1) s_c[kMaxRank] = c[u];
+      if (k == 0) s_cs[0][0].x = c[u];
+    }
+  }
+  __syncthreads();
+  if (lead && tid == 0) {
+    int flags = 0;
+    if (any_floored) flags |= kFlagFloored | kFlagOrthCheck;
+    if (s_cs[0][0].x > kOrthoCondLimit * s_c[kMaxRank]) flags |= kFlagOrthCheck;
+    if (!converged) flags |= kFlagNoConverge;
+    st->flags = flags;
+    st->sweeps = sweeps;
+    st->rho = rho_new;
+    st->beta = beta_new;
+  }
+  if (direct) {
+    constexpr int TILES = FUSED ? K * K : K;
+    for (int tile = wave; tile < TILES; tile += NW) {
+      const int ti = FUSED ? tile / K : 0, tj = tile % K;
+      if (16 * ti >= R || 16 * tj >= R) continue;   // uniform
+      doublex4 acc = {0, 0, 0, 0};
+      for (int s0 = 0; s0 < R; s0 += 16) {   // (M has no columns beyond the last tile)
+#pragma unroll
+        for (int s = s0; s < s0 + 16; s += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(M[(16 * ti + l16) * SU + s + g4], U[(s + g4) * SU + 16 * tj + l16], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = first_row + 16 * ti + 4 * r + g4, j = 16 * tj + l16;
+        if (i < R && j < R) a.At[(size_t)i * a.ldat + j] = (float)(s_col[i] * acc[r] * s_ise[j]);
+      }
+    }
+  } else {
+    __threadfence_block();   // the log
+    replay_rotations<(T + NW - 1) / NW, NT>(a, rounds, s_rank, s_col, s_ise);
+  }
+  if (lead)
+    for (int idx = tid; idx < R * R; idx += NT) a.K[idx] = 0.0;
 }
 
 // App. B.3.1 on the new factor: O = E^{-1/2} (W W^T) E^{-1/2}; if any entry is off the identity by more than

@@ -1,0 +1,70 @@
+"""GPU parity of the R x R update at the edges of its kernels' tiles, and where the direct eigen-solver hands over to Jacobi."""
+import numpy as np
+import pytest
+
+from oracle.online_ng import OnlineNaturalGradient, smoothing_and_scales
+from test_gpu_precondition import TOL, compare_states, data, gpu_call, rel, upload_state
+
+pytestmark = pytest.mark.gpu
+
+
+def orthogonality(pre, alpha, D):
+    """Largest |W W^T - E| over sqrt(E_ii E_jj) (App. B.3.1)."""
+    W, d, rho, _ = pre.get_state()
+    W, d = W.cpu().numpy().astype(np.float64), d.cpu().numpy()
+    _, e = smoothing_and_scales(d, rho, alpha, D)
+    return float(np.abs(W @ W.T / np.sqrt(np.outer(e, e)) - np.eye(len(e))).max())
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 15, 16, 17, 18, 19, 31, 32, 33, 34, 35, 47, 48, 49, 63, 64, 65, 79, 80, 81, 95, 96])
+def test_update_at_the_edges_of_its_tiles(ngsgd, R):
+    """16 columns a stage, one kernel up to rank 32, tiles for ranks up to 48, 80 and 96, four reflections at a time."""
+    import torch
+    N, D = 140, 260
+    rng = np.random.default_rng(9100 + R)
+    kw = dict(num_samples_history=500.0, update_period=1)
+    ora = OnlineNaturalGradient(D, R, **kw)
+    ora.precondition(data(rng, N, D))
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, **kw)
+    upload_state(torch, pre, ora)
+    for _ in range(3):
+        M = data(rng, N, D)
+        expect, g_o, rn_o = ora.precondition(M)
+        got, g_g, rn_g = gpu_call(torch, pre, M)
+        assert rel(got, expect) < TOL
+        assert rel(rn_g, rn_o) < 2e-4
+    compare_states(torch, pre, ora, rng)
+    # fp32 rows of J and W: 2^-24 times the square root of the eigenvalues' span, here below 1e4
+    assert orthogonality(pre, ora.alpha, D) < 2e-5
+
+
+@pytest.mark.parametrize("kind", ["equal", "one cluster", "graded"])
+@pytest.mark.parametrize("R", [6, 20, 32, 33, 48, 80, 96])
+def test_eigenvalues_that_the_direct_solver_leaves_to_jacobi(ngsgd, R, kind):
+    """Rows that do not meet the factor leave Z_t diagonal: with equal eigenvalues (the vectors of a tridiagonal matrix that is
+    diagonal are not told apart), or with a span beyond the direct solver's limit."""
+    import torch
+    N, D = 130, 300
+    rng = np.random.default_rng(9200 + R)
+    kw = dict(num_samples_history=700.0, update_period=1)
+    ora = OnlineNaturalGradient(D, R, **kw)
+    ora.precondition(data(rng, N, D))
+    ora.R = np.eye(R, D)
+    ora.d = {"equal": np.full(R, 0.5), "one cluster": np.where(np.arange(R) < R // 2, 0.5, 0.25 / (1.0 + np.arange(R))),
+             "graded": 10.0 ** (-14.0 * np.arange(R) / (R - 1))}[kind]
+    ora.rho = 1e-9
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, **kw)
+    upload_state(torch, pre, ora)
+    M = data(rng, N, D)
+    M[:, :R] = 0.0
+    expect, g_o, _ = ora.precondition(M)
+    got, g_g, _ = gpu_call(torch, pre, M)
+    assert rel(got, expect) < TOL
+    flags, sweeps = pre.diagnostics()
+    assert flags & 8 == 0 and 1 <= sweeps <= 20
+    compare_states(torch, pre, ora, rng)
+    assert orthogonality(pre, ora.alpha, D) < 2e-6   # the rows stay what they were, rounded to fp32
+    M = data(rng, N, D)
+    expect, g_o, _ = ora.precondition(M)
+    got, g_g, _ = gpu_call(torch, pre, M)
+    assert rel(got, expect) < TOL
