@@ -53,6 +53,7 @@ struct FusedArgs {
   int* deferred;           // [n_rb * n_chunks] patches left for the finishing kernel: rb * n_chunks + chunk
   float* rownorm_part;     // [n_chunks][N] squared row norms of Xhat per column chunk
   double* sumsq_part;      // [n_chunks * n_rb] sums of squares of X per patch
+  double* hat_part;        // [n_chunks * n_rb] and of Xhat
   int ldx, ldo, ldw, ldh;
   int N, D, R;
   int n_rb, n_chunks, n_chunks_pad;   // the chunk count is padded to a multiple of the die count
@@ -298,6 +299,12 @@ __global__ __launch_bounds__(kFusedThreads, (RC <= 80 ? 3 : 2)) void fused_apply
       }
     }
     __builtin_amdgcn_sched_barrier(0);   // one pair at a time
+  }
+  {   // (red was last read before two barriers)
+    const double s = wave_sum_uniform((double)sq);
+    if (lane == 0) red[wave] = s;
+    __syncthreads();
+    if (tid == 0) P.hat_part[chunk * P.n_rb + rb] = (red[0] + red[1]) + (red[2] + red[3]);
   }
   sq += __shfl_xor(sq, 16);
   sq += __shfl_xor(sq, 32);

@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "wave_f64.h"
+
 namespace ngsgd {
 
 constexpr int kMaxGroup = 16;
@@ -26,7 +28,7 @@ enum Epilogue : int {
   EPI_STORE = 0,        // C = alpha*acc
   EPI_ATOMIC_F32 = 1,   // C += alpha*acc            (split-K, float atomics)
   EPI_ATOMIC_F64 = 2,   // (double)C += alpha*acc    (split-K, double atomics)
-  EPI_SUB_ROWNORM = 3,  // C = C - acc; aux[tile_n][row] = sum over the tile's columns of C^2
+  EPI_SUB_ROWNORM = 3,  // C = C - acc; aux[tile_n][row] = sum over the tile's columns of C^2, sumsq[tile_n][tile_m] that over the tile
 };
 
 struct GemmProblem {
@@ -43,7 +45,7 @@ struct GemmProblem {
   int sym;                     // C is symmetric (A = B): only the tiles on and above the diagonal are computed
   int tile_begin;              // first workgroup index of this problem
   float* aux;                  // EPI_SUB_ROWNORM: [tiles_n][M] row-norm partials
-  double* sumsq;               // SUMSQ_A: [splits*tiles_m] partial sums of squares of A
+  double* sumsq;               // SUMSQ_A: [splits*tiles_m] partial sums of squares of A; EPI_SUB_ROWNORM: [tiles_n][tiles_m] of C
   long long c_split_stride;    // split_gemm_kernel with splits > 1: split s writes its partial product to C + s*stride
   const int* gate;             // optional: the problem is skipped unless (*gate & gate_mask) != 0
   int gate_mask;
@@ -548,6 +550,7 @@ __device__ __forceinline__ void gemm_unit(const Group& g, const int pi, const in
       }
     }
     __syncthreads();
+    double tile_sum = 0.0;
     for (int lrow = tid; lrow < BM; lrow += NT) {
       const int row = m0 + lrow;
       if (row < M) {
@@ -555,7 +558,17 @@ __device__ __forceinline__ void gemm_unit(const Group& g, const int pi, const in
 #pragma unroll
         for (int w = 0; w < WGN; ++w) s += rowsum[w * BM + lrow];
         P.aux[(size_t)tn * M + row] = s;
+        tile_sum += (double)s;
       }
+    }
+    tile_sum = wave_sum_uniform(tile_sum);
+    if (lane == 0) red[wave] = tile_sum;
+    __syncthreads();
+    if (tid == 0) {
+      tile_sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < NT / 64; ++w) tile_sum += red[w];
+      P.sumsq[(size_t)tn * P.tiles_m + tm] = tile_sum;
     }
     return;
   }

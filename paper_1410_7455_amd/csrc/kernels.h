@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "state.h"
+#include "wave_f64.h"
 
 namespace ngsgd {
 
@@ -397,49 +398,64 @@ __global__ __launch_bounds__(NT) void softmax_xent_kernel(float* __restrict__ AO
 }
 
 // ---- preconditioner helpers -----------------------------------------------------------------------
-// After Xhat = X - H W: reduce the partial sums, gamma_t = sqrt(tr(X X^T) / tr(Xhat Xhat^T)) (eq. gammat;
-// 1 if the denominator is 0), per-row squared norms of the output.  One workgroup per instance.
+// After Xhat = X - H W: gamma_t = sqrt(tr(X X^T) / tr(Xhat Xhat^T)) (eq. gammat; 1 if the denominator is 0), the
+// squared norms of the output's rows and, with SCALE, gamma Xhat in place of Xhat.
 struct FinishArgs {
   PrecondScalars* st;
   const double* sumsq_part;  // partial sums of squares of X
-  int n_sumsq;
+  const double* hat_part;    // and of Xhat, one per tile of the kernel that formed it
+  int n_sumsq, n_hat;
   const float* rownorm_part; // [n_col_tiles][N] partial row norms of Xhat
   int n_col_tiles;
   int N;
   double* prow;              // out: p_i (eq. pi), N doubles
   float* gamma_out;          // optional
   float* rownorm2_out;       // optional, gamma^2 p_i
+  float* X;                  // N x D, Xhat in place
+  int ldx, D;
   // patches the fused apply kernel left undone (its bounded wait ran out): Xhat = X - H W is completed here
-  const int* deferred_count; // nullptr: none
   const int* deferred;       // rb * n_col_tiles + chunk for each such patch of 64 rows x chunk_cols columns
-  float* X;                  // N x D, in place
   const float* W;            // R x D
-  const float* H;            // N x ldh, final
-  int ldx, ldw, ldh, D, R, chunk_cols;
-  // what the fused apply kernel accumulated into (arrival counters and H, contiguous): cleared on exit, so that the
-  // next call without a factor update needs no clearing launch in front of it (nullptr: left as it is)
-  float* clear_ptr;
-  int clear_floats;          // a multiple of 4
+  float* H;                  // N x ldh, final
+  int ldw, ldh, R, chunk_cols;
+  // what the fused apply kernel accumulated into, H and the arrival counters: cleared here, so that the
+  // next call without a factor update needs no clearing launch in front of it
+  int* arrive;               // [n_arrive], then the ticket below and the number of deferred patches
+  int n_arrive;              // 0: not behind the fused apply kernel
+  __device__ int* ticket() const { return arrive + n_arrive; }   // zero on entry and exit: the last workgroup to have read the count clears it
+  __device__ int* deferred_count() const { return arrive + n_arrive + 1; }
 };
 struct FinishGroup {
   int count;
   FinishArgs a[kMaxInstances];
 };
 
-__global__ __launch_bounds__(1024) void finish_apply_kernel(const FinishGroup g) {
-  __shared__ double scratch[32];
-  const FinishArgs& a = g.a[blockIdx.x];
-  const int n_deferred = a.deferred_count != nullptr ? *a.deferred_count : 0;
-  if (n_deferred > 0) {
-    // 16 threads per row of a 64-row patch; plain dot products over the rank (this path is rare and small)
-    const int sub = threadIdx.x & 15;
-    for (int e = 0; e < n_deferred; ++e) {
-      const int id = a.deferred[e];
-      const int rb = id / a.n_col_tiles, chunk = id % a.n_col_tiles;
-      const int r = rb * 64 + (threadIdx.x >> 4);
-      const int c_end = min(a.D, (chunk + 1) * a.chunk_cols);
+// The sums of both arguments over the 256 threads, to all of them; `red` holds 8 doubles.
+__device__ __forceinline__ void block256_sum_pair(double& x, double& y, double* red) {
+  x = wave_sum_uniform(x);
+  y = wave_sum_uniform(y);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6] = x;
+    red[4 + (threadIdx.x >> 6)] = y;
+  }
+  __syncthreads();
+  x = (red[0] + red[1]) + (red[2] + red[3]);
+  y = (red[4] + red[5]) + (red[6] + red[7]);
+}
+
+// The deferred patches, then everything for the whole instance, by one workgroup: plain dot products over the rank, 16 threads
+// per row (this path is rare and small).
+template <bool SCALE>
+__device__ __forceinline__ void finish_deferred(const FinishArgs& a, const int n_deferred, double* red) {
+  const int tid = threadIdx.x, sub = tid & 15;
+  for (int e = 0; e < n_deferred; ++e) {
+    const int id = a.deferred[e];
+    const int rb = id / a.n_col_tiles, chunk = id % a.n_col_tiles;
+    const int c_end = min(a.D, (chunk + 1) * a.chunk_cols);
+    for (int r = rb * 64 + (tid >> 4); r < rb * 64 + 64; r += 16) {
       float sq = 0.f;
-      if (r < a.N && threadIdx.x < 1024) {
+      if (r < a.N) {
         const float* h = a.H + (size_t)r * a.ldh;
         float* x = a.X + (size_t)r * a.ldx;
         for (int c = chunk * a.chunk_cols + sub; c < c_end; c += 16) {
@@ -456,97 +472,120 @@ __global__ __launch_bounds__(1024) void finish_apply_kernel(const FinishGroup g)
       sq += __shfl_xor(sq, 8);
       if (r < a.N && sub == 0) const_cast<float*>(a.rownorm_part)[(size_t)chunk * a.N + r] = sq;
     }
-    __threadfence();
-    __syncthreads();   // the partial row norms written above are read below by other lanes
   }
-  // Everything below hangs on a few rounds of loads from memory that no cache of this workgroup's die holds yet:
-  // they are issued together, and what a row's four lanes find stays in registers until gamma is known.
-  double t = 0.0;
-  for (int i = threadIdx.x; i < a.n_sumsq; i += blockDim.x) t += a.sumsq_part[i];
-  // four lanes share a row: each adds every fourth column tile (independent loads), then the quad is combined
-  const int part = threadIdx.x & 3;
-  const int N = a.N, nct = a.n_col_tiles;
-  const int rows_per_pass = blockDim.x >> 2;
-  auto row_sum = [&](int r) -> double {
-    float p0 = 0.f, p1 = 0.f;
-    if (r < N) {
-      for (int c = part; c < nct; c += 32) {   // eight loads at a time: the latency of each batch is what this costs
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = a.rownorm_part[(size_t)min(c + 4 * u, nct - 1) * N + r];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const float x = c + 4 * u < nct ? v[u] : 0.f;
-          if (u & 1) p1 += x; else p0 += x;
-        }
-      }
-    }
-    double p = (double)p0 + (double)p1;
-    p += __shfl_xor(p, 1);
-    p += __shfl_xor(p, 2);
-    return p;
-  };
-  constexpr int kKeep = 4;   // passes whose row sums stay in registers (N <= 1024 with 1024 threads)
-  double pv[kKeep];
-  double ph = 0.0;
-#pragma unroll
-  for (int ps = 0; ps < kKeep; ++ps) {
-    const int r = ps * rows_per_pass + (threadIdx.x >> 2);
-    pv[ps] = row_sum(r);
-    if (r < N && part == 0) {
-      a.prow[r] = pv[ps];
-      ph += pv[ps];
-    }
+  __threadfence();
+  __syncthreads();   // what was written above is read below by other lanes
+  double t = 0.0, ph = 0.0;
+  for (int i = tid; i < a.n_sumsq; i += 256) t += a.sumsq_part[i];
+  for (int r = tid; r < a.N; r += 256) {
+    double p = 0.0;
+    for (int c = 0; c < a.n_col_tiles; ++c) p += (double)a.rownorm_part[(size_t)c * a.N + r];
+    a.prow[r] = p;
+    ph += p;
   }
-  for (int r0 = kKeep * rows_per_pass; r0 < N; r0 += rows_per_pass) {   // (larger minibatches: through memory)
-    const int r = r0 + (threadIdx.x >> 2);
-    const double p = row_sum(r);
-    if (r < N && part == 0) {
-      a.prow[r] = p;
-      ph += p;
-    }
-  }
-  // tr(X X^T) and tr(Xhat Xhat^T) in one reduction
-  {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-    t = wave_sum(t);
-    ph = wave_sum(ph);
-    __syncthreads();
-    if (lane == 0) {
-      scratch[wave] = t;
-      scratch[16 + wave] = ph;
-    }
-    __syncthreads();
-    t = 0.0;
-    ph = 0.0;
-    for (int w = 0; w < nw; ++w) {
-      t += scratch[w];
-      ph += scratch[16 + w];
-    }
-  }
-  const double tr_M = t, tr_Mhat = ph;
-  const double gamma = tr_Mhat > 0.0 ? sqrt(tr_M / tr_Mhat) : 1.0;
-  if (threadIdx.x == 0) {
+  block256_sum_pair(t, ph, red);
+  const double gamma = ph > 0.0 ? sqrt(t / ph) : 1.0;
+  for (int r = tid; r < a.N && a.rownorm2_out != nullptr; r += 256) a.rownorm2_out[r] = (float)(gamma * gamma * a.prow[r]);   // (its own rows)
+  if (tid == 0) {
     a.st->gamma = gamma;
-    a.st->tr_M = tr_M;
-    a.st->tr_Mhat = tr_Mhat;
+    a.st->tr_M = t;
+    a.st->tr_Mhat = ph;
     if (a.gamma_out != nullptr) *a.gamma_out = (float)gamma;
   }
-  if (a.rownorm2_out != nullptr) {
+  if (SCALE) {
+    for (int r = 0; r < a.N; ++r)
+      for (int c = tid; c < a.D; c += 256) a.X[(size_t)r * a.ldx + c] *= (float)gamma;
+  }
+  for (int i = tid; i < a.N * a.ldh; i += 256) a.H[i] = 0.f;
+  for (int i = tid; i < a.n_arrive; i += 256) a.arrive[i] = 0;
+}
+
+// Grid (ceil(N / ROWS), instance), 256 threads: every workgroup sums the tiles' partial sums for itself (a few hundred numbers) and
+// takes ROWS rows.  Bound: the latency of loads from memory that no cache of
+// the workgroup's die holds yet.  With one workgroup per instance, which summed the row norms for the traces and cleared H, and a
+// launch of its own for the scaling: 512 x 5000 10.1 + 7.9 us, 512 x 3001 7.8 + 4.9.
+constexpr int kFinishRows = 64, kFinishScaleRows = 2;
+template <bool SCALE>
+__global__ __launch_bounds__(256) void finish_apply_kernel(const FinishGroup g) {
+  constexpr int ROWS = SCALE ? kFinishScaleRows : kFinishRows;
+  __shared__ double red[8], s_row[4][ROWS];
+  const FinishArgs& a = g.a[blockIdx.y];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N, D = a.D;
+  const int row0 = blockIdx.x * ROWS, groups = (N + ROWS - 1) / ROWS;
+  if (row0 >= N) return;
+  const int n_deferred = a.n_arrive > 0 ? *a.deferred_count() : 0;
+  // Everything is requested before the first wait: the row pieces that this wavefront scales (256 / ROWS threads take a row) ...
+  constexpr int AHEAD = 10, WIDTH = 256 / ROWS;
+  float4 x[AHEAD];
+  float4* const xrow = reinterpret_cast<float4*>(a.X + (size_t)min(row0 + tid / WIDTH, N - 1) * a.ldx);
+  const int d4 = D >> 2, c0 = tid % WIDTH;   // whole pieces
+  if (SCALE) {
 #pragma unroll
-    for (int ps = 0; ps < kKeep; ++ps) {
-      const int r = ps * rows_per_pass + (threadIdx.x >> 2);
-      if (r < N && part == 0) a.rownorm2_out[r] = (float)(gamma * gamma * pv[ps]);
-    }
-    if (N > kKeep * rows_per_pass) {
-      __syncthreads();   // prow was written by other lanes
-      for (int r = kKeep * rows_per_pass + threadIdx.x; r < N; r += blockDim.x)
-        a.rownorm2_out[r] = (float)(gamma * gamma * a.prow[r]);
+    for (int u = 0; u < AHEAD; ++u) x[u] = xrow[min(c0 + WIDTH * u, max(d4 - 1, 0))];   // (a row has at least a piece, see ld)
+  }
+  // ... the partial sums ...
+  double t = 0.0, ph = 0.0;
+  for (int i = tid; i < a.n_sumsq; i += 256) t += a.sumsq_part[i];
+  for (int i = tid; i < a.n_hat; i += 256) ph += a.hat_part[i];
+  // ... and the rows' partial norms: 256 / ROWS threads share a row and add every so many'th column tile
+  const int r = row0 + tid % ROWS;
+  constexpr int STEP = 256 / ROWS;
+  float part[2] = {0.f, 0.f};
+  if (r < N) {
+    for (int c = tid / ROWS; c < a.n_col_tiles; c += 8 * STEP) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = a.rownorm_part[(size_t)min(c + STEP * u, a.n_col_tiles - 1) * N + r];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) part[u & 1] += c + STEP * u < a.n_col_tiles ? v[u] : 0.f;
     }
   }
-  if (a.clear_ptr != nullptr) {   // (every read of H and of the deferred count lies before a barrier above)
-    float4* z = reinterpret_cast<float4*>(a.clear_ptr);
-    for (int i = threadIdx.x; i < a.clear_floats / 4; i += blockDim.x) z[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (n_deferred > 0) {   // (the same for all workgroups of the instance)
+    __shared__ int s_last;
+    if (tid == 0) s_last = __hip_atomic_fetch_add(a.ticket(), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == groups - 1 ? 1 : 0;
+    __syncthreads();
+    if (s_last != 0 && tid == 0) {   // everyone has read the count
+      *a.deferred_count() = 0;
+      *a.ticket() = 0;
+    }
+    if (blockIdx.x == 0) finish_deferred<SCALE>(a, n_deferred, red);
+    return;
+  }
+  double p = (double)part[0] + (double)part[1];
+#pragma unroll
+  for (int off = ROWS; off < 64; off <<= 1) p += __shfl_xor(p, off);
+  if (lane < ROWS) s_row[wave][lane] = p;
+  block256_sum_pair(t, ph, red);
+  const double gamma = ph > 0.0 ? sqrt(t / ph) : 1.0;
+  if (tid < ROWS && r < N) {
+    p = (s_row[0][tid] + s_row[1][tid]) + (s_row[2][tid] + s_row[3][tid]);
+    a.prow[r] = p;
+    if (a.rownorm2_out != nullptr) a.rownorm2_out[r] = (float)(gamma * gamma * p);
+  }
+  if (blockIdx.x == 0 && tid == 0) {
+    a.st->gamma = gamma;
+    a.st->tr_M = t;
+    a.st->tr_Mhat = ph;
+    if (a.gamma_out != nullptr) *a.gamma_out = (float)gamma;
+  }
+  if (SCALE && row0 + tid / WIDTH < N) {
+    const float s = (float)gamma;
+    auto scaled = [&](float4 v) {
+      v.x *= s; v.y *= s; v.z *= s; v.w *= s;
+      return v;
+    };
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+      if (c0 + WIDTH * u < d4) xrow[c0 + WIDTH * u] = scaled(x[u]);
+    for (int c = c0 + WIDTH * AHEAD; c < d4; c += WIDTH) xrow[c] = scaled(xrow[c]);
+    if (c0 < D - 4 * d4) reinterpret_cast<float*>(xrow)[4 * d4 + c0] *= s;
+  }
+  if (a.n_arrive > 0) {   // (no workgroup reads H or the counters: nothing was deferred)
+    const int rows = min(ROWS, N - row0);
+    float4* const h = reinterpret_cast<float4*>(a.H + (size_t)row0 * a.ldh);
+    for (int i = tid; i < rows * a.ldh / 4; i += 256) h[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (blockIdx.x == 0)
+      for (int i = tid; i < a.n_arrive; i += 256) a.arrive[i] = 0;
   }
 }
 

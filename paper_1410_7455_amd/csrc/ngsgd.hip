@@ -158,8 +158,8 @@ struct ngsgd_precond {
   int clean_rows = 0;             // the counters and this many rows of H are known to be clear (left so by the
                                   // finishing kernel of a call that went through the fused apply kernel)
   size_t zero_floats_all = 0;
-  size_t arrive_slots = 0;        // arrival counters of the fused apply kernel, one per block of 64 rows, and
-  int* arrive = nullptr;          // (last slot) the number of patches it deferred; padded to 256 bytes
+  size_t arrive_slots = 0;        // arrival counters of the fused apply kernel, one per block of 64 rows, and (last
+  int* arrive = nullptr;          // two slots) the finishing kernel's ticket, the number of deferred patches; padded to 256 bytes
   int* deferred = nullptr;        // list of deferred patches
   float* H = nullptr;
   float* J = nullptr;
@@ -168,6 +168,7 @@ struct ngsgd_precond {
   float* W = nullptr;
   float* At = nullptr;
   float* rownorm_part = nullptr;
+  double* hat_part = nullptr;     // sums of squares of Xhat per tile
   int max_col_tiles = 0;
   double* sumsq_part = nullptr;
   double* prow = nullptr;
@@ -198,7 +199,7 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.prow = c.take<double>(NB);
   if (R == 0) return;
   const size_t h_floats = (size_t)NB * p.ldh, kl_floats = (size_t)4 * R * R;   // ldh is a multiple of 16
-  p.arrive_slots = align_up((size_t)(NB + kFusedRows - 1) / kFusedRows + 1, 64);
+  p.arrive_slots = align_up((size_t)(NB + kFusedRows - 1) / kFusedRows + 2, 64);
   p.zero_floats_all = p.arrive_slots + h_floats + kl_floats;
   p.zero_region = c.take<float>(p.zero_floats_all);
   if (p.zero_region) {
@@ -212,6 +213,7 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.At = c.take<float>((size_t)R * p.ldh);
   p.max_col_tiles = (D + 63) / 64;
   p.rownorm_part = c.take<float>((size_t)p.max_col_tiles * NB);
+  p.hat_part = c.take<double>((size_t)p.max_col_tiles * ((NB + 63) / 64));   // (the fused kernel's patches are larger than 64 x 64)
   p.sumsq_part = c.take<double>(kSumsqMax);
   p.deferred = c.take<int>(kSumsqMax);
   p.n_init_max = NB < D ? NB : D;
@@ -693,7 +695,7 @@ inline int fused_row_blocks(int N) { return (N + kFusedRows - 1) / kFusedRows; }
 
 // Whether the fused kernel's bookkeeping has room for this call (partial sums of tr(X X^T) per patch).
 inline bool fused_fits(const ngsgd_precond& p, int N) {
-  return fused_chunks(p.dim) * fused_row_blocks(N) <= kSumsqMax && (size_t)fused_row_blocks(N) < p.arrive_slots;
+  return fused_chunks(p.dim) * fused_row_blocks(N) <= kSumsqMax && (size_t)fused_row_blocks(N) + 1 < p.arrive_slots;
 }
 
 // Xhat = X - (X W^T) W, row-norm partials and the partial sums of tr(X X^T) in one pass over each matrix
@@ -718,6 +720,7 @@ int launch_fused_apply(std::vector<PrecondCall>& list, hipStream_t s) {
       a.deferred = p.deferred;
       a.rownorm_part = p.rownorm_part;
       a.sumsq_part = p.sumsq_part;
+      a.hat_part = p.hat_part;
       a.N = c.N; a.D = p.dim; a.R = p.rank;
       a.n_rb = fused_row_blocks(c.N);
       a.n_chunks = fused_chunks(p.dim);
@@ -796,54 +799,53 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
       g.C = c.M; g.ldc = c.ld;
       g.M = c.N; g.N = p.dim; g.K = p.rank;
       g.aux = p.rownorm_part;
+      g.sumsq = p.hat_part;
       d.push_back(g);
     }
     ProfScope prof(NGSGD_PROF_PRECOND_XHAT, s);
     HIP_TRY((launch_gemm_group<64, 64, BK, 2, 2, true, false, EPI_SUB_ROWNORM, false>(d.data(), (int)d.size(), s)));
   }
-  // gamma_t, tr(X X^T), tr(Xhat Xhat^T)
+  // gamma_t, tr(X X^T), tr(Xhat Xhat^T), row norms; gamma Xhat
   for (size_t done = 0; do_finish && done < full.size();) {
     ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
     FinishGroup g;
     const int n = (int)std::min<size_t>(kMaxInstances, full.size() - done);
     g.count = n;
+    int n_max = 0;
     for (int i = 0; i < n; ++i) {
       const PrecondCall& c = full[done + i];
       ngsgd_precond& p = *c.p;
       FinishArgs& a = g.a[i];
       a.st = p.st;
       a.sumsq_part = p.sumsq_part;
+      a.hat_part = p.hat_part;
       a.n_sumsq = p.n_sumsq;
+      a.n_hat = fused ? fused_chunks(p.dim) * fused_row_blocks(c.N) : ((p.dim + 63) / 64) * ((c.N + 63) / 64);
       a.rownorm_part = p.rownorm_part;
       a.n_col_tiles = fused ? fused_chunks(p.dim) : (p.dim + 63) / 64;
       a.N = c.N;
       a.prow = p.prow;
       a.gamma_out = c.gamma_out;
       a.rownorm2_out = c.rownorm2_out;
-      a.deferred_count = fused ? p.arrive + (p.arrive_slots - 1) : nullptr;
+      a.X = c.M; a.ldx = c.ld; a.D = p.dim;
       a.deferred = p.deferred;
-      a.X = c.M; a.ldx = c.ld;
       a.W = p.W; a.ldw = p.ldw;
       a.H = p.H; a.ldh = p.ldh;
-      a.D = p.dim; a.R = p.rank;
+      a.R = p.rank;
       a.chunk_cols = kFusedChunk;
-      a.clear_ptr = fused ? p.zero_region : nullptr;
-      a.clear_floats = p.arrive_slots + c.N * p.ldh;
+      a.arrive = p.arrive;
+      a.n_arrive = fused ? (int)p.arrive_slots - 2 : 0;
+      n_max = std::max(n_max, c.N);
     }
-    hipLaunchKernelGGL(finish_apply_kernel, dim3(n), dim3(1024), 0, s, g);
+    if (scale_output) {
+      hipLaunchKernelGGL(finish_apply_kernel<true>, dim3((n_max + kFinishScaleRows - 1) / kFinishScaleRows, n), dim3(256), 0, s, g);
+    } else {
+      hipLaunchKernelGGL(finish_apply_kernel<false>, dim3((n_max + kFinishRows - 1) / kFinishRows, n), dim3(256), 0, s, g);
+    }
     LAUNCH_CHECK();
     if (fused && !captured)
       for (int i = 0; i < n; ++i) full[done + i].p->clean_rows = full[done + i].N;
     done += n;
-  }
-  if (scale_output && do_finish) {
-    ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
-    for (auto& c : full) {
-      ngsgd_precond& p = *c.p;
-      hipLaunchKernelGGL(scale_rows_kernel, dim3((p.dim + 1023) / 1024, c.N), dim3(256), 0, s, c.M, c.ld, c.N, p.dim,
-                         &p.st->gamma);
-      LAUNCH_CHECK();
-    }
   }
   if (do_products) to_update_out.insert(to_update_out.end(), to_update.begin(), to_update.end());
   return NGSGD_OK;
