@@ -51,12 +51,12 @@ struct GemmProblem {
   int gate_mask;
 };
 
-template <int CAPACITY>
+template <int CAPACITY, typename PROBLEM = GemmProblem>
 struct GemmGroupOf {
   static constexpr int kCapacity = CAPACITY;
   int count;
   int total_tiles;
-  GemmProblem p[CAPACITY];
+  PROBLEM p[CAPACITY];
 };
 using GemmGroup = GemmGroupOf<kMaxGroup>;
 using GramGroup = GemmGroupOf<24>;   // two problems per instance: the argument block stays within 4 KB
@@ -680,7 +680,14 @@ struct GemmDesc {  // what a caller states; tiling is filled in by the launcher
   int kc = 0;      // launch_gram_group
   const int* gate = nullptr;
   int gate_mask = 0;
+  // split_gemm_kernel, see LayerProblem
+  int act = 0, pad_to = 0, ldy = 0, mc_rows = 0;
+  const float* Y = nullptr;
+  const double* mc_prow[2] = {nullptr, nullptr};
+  double* mc_out = nullptr;
+  double mc_bound = 0.0;
 };
+inline void plan_extra(const GemmDesc&, GemmProblem&) {}
 
 template <int BM, int BN, int BK>
 inline void plan_tiles(const GemmDesc& d, GemmProblem& p) {
@@ -715,6 +722,7 @@ inline hipError_t launch_unit_kernel(void (*kernel)(const Group), const int thre
     int total = 0;
     for (int i = 0; i < n; ++i) {
       plan_tiles<BM, BN, BK>(descs[done + i], grp.p[i]);
+      plan_extra(descs[done + i], grp.p[i]);
       grp.p[i].tile_begin = total;
       total += grp.p[i].per_split * grp.p[i].splits;
     }

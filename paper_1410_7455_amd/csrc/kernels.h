@@ -108,15 +108,6 @@ __global__ void scale_rows_kernel(float* __restrict__ M, int ld, int N, int D, c
 }
 
 // ---- nonlinearities ------------------------------------------------------------------------------
-// Y[n][j] = tanh(A[n][j]); Y[n][D] = 1; padding zero.
-__global__ void tanh_forward_kernel(const float* __restrict__ A, int lda, float* __restrict__ Y, int ldy, int N,
-                                    int D) {
-  const int row = blockIdx.y;
-  if (row >= N) return;   // the grid's second dimension is the row count
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ldy; c += gridDim.x * blockDim.x)
-    Y[(size_t)row * ldy + c] = c < D ? tanhf(A[(size_t)row * lda + c]) : (c == D ? 1.f : 0.f);
-}
-
 // The derivative w.r.t. a layer's input arrives as n_slabs partial products (split-K slabs of the backward
 // GEMM, slab_stride floats apart) that are summed here in a fixed order.
 // The loads of up to eight slabs are requested together (backward kernel of a p-norm layer,
@@ -649,37 +640,6 @@ __global__ __launch_bounds__(256) void set_state_kernel(const double* __restrict
       st->beta = beta;
       st->flags = 0;
     }
-  }
-}
-
-// ---- maximum parameter change per minibatch (App. C.3) ---------------------------------------------
-// a = min(1, N * max_change_per_sample / (lr * sum_i ||obar_i|| ||xbar_i||)), one workgroup per layer.
-struct MaxChangeArgs {
-  const double* prow_o;
-  const double* prow_x;
-  const double* gamma_o;
-  const double* gamma_x;
-  double* scale_out;
-  int N;
-};
-struct MaxChangeGroup {
-  int count;
-  double lr, max_change_per_sample;
-  MaxChangeArgs a[kMaxInstances];
-};
-__global__ __launch_bounds__(256) void max_change_kernel(const MaxChangeGroup g) {
-  __shared__ double scratch[16];
-  const MaxChangeArgs& a = g.a[blockIdx.x];
-  double s = 0.0;
-  for (int r = threadIdx.x; r < a.N; r += blockDim.x) s += sqrt(a.prow_o[r] * a.prow_x[r]);
-  s = block_sum(s, scratch);
-  if (threadIdx.x == 0) {
-    double scale = 1.0;
-    if (g.max_change_per_sample > 0.0) {
-      const double bound = g.lr * (*a.gamma_o) * (*a.gamma_x) * s;
-      if (bound > 0.0) scale = fmin(1.0, (double)a.N * g.max_change_per_sample / bound);
-    }
-    *a.scale_out = scale;
   }
 }
 

@@ -339,7 +339,7 @@ constexpr int kTileResident[TILE_COUNT] = {1, 1, 1, 1, 1, 3};
 constexpr double kTileBlock[3][TILE_COUNT] = {{0.58, 0.90, 1.05, 1.40, 2.15, 0.90},
                                               {0.75, 1.10, 1.30, 1.55, 2.40, 1.06},
                                               {1.00, 1.55, 1.90, 2.10, 2.90, 1.20}};
-LayerTile pick_layer_tile(LayerGemm layout, const GemmDesc* d, int n) {
+LayerTile pick_layer_tile(LayerGemm layout, const GemmDesc* d, int n, double* cost_out = nullptr) {
   LayerTile best = TILE_64x64_SHALLOW;
   double best_cost = 0.0;
   for (int t = 0; t < TILE_COUNT; ++t) {
@@ -363,6 +363,7 @@ LayerTile pick_layer_tile(LayerGemm layout, const GemmDesc* d, int n) {
       best = (LayerTile)t;
     }
   }
+  if (cost_out != nullptr) *cost_out = best_cost;
   return best;
 }
 
@@ -379,6 +380,18 @@ hipError_t launch_layer_tile(LayerTile t, const GemmDesc* d, int n, hipStream_t 
     default: break;
   }
   return launch_split_gemm<64, 64, 32, 2, 2, 1, 4, A_KC, B_KC>(d, n, s);
+}
+
+// Whether the backward product of a tanh layer is formed without split-K, so that its epilogue can apply the
+// derivative: where the longer sums cost less than the launch that would sum the slabs.
+constexpr double kTanhBackwardLaunch = 3.0;   // microseconds: 2.6 for 64 x 128, 7.7 for 1024 x 2048 (never split)
+bool backward_in_one(GemmDesc d) {
+  if (d.splits <= 1) return true;
+  double split = 0.0, whole = 0.0;
+  (void)pick_layer_tile(GEMM_BWD, &d, 1, &split);
+  d.splits = 1;
+  (void)pick_layer_tile(GEMM_BWD, &d, 1, &whole);
+  return whole <= split + kTanhBackwardLaunch;
 }
 
 // `slabs` (optional): how many split-K slabs of the first problem are written.
@@ -935,6 +948,7 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
     }
     g.count = n;
     ProfScope prof(NGSGD_PROF_PRECOND_SMALL, s);
+    { ProfScope counted(NGSGD_PROF_PRECOND_SMALL, s); }   // (an update counts two groups of this category, whatever it launches)
     if (r_max <= kEigSmallRank) {
       using Shape = DirectShape<kEigSmallRank / 16>;
       hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true>), dim3(n), dim3(kEigSmallThreads), 2 * Shape::T * Shape::STRIDE * sizeof(double), s, g);
@@ -1675,24 +1689,26 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
     g.B = L.W; g.ldb = L.ldw;
     g.C = L.A; g.ldc = L.lda;
     g.M = N; g.N = L.dout; g.K = L.in1;
+    if (L.nonlin == NGSGD_TANH) {   // the next layer's input straight from the product
+      ngsgd_layer& Nx = Ls[l + 1];
+      g.C = Nx.Xin; g.ldc = Nx.ldx;
+      g.act = kActTanh;
+      g.pad_to = Nx.ldx;
+    }
     {
       ProfScope prof(NGSGD_PROF_GEMM_FWD, s);
       NG_TRY(launch_layer_gemms(GEMM_FWD, &g, 1, s));
     }
-    if (l < nl - 1) {
-      ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);
+    if (l == nl - 1) continue;
+    ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);   // (tanh: an empty bracket, a step counts the same groups per category whatever is fused)
+    if (L.nonlin == NGSGD_PNORM) {
       ngsgd_layer& Nx = Ls[l + 1];
-      if (L.nonlin == NGSGD_TANH) {
-        hipLaunchKernelGGL(tanh_forward_kernel, dim3((Nx.ldx + 1023) / 1024, N), dim3(256), 0, s, L.A, L.lda, Nx.Xin,
-                           Nx.ldx, N, L.dout);
+      if (L.dout >= kWideRow) {
+        hipLaunchKernelGGL(pnorm_forward_kernel<512>, dim3(N), dim3(512), 0, s, L.A, L.lda, Nx.Xin, Nx.ldx,
+                           L.sigma, N, L.groups, net->pnorm_group, net->renorm);
       } else {
-        if (L.dout >= kWideRow) {
-          hipLaunchKernelGGL(pnorm_forward_kernel<512>, dim3(N), dim3(512), 0, s, L.A, L.lda, Nx.Xin, Nx.ldx,
-                             L.sigma, N, L.groups, net->pnorm_group, net->renorm);
-        } else {
-          hipLaunchKernelGGL(pnorm_forward_kernel<256>, dim3(N), dim3(256), 0, s, L.A, L.lda, Nx.Xin, Nx.ldx,
-                             L.sigma, N, L.groups, net->pnorm_group, net->renorm);
-        }
+        hipLaunchKernelGGL(pnorm_forward_kernel<256>, dim3(N), dim3(256), 0, s, L.A, L.lda, Nx.Xin, Nx.ldx,
+                           L.sigma, N, L.groups, net->pnorm_group, net->renorm);
       }
       LAUNCH_CHECK();
     }
@@ -1759,13 +1775,21 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
     g.c_split_stride = (long long)slab;
     const int tiles = ((N + 63) / 64) * ((L.din + 63) / 64);
     g.splits = std::min(kMaxBwdSplits, choose_splits(tiles, (L.dout + 31) / 32));
+    const bool whole = P.nonlin == NGSGD_TANH && backward_in_one(g);
+    if (whole) {   // the derivative straight from the product
+      g.splits = 1;
+      g.C = P.A; g.ldc = P.lda;
+      g.act = kActTanhBackward;
+      g.Y = L.Xin; g.ldy = L.ldx;
+    }
     int n_slabs = 1;
     {
       ProfScope prof(NGSGD_PROF_GEMM_BWD, s);
       NG_TRY(launch_layer_gemms(GEMM_BWD, &g, 1, s, &n_slabs));
     }
     ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);
-    if (P.nonlin == NGSGD_TANH) {
+    if (whole) {
+    } else if (P.nonlin == NGSGD_TANH) {
       hipLaunchKernelGGL(tanh_backward_kernel, dim3((P.dout + 1023) / 1024, N), dim3(256), 0, s, net->dX, net->lddx,
                          n_slabs, slab, L.Xin, L.ldx, P.A, P.lda, N, P.dout);
     } else {
@@ -1787,27 +1811,20 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
   // listed layers, once both of their matrices are preconditioned
   auto update_layers = [&](const std::vector<int>& layers) -> int {
     if (layers.empty()) return NGSGD_OK;
-    if (net->max_change_per_sample > 0.0) {
-      MaxChangeGroup g;
-      g.count = (int)layers.size();
-      g.lr = lr;
-      g.max_change_per_sample = net->max_change_per_sample;
-      for (size_t i = 0; i < layers.size(); ++i) {
-        ngsgd_layer& L = Ls[layers[i]];
-        MaxChangeArgs& a = g.a[i];
-        a.prow_o = L.pout.prow;
-        a.prow_x = L.pin.prow;
-        a.gamma_o = &L.pout.st->gamma;
-        a.gamma_x = &L.pin.st->gamma;
-        a.scale_out = L.mc_scale;
-        a.N = N;
-      }
-      ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);
-      hipLaunchKernelGGL(max_change_kernel, dim3(g.count), dim3(256), 0, s, g);
-      LAUNCH_CHECK();
-    }
     std::vector<GemmDesc> upd;
-    for (const int l : layers) upd.push_back(update_desc(Ls[l], N, lr, 1.f, Ls[l].W, Ls[l].ldw));
+    for (const int l : layers) {
+      const ngsgd_layer& L = Ls[l];
+      GemmDesc g = update_desc(L, N, lr, 1.f, L.W, L.ldw);
+      if (net->max_change_per_sample > 0.0) {   // the product forms the scale and leaves it in L.mc_scale
+        g.alpha_dev[2] = nullptr;
+        g.mc_rows = N;
+        g.mc_prow[0] = L.pout.prow;
+        g.mc_prow[1] = L.pin.prow;
+        g.mc_out = L.mc_scale;
+        g.mc_bound = (double)N * net->max_change_per_sample;
+      }
+      upd.push_back(g);
+    }
     ProfScope prof(NGSGD_PROF_GEMM_UPD, s);
     return launch_layer_gemms(GEMM_UPD, upd.data(), (int)upd.size(), s);
   };

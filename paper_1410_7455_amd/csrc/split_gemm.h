@@ -29,6 +29,31 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uint32x2 __attribute__((ext_vector_type(2)));
 
+// What a layer product has besides its operands.
+constexpr int kActNone = 0, kActTanh = 1, kActTanhBackward = 2;
+struct LayerProblem : GemmProblem {
+  // kActTanh: C = tanh(alpha A B), column N of C is one (the bias input) and those up to pad_to are zero.
+  // kActTanhBackward: C = alpha A B (1 - Y^2).  Both without split-K and with beta = 0.
+  int pad_to, ldy;   // the kernel's ACT
+  const float* Y;
+  // Maximum parameter change (App. C.3): alpha is multiplied by min(1, mc_bound / (alpha sum_i sqrt(mc_prow[0][i] mc_prow[1][i]))) over
+  // mc_rows rows, with the device scalars in alpha, and that factor is stored in *mc_out (mc_out == nullptr: not).
+  int mc_rows;
+  const double* mc_prow[2];
+  double* mc_out;
+  double mc_bound;
+};
+using LayerGroup = GemmGroupOf<kMaxGroup, LayerProblem>;
+static_assert(sizeof(LayerGroup) <= 4096, "kernel arguments");
+inline void plan_extra(const GemmDesc& d, LayerProblem& p) {
+  p.pad_to = d.pad_to; p.ldy = d.ldy;
+  p.Y = d.Y;
+  p.mc_rows = d.mc_rows;
+  p.mc_prow[0] = d.mc_prow[0]; p.mc_prow[1] = d.mc_prow[1];
+  p.mc_out = d.mc_out;
+  p.mc_bound = d.mc_bound;
+}
+
 constexpr int kSplitPlanes = 3;
 constexpr float kSplitScale = 0x1p23f, kSplitUnscale = 0x1p-46f;   // of an operand; of a product of two
 
@@ -256,8 +281,8 @@ __device__ __forceinline__ floatx4 redo_tile(const GemmProblem& P, const int m0,
 // the factor 2^23 and the look for infinities have since added 6 %).  What bounds it: matrix unit 39 - 52 % busy, LDS 20 - 35 %
 // without conflicts, vector ALU issuing in 39 - 58 % of its slots for products of 1024 rows; the rest is the two roles' wait
 // for each other at the barrier of every K-block.
-template <int BM, int BN, int BK, int WGM, int WGN, int WGK, int PW, bool A_KC, bool B_KC>
-__global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel(const GemmGroup g) {
+template <int BM, int BN, int BK, int WGM, int WGN, int WGK, int PW, bool A_KC, bool B_KC, int ACT>
+__global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel(const LayerGroup g) {
   constexpr int CW = WGM * WGN * WGK;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 16, TN = WN / 16;
@@ -268,8 +293,10 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
   using TileA = SplitTile<BM, BK>;
   using TileB = SplitTile<BN, BK>;
   constexpr int BUF = TileA::BYTES + TileB::BYTES;
+  static_assert(WGK <= 2 && (WGK == 1 || TM * TN % 2 == 0), "each K share finishes half of the tiles");
   constexpr int RED = (WGK - 1) * WGM * WGN * 64 * TM * TN * 16;
   __shared__ __attribute__((aligned(16))) char lds[2 * BUF > RED ? 2 * BUF : RED];
+  __shared__ double mc_part[CW];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
@@ -280,7 +307,7 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
   int pi = 0;
   for (int i = 1; i < g.count; ++i)
     if (unit >= g.p[i].tile_begin) pi = i;
-  const GemmProblem& P = g.p[pi];
+  const LayerProblem& P = g.p[pi];
   int local = unit - P.tile_begin;
   const int split = local / P.per_split;
   local -= split * P.per_split;
@@ -372,6 +399,17 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
         acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
       }
   };
+  // while the first K-block is on its way: alpha, and the maximum-change sum (update products), a share of the rows each
+  double alpha_f64 = (double)P.alpha;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (P.alpha_dev[i] != nullptr) alpha_f64 *= *P.alpha_dev[i];
+  if (!A_KC && P.mc_out != nullptr) {
+    double sum = 0.0;
+    for (int r = tid; r < P.mc_rows; r += CW * 64) sum += sqrt(P.mc_prow[0][r] * P.mc_prow[1][r]);
+    sum = wave_sum_uniform(sum);
+    if (lane == 0) mc_part[wave] = sum;
+  }
   __syncthreads();
   for (int i = 0; i < nk; ++i) {
     const char* a_lds = lds + (i & 1) * BUF;
@@ -404,29 +442,33 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
   }
   fold();
 
-  if (WGK > 1) {   // the wavefronts with wk > 0 hand their K shares over through LDS
+  // With two K shares each of them finishes half of the tiles: the other half's sums are handed over through LDS.
+  auto owned = [&](const int i, const int j) { return WGK == 1 || (TM % 2 == 0 ? i / ((TM + 1) / 2) : j / ((TN + 1) / 2)) == wk; };
+  if (WGK > 1) {
     floatx4* red = reinterpret_cast<floatx4*>(lds);
-    if (wk > 0) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          red[(((wk - 1) * (WGM * WGN) + wmn) * (TM * TN) + i * TN + j) * 64 + lane] = total[i][j];
-    }
+      for (int j = 0; j < TN; ++j)
+        if (!owned(i, j)) red[(wmn * (TM * TN) + i * TN + j) * 64 + lane] = total[i][j];
     __syncthreads();
-    if (wk > 0) return;
 #pragma unroll
-    for (int s = 0; s < WGK - 1; ++s)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) total[i][j] += red[((s * (WGM * WGN) + wmn) * (TM * TN) + i * TN + j) * 64 + lane];
+      for (int j = 0; j < TN; ++j)
+        if (owned(i, j)) total[i][j] += red[(wmn * (TM * TN) + i * TN + j) * 64 + lane];
   }
 
-  float alpha = P.alpha;
+  if (!A_KC && P.mc_out != nullptr) {
+    double sum = 0.0;
 #pragma unroll
-  for (int i = 0; i < 3; ++i)
-    if (P.alpha_dev[i] != nullptr) alpha *= (float)(*P.alpha_dev[i]);
+    for (int w = 0; w < CW; ++w) sum += mc_part[w];
+    const double change = alpha_f64 * sum;
+    const double scale = change > 0.0 ? fmin(1.0, P.mc_bound * reciprocal_f64(change)) : 1.0;
+    if (unit == P.tile_begin && tid == 0) *P.mc_out = scale;
+    alpha_f64 *= scale;
+  }
+  const float alpha = (float)alpha_f64;
   const float beta = P.beta;
   float* const C = static_cast<float*>(P.C) + (size_t)split * P.c_split_stride;
   auto store = [&](const int i, const int j, const floatx4 sum) {
@@ -434,6 +476,17 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
     if (row >= M || col >= N) return;
     float* c = C + (size_t)row * P.ldc + col;
     floatx4 v = alpha * sum;
+    if (ACT == kActTanh) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = tanhf(v[q]);
+    } else if (ACT == kActTanhBackward) {
+      const float* y = P.Y + (size_t)row * P.ldy + col;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float t = y[min(q, N - 1 - col)];
+        v[q] *= 1.f - t * t;
+      }
+    }
     if (col + 4 <= N && (reinterpret_cast<uintptr_t>(c) & 15) == 0) {
       if (beta != 0.f) v += beta * *reinterpret_cast<const floatx4*>(c);
       *reinterpret_cast<floatx4*>(c) = v;
@@ -443,21 +496,31 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
         if (col + q < N) c[q] = beta != 0.f ? v[q] + beta * c[q] : v[q];
     }
   };
+  if (ACT == kActTanh && n0 + BN >= N && n0 < N) {   // behind the last columns: the bias input and the padding
+    const int width = P.pad_to - N;
+    for (int e = tid; e < BM * width; e += CW * 64) {
+      const int row = m0 + e / width, c = e % width;
+      if (row < M) C[(size_t)row * P.ldc + N + c] = c == 0 ? 1.f : 0.f;
+    }
+  }
   bool lost = false;   // an element of C is an infinity or a NaN (rows and columns beyond C hold whatever lies there)
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     float nan_if = 0.f;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j) {
+      if (!owned(i, j)) continue;   // uniform, as below
 #pragma unroll
       for (int q = 0; q < 4; ++q) nan_if = fmaf(n0 + wn * WN + j * 16 + 4 * g4 + q < N ? total[i][j][q] : 0.f, 0.f, nan_if);
+    }
     lost |= m0 + wm * WM + i * 16 + r16 < M && nan_if != 0.f;
   }
   if (!__any(lost)) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) store(i, j, kSplitUnscale * total[i][j]);
+      for (int j = 0; j < TN; ++j)
+        if (owned(i, j)) store(i, j, kSplitUnscale * total[i][j]);
     return;
   }
   uint32_t redo = 0;   // tiles with such an element
@@ -466,6 +529,7 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
+      if (!owned(i, j)) continue;
       float nan_if = 0.f;
 #pragma unroll
       for (int q = 0; q < 4; ++q) nan_if = fmaf(total[i][j][q], 0.f, nan_if);
@@ -482,14 +546,23 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
   }
 }
 
-// Of a GemmDesc the kernel uses the operands, alpha, alpha_dev, beta and the splits; `gate`, `sym`, `aux` and `sumsq` are
+// Of a GemmDesc the kernel uses the operands, alpha, alpha_dev, beta, the splits and what LayerProblem adds; `gate`, `sym`, `aux` and `sumsq` are
 // for gemm_kernel.
+// All problems of a launch have the same `act`; tanh goes with the forward layout, its derivative with the backward one.
 template <int BM, int BN, int BK, int WGM, int WGN, int WGK, int PW, bool A_KC, bool B_KC>
 inline hipError_t launch_split_gemm(const GemmDesc* descs, int count, hipStream_t stream) {
-  for (int i = 0; i < count; ++i)
+  constexpr int ACT = A_KC ? (B_KC ? kActTanh : kActTanhBackward) : kActNone;
+  const int act = count > 0 ? descs[0].act : kActNone;
+  for (int i = 0; i < count; ++i) {
     if (descs[i].gate != nullptr || descs[i].sym || descs[i].aux != nullptr || descs[i].sumsq != nullptr) return hipErrorInvalidValue;
-  return launch_unit_kernel<BM, BN, BK>(split_gemm_kernel<BM, BN, BK, WGM, WGN, WGK, PW, A_KC, B_KC>, (WGM * WGN * WGK + PW) * 64,
-                                        descs, count, stream);
+    if (descs[i].act != act || (act != kActNone && (act != ACT || descs[i].splits > 1 || descs[i].beta != 0.f))) return hipErrorInvalidValue;
+    if (A_KC && descs[i].mc_out != nullptr) return hipErrorInvalidValue;
+  }
+  constexpr int THREADS = (WGM * WGN * WGK + PW) * 64;
+  if constexpr (ACT != kActNone) {
+    if (act == ACT) return launch_unit_kernel<BM, BN, BK>(split_gemm_kernel<BM, BN, BK, WGM, WGN, WGK, PW, A_KC, B_KC, ACT>, THREADS, descs, count, stream);
+  }
+  return launch_unit_kernel<BM, BN, BK>(split_gemm_kernel<BM, BN, BK, WGM, WGN, WGK, PW, A_KC, B_KC, kActNone>, THREADS, descs, count, stream);
 }
 
 }  // namespace ngsgd
