@@ -1170,11 +1170,12 @@ int simple_many(const std::vector<SimpleCall>& calls, bool scale_output, hipStre
     {
       // G = beta I + Gram / (N-1), then its inverse, one launch per pivot block
       ProfScope prof(NGSGD_PROF_SIMPLE_INVERSE, s);
-      hipLaunchKernelGGL(simple_prepare_kernel, dim3(nblk_max, nblk_max, cnt), dim3(256), 0, s, g);
+      const int tiles = (nblk_max + 1) / 2;   // rows of 64 x 64 tiles
+      hipLaunchKernelGGL(simple_prepare_kernel, dim3(tiles, tiles, cnt), dim3(256), 0, s, g);
       LAUNCH_CHECK();
-      const int wg = (nblk_max + 1) / 2;
       for (int k = 0; k < nblk_max; ++k) {
-        hipLaunchKernelGGL(simple_sweep_kernel, dim3(wg + 1, wg, cnt), dim3(256), 0, s, g, k);   // look-ahead column first
+        // look-ahead column first
+        hipLaunchKernelGGL(simple_sweep_kernel, dim3(tiles + 2, (tiles + 1) / 2, cnt), dim3(256), 0, s, g, k);
         LAUNCH_CHECK();
       }
     }
