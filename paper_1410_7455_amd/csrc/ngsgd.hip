@@ -186,6 +186,7 @@ struct ngsgd_precond {
   bool owned_by_net = false;
   SideSync* sync = nullptr;   // set for instances of a network
   int last_N = 0;             // rows of the latest call
+  int fused_columns = kFusedChunk;   // columns of a patch in the last fused launch
   int n_sumsq = 0;            // partial sums of tr(X X^T) its H product left in sumsq_part
 };
 
@@ -703,12 +704,30 @@ int launch_j_products(std::vector<PrecondCall>& list, hipStream_t s) {
 // forms the H rows itself (microseconds; the kernel's clock runs at 100 MHz).
 std::atomic<long long> g_fused_wait_us{2000};
 
-inline int fused_chunks(int D) { return (D + kFusedChunk - 1) / kFusedChunk; }
+inline int fused_chunks(int D, int columns = kFusedChunk) { return (D + columns - 1) / columns; }
 inline int fused_row_blocks(int N) { return (N + kFusedRows - 1) / kFusedRows; }
 
 // Whether the fused kernel's bookkeeping has room for this call (partial sums of tr(X X^T) per patch).
 inline bool fused_fits(const ngsgd_precond& p, int N) {
   return fused_chunks(p.dim) * fused_row_blocks(N) <= kSumsqMax && (size_t)fused_row_blocks(N) + 1 < p.arrive_slots;
+}
+
+// Columns of a patch in a launch of `units` patches of 64 x 160 and rank class rc.  Every patch adds its part of H to memory by
+// float atomics, and workgroups that run at the same time wait for the slowest of these: wide patches need half as many, but
+// are fewer and have two wavefronts per SIMD instead of three.  160 / 320 columns, rank 80: ten matrices of a p-norm network (952
+// patches) 65 / 77 us; of a tanh network with 1024 rows and 2048 columns (above 2000) 283 / 178; one matrix of 512 x 5000 (256) 36 / 45,
+// 2048 x 5000 (1024) 111 / 78.
+constexpr int kFusedWideUnits = 1023;   // at least four per compute unit
+inline int fused_columns(int units, int rc) { return rc > 32 && units > kFusedWideUnits ? kFusedWide : kFusedChunk; }
+
+template <int RC>
+void launch_fused(const FusedGroup& g, int columns, hipStream_t s) {
+  if constexpr (RC > 32)
+    if (columns == kFusedWide) {
+      hipLaunchKernelGGL((fused_apply_kernel<RC, kFusedWide, 64>), dim3(g.total_units), dim3(kFusedThreads), 0, s, g);
+      return;
+    }
+  hipLaunchKernelGGL((fused_apply_kernel<RC, kFusedChunk, kFusedChunk>), dim3(g.total_units), dim3(kFusedThreads), 0, s, g);
 }
 
 // Xhat = X - (X W^T) W, row-norm partials and the partial sums of tr(X X^T) in one pass over each matrix
@@ -720,6 +739,14 @@ int launch_fused_apply(std::vector<PrecondCall>& list, hipStream_t s) {
     g.count = n;
     g.spin_limit = g_fused_wait_us.load() * 100;
     int units = 0, rc = 0;
+    for (int i = 0; i < n; ++i) {
+      const PrecondCall& c = list[done + i];
+      units += fused_row_blocks(c.N) * fused_chunks(c.p->dim);
+      rc = std::max(rc, c.p->ldh);
+    }
+    const int columns = fused_columns(units, rc);
+    units = 0;
+    int chunks = 0;
     for (int i = 0; i < n; ++i) {
       const PrecondCall& c = list[done + i];
       ngsgd_precond& p = *c.p;
@@ -736,22 +763,24 @@ int launch_fused_apply(std::vector<PrecondCall>& list, hipStream_t s) {
       a.hat_part = p.hat_part;
       a.N = c.N; a.D = p.dim; a.R = p.rank;
       a.n_rb = fused_row_blocks(c.N);
-      a.n_chunks = fused_chunks(p.dim);
+      a.n_chunks = fused_chunks(p.dim, columns);
       a.n_chunks_pad = (a.n_chunks + kXcds - 1) / kXcds * kXcds;
+      a.first_die = chunks % kXcds;
+      chunks += a.n_chunks;
       a.unit_begin = units;
       units += a.n_rb * a.n_chunks_pad;
       p.last_N = c.N;
       p.n_sumsq = a.n_chunks * a.n_rb;
-      rc = std::max(rc, p.ldh);
+      p.fused_columns = columns;
     }
     g.total_units = units;
     ProfScope prof(NGSGD_PROF_PRECOND_FUSED, s);
     if (rc == 32) {
-      hipLaunchKernelGGL((fused_apply_kernel<32, kFusedChunk>), dim3(units), dim3(kFusedThreads), 0, s, g);
+      launch_fused<32>(g, columns, s);
     } else if (rc == 80) {
-      hipLaunchKernelGGL((fused_apply_kernel<80, kFusedChunk>), dim3(units), dim3(kFusedThreads), 0, s, g);
+      launch_fused<80>(g, columns, s);
     } else {
-      hipLaunchKernelGGL((fused_apply_kernel<96, kFusedChunk>), dim3(units), dim3(kFusedThreads), 0, s, g);
+      launch_fused<96>(g, columns, s);
     }
     LAUNCH_CHECK();
     done += n;
@@ -833,9 +862,9 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
       a.sumsq_part = p.sumsq_part;
       a.hat_part = p.hat_part;
       a.n_sumsq = p.n_sumsq;
-      a.n_hat = fused ? fused_chunks(p.dim) * fused_row_blocks(c.N) : ((p.dim + 63) / 64) * ((c.N + 63) / 64);
+      a.n_hat = fused ? fused_chunks(p.dim, p.fused_columns) * fused_row_blocks(c.N) : ((p.dim + 63) / 64) * ((c.N + 63) / 64);
       a.rownorm_part = p.rownorm_part;
-      a.n_col_tiles = fused ? fused_chunks(p.dim) : (p.dim + 63) / 64;
+      a.n_col_tiles = fused ? fused_chunks(p.dim, p.fused_columns) : (p.dim + 63) / 64;
       a.N = c.N;
       a.prow = p.prow;
       a.gamma_out = c.gamma_out;
@@ -845,7 +874,7 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
       a.W = p.W; a.ldw = p.ldw;
       a.H = p.H; a.ldh = p.ldh;
       a.R = p.rank;
-      a.chunk_cols = kFusedChunk;
+      a.chunk_cols = p.fused_columns;
       a.arrive = p.arrive;
       a.n_arrive = fused ? (int)p.arrive_slots - 2 : 0;
       n_max = std::max(n_max, c.N);

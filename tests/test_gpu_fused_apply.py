@@ -88,3 +88,30 @@ def test_c2_full_size_without_update(ngsgd, which):
         assert rel(got, expect) < TOL, f"step {step}"
         assert g_g == pytest.approx(g_o, rel=1e-4)
         assert rel(rn_g, rn_o) < 2e-4
+
+
+# wide patches: 1024 patches of 64 x 160 (ceil(N / 64) * ceil(D / 160)), the fewest for them and the most of one matrix.  The
+# last patch of 320 columns has 161 (two pieces of 64 and 33), all, four pieces and one column, 201, and of the only patch two and
+# one; the last row block one row, all, a few
+WIDE = [(8129, 1121, 80), (8192, 1280, 33), (4033, 2497, 41), (1990, 5001, 96), (65473, 129, 81)]
+
+
+@pytest.mark.parametrize("N,D,R", WIDE)
+def test_wide_patches_match_oracle(ngsgd, N, D, R):
+    import torch
+    rng = np.random.default_rng(8000 + N + D + R)
+    kw = dict(num_samples_history=4000.0, update_period=4, always_update_first=1)
+    ora = OnlineNaturalGradient(D, R, **kw)
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, **kw)
+    try:
+        for step, wait_us in enumerate([2000, 2000, 0]):   # one update, one call as it should go, one that leaves patches over
+            ngsgd.set_wait_limit_us(wait_us)
+            M = data(rng, N, D)
+            print(f"wide patches N={N} D={D} R={R} step={step} wait_us={wait_us}", flush=True)
+            expect, g_o, rn_o = ora.precondition(M)
+            got, g_g, rn_g = gpu_call(torch, pre, M, ld=D + (-D) % 4)
+            assert rel(got, expect) < TOL, f"step {step}"
+            assert g_g == pytest.approx(g_o, rel=1e-4)
+            assert rel(rn_g, rn_o) < 2e-4
+    finally:
+        ngsgd.set_wait_limit_us(2000)
