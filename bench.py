@@ -70,9 +70,9 @@ def measured_traffic_per_launch(category):
     WRITE_SIZE runs of this file, scaled by a plain copy of known size; see the summary for the commands).
     None when the summary is missing or does not list the kernels."""
     import re
-    # template arguments: tile, K-block, wavefronts (M, N, K shares, staging), A K-contiguous, B K-contiguous
+    # template arguments: tile, K-block, wavefronts (M, N, K shares, staging), A K-contiguous, B K-contiguous, epilogue
     layout = {"gemm_fwd": "true, true", "gemm_bwd": "true, false", "gemm_upd": "false, false"}.get(category)
-    pattern = layout and r"split_gemm_kernel<\d+, \d+, \d+, \d, \d, \d, \d+, " + layout + ">"
+    pattern = layout and r"split_gemm_kernel<\d+, \d+, \d+, \d, \d, \d, \d+, " + layout + r", \d>"
     path = os.path.join(ROOT, "profiles", "step_c1_pnorm_hbm_traffic.txt")
     if pattern is None or not os.path.exists(path):
         return None
