@@ -2,12 +2,15 @@
 // eigenvalues of T by multisection, eigenvectors by a twisted factorisation, back through the reflections.  (One
 // Newton-Schulz step in the kernel that finishes the update makes the vectors orthogonal to working precision.)
 //
+// The errors of the reduction are a few eps sqrt(z_ii z_jj) where the diagonal descends, and of the eigenvalues a few eps each: the
+// smallest keep their digits.  So rows and columns are sorted where the diagonal spans more than kDirectOrderSpan.  (Factors of the
+// last layers' inputs of the speech-shaped network, eigenvalues over 4e10 and 3e12, about descending: 2e-13 and 1e-11 off;
+// the same matrices in a random order 2e-5 and 6e-4.)
 // Its chain has R columns of one barrier and a dozen serial runs of R steps; cyclic Jacobi, which it replaces, goes through
 // R - 1 dependent rounds per sweep and 5 to 10 sweeps.  Factors of 512 x 5000 and 512 x 3001 matrices, fresh data: rank 80 273 us (six
-// sweeps 243, the vectors 30), now 110 (reduction 68, eigenpairs 28, finish 14); rank 20 50, now 33.  The errors are a few eps |Z|.  Jacobi's stopping rule leaves
-// off-diagonal entries up to 1e-13 |Z|, but on strongly graded matrices it is more accurate than that in practice: where the
-// eigenvalues span more than kDirectCondLimit, where a vector's residual is large or where the vectors are too far from
-// orthogonal (eigenvalues that agree to working precision), the finishing kernel runs Jacobi instead.
+// sweeps 243, the vectors 30), now 119 (reduction 75, eigenpairs 30, finish 14); rank 20 50, now 35.
+// Where the eigenvalues span more than kDirectCondLimit, where a vector's residual is large or where the vectors are too far
+// from orthogonal (eigenvalues that agree to working precision), the finishing kernel runs Jacobi instead.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -20,8 +23,11 @@
 namespace ngsgd {
 
 constexpr double kDirectEps = 2.220446049250313e-16;
-constexpr double kDirectCondLimit = 1.0e12;     // most that eigenvalues may span: c_min then keeps four digits, its W row fewer in fp32
+constexpr double kDirectCondLimit = 1.0e16;     // most that eigenvalues may span
+constexpr double kDirectOrderSpan = 1.0e6;      // of the diagonal: below it the order does not matter to the digits that fp32 factors have
 constexpr double kDirectResidual = 1.0e-13;     // |T x - lambda x| / |T| of a unit vector, at most
+constexpr double kDirectRelResidual = 1.0e-8;   // and over lambda
+constexpr double kDirectTiny = 1.0e-19;         // of the norm: eigenvalues below it are not told apart
 constexpr double kDirectOrthoLimit = 1.0e-4;    // |U U^T - I| before the Newton-Schulz step, which squares it
 constexpr int kDirectPasses = 16;               // multisection passes at most, a factor of 17 each
 
@@ -315,10 +321,14 @@ __device__ __forceinline__ void direct_pair(const DirectTridiagonal<K>& t, const
   const int lane = threadIdx.x & 63, l16 = lane & 15;
   double lo = lo0, hi = hi0;
   const int blocks = (R + 6) / 8;   // of eight steps behind the first
+  const int point = LANES == 16 ? l16 : lane;
   for (int pass = 0; pass < kDirectPasses; ++pass) {
     const double width = hi - lo;
-    if (!(width > 0.5 * kDirectEps)) break;
-    const double step = width * (1.0 / (LANES + 1)), at = fma(step, (double)((LANES == 16 ? l16 : lane) + 1), lo);
+    if (!(width > kDirectEps * fmax(hi, kDirectTiny))) break;
+    // the first pass finds the eigenvalue's size: 64 binary orders below the largest
+    constexpr int ORDERS = 64 / LANES;
+    const double step = width * (1.0 / (LANES + 1));
+    const double at = pass == 0 ? __builtin_amdgcn_ldexp(hi, -ORDERS * (point + 1)) : fma(step, (double)(point + 1), lo);
     double p = t.step[0][0].x - at, p1 = 1.0;
     uint32_t signs = (uint32_t)(__builtin_bit_cast(uint64_t, p) >> 63);
     int below = (int)signs;
@@ -350,8 +360,14 @@ __device__ __forceinline__ void direct_pair(const DirectTridiagonal<K>& t, const
     const uint64_t votes = __ballot(below <= R - 1 - k);   // points at or below the eigenvalue
     const int m = LANES == 16 ? __popc((uint32_t)(votes >> (lane & 48)) & 0xffffu) : __popcll(votes);
     const double base = lo;
-    if (m > 0) lo = fma(step, (double)m, base);
-    if (m < LANES) hi = fma(step, (double)(m + 1), base);
+    if (pass == 0) {
+      const double top = hi;
+      if (m > 0) lo = __builtin_amdgcn_ldexp(top, -ORDERS * (LANES - m + 1));
+      if (m < LANES) hi = __builtin_amdgcn_ldexp(top, -ORDERS * (LANES - m));
+    } else {
+      if (m > 0) lo = fma(step, (double)m, base);
+      if (m < LANES) hi = fma(step, (double)(m + 1), base);
+    }
   }
   lambda = 0.5 * (lo + hi);
 

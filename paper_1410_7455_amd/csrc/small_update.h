@@ -38,7 +38,7 @@ constexpr double kJacobiLargeAbs = 1.0e3;    // ... and above this many absolute
 constexpr double kOrthoCondLimit = 1.0e6;    // App. B.3.1
 constexpr double kOrthoTolerance = 1.0e-3;   // App. B.3.1
 
-constexpr size_t direct_scratch_doubles(const int R) { return (size_t)R * (2 * kMaxRank + 6) + 1; }
+constexpr size_t direct_scratch_doubles(const int R) { return (size_t)R * (2 * kMaxRank + 7) + 1; }
 struct SmallArgs {
   PrecondScalars* st;
   double* K;         // R x R, J J^T; cleared on exit (the orthogonality check accumulates W W^T into it)
@@ -49,7 +49,7 @@ struct SmallArgs {
   const double* sumsq_part;   // partial sums of tr(X X^T) left by the H product
   int n_sumsq;
   double2* rotlog;   // [kMaxRounds][half] (c, s) of every pair of every round of Jacobi
-  // What the kernels of the direct method hand on: R rows of `ldv` doubles of reflections and of eigenvectors, six vectors, rho_t.
+  // What the kernels of the direct method hand on: R rows of `ldv` doubles of reflections and of eigenvectors, seven vectors, rho_t.
   double* direct;
   __device__ double* V() const { return direct; }
   __device__ double* U(const int ldv) const { return direct + (size_t)R * ldv; }
@@ -59,7 +59,8 @@ struct SmallArgs {
   __device__ double* off(const int ldv) const { return vec(ldv, 2); }
   __device__ double* lambda(const int ldv) const { return vec(ldv, 3); }
   __device__ double* residual(const int ldv) const { return vec(ldv, 4); }
-  __device__ double* d_rho(const int ldv) const { return vec(ldv, 5); }   // diag(D_t), then rho_t
+  __device__ double* order(const int ldv) const { return vec(ldv, 5); }
+  __device__ double* d_rho(const int ldv) const { return vec(ldv, 6); }   // diag(D_t), then rho_t
 };
 struct SmallGroup {
   int count;
@@ -445,31 +446,67 @@ __device__ __forceinline__ void replay_rotations(const SmallArgs& a, const int n
   }
 }
 
-// K_t and L_t, all elements requested together, in the registers of NT threads, see eig_direct.h; then Z_t from them.
+// Z_t in the registers of NT threads (see eig_direct.h), all elements of K_t and L_t requested together.
 template <int K, int NT>
 struct ZLoad {
   static constexpr int A = DirectTile<K, NT>::A, ROWS = DirectTile<K, NT>::ROWS;
   double k[A][K], l[A][K];
-  __device__ __forceinline__ void request(const SmallArgs& a) {
+  template <typename ORDER>
+  __device__ __forceinline__ void request(const SmallArgs& a, ORDER order) {
     const int ti = DirectTile<K, NT>::ti(), tj = DirectTile<K, NT>::tj(), last = a.R - 1;
 #pragma unroll
     for (int x = 0; x < A; ++x)
 #pragma unroll
       for (int b = 0; b < K; ++b) {
-        const int at = min(ti + ROWS * x, last) * a.R + min(tj + 16 * b, last);
+        const int at = order(min(ti + ROWS * x, last)) * a.R + order(min(tj + 16 * b, last));
         k[x][b] = a.K[at];
         l[x][b] = a.L[at];
       }
   }
-  __device__ __forceinline__ void form(const SmallArgs& a, const UpdateFactors& f, const double* s_ise, const double* s_dr, double (&S)[A][K]) const {
+  template <typename ORDER>
+  __device__ __forceinline__ void form(const SmallArgs& a, const UpdateFactors& f, const double* s_ise, const double* s_dr, double (&S)[A][K],
+                                       ORDER order) const {
     const int ti = DirectTile<K, NT>::ti(), tj = DirectTile<K, NT>::tj();
 #pragma unroll
     for (int x = 0; x < A; ++x)
 #pragma unroll
       for (int b = 0; b < K; ++b) {
         const int i = ti + ROWS * x, j = tj + 16 * b;
-        S[x][b] = i < a.R && j < a.R ? z_entry(f, i, j, k[x][b], l[x][b], s_ise, s_dr) : 0.0;
+        S[x][b] = i < a.R && j < a.R ? z_entry(f, order(i), order(j), k[x][b], l[x][b], s_ise, s_dr) : 0.0;
       }
+  }
+  // Behind request(): Z_t, with rows and columns sorted by the diagonal where that spans much; s_order[i] is the index that
+  // stands at i.  All threads of the workgroup; s_diag is scratch.
+  __device__ __forceinline__ void ordered(const SmallArgs& a, const UpdateFactors& f, const double* s_ise, const double* s_dr, double (&S)[A][K],
+                                          double* s_diag, int* s_order) {
+    const int tid = threadIdx.x, lane = tid & 63, R = a.R;
+    auto same = [](const int i) { return i; };
+    form(a, f, s_ise, s_dr, S, same);
+#pragma unroll
+    for (int x = 0; x < A; ++x)
+#pragma unroll
+      for (int b = 0; b < K; ++b) {
+        const int i = DirectTile<K, NT>::ti() + ROWS * x;
+        if (i == DirectTile<K, NT>::tj() + 16 * b && i < R) s_diag[i] = S[x][b];
+      }
+    if (tid < 16 * K) s_order[tid] = tid;
+    __syncthreads();
+    const double d0 = s_diag[min(lane, R - 1)], d1 = s_diag[min(lane + 64, R - 1)];
+    const double up = row16_max_f64(fmax(d0, d1)), down = row16_max_f64(-fmin(d0, d1));
+    const double largest = fmax(fmax(read_lane_f64(up, 0), read_lane_f64(up, 16)), fmax(read_lane_f64(up, 32), read_lane_f64(up, 48)));
+    const double smallest = -fmax(fmax(read_lane_f64(down, 0), read_lane_f64(down, 16)), fmax(read_lane_f64(down, 32), read_lane_f64(down, 48)));
+    if (!(largest > kDirectOrderSpan * smallest)) return;   // the same for all threads
+    __syncthreads();
+    if (tid < R) {
+      const double z = s_diag[tid];
+      int rank = 0;
+      for (int j = 0; j < R; ++j) rank += s_diag[j] > z || (s_diag[j] == z && j < tid) ? 1 : 0;
+      s_order[rank] = tid;   // (a NaN leaves some as they are: all stay indices)
+    }
+    __syncthreads();
+    auto sorted = [&](const int i) { return s_order[i]; };
+    request(a, sorted);
+    form(a, f, s_ise, s_dr, S, sorted);
   }
 };
 
@@ -481,23 +518,25 @@ __global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const Sma
   constexpr int T = Shape::T;
   extern __shared__ double eig_reserved[];   // not used: see the launch
   __shared__ double s_ise[T], s_dr[T], s_tau[T], s_diag[T], s_off[T];
+  __shared__ int s_order[T];
   __shared__ DirectLds<K, NT> lds;
   __shared__ __attribute__((aligned(16))) double s_V[T * T];
   const SmallArgs& a = g.a[blockIdx.x];
   const int R = a.R, tid = threadIdx.x;
   ZLoad<K, NT> load;
-  load.request(a);
+  load.request(a, [](const int i) { return i; });
   const double rho = a.st->rho;
   const UpdateFactors f = update_factors(a, g, a.st->d, rho, s_ise, s_dr, T);
   // handed on: the last kernel's workgroups cannot read what one of them replaces
   for (int i = tid; i <= R; i += NT) a.d_rho(T)[i] = i < R ? a.st->d[i] : rho;
   typename DirectTile<K, NT>::Regs S;
-  load.form(a, f, s_ise, s_dr, S);
+  load.ordered(a, f, s_ise, s_dr, S, s_diag, s_order);
   direct_reduce<K, NT>(S, R, lds, s_V, s_tau, s_off);
   direct_store_tridiagonal<K, NT>(S, R, s_diag, s_off);
   __syncthreads();
   for (int e = tid; e < (R - 2) * T / 2; e += NT) reinterpret_cast<double2*>(a.V())[e] = reinterpret_cast<const double2*>(s_V)[e];
   if (tid < R) {
+    a.order(T)[tid] = (double)s_order[tid];
     a.diag(T)[tid] = s_diag[tid];
     if (tid < R - 1) a.off(T)[tid] = s_off[tid];
     if (tid < R - 2) a.tau(T)[tid] = s_tau[tid];
@@ -566,7 +605,7 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
   __shared__ double scratch[16];
   __shared__ double s_ise[T], s_dr[T], s_col[T], s_c[kMaxRank + 1];
   __shared__ __attribute__((aligned(16))) double2 s_cs[2][kMaxHalf];
-  __shared__ int s_perm[kMaxRank], s_rank[kMaxRank];
+  __shared__ int s_perm[kMaxRank], s_rank[kMaxRank], s_order[T];
   __shared__ int s_rotated[2];
   __shared__ FusedLds<K, NT, FUSED> s_fused;
   static_assert(kMaxRank <= NT && T <= NT, "a thread per eigenvalue");
@@ -592,15 +631,16 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
       lambda = a.lambda(T)[tid];
       residual = a.residual(T)[tid];
     }
+    if (tid < T) s_order[tid] = tid < R ? (int)a.order(T)[tid] : tid;
   }
   ZLoad<K, 256> load;
-  if constexpr (FUSED) load.request(a);   // (the upper half of the threads as well, and drops it)
+  if constexpr (FUSED) load.request(a, [](const int i) { return i; });   // (the upper half of the threads as well, and drops it)
   const UpdateFactors f = update_factors(a, g, FUSED ? st->d : a.d_rho(T), FUSED ? st->rho : a.d_rho(T)[R], s_ise, s_dr, T);
   if constexpr (FUSED) {
     static_assert(NT >= 256 && NT >= 16 * T, "all pairs at once");
+    typename DirectTile<K, 256>::Regs S;
+    load.ordered(a, f, s_ise, s_dr, S, s_fused.t.diag, s_order);
     if (tid < 256) {
-      typename DirectTile<K, 256>::Regs S;
-      load.form(a, f, s_ise, s_dr, S);
       direct_reduce<K, 256>(S, R, s_fused.reduce, s_fused.V, s_fused.s_tau, s_fused.t.off);
       direct_store_tridiagonal<K, 256>(S, R, s_fused.t.diag, s_fused.t.off);
     } else {
@@ -685,7 +725,11 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
       }
     }
   }
-  if (tid < R) bad |= !(residual <= kDirectResidual) || !(lambda <= s_c[0] && s_c[R - 1] > 0.0 && s_c[0] <= kDirectCondLimit * s_c[R - 1]);
+  if (tid < R) {
+    const double largest = s_c[0], smallest = s_c[R - 1];
+    bad |= !(residual <= kDirectResidual && residual * largest <= kDirectRelResidual * lambda);
+    bad |= !(lambda <= largest && smallest > 0.0 && largest <= kDirectCondLimit * smallest);
+  }
   const bool direct = __syncthreads_or(bad ? 1 : 0) == 0;   // (M is complete behind it)
   if (!direct && !lead) return;
 
@@ -786,7 +830,7 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = first_row + 16 * ti + 4 * r + g4, j = 16 * tj + l16;
-        if (i < R && j < R) a.At[(size_t)i * a.ldat + j] = (float)(s_col[i] * acc[r] * s_ise[j]);
+        if (i < R && j < R) a.At[(size_t)i * a.ldat + s_order[j]] = (float)(s_col[i] * acc[r] * s_ise[s_order[j]]);
       }
     }
   } else {
