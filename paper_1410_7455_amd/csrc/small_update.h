@@ -594,7 +594,7 @@ struct FusedLds<K, NT, false> {};
 // The last kernel, and with FUSED the only one: checks the eigenvectors U (rows) and makes them orthogonal to working
 // precision, U <- (3/2 - U U^T / 2) U on the fp64 matrix unit, or has Jacobi find them; then the floors, rho_{t+1}, D_{t+1}, E_{t+1}
 // (eq. rhodash2, dt1, rhot1, beta2, etii) and A_t (eq. wt1).  Above rank 32 a workgroup per 16 rows of A_t: each checks all
-// vectors (so that they agree) and takes its rows' share of the second product; the first one does what is left.
+// vectors, by the same arithmetic so that all decide alike, and takes its rows' share of the second product; the first one does what is left.
 // Grid (instance, FUSED ? 1 : ceil(R / 16)).
 template <int K, int ITEMS, int NT, bool FUSED>
 __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
@@ -678,39 +678,57 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
 #pragma unroll
   for (int w = 0; w < NW; ++w) tr_M += scratch[w];
 
-  // U U^T, tiles on and above the diagonal.  v_mfma_f64_16x16x4_f64: lane l supplies A[l%16][l/16] and B[l/16][l%16]; register r
-  // holds row 4r + l/16, column l%16 (v_mfma_f32_16x16x4_f32 row 4 (l/16) + r).  M has the rows that this workgroup needs (all with
-  // FUSED): those are formed in fp64, five tiles of 20 matrix instructions by as many wavefronts; the others are only
-  // checked, against a limit that fp32 products (a quarter of the time) resolve.
+  // M = 3/2 - U U^T / 2 in fp64 and the check of U U^T.  v_mfma_f64_16x16x4_f64: lane l supplies A[l%16][l/16] and B[l/16][l%16];
+  // register r holds row 4r + l/16, column l%16 (v_mfma_f32_16x16x4_f32 row 4 (l/16) + r).  With FUSED both by the tiles on and above
+  // the diagonal.  Otherwise the first K wavefronts form this workgroup's rows of M, and the others check all tiles on and above
+  // the diagonal with fp32 products (a quarter of the time, and the limit is far above their rounding): the same products
+  // and sums in every workgroup of the instance, so that all decide alike however near the limit an element lies.
   const int first_row = FUSED ? 0 : 16 * (int)blockIdx.y;
   bool bad = false;
-  for (int tile = wave; tile < K * (K + 1) / 2; tile += NW) {
-    int ti = 0, tj = tile;
-    while (tj >= K - ti) {
-      tj -= K - ti;
-      ++ti;
-    }
-    tj += ti;
-    if (16 * tj >= R) continue;   // uniform
-    const double* const ui = U + (16 * ti + l16) * SU + g4;
-    const double* const uj = U + (16 * tj + l16) * SU + g4;
-    if (FUSED || 16 * ti == first_row || 16 * tj == first_row) {
-      doublex4 part[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-      for (int s0 = 0; s0 < R; s0 += 16) {
+  auto product_f64 = [&](const int i0, const int j0) {
+    const double* const ui = U + (i0 + l16) * SU + g4;
+    const double* const uj = U + (j0 + l16) * SU + g4;
+    doublex4 part[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+    for (int s0 = 0; s0 < R; s0 += 16) {
 #pragma unroll
-        for (int s = 0; s < 16; s += 4) part[(s >> 2) & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ui[s0 + s], uj[s0 + s], part[(s >> 2) & 1], 0, 0, 0);
-      }
-      const doublex4 acc = part[0] + part[1];
+      for (int s = 0; s < 16; s += 4) part[(s >> 2) & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ui[s0 + s], uj[s0 + s], part[(s >> 2) & 1], 0, 0, 0);
+    }
+    return part[0] + part[1];
+  };
+  auto tile_of = [](int tile, int& ti, int& tj) {
+    for (ti = 0; tile >= K - ti; ++ti) tile -= K - ti;
+    tj = ti + tile;
+  };
+  if constexpr (FUSED) {
+    for (int tile = wave; tile < K * (K + 1) / 2; tile += NW) {
+      int ti, tj;
+      tile_of(tile, ti, tj);
+      if (16 * tj >= R) continue;   // uniform
+      const doublex4 acc = product_f64(16 * ti, 16 * tj);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = 16 * ti + 4 * r + g4, j = 16 * tj + l16;
         const double one = i == j ? 1.0 : 0.0;
         if (i < R && j < R) bad |= !(fabs(acc[r] - one) <= kDirectOrthoLimit);   // (NaN fails)
-        const double v = fma(-0.5, acc[r], 1.5 * one);
-        if (FUSED || 16 * ti == first_row) M[(i - first_row) * SU + j] = v;
-        if (FUSED || 16 * tj == first_row) M[(j - first_row) * SU + i] = v;
+        M[i * SU + j] = M[j * SU + i] = fma(-0.5, acc[r], 1.5 * one);
       }
-    } else {
+    }
+  } else if (wave < K) {
+    if (16 * wave < R) {
+      const doublex4 acc = product_f64(first_row, 16 * wave);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 4 * r + g4, j = 16 * wave + l16;
+        M[i * SU + j] = fma(-0.5, acc[r], first_row + i == j ? 1.5 : 0.0);
+      }
+    }
+  } else {
+    for (int tile = wave - K; tile < K * (K + 1) / 2; tile += NW - K) {
+      int ti, tj;
+      tile_of(tile, ti, tj);
+      if (16 * tj >= R) continue;   // uniform
+      const double* const ui = U + (16 * ti + l16) * SU + g4;
+      const double* const uj = U + (16 * tj + l16) * SU + g4;
       floatx4 part[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
       for (int s0 = 0; s0 < R; s0 += 16) {
 #pragma unroll
@@ -721,7 +739,7 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = 16 * ti + 4 * g4 + r, j = 16 * tj + l16;
-        if (i < R && j < R) bad |= !(fabsf(acc[r] - (i == j ? 1.f : 0.f)) <= (float)kDirectOrthoLimit);
+        if (i < R && j < R) bad |= !(fabsf(acc[r] - (i == j ? 1.f : 0.f)) <= (float)kDirectOrthoLimit);   // (NaN fails)
       }
     }
   }

@@ -1,4 +1,6 @@
 """GPU parity of the R x R update at the edges of its kernels' tiles, and where the direct eigen-solver hands over to Jacobi."""
+import math
+
 import numpy as np
 import pytest
 
@@ -96,3 +98,60 @@ def test_graded_factors_in_any_order(ngsgd, R):
     flags, sweeps = pre.diagnostics()
     # (eigenvalues that meet by chance may still be left to Jacobi: at rank 96 the gaps are a fifth of their size)
     assert flags & 8 == 0 and 1 <= sweeps <= 20
+
+
+
+def wells(R, gap, N, D, S):
+    """A factor whose D_t falls and rises again the same way, and a minibatch that couples neighbouring rows of it: Z_t has pairs of
+    eigenvalues, one vector of each even and one odd, the closer the larger they are.  The coupling is chosen for the closest pair to
+    have about the relative distance `gap`."""
+    eta = 1.0 - math.exp(-N / S)
+    i = np.arange(R)
+    d, rho = 0.05 + np.abs(i - 0.5 * (R - 1)) / R, 0.01
+
+    def eigenvalues(coupling):
+        M = np.zeros((N, D), np.float32)
+        M[i[:-1], i[:-1]] = M[i[:-1], i[1:]] = np.float32(coupling)
+        x = M[:, :R].astype(np.float64)
+        return M, np.linalg.eigvalsh((1.0 - eta) * np.diag(d + rho) + eta / N * (x.T @ x)) ** 2
+
+    low, high = 0.0, 40.0
+    for _ in range(40):
+        coupling = 0.5 * (low + high)
+        M, c = eigenvalues(coupling)
+        low, high = (coupling, high) if (c[-1] - c[-2]) / c[-1] < gap else (low, coupling)
+    return M, d, rho
+
+
+@pytest.mark.parametrize("R", [6, 20, 31, 33, 48, 65, 80, 96])
+def test_pairs_of_eigenvalues_around_the_limit_of_the_direct_solver(ngsgd, R):
+    """The vectors of a pair get worse as its gap closes: from orthogonal to working precision to not told apart.  The check
+    behind the direct solver draws a line in between, and all workgroups of an update have to draw the same.  An ordinary
+    update in front of each leaves other rows in the scratch, which a workgroup that dropped out would leave as they are."""
+    import torch
+    N, D, S = 210, 300, 700.0
+    rng = np.random.default_rng(9400 + R)
+    kw = dict(num_samples_history=S, update_period=1)
+    ora = OnlineNaturalGradient(D, R, **kw)
+    ora.precondition(data(rng, N, D))
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, **kw)
+    served = []
+    for k in range(32):
+        ora.R, ora.d, ora.rho = np.eye(R, D), np.linspace(1.0, 0.2, R), 0.01
+        upload_state(torch, pre, ora)
+        M = data(rng, N, D)
+        ora.precondition(M)
+        gpu_call(torch, pre, M)
+        M, ora.d, ora.rho = wells(R, 10.0 ** (-15.0 + 0.25 * k), N, D, S)
+        ora.R = np.eye(R, D)
+        upload_state(torch, pre, ora)
+        expect, g_o, _ = ora.precondition(M)
+        got, g_g, _ = gpu_call(torch, pre, M)
+        assert rel(got, expect) < TOL, k
+        flags, sweeps = pre.diagnostics()
+        assert flags & 8 == 0, k
+        served.append(sweeps == 1)
+        compare_states(torch, pre, ora, rng)
+        assert orthogonality(pre, ora.alpha, D) < 2e-5, k   # as in test_update_at_the_edges_of_its_tiles
+    print("served by the direct solver, gaps of 1e-15 and up:", "".join("01"[s] for s in served))
+    assert served[-1] and not all(served)   # Jacobi rotates such a matrix for several sweeps; the direct solver reports one

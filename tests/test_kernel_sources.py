@@ -100,3 +100,29 @@ def test_traffic_summary_lists_the_layer_products():
         traffic = bench.measured_traffic_per_launch(category)
         assert traffic is not None and 1e6 < traffic < 1e9, category
     assert bench.measured_traffic_per_launch("elementwise") is None
+
+
+def enclosing(text, at):
+    """What stands in front of the braces around a position, innermost first: the conditions under which it runs."""
+    depth, out = 0, []
+    for i in range(at, -1, -1):
+        if text[i] == "}":
+            depth += 1
+        elif text[i] == "{":
+            if depth == 0:
+                out.append(re.split(r"[;{}]", text[:i])[-1].strip())
+            depth = max(depth - 1, 0)
+    return out
+
+
+def test_workgroups_of_an_eigen_update_decide_alike():
+    """Every workgroup of an instance decides for itself whether the direct solver served, and writes its rows of A_t or leaves
+    them to the first one: what they compare with the limits has to be the same numbers in all of them, so no comparison may
+    depend on which workgroup makes it."""
+    text = dict(sources())["small_update.h"]
+    body = text[text.index("void eig_finish_kernel"):text.index("__syncthreads_or(bad")]
+    comparisons = [m.start() for m in re.finditer(r"bad \|=", body)]
+    assert len(comparisons) >= 4
+    for at in comparisons:
+        conditions = enclosing(body, at) + [re.split(r"[;{}]", body[:at])[-1]]
+        assert not any(re.search(r"blockIdx|first_row|lead", c) for c in conditions), conditions
