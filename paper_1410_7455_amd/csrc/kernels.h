@@ -531,8 +531,9 @@ __global__ __launch_bounds__(256) void finish_apply_kernel(const FinishGroup g) 
       for (int u = 0; u < 8; ++u) part[u & 1] += c + STEP * u < a.n_col_tiles ? v[u] : 0.f;
     }
   }
-  if (n_deferred > 0) {   // (the same for all workgroups of the instance)
+  if (n_deferred > 0) {   // (the same for all wavefronts of the instance: each has read the count before its workgroup takes a ticket)
     __shared__ int s_last;
+    __syncthreads();
     if (tid == 0) s_last = __hip_atomic_fetch_add(a.ticket(), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == groups - 1 ? 1 : 0;
     __syncthreads();
     if (s_last != 0 && tid == 0) {   // everyone has read the count

@@ -126,3 +126,12 @@ def test_workgroups_of_an_eigen_update_decide_alike():
     for at in comparisons:
         conditions = enclosing(body, at) + [re.split(r"[;{}]", body[:at])[-1]]
         assert not any(re.search(r"blockIdx|first_row|lead", c) for c in conditions), conditions
+
+
+def test_deferred_count_is_read_before_the_ticket():
+    """The last workgroup of an instance clears the number of deferred patches, by which every wavefront of every workgroup chooses
+    its way: a workgroup takes its ticket only behind a barrier that all of its wavefronts reach with the number in hand."""
+    text = dict(sources())["kernels.h"]
+    start = text.index("void finish_apply_kernel")
+    read, ticket = text.index("*a.deferred_count()", start), text.index("a.ticket()", start)
+    assert read < text.index("if (n_deferred > 0)", start) < text.index("__syncthreads();", text.index("if (n_deferred > 0)", start)) < ticket
