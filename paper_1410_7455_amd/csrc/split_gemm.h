@@ -464,7 +464,8 @@ __global__ __launch_bounds__((WGM * WGN * WGK + PW) * 64) void split_gemm_kernel
 #pragma unroll
     for (int w = 0; w < CW; ++w) sum += mc_part[w];
     const double change = alpha_f64 * sum;
-    const double scale = change > 0.0 ? fmin(1.0, P.mc_bound * reciprocal_f64(change)) : 1.0;
+    const double inverse = change < 1.0e300 ? reciprocal_f64(change) : 0.0;   // (its steps make a NaN of an infinity)
+    const double scale = change > 0.0 ? fmin(1.0, P.mc_bound * inverse) : 1.0;
     if (unit == P.tile_begin && tid == 0) *P.mc_out = scale;
     alpha_f64 *= scale;
   }

@@ -64,6 +64,31 @@ def test_maximum_change(ngsgd, n, din, hidden, classes):
             assert rel(gpu.get_params(l).cpu().numpy(), ora.W[l]) < TOL, l
 
 
+def test_maximum_change_of_rows_beyond_fp32_squares(ngsgd):
+    """Rows whose squares sum to infinity in fp32: the change stays limited, here to nothing.  The large input has no weight, so the
+    layer's outputs and derivatives are ordinary."""
+    import torch
+    n, dims = 70, [8, 40, 9]
+    rng = np.random.default_rng(9700)
+    weights = random_weights(rng, dims)
+    weights[0][:, 2] = 0.0
+    x = rng.standard_normal((n, dims[0])).astype(np.float32)
+    x[:, 2] = 1.0e20
+    y = rng.integers(0, dims[2], n).astype(np.int32)
+    for limit in (0.0, 0.1):   # without and with
+        gpu = ngsgd.Network(dims, [workloads.TANH], n, rank_in=0, rank_out=0, max_change_per_sample=limit)
+        for l, w in enumerate(weights):
+            gpu.set_params(l, torch.from_numpy(w).cuda())
+        gpu.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.5)
+        got = gpu.get_params(0).cpu().numpy()
+        if limit == 0.0:
+            assert np.abs(got[:, 2]).max() > 1.0e18
+        else:
+            assert float(gpu.last_max_change_scale(0).item()) == 0.0
+            assert np.array_equal(got, weights[0])
+            assert 0.0 < float(gpu.last_max_change_scale(1).item()) <= 1.0
+
+
 # two rows to a workgroup; rows longer than it keeps in registers (5120), a last piece of one to three columns, a single row
 @pytest.mark.parametrize("N,D,R", [(1, 5, 1), (2, 1025, 3), (3, 5119, 2), (65, 5121, 20), (66, 6002, 33), (129, 10243, 20)])
 def test_scaled_rows(ngsgd, N, D, R):
