@@ -411,11 +411,15 @@ struct FinishArgs {
   int ldw, ldh, R, chunk_cols;
   // what the fused apply kernel accumulated into, H and the arrival counters: cleared here, so that the
   // next call without a factor update needs no clearing launch in front of it
-  int* arrive;               // [n_arrive], then the ticket below and the number of deferred patches
+  int* arrive;               // [n_arrive], then kFinishSlots numbers that are zero on entry, but for the last one, and on exit:
   int n_arrive;              // 0: not behind the fused apply kernel
-  __device__ int* ticket() const { return arrive + n_arrive; }   // zero on entry and exit: the last workgroup to have read the count clears it
-  __device__ int* deferred_count() const { return arrive + n_arrive + 1; }
+  __device__ int* ticket() const { return arrive + n_arrive; }         // workgroups that are done with their deferred patches
+  __device__ int* ready() const { return arrive + n_arrive + 1; }      // not 0: gamma is known
+  __device__ int* claim() const { return arrive + n_arrive + 2; }      // rows handed out for scaling, by workgroup shares
+  __device__ int* left() const { return arrive + n_arrive + 3; }       // workgroups that use none of these any more
+  __device__ int* deferred_count() const { return arrive + n_arrive + 4; }
 };
+constexpr int kFinishSlots = 5;
 struct FinishGroup {
   int count;
   FinishArgs a[kMaxInstances];
@@ -435,12 +439,20 @@ __device__ __forceinline__ void block256_sum_pair(double& x, double& y, double* 
   y = (red[4] + red[5]) + (red[6] + red[7]);
 }
 
-// The deferred patches, then everything for the whole instance, by one workgroup: plain dot products over the rank, 16 threads
-// per row (this path is rare and small).
+// The way where patches were deferred, of all workgroups of an instance.  They take the patches in turn (plain dot products over
+// the rank, 16 threads per row); the one with the last ticket finds all done, forms the sums and gamma and hands out the rows to be
+// scaled and the rows of H to be cleared, to itself and to those of the last tickets, which wait for it for a bounded time (nothing
+// depends on them).  512 x 5000 rank 80, all patches deferred: 0.41 ms a call (by one workgroup
+// 84; the patches by one of 1024 threads and the scaling by a launch of its own 27).
+constexpr int kFinishRows = 64, kFinishScaleRows = 2;   // rows of a workgroup, without and with the scaling
+constexpr int kFinishHelpers = 512;            // two per compute unit
+constexpr long long kFinishWait = 100000;      // 1 ms at the clock's 100 MHz
 template <bool SCALE>
-__device__ __forceinline__ void finish_deferred(const FinishArgs& a, const int n_deferred, double* red) {
+__device__ __forceinline__ void finish_deferred(const FinishArgs& a, const int n_deferred, const int groups, double* red) {
+  constexpr int ROWS = SCALE ? kFinishScaleRows : kFinishRows, WIDTH = 256 / ROWS;
+  __shared__ int s_at;
   const int tid = threadIdx.x, sub = tid & 15;
-  for (int e = 0; e < n_deferred; ++e) {
+  for (int e = blockIdx.x; e < n_deferred; e += groups) {
     const int id = a.deferred[e];
     const int rb = id / a.n_col_tiles, chunk = id % a.n_col_tiles;
     const int c_end = min(a.D, (chunk + 1) * a.chunk_cols);
@@ -464,38 +476,77 @@ __device__ __forceinline__ void finish_deferred(const FinishArgs& a, const int n
       if (r < a.N && sub == 0) const_cast<float*>(a.rownorm_part)[(size_t)chunk * a.N + r] = sq;
     }
   }
-  __threadfence();
-  __syncthreads();   // what was written above is read below by other lanes
-  double t = 0.0, ph = 0.0;
-  for (int i = tid; i < a.n_sumsq; i += 256) t += a.sumsq_part[i];
-  for (int r = tid; r < a.N; r += 256) {
-    double p = 0.0;
-    for (int c = 0; c < a.n_col_tiles; ++c) p += (double)a.rownorm_part[(size_t)c * a.N + r];
-    a.prow[r] = p;
-    ph += p;
+  __threadfence();   // on all dies before the ticket
+  __syncthreads();   // and every wavefront has the deferred count
+  if (tid == 0) s_at = __hip_atomic_fetch_add(a.ticket(), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int before = s_at;
+  bool ready = before == groups - 1;
+  if (ready) {
+    __threadfence();   // (what this die holds of the others' patches)
+    double t = 0.0, ph = 0.0;
+    for (int i = tid; i < a.n_sumsq; i += 256) t += a.sumsq_part[i];
+    for (int r = tid; r < a.N; r += 256) {
+      double p = 0.0;
+      for (int c = 0; c < a.n_col_tiles; ++c) p += (double)a.rownorm_part[(size_t)c * a.N + r];
+      a.prow[r] = p;
+      ph += p;
+    }
+    block256_sum_pair(t, ph, red);
+    const double gamma = ph > 0.0 ? sqrt(t / ph) : 1.0;
+    for (int r = tid; r < a.N && a.rownorm2_out != nullptr; r += 256) a.rownorm2_out[r] = (float)(gamma * gamma * a.prow[r]);   // (its own rows)
+    if (tid == 0) {
+      a.st->gamma = gamma;
+      a.st->tr_M = t;
+      a.st->tr_Mhat = ph;
+      if (a.gamma_out != nullptr) *a.gamma_out = (float)gamma;
+    }
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) __hip_atomic_store(a.ready(), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else if (before >= groups - 1 - kFinishHelpers) {   // (uniform)
+    __syncthreads();
+    if (tid == 0) {
+      const long long t0 = wall_clock64();
+      int seen = 0;
+      while ((seen = __hip_atomic_load(a.ready(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0 && wall_clock64() - t0 < kFinishWait)
+        __builtin_amdgcn_s_sleep(16);
+      s_at = seen;
+    }
+    __syncthreads();
+    ready = s_at != 0;
+    __threadfence();
   }
-  block256_sum_pair(t, ph, red);
-  const double gamma = ph > 0.0 ? sqrt(t / ph) : 1.0;
-  for (int r = tid; r < a.N && a.rownorm2_out != nullptr; r += 256) a.rownorm2_out[r] = (float)(gamma * gamma * a.prow[r]);   // (its own rows)
-  if (tid == 0) {
-    a.st->gamma = gamma;
-    a.st->tr_M = t;
-    a.st->tr_Mhat = ph;
-    if (a.gamma_out != nullptr) *a.gamma_out = (float)gamma;
+  while (ready) {
+    __syncthreads();
+    if (tid == 0) s_at = __hip_atomic_fetch_add(a.claim(), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_at >= groups) break;
+    const int row0 = s_at * ROWS, row = row0 + tid / WIDTH;
+    if (SCALE && row < a.N) {
+      const float s = (float)__hip_atomic_load(&a.st->gamma, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      float* const x = a.X + (size_t)row * a.ldx;
+      for (int c = tid % WIDTH; c < a.D >> 2; c += WIDTH) {
+        float4 v = reinterpret_cast<const float4*>(x)[c];
+        v.x *= s; v.y *= s; v.z *= s; v.w *= s;
+        reinterpret_cast<float4*>(x)[c] = v;
+      }
+      for (int c = (a.D & ~3) + tid % WIDTH; c < a.D; c += WIDTH) x[c] *= s;
+    }
+    float4* const h = reinterpret_cast<float4*>(a.H + (size_t)row0 * a.ldh);
+    for (int i = tid; i < min(ROWS, a.N - row0) * a.ldh / 4; i += 256) h[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  if (SCALE) {
-    for (int r = 0; r < a.N; ++r)
-      for (int c = tid; c < a.D; c += 256) a.X[(size_t)r * a.ldx + c] *= (float)gamma;
-  }
-  for (int i = tid; i < a.N * a.ldh; i += 256) a.H[i] = 0.f;
-  for (int i = tid; i < a.n_arrive; i += 256) a.arrive[i] = 0;
+  __syncthreads();
+  if (tid == 0) s_at = __hip_atomic_fetch_add(a.left(), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (s_at == groups - 1)
+    for (int i = tid; i < a.n_arrive + kFinishSlots; i += 256) __hip_atomic_store(a.arrive + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Grid (ceil(N / ROWS), instance), 256 threads: every workgroup sums the tiles' partial sums for itself (a few hundred numbers) and
 // takes ROWS rows.  Bound: the latency of loads from memory that no cache of
 // the workgroup's die holds yet.  With one workgroup per instance, which summed the row norms for the traces and cleared H, and a
 // launch of its own for the scaling: 512 x 5000 10.1 + 7.9 us, 512 x 3001 7.8 + 4.9.
-constexpr int kFinishRows = 64, kFinishScaleRows = 2;
 template <bool SCALE>
 __global__ __launch_bounds__(256) void finish_apply_kernel(const FinishGroup g) {
   constexpr int ROWS = SCALE ? kFinishScaleRows : kFinishRows;
@@ -531,16 +582,8 @@ __global__ __launch_bounds__(256) void finish_apply_kernel(const FinishGroup g) 
       for (int u = 0; u < 8; ++u) part[u & 1] += c + STEP * u < a.n_col_tiles ? v[u] : 0.f;
     }
   }
-  if (n_deferred > 0) {   // (the same for all wavefronts of the instance: each has read the count before its workgroup takes a ticket)
-    __shared__ int s_last;
-    __syncthreads();
-    if (tid == 0) s_last = __hip_atomic_fetch_add(a.ticket(), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == groups - 1 ? 1 : 0;
-    __syncthreads();
-    if (s_last != 0 && tid == 0) {   // everyone has read the count
-      *a.deferred_count() = 0;
-      *a.ticket() = 0;
-    }
-    if (blockIdx.x == 0) finish_deferred<SCALE>(a, n_deferred, red);
+  if (n_deferred > 0) {   // (the same for all wavefronts of the instance: it is cleared when all workgroups have left)
+    finish_deferred<SCALE>(a, n_deferred, groups, red);
     return;
   }
   double p = (double)part[0] + (double)part[1];

@@ -158,8 +158,8 @@ struct ngsgd_precond {
   int clean_rows = 0;             // the counters and this many rows of H are known to be clear (left so by the
                                   // finishing kernel of a call that went through the fused apply kernel)
   size_t zero_floats_all = 0;
-  size_t arrive_slots = 0;        // arrival counters of the fused apply kernel, one per block of 64 rows, and (last
-  int* arrive = nullptr;          // two slots) the finishing kernel's ticket, the number of deferred patches; padded to 256 bytes
+  size_t arrive_slots = 0;        // arrival counters of the fused apply kernel, one per block of 64 rows, and (last five
+  int* arrive = nullptr;          // slots) the finishing kernel's, of which the last is the number of deferred patches; padded to 256 bytes
   int* deferred = nullptr;        // list of deferred patches
   float* H = nullptr;
   float* J = nullptr;
@@ -200,7 +200,7 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.prow = c.take<double>(NB);
   if (R == 0) return;
   const size_t h_floats = (size_t)NB * p.ldh, kl_floats = (size_t)4 * R * R;   // ldh is a multiple of 16
-  p.arrive_slots = align_up((size_t)(NB + kFusedRows - 1) / kFusedRows + 2, 64);
+  p.arrive_slots = align_up((size_t)(NB + kFusedRows - 1) / kFusedRows + kFinishSlots, 64);
   p.zero_floats_all = p.arrive_slots + h_floats + kl_floats;
   p.zero_region = c.take<float>(p.zero_floats_all);
   if (p.zero_region) {
@@ -709,7 +709,7 @@ inline int fused_row_blocks(int N) { return (N + kFusedRows - 1) / kFusedRows; }
 
 // Whether the fused kernel's bookkeeping has room for this call (partial sums of tr(X X^T) per patch).
 inline bool fused_fits(const ngsgd_precond& p, int N) {
-  return fused_chunks(p.dim) * fused_row_blocks(N) <= kSumsqMax && (size_t)fused_row_blocks(N) + 1 < p.arrive_slots;
+  return fused_chunks(p.dim) * fused_row_blocks(N) <= kSumsqMax && (size_t)fused_row_blocks(N) + kFinishSlots <= p.arrive_slots;
 }
 
 // Columns of a patch in a launch of `units` patches of 64 x 160 and rank class rc.  Every patch adds its part of H to memory by
@@ -876,7 +876,7 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
       a.R = p.rank;
       a.chunk_cols = p.fused_columns;
       a.arrive = p.arrive;
-      a.n_arrive = fused ? (int)p.arrive_slots - 2 : 0;
+      a.n_arrive = fused ? (int)p.arrive_slots - kFinishSlots : 0;
       n_max = std::max(n_max, c.N);
     }
     if (scale_output) {

@@ -115,3 +115,28 @@ def test_wide_patches_match_oracle(ngsgd, N, D, R):
             assert rel(rn_g, rn_o) < 2e-4
     finally:
         ngsgd.set_wait_limit_us(2000)
+
+
+def test_deferred_patches_are_shared_by_the_workgroups(ngsgd):
+    """A call that leaves all of its patches to the finishing kernel: 0.4 ms for 512 x 5000 with all of the chip, 84 when one
+    workgroup is left to do it."""
+    import torch
+    N, D, R = 512, 5000, 80
+    rng = np.random.default_rng(7700)
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, update_period=1000, always_update_first=1)
+    M = data(rng, N, D)
+    gpu_call(torch, pre, M, ld=D)
+    buf, gamma, rn2 = torch.from_numpy(M).cuda().contiguous(), torch.zeros(1, device="cuda"), torch.zeros(N, device="cuda")
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    ngsgd.set_wait_limit_us(0)
+    try:
+        times = []
+        for _ in range(5):
+            start.record()
+            pre.precondition(buf, gamma, rn2)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+    finally:
+        ngsgd.set_wait_limit_us(2000)
+    assert min(times) < 5.0, times

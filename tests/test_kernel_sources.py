@@ -132,6 +132,7 @@ def test_deferred_count_is_read_before_the_ticket():
     """The last workgroup of an instance clears the number of deferred patches, by which every wavefront of every workgroup chooses
     its way: a workgroup takes its ticket only behind a barrier that all of its wavefronts reach with the number in hand."""
     text = dict(sources())["kernels.h"]
-    start = text.index("void finish_apply_kernel")
-    read, ticket = text.index("*a.deferred_count()", start), text.index("a.ticket()", start)
-    assert read < text.index("if (n_deferred > 0)", start) < text.index("__syncthreads();", text.index("if (n_deferred > 0)", start)) < ticket
+    kernel = text[text.index("void finish_apply_kernel"):]
+    assert "a.deferred_count()" in kernel[:kernel.index("finish_deferred<SCALE>")] and "a.ticket()" not in kernel
+    way = text[text.index("void finish_deferred"):text.index("void finish_apply_kernel")]
+    assert way.index("__syncthreads();") < way.index("a.ticket()") < way.index("a.left()") < way.index("a.arrive + i, 0")
