@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void simple_sweep_kernel(const SimpleGroup g, 
     tx = ty + over;
     if (ty <= (int)blockIdx.y) return;   // uniform per workgroup, as all of these
   }
-  if (k >= nblk || 2 * (int)blockIdx.y >= tiles + 1) return;
+  if (k >= nblk || 2 * (int)blockIdx.y >= tiles) return;
   if (ahead && (blockIdx.y != 0 || k + 1 >= nblk)) return;
   if (!ahead && tx >= tiles) return;
   constexpr int B = kSimpleBlock, LD = B + 2;   // rows 4 banks apart: an operand's read takes each bank once

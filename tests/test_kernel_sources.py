@@ -136,3 +136,30 @@ def test_deferred_count_is_read_before_the_ticket():
     assert "a.deferred_count()" in kernel[:kernel.index("finish_deferred<SCALE>")] and "a.ticket()" not in kernel
     way = text[text.index("void finish_deferred"):text.index("void finish_apply_kernel")]
     assert way.index("__syncthreads();") < way.index("a.ticket()") < way.index("a.left()") < way.index("a.arrive + i, 0")
+
+
+def test_every_tile_of_the_elimination_has_one_workgroup():
+    """simple_sweep_kernel deals the tiles on and above the diagonal to a grid that is made for the largest matrix of its group: with
+    the kernel's own rules every tile of a smaller one is met once too."""
+    text = dict(sources())["simple_ng.h"]
+    body = text[text.index("void simple_sweep_kernel"):]
+    body = body[:body.index("__shared__")]
+    rules = ["int ty = blockIdx.y, tx = ty + (int)blockIdx.x - 1;", "const int over = tx - tiles;", "ty = tiles - 1 - ty;", "tx = ty + over;",
+             "if (ty <= (int)blockIdx.y) return;", "if (!ahead && tx >= tiles) return;"]
+    assert all(r in body for r in rules)
+    dropped = re.search(r"if \(k >= nblk \|\| (.*)\) return;", body).group(1).replace("(int)blockIdx.y", "y")
+    for largest in range(1, 18):
+        for tiles in range(1, largest + 1):
+            met = []
+            for y in range((largest + 1) // 2):
+                for x in range(1, largest + 2):
+                    ty, tx = y, y + x - 1
+                    if tx >= tiles:
+                        over, ty = tx - tiles, tiles - 1 - ty
+                        tx = ty + over
+                        if ty <= y:
+                            continue
+                    if eval(dropped, {"__builtins__": {}}, dict(y=y, tiles=tiles)) or tx >= tiles:
+                        continue
+                    met.append((ty, tx))
+            assert sorted(met) == [(i, j) for i in range(tiles) for j in range(i, tiles)], (largest, tiles)
