@@ -712,13 +712,28 @@ inline bool fused_fits(const ngsgd_precond& p, int N) {
   return fused_chunks(p.dim) * fused_row_blocks(N) <= kSumsqMax && (size_t)fused_row_blocks(N) + kFinishSlots <= p.arrive_slots;
 }
 
-// Columns of a patch in a launch of `units` patches of 64 x 160 and rank class rc.  Every patch adds its part of H to memory by
+// Columns of a patch in the launch of calls list[done .. done + n).  Every patch adds its part of H to memory by
 // float atomics, and workgroups that run at the same time wait for the slowest of these: wide patches need half as many, but
-// are fewer and have two wavefronts per SIMD instead of three.  160 / 320 columns, rank 80: ten matrices of a p-norm network (952
-// patches) 65 / 77 us; of a tanh network with 1024 rows and 2048 columns (above 2000) 283 / 178; one matrix of 512 x 5000 (256) 36 / 45,
-// 2048 x 5000 (1024) 111 / 78.
-constexpr int kFusedWideUnits = 1023;   // at least four per compute unit
-inline int fused_columns(int units, int rc) { return rc > 32 && units > kFusedWideUnits ? kFusedWide : kFusedChunk; }
+// are fewer and have two wavefronts per SIMD instead of three.  They are taken from four narrow patches per compute unit on, if
+// that takes work off the busiest die (a chunk of columns has one die, and few chunks leave dies idle).  160 / 320 columns, rank
+// 80: p-norm network with 512 rows (952 narrow patches) 64 / 78 us, 576 (1071) 82 / 83, 640 (1190) 90 / 89, 700 (1309) 108 / 92, 1024
+// (1904) 167 / 125; tanh network of 2048 with 1024 rows (3344) 268 / 178; one matrix of 512 x 5000 (256) 24 / 33, 2048 x 5000
+// (1024) 88 / 59, 8192 x 1280 (1024, four wide chunks for eight dies) 69 / 93.
+constexpr int kFusedWideUnits = 1023;
+int busiest_die(const std::vector<PrecondCall>& list, size_t done, int n, int columns) {
+  int load[kXcds] = {}, chunk = 0;
+  for (int i = 0; i < n; ++i) {
+    const PrecondCall& c = list[done + i];
+    for (int k = fused_chunks(c.p->dim, columns); k > 0; --k) load[chunk++ % kXcds] += fused_row_blocks(c.N);
+  }
+  return *std::max_element(load, load + kXcds);
+}
+int fused_columns(const std::vector<PrecondCall>& list, size_t done, int n, int rc) {
+  int units = 0;
+  for (int i = 0; i < n; ++i) units += fused_row_blocks(list[done + i].N) * fused_chunks(list[done + i].p->dim);
+  if (rc <= 32 || units <= kFusedWideUnits) return kFusedChunk;
+  return 4 * busiest_die(list, done, n, kFusedWide) <= 3 * busiest_die(list, done, n, kFusedChunk) ? kFusedWide : kFusedChunk;
+}
 
 template <int RC>
 void launch_fused(const FusedGroup& g, int columns, hipStream_t s) {
@@ -738,15 +753,9 @@ int launch_fused_apply(std::vector<PrecondCall>& list, hipStream_t s) {
     const int n = (int)std::min<size_t>(kMaxInstances, list.size() - done);
     g.count = n;
     g.spin_limit = g_fused_wait_us.load() * 100;
-    int units = 0, rc = 0;
-    for (int i = 0; i < n; ++i) {
-      const PrecondCall& c = list[done + i];
-      units += fused_row_blocks(c.N) * fused_chunks(c.p->dim);
-      rc = std::max(rc, c.p->ldh);
-    }
-    const int columns = fused_columns(units, rc);
-    units = 0;
-    int chunks = 0;
+    int units = 0, chunks = 0, rc = 0;
+    for (int i = 0; i < n; ++i) rc = std::max(rc, list[done + i].p->ldh);
+    const int columns = fused_columns(list, done, n, rc);
     for (int i = 0; i < n; ++i) {
       const PrecondCall& c = list[done + i];
       ngsgd_precond& p = *c.p;

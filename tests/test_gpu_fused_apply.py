@@ -90,10 +90,10 @@ def test_c2_full_size_without_update(ngsgd, which):
         assert rel(rn_g, rn_o) < 2e-4
 
 
-# wide patches: 1024 patches of 64 x 160 (ceil(N / 64) * ceil(D / 160)), the fewest for them and the most of one matrix.  The
-# last patch of 320 columns has 161 (two pieces of 64 and 33), all, four pieces and one column, 201, and of the only patch two and
-# one; the last row block one row, all, a few
-WIDE = [(8129, 1121, 80), (8192, 1280, 33), (4033, 2497, 41), (1990, 5001, 96), (65473, 129, 81)]
+# 1024 patches of 64 x 160 (ceil(N / 64) * ceil(D / 160)), the fewest for wide ones and the most of one matrix.  Four of these go
+# wide: the last patch of 320 columns has four pieces of 64 and one column, 201 columns, 161 (two pieces and 33), all; the last row
+# block one row, a few, all.  The others would leave dies idle and stay narrow.
+WIDE = [(8129, 1121, 80), (8192, 1280, 33), (4033, 2497, 41), (1990, 5001, 96), (65473, 129, 81), (4096, 2401, 80), (4090, 2560, 33)]
 
 
 @pytest.mark.parametrize("N,D,R", WIDE)

@@ -163,3 +163,23 @@ def test_every_tile_of_the_elimination_has_one_workgroup():
                         continue
                     met.append((ty, tx))
             assert sorted(met) == [(i, j) for i in range(tiles) for j in range(i, tiles)], (largest, tiles)
+
+
+def test_wide_patches_leave_no_dies_idle():
+    """The fused apply kernel's patches of 320 columns: four narrow ones per compute unit, and a busiest die with at most three
+    quarters of the work.  The shapes of their test that are meant to take them do."""
+    from test_gpu_fused_apply import WIDE
+    text = dict(sources())["ngsgd.hip"]
+    number = {n: int(re.search(n + r" = (\d+);", " ".join(t for _, t in sources())).group(1))
+              for n in ("kFusedWideUnits", "kFusedChunk", "kFusedWide", "kFusedRows", "kXcds")}
+    assert "return 4 * busiest_die(list, done, n, kFusedWide) <= 3 * busiest_die(list, done, n, kFusedChunk) ? kFusedWide : kFusedChunk;" in text
+
+    def busiest(n, d, columns):   # of one matrix
+        load = [0] * number["kXcds"]
+        for c in range(-(-d // columns)):
+            load[c % number["kXcds"]] += -(-n // number["kFusedRows"])
+        return max(load)
+
+    wide = {(n, d, r): r > 32 and -(-n // number["kFusedRows"]) * -(-d // number["kFusedChunk"]) > number["kFusedWideUnits"] and
+            4 * busiest(n, d, number["kFusedWide"]) <= 3 * busiest(n, d, number["kFusedChunk"]) for n, d, r in WIDE + [(2048, 5000, 80), (512, 5000, 80)]}
+    assert [k for k in wide if wide[k]] == [(4033, 2497, 41), (1990, 5001, 96), (4096, 2401, 80), (4090, 2560, 33), (2048, 5000, 80)]
