@@ -100,6 +100,16 @@ struct ProfScope {
   }
 };
 
+// A group whose work another group's kernel does: no events, time or count, but its place among the groups that are kept between
+// reads, so that a program that reads every so many steps meets the limit where it did.
+void prof_place() {
+  if (!g_prof.on) return;
+  if (g_prof.used + 2 > kProfMaxEvents)
+    g_prof.dropped += 1;
+  else
+    g_prof.used += 2;
+}
+
 constexpr int kSumsqMax = 1024;   // partial sums of squares per preconditioner call
 constexpr int kWideRow = 2048;    // rows at least this wide get 512-thread workgroups in the row-wise kernels
 constexpr int kTargetBlocks = 512;
@@ -986,7 +996,7 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
     }
     g.count = n;
     ProfScope prof(NGSGD_PROF_PRECOND_SMALL, s);
-    { ProfScope counted(NGSGD_PROF_PRECOND_SMALL, s); }   // (an update counts two groups of this category, whatever it launches)
+    prof_place();   // (the eigenvectors' group)
     if (r_max <= kEigSmallRank) {
       using Shape = DirectShape<kEigSmallRank / 16>;
       hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true>), dim3(n), dim3(kEigSmallThreads), 2 * Shape::T * Shape::STRIDE * sizeof(double), s, g);
@@ -1739,8 +1749,10 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
       NG_TRY(launch_layer_gemms(GEMM_FWD, &g, 1, s));
     }
     if (l == nl - 1) continue;
-    ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);   // (tanh: an empty bracket, a step counts the same groups per category whatever is fused)
-    if (L.nonlin == NGSGD_PNORM) {
+    if (L.nonlin == NGSGD_TANH) {
+      prof_place();
+    } else {
+      ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);
       ngsgd_layer& Nx = Ls[l + 1];
       if (L.dout >= kWideRow) {
         hipLaunchKernelGGL(pnorm_forward_kernel<512>, dim3(N), dim3(512), 0, s, L.A, L.lda, Nx.Xin, Nx.ldx,
@@ -1826,21 +1838,22 @@ extern "C" int ngsgd_step(ngsgd_net* net, const float* dev_x, const int32_t* dev
       ProfScope prof(NGSGD_PROF_GEMM_BWD, s);
       NG_TRY(launch_layer_gemms(GEMM_BWD, &g, 1, s, &n_slabs));
     }
-    ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);
     if (whole) {
-    } else if (P.nonlin == NGSGD_TANH) {
-      hipLaunchKernelGGL(tanh_backward_kernel, dim3((P.dout + 1023) / 1024, N), dim3(256), 0, s, net->dX, net->lddx,
-                         n_slabs, slab, L.Xin, L.ldx, P.A, P.lda, N, P.dout);
+      prof_place();
     } else {
-      if (P.dout >= kWideRow) {
+      ProfScope prof(NGSGD_PROF_ELEMENTWISE, s);
+      if (P.nonlin == NGSGD_TANH) {
+        hipLaunchKernelGGL(tanh_backward_kernel, dim3((P.dout + 1023) / 1024, N), dim3(256), 0, s, net->dX, net->lddx,
+                           n_slabs, slab, L.Xin, L.ldx, P.A, P.lda, N, P.dout);
+      } else if (P.dout >= kWideRow) {
         hipLaunchKernelGGL(pnorm_backward_kernel<512>, dim3(N), dim3(512), 0, s, net->dX, net->lddx, n_slabs, slab,
                            L.Xin, L.ldx, P.sigma, P.A, P.lda, N, P.groups, net->pnorm_group, net->renorm);
       } else {
         hipLaunchKernelGGL(pnorm_backward_kernel<256>, dim3(N), dim3(256), 0, s, net->dX, net->lddx, n_slabs, slab,
                            L.Xin, L.ldx, P.sigma, P.A, P.lda, N, P.groups, net->pnorm_group, net->renorm);
       }
+      LAUNCH_CHECK();
     }
-    LAUNCH_CHECK();
     // the derivatives of layer l - 1 exist now: start the group of which it is the lowest layer
     for (int k = 0; k < kSideStreams; ++k)
       if (ready_layer[k] == l - 1) NG_TRY(early_start(k));

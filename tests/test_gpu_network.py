@@ -290,6 +290,26 @@ def test_kernel_group_timing(ngsgd):
     torch.cuda.synchronize()
 
 
+def test_kernel_groups_are_counted_where_something_is_launched(ngsgd):
+    """Tanh and its derivative are formed by the layer products, an update up to rank 32 by one kernel: no group of their own."""
+    import torch
+    spec = workloads.c0_tiny()
+    _, gpu = make_pair(ngsgd, spec)
+    x, y = workloads.minibatch(spec, 0)
+    x, y = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    for _ in range(12):
+        gpu.step(x, y, spec.lr)
+    ngsgd.profile_enable(True)
+    for _ in range(4):                       # one update period
+        gpu.step(x, y, spec.lr)
+    gpu.join()
+    prof = ngsgd.profile_read()
+    ngsgd.profile_enable(False)
+    assert prof["elementwise"][1] == 4 * 2   # the features' copy, log-softmax
+    assert prof["precond_small"][1] == 1
+    torch.cuda.synchronize()
+
+
 def test_average_replicas(ngsgd):
     """Sec. 3.1: every replica ends with the arithmetic mean; preconditioners restart as new processes do."""
     import torch
