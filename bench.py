@@ -182,7 +182,7 @@ def run_step_bench(args):
     always_first = 10                    # App. B.4: the factors are updated on each of the first 10 minibatches
     net = ng.Network(spec.dims, spec.nonlin, n, spec.pnorm_group, spec.rank_in, spec.rank_out, spec.alpha,
                      spec.num_samples_history, spec.epsilon, spec.update_period, renorm=True,
-                     max_change_per_sample=0.075, side_streams=2)   # one network alone on its GPU (one stream: 2 - 4 % slower)
+                     max_change_per_sample=0.075)   # one side stream (two: 2 - 3 % slower)
     for l, w in enumerate(workloads.initial_weights(spec)):
         net.set_params(l, torch.from_numpy(w).cuda())
     # Untimed: at least --warmup steps, and whatever it takes to leave the start-up phase of the schedule (state

@@ -124,26 +124,16 @@ inline int rank_class(int rank) { return rank <= 32 ? 32 : (rank <= 80 ? 80 : 96
 // and all layer inputs after the forward pass, the other derivatives as the backward pass produces them), so that
 // each group's products H, J and its R x R work start as early as possible.
 constexpr int kSideStreams = 3;          // most
-// Without the caller's choice: one stream, or two (the last layer's derivatives and the layer inputs; the other
-// derivatives after the backward pass).  The second one takes the early group out of the chain that the next step waits
-// for, and costs a dozen launches and some events per update, and longer gaps on every queue.  It pays where that chain is
-// long (a large rank), most of the factors are in the early group's way (layers) and the products of a step do not cover the
-// chain anyway.  Products grow with rows x parameters, the chain about with the rank's third power; where their ratio is
-// small two streams are the better choice whatever the data.  Time per step with two over that with one, rank 64 to 96,
-// fresh minibatches:
-//   5 to 8 layers, ratio up to 4400: 0.93 - 1.00, and 1.01 and 1.02 once (42 networks, 0.975 on average);
-//   ratio above: by the sweeps that the eigen-updates take.  5 x 3000 (300) with 512 rows, rank 80: 0.96 - 0.98 at a learning
-//   rate of 0.01 (8 to 10 sweeps), 1.00 - 1.01 at 0.002 (6 or 7), and 1.06 with three such networks in the process, which
-//   share four hardware queues; 6 layers 0.98 - 0.99 and 1.04; tanh layers of 1000 and 2000: 0.99 - 1.06;
-//   3 and 4 layers: 0.95 - 1.02.  Ranks 24 to 60: 0.99 - 1.08 with 5 or 6 layers, 1.02 - 1.25 with 3.
+// Without the caller's choice one stream.  A second one (the last layer's derivatives and the layer inputs; the other
+// derivatives after the backward pass) takes the early group out of the chain that the next step waits for, and costs a dozen
+// launches and some events per update, and longer gaps on every queue.  Time per step with two over that with one, fresh
+// minibatches: rank 64 to 96 and 5 to 8 layers 0.96 - 1.08 (49 networks, 1.025 on
+// average), 3 and 4 layers 1.00 - 1.07 (18, 1.03), rank 24 to 60 1.03 - 1.09 (23, 1.06); the
+// speech-shaped network 1.03 (0.369 - 0.373 ms with one, 0.380 with two).  Seven narrow networks of rank 81 to 93, most with
+// thousands of classes, were better off with two, by 0.3 to 4 %.
 // A third stream, which starts the upper hidden layers' derivatives in the middle of the backward pass, measured 1 - 2 %
 // slower than two on the speech-shaped network.
-constexpr int kTwoStreamsFromRank = 64, kTwoStreamsFromLayers = 5;
-constexpr double kTwoStreamsMostRatio = 4400.0;   // rows x parameters / rank^3
-inline int default_side_streams(const int rank, const int n_layers, const double rows_by_params) {
-  const double chain = (double)rank * rank * rank;
-  return rank >= kTwoStreamsFromRank && n_layers >= kTwoStreamsFromLayers && rows_by_params <= kTwoStreamsMostRatio * chain ? 2 : 1;
-}
+constexpr int kDefaultSideStreams = 1;
 struct SideSync {
   hipStream_t stream = nullptr;
   hipEvent_t inputs_ready = nullptr;   // recorded on the caller's stream: the group's matrices exist
@@ -1573,9 +1563,7 @@ void net_layout(ngsgd_net& net, const ngsgd_config* cfg, Carver& c) {
     din = L.groups;
   }
   net.n_params_padded = n_params;
-  net.n_side = cfg->side_streams > 0 ? cfg->side_streams
-                                     : default_side_streams(std::max(cfg->rank_in, cfg->rank_out), cfg->n_layers,
-                                                            (double)cfg->max_batch * (double)n_params);
+  net.n_side = cfg->side_streams > 0 ? cfg->side_streams : kDefaultSideStreams;
   net.params = c.take<float>(n_params);
   size_t off = 0;
   for (auto& L : net.layers) {
