@@ -12,7 +12,7 @@ SOURCES = [os.path.join(HERE, "csrc", "ngsgd.hip")]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
-    # packed fp32 instructions are kept off on the test machines
+    # no packed fp32 instructions: some of their forms have given wrong results on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-result",
 ]

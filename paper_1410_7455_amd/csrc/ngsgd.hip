@@ -1190,8 +1190,7 @@ int simple_many(const std::vector<SimpleCall>& calls, bool scale_output, hipStre
       const unsigned blocks = (unsigned)std::min<size_t>((fill_max + 2047) / 2048, 256);
       hipLaunchKernelGGL(fill_zero_group_kernel, dim3(blocks > 0 ? blocks : 1, cnt), dim3(256), 0, s, fg);
       LAUNCH_CHECK();
-      // the Gram matrix is symmetric: only the tiles on and above the diagonal are computed, the kernel that forms G
-      // mirrors them
+      // the Gram matrix is symmetric: only the tiles on and above the diagonal are computed, and the elimination keeps to those
       std::vector<GemmDesc> rows, cols;
       for (int i = 0; i < cnt; ++i) {
         const SimpleArgs& a = g.a[i];

@@ -1,7 +1,7 @@
 // The R x R part of the online natural-gradient update, entirely on the device (App. B.3, B.3.1).
 //
 // Z_t is formed from K_t and L_t (eq. zt:compute) and its eigenpairs come from the direct method of eig_direct.h, in one
-// kernel up to rank 32 and in three above (reduction, a workgroup per instance; eigenpairs, sixteen per workgroup; the rest).
+// kernel up to rank 32 and in three above (reduction, a workgroup per instance; eigenpairs, four per workgroup; the rest).
 // The finishing kernel floors the eigenvalues and produces rho_{t+1}, D_{t+1}, E_{t+1} and A_t (eq. wt1).  Where the direct
 // method's checks fail it runs cyclic Jacobi first: only Z is rotated, its upper triangle in LDS in "position space"
 // (Brent-Luk: the members of pair k stand at positions 2k and 2k+1, and a fixed permutation between rounds brings the
