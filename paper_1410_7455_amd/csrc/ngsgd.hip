@@ -181,8 +181,7 @@ struct ngsgd_precond {
   InitGroup* init_group = nullptr;   // device copy of the instance list of an initialisation this instance leads
   int* idx = nullptr;
   double* vwork = nullptr;
-  double2* rotlog = nullptr;      // scratch of a factor update's eigen-problem: Jacobi's rotation log,
-  double* direct = nullptr;       // what the kernels of the direct method hand on
+  double* direct = nullptr;       // scratch of a factor update's eigen-problem
   bool owned_by_net = false;
   SideSync* sync = nullptr;   // set for instances of a network
   int last_N = 0;             // rows of the latest call
@@ -226,12 +225,7 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.init_group = c.take<InitGroup>(1);
   p.idx = c.take<int>(kMaxRank);
   p.vwork = c.take<double>((size_t)kMaxRank + D);
-  {
-    const int m = (R + 1) & ~1;
-    const size_t rounds = ((size_t)kMaxSweeps * (m - 1) + 31) / 32 * 32;
-    p.rotlog = c.take<double2>((rounds + kEigLogPad) * (m / 2));
-    p.direct = c.take<double>(direct_scratch_doubles(R));
-  }
+  p.direct = c.take<double>(direct_scratch_doubles(R));
 }
 
 int precond_check_config(int dim, int rank, int max_batch, float alpha, float S, float eps, int period, int first) {
@@ -979,7 +973,7 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
       SmallArgs& a = g.a[i];
       a.st = p.st; a.K = p.K; a.L = p.L; a.At = p.At; a.ldat = p.ldh;
       a.R = p.rank; a.D = p.dim; a.N = p.last_N;
-      a.rotlog = p.rotlog; a.direct = p.direct;
+      a.direct = p.direct;
       a.sumsq_part = p.sumsq_part;
       a.n_sumsq = p.n_sumsq;
       r_max = std::max(r_max, p.rank);

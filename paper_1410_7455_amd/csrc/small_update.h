@@ -5,8 +5,8 @@
 // The finishing kernel floors the eigenvalues and produces rho_{t+1}, D_{t+1}, E_{t+1} and A_t (eq. wt1).  Where the direct
 // method's checks fail it runs cyclic Jacobi first: only Z is rotated, its upper triangle in LDS in "position space"
 // (Brent-Luk: the members of pair k stand at positions 2k and 2k+1, and a fixed permutation between rounds brings the
-// next partners together), in two copies used alternately, so a round costs one barrier; every rotation is written to
-// a log, which is replayed on the rows of the identity.
+// next partners together), in two copies used alternately, so a round costs one barrier; the eigenvectors' rows go through
+// the rotations in registers.
 // orth_fix_kernel: the orthogonality check of App. B.3.1 and, when it fails, the Cholesky fix folded into A_t.
 #pragma once
 
@@ -28,9 +28,7 @@ constexpr int kEigReduceThreads = 256;
 constexpr int kEigSmallRank = 32;
 constexpr int kEigSmallThreads = 512;
 constexpr int kMaxSweeps = 20;
-constexpr int kEigLogPad = 32;               // rounds that the log has room for beyond the last
 constexpr int kMaxHalf = kMaxRank / 2;
-constexpr int kMaxRounds = kMaxSweeps * (kMaxRank - 1);
 constexpr double kJacobiTol = 1.0e-13;       // a pair is left alone once |z_pq| <= tol * sqrt(z_pp z_qq)
 constexpr double kJacobiAbsTol = 1.0e-13;    // ... or once |z_pq| <= this * max_i z_ii (rounding noise level)
 constexpr double kJacobiLargeTol = 1.0e-6;   // a sweep without a rotated entry above this (same measure) ...
@@ -38,7 +36,7 @@ constexpr double kJacobiLargeAbs = 1.0e3;    // ... and above this many absolute
 constexpr double kOrthoCondLimit = 1.0e6;    // App. B.3.1
 constexpr double kOrthoTolerance = 1.0e-3;   // App. B.3.1
 
-constexpr size_t direct_scratch_doubles(const int R) { return (size_t)R * (2 * kMaxRank + 7) + 1; }
+constexpr size_t direct_scratch_doubles(const int R) { return (size_t)R * (2 * kMaxRank + 7) + 2; }
 struct SmallArgs {
   PrecondScalars* st;
   double* K;         // R x R, J J^T; cleared on exit (the orthogonality check accumulates W W^T into it)
@@ -48,8 +46,8 @@ struct SmallArgs {
   int R, D, N;
   const double* sumsq_part;   // partial sums of tr(X X^T) left by the H product
   int n_sumsq;
-  double2* rotlog;   // [kMaxRounds][half] (c, s) of every pair of every round of Jacobi
-  // What the kernels of the direct method hand on: R rows of `ldv` doubles of reflections and of eigenvectors, seven vectors, rho_t.
+  // What the kernels of the direct method hand on: R rows of `ldv` doubles of reflections and of eigenvectors, seven vectors, rho_t; and
+  // how many workgroups have left K alone.
   double* direct;
   __device__ double* V() const { return direct; }
   __device__ double* U(const int ldv) const { return direct + (size_t)R * ldv; }
@@ -61,6 +59,7 @@ struct SmallArgs {
   __device__ double* residual(const int ldv) const { return vec(ldv, 4); }
   __device__ double* order(const int ldv) const { return vec(ldv, 5); }
   __device__ double* d_rho(const int ldv) const { return vec(ldv, 6); }   // diag(D_t), then rho_t
+  __device__ int* k_tickets(const int ldv) const { return reinterpret_cast<int*>(d_rho(ldv) + R + 1); }
 };
 struct SmallGroup {
   int count;
@@ -174,13 +173,82 @@ __device__ __forceinline__ double z_entry(const UpdateFactors& f, const int i, c
   return i == j ? fma(f.cd * s_dr[i], s_dr[i], z) : z;
 }
 
-// Eigenvalues of Z_t by cyclic Jacobi (upper triangle in position space, two LDS copies used alternately); every rotation is
-// logged.  A round: the first wavefront computes the next round's rotations from the old copy while the others rotate
+// Whole shifts by one lane through the DPP path of the vector ALU (no LDS traffic), of a wavefront or of each of its rows of 16
+// lanes: lane i receives the value of lane i-1 (up) or i+1 (down); the lane without a source receives zero.
+template <int CTRL>
+__device__ __forceinline__ double shift_lane(const double x) {
+  int lo = __double2loint(x), hi = __double2hiint(x);
+  lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, true);
+  hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// Rows of U_t that go through Jacobi's rotations with the matrix.  U <- U J only mixes two columns, so rows are independent: a
+// wavefront has one, with K = 2 (ranks up to 32) one in each of its rows of 16 lanes, and keeps it in registers.  Lane k holds the
+// two columns that pair k rotates; between rounds the columns move to the neighbouring lanes exactly as the players of the
+// round-robin schedule do (the first lane's second player never moves).  All wavefronts but the first, whose rotations bound a
+// round, take rows in turn.
+// (With the rotations in a log in memory, replayed by the first workgroup alone, it took longer than the iteration: 881 us a call of
+// 512 x 1000 at rank 80 with equal eigenvalues, now 629.)
+template <int K, int NT>
+struct JacobiRows {
+  static constexpr int PER_WAVE = K == 2 ? 4 : 1, LANES = 64 / PER_WAVE, SHARE = (NT / 64 - 1) * PER_WAVE;
+  static constexpr int COUNT = K == 2 ? 16 * K : 16;           // rows of a workgroup
+  static constexpr int SETS = (COUNT + SHARE - 1) / SHARE;
+  double top[SETS], bot[SETS];
+  __device__ __forceinline__ static int lane() { return (threadIdx.x & 63) % LANES; }
+  __device__ __forceinline__ static int first_of(const int set) { return ((int)(threadIdx.x >> 6) - 1) * PER_WAVE + set * SHARE; }   // uniform
+  __device__ __forceinline__ static bool has(const int set) { return threadIdx.x >= 64 && first_of(set) < COUNT; }
+  __device__ __forceinline__ static int row(const int set) { return first_of(set) + (threadIdx.x & 63) / LANES; }   // of the workgroup's
+  __device__ __forceinline__ void start(const int first_row, const int m) {
+#pragma unroll
+    for (int q = 0; q < SETS; ++q) {   // players of round 0: first k, second m-1-k (lane 0: the fixed player m-1)
+      const int i = first_row + row(q), k = lane();
+      top[q] = k < m / 2 && k == i ? 1.0 : 0.0;
+      bot[q] = k < m / 2 && m - 1 - k == i ? 1.0 : 0.0;
+    }
+  }
+  // cs: this round's rotations.  Lanes beyond the last pair repeat it on zeros: nothing of theirs reaches another (a lane takes from
+  // its lower neighbour, and the last active lane takes its own second member).
+  __device__ __forceinline__ void rotate(const double2* cs_of, const int half) {
+    const int k = lane();
+    const double2 cs = cs_of[min(k, half - 1)];
+    const bool last_lane = k == half - 1, lane0 = k == 0, lane1 = k == 1, single = half == 1;   // one pair: nothing moves
+#pragma unroll
+    for (int q = 0; q < SETS; ++q) {
+      if (!has(q)) continue;   // uniform
+      const double t = top[q] * cs.x - bot[q] * cs.y, b = top[q] * cs.y + bot[q] * cs.x;
+      // firsts move one lane down (the last lane takes its own second), seconds one lane up (lane 1 takes lane 0's first)
+      const double t_down = shift_lane<PER_WAVE == 1 ? 0x130 : 0x101>(t);
+      const double b_up = shift_lane<PER_WAVE == 1 ? 0x138 : 0x111>(b);
+      const double t_up = shift_lane<PER_WAVE == 1 ? 0x138 : 0x111>(t);
+      top[q] = last_lane ? (single ? t : b) : t_down;
+      bot[q] = lane0 ? b : (lane1 ? t_up : b_up);
+    }
+  }
+  // As columns of A_t (eq. wt1), after `rounds` rounds.
+  __device__ __forceinline__ void store(const SmallArgs& a, const int first_row, const int m, const int rounds, const int* s_rank, const double* s_col,
+                                        const double* s_ise) const {
+    const int k = lane(), R = a.R;
+    if (k >= m / 2) return;
+    const int tp = player_at(2 * k, rounds, m), bp = player_at(2 * k + 1, rounds, m);
+#pragma unroll
+    for (int q = 0; q < SETS; ++q) {
+      const int j = first_row + row(q);
+      if (!has(q) || row(q) >= COUNT || j >= R) continue;
+      if (tp < R) a.At[(size_t)s_rank[tp] * a.ldat + j] = (float)(s_col[s_rank[tp]] * top[q] * s_ise[j]);
+      if (bp < R) a.At[(size_t)s_rank[bp] * a.ldat + j] = (float)(s_col[s_rank[bp]] * bot[q] * s_ise[j]);
+    }
+  }
+};
+
+// Eigenvalues of Z_t by cyclic Jacobi (upper triangle in position space, two LDS copies used alternately), `rows` with them.
+// A round: the first wavefront computes the next round's rotations from the old copy while the others rotate
 // the 2x2 blocks into their next positions in the other copy | barrier.
-// On return s_c[i] is the eigenvalue that player i carries.  All threads of the workgroup.
-template <int ITEMS, int NT>
+// On return s_c[i] is the eigenvalue that player i carries; K and L have been read.  All threads of the workgroup.
+template <int ITEMS, int NT, typename ROWS>
 __device__ __forceinline__ void jacobi_eigenvalues(const SmallArgs& a, const UpdateFactors& f, const double* s_ise, const double* s_dr, double* dyn,
-                                                   double* scratch, double2 (*s_cs)[kMaxHalf], int* s_rotated, double* s_c, int& sweeps_out,
+                                                   double* scratch, double2 (*s_cs)[kMaxHalf], int* s_rotated, double* s_c, ROWS& rows, int& sweeps_out,
                                                    int& rounds_out, bool& converged_out) {
   const int R = a.R, tid = threadIdx.x;
   constexpr int nt = NT;
@@ -279,7 +347,6 @@ __device__ __forceinline__ void jacobi_eigenvalues(const SmallArgs& a, const Upd
     rz_da = slot(pa, pa);
     rz_db = slot(pb, pb);
   }
-  double2* __restrict__ rotlog = a.rotlog;   // (what the direct method left there has been read)
   if (tid < 64) __builtin_amdgcn_s_setprio(3);   // the rotation wave's dependent chain bounds the round
   if (tid < 2) s_rotated[tid] = 0;
   __syncthreads();
@@ -290,7 +357,6 @@ __device__ __forceinline__ void jacobi_eigenvalues(const SmallArgs& a, const Upd
     if (!(odd_pad && rot_k == 0)) jacobi_rotation(dyn[t], dyn[3 * np + t], dyn[np + t], abs_tol2, c, s, large);
     if (large) s_rotated[0] = 1;
     s_cs[0][rot_k] = make_double2(c, s);
-    rotlog[rot_k] = make_double2(c, s);
   }
   __syncthreads();
 
@@ -323,7 +389,6 @@ __device__ __forceinline__ void jacobi_eigenvalues(const SmallArgs& a, const Upd
           if (large) s_rotated[(sweeps + (r == m - 2 ? 1 : 0)) & 1] = 1;
         }
         s_cs[cur ^ 1][rot_k] = make_double2(c, s);
-        rotlog[(size_t)(rounds + 1) * half + rot_k] = make_double2(c, s);
       }
       if (diag_lane) {   // this round's rotation of pair diag_k, applied to its diagonal block
         const double2 csk = cs[diag_k];
@@ -348,6 +413,7 @@ __device__ __forceinline__ void jacobi_eigenvalues(const SmallArgs& a, const Upd
         dyn[no + dst[it][2]] = y10 * cj - y11 * sj;
         dyn[no + dst[it][3]] = y10 * sj + y11 * cj;
       }
+      rows.rotate(cs, half);
       __syncthreads();
     }
     if (s_rotated[sweeps & 1] == 0) converged = true;   // same value for every thread: read after the barrier
@@ -364,86 +430,6 @@ __device__ __forceinline__ void jacobi_eigenvalues(const SmallArgs& a, const Upd
   sweeps_out = sweeps;
   rounds_out = rounds;
   converged_out = converged;
-}
-
-// Whole-wavefront shifts by one lane through the DPP path of the vector ALU (no LDS traffic): lane i receives the
-// value of lane i-1 (up) or i+1 (down); the lane without a source receives zero.
-__device__ __forceinline__ double wave_shift_up(double x) {
-  int lo = __double2loint(x), hi = __double2hiint(x);
-  lo = __builtin_amdgcn_update_dpp(0, lo, 0x138, 0xf, 0xf, true);   // wave_shr:1
-  hi = __builtin_amdgcn_update_dpp(0, hi, 0x138, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_shift_down(double x) {
-  int lo = __double2loint(x), hi = __double2hiint(x);
-  lo = __builtin_amdgcn_update_dpp(0, lo, 0x130, 0xf, 0xf, true);   // wave_shl:1
-  hi = __builtin_amdgcn_update_dpp(0, hi, 0x130, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-
-// U_t by replaying the rotation log on rows of the identity, written as A_t (eq. wt1).  U <- U J only mixes two
-// columns, so rows are independent: a wavefront owns ROWS rows and keeps them in registers.  Lane k holds the two
-// columns that pair k rotates; between rounds the columns move to the neighbouring lanes exactly as the players
-// of the round-robin schedule do (the first lane's second player never moves).
-template <int ROWS, int NT>
-__device__ __forceinline__ void replay_rotations(const SmallArgs& a, const int n_rounds, const int* s_rank, const double* s_col, const double* s_ise) {
-  const int R = a.R;
-  const int m = (R + 1) & ~1, half = m / 2;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int NW = NT / 64;
-  const bool active = lane < half;
-  // Lanes beyond the last pair replay the last pair's rotations on zeros: nothing of theirs reaches an active
-  // lane (a lane takes from its lower neighbour, and the last active lane takes its own second member).
-  const double2* lg = a.rotlog + (active ? lane : half - 1);
-  // players held by this lane in round 0: first k, second m-1-k (lane 0: the fixed player m-1)
-  double top[ROWS], bot[ROWS];
-#pragma unroll
-  for (int q = 0; q < ROWS; ++q) {
-    top[q] = active && lane == wave + NW * q ? 1.0 : 0.0;
-    bot[q] = active && m - 1 - lane == wave + NW * q ? 1.0 : 0.0;
-  }
-  const bool last_lane = lane == half - 1, lane0 = lane == 0, lane1 = lane == 1;
-  const bool single = m == 2;   // one pair: nothing moves
-  auto replay = [&](const double2 cs) {
-#pragma unroll
-    for (int q = 0; q < ROWS; ++q) {
-      // the logged rotation acts on (first, second) of the pair
-      const double nt_ = top[q] * cs.x - bot[q] * cs.y, nb_ = top[q] * cs.y + bot[q] * cs.x;
-      // players move: firsts shift one lane down (the last lane takes its own second), seconds shift one lane
-      // up (lane 1 takes lane 0's first); lane 0's second is fixed.  With a single pair (m = 2) lane 0 is the
-      // last lane as well and both members stay.
-      const double t_dn = wave_shift_down(nt_);
-      const double b_up = wave_shift_up(nb_);
-      const double t_up = wave_shift_up(nt_);
-      top[q] = last_lane ? (single ? nt_ : nb_) : t_dn;
-      bot[q] = lane0 ? nb_ : (lane1 ? t_up : b_up);
-    }
-  };
-  constexpr int AHEAD = 8;   // rounds requested ahead; the log is longer than the last round by more than that
-  double2 cs[AHEAD];
-#pragma unroll
-  for (int u = 0; u < AHEAD; ++u) cs[u] = lg[u * half];
-  for (int rr = 0; rr < n_rounds; rr += AHEAD) {
-    double2 next[AHEAD];
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) next[u] = lg[(size_t)(rr + AHEAD + u) * half];
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) {
-      if (rr + u < n_rounds) replay(cs[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) cs[u] = next[u];
-  }
-  if (!active) return;
-  // the players standing at this lane's two positions after n_rounds rounds
-  const int tp = player_at(2 * lane, n_rounds, m), bp = player_at(2 * lane + 1, n_rounds, m);
-#pragma unroll
-  for (int q = 0; q < ROWS; ++q) {
-    const int j = wave + NW * q;   // row of U = column of A_t
-    if (j >= R) continue;
-    if (tp < R) a.At[(size_t)s_rank[tp] * a.ldat + j] = (float)(s_col[s_rank[tp]] * top[q] * s_ise[j]);
-    if (bp < R) a.At[(size_t)s_rank[bp] * a.ldat + j] = (float)(s_col[s_rank[bp]] * bot[q] * s_ise[j]);
-  }
 }
 
 // Z_t in the registers of NT threads (see eig_direct.h), all elements of K_t and L_t requested together.
@@ -529,6 +515,7 @@ __global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const Sma
   const UpdateFactors f = update_factors(a, g, a.st->d, rho, s_ise, s_dr, T);
   // handed on: the last kernel's workgroups cannot read what one of them replaces
   for (int i = tid; i <= R; i += NT) a.d_rho(T)[i] = i < R ? a.st->d[i] : rho;
+  if (tid == 0) *a.k_tickets(T) = 0;
   typename DirectTile<K, NT>::Regs S;
   load.ordered(a, f, s_ise, s_dr, S, s_diag, s_order);
   direct_reduce<K, NT>(S, R, lds, s_V, s_tau, s_off);
@@ -749,13 +736,19 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
     bad |= !(lambda <= largest && smallest > 0.0 && largest <= kDirectCondLimit * smallest);
   }
   const bool direct = __syncthreads_or(bad ? 1 : 0) == 0;   // (M is complete behind it)
-  if (!direct && !lead) return;
 
+  // Jacobi: all workgroups of the instance find the same rotations, each takes its rows of U through them, and the last to have read K
+  // clears it.
   int sweeps = 1, rounds = 0;
-  bool converged = true;
+  bool converged = true, clears = lead;
+  JacobiRows<K, NT> rows;
   if (!direct) {
-    jacobi_eigenvalues<ITEMS, NT>(a, f, s_ise, s_dr, dyn, scratch, s_cs, s_rotated, s_c, sweeps, rounds, converged);
+    rows.start(first_row, (R + 1) & ~1);
+    jacobi_eigenvalues<ITEMS, NT>(a, f, s_ise, s_dr, dyn, scratch, s_cs, s_rotated, s_c, rows, sweeps, rounds, converged);
+    if (!FUSED && tid == 0)
+      s_rotated[0] = __hip_atomic_fetch_add(a.k_tickets(T), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (R + 15) / 16 - 1 ? 1 : 0;
     __syncthreads();
+    if (!FUSED) clears = s_rotated[0] != 0;
   }
 
   // Every wavefront handles all eigenvalues, two per lane.  Floor (after eq. zt:eig:repeat), decreasing order:
@@ -852,10 +845,9 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
       }
     }
   } else {
-    __threadfence_block();   // the log
-    replay_rotations<(T + NW - 1) / NW, NT>(a, rounds, s_rank, s_col, s_ise);
+    rows.store(a, first_row, (R + 1) & ~1, rounds, s_rank, s_col, s_ise);
   }
-  if (lead)
+  if (clears)
     for (int idx = tid; idx < R * R; idx += NT) a.K[idx] = 0.0;
 }
 
