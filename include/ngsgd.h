@@ -89,15 +89,18 @@ typedef struct {
   float max_change_per_sample;    /* App. C.3; 0 disables the limit (paper: 0.075)     */
   int32_t method;                 /* NGSGD_METHOD_ONLINE (App. B) or _SIMPLE (App. A)  */
   float simple_epsilon;           /* floor on tr(X^T X) in beta, App. A.2 (1e-20)      */
-  int32_t side_streams;           /* internal streams for the factor updates: 0 = the
-                                   * default (one), else 1..3.  One: all updates
-                                   * start after the backward pass; two: the last layer's
-                                   * derivatives and the layer inputs start after the
-                                   * forward pass, the other derivatives after the backward
-                                   * pass (up to 4 % shorter for some narrow networks with
-                                   * many classes and a rank above 80, alone on their GPU,
-                                   * mostly 2 to 6 % longer); three start the upper hidden
-                                   * layers in the middle of the backward pass             */
+  int32_t side_streams;           /* internal streams for the factor updates: 0 = chosen
+                                   * by the layers, the ranks and the classes (1 or 2), else
+                                   * 1..3.  One: all updates start after the backward pass;
+                                   * two: the last layer's derivatives and the layer inputs
+                                   * start after the forward pass, the other derivatives
+                                   * after the backward pass (2 % shorter for deep networks
+                                   * with a rank above 80 and ten times as many classes as
+                                   * units in a layer, mostly 2 to 6 % longer for others);
+                                   * three start the upper hidden layers in the middle of
+                                   * the backward pass.  One is better when
+                                   * many networks share the GPU, which has few hardware
+                                   * queues per process                                    */
 } ngsgd_config;
 
 /* ---- one preconditioner instance (App. B) ------------------------------------------------- */

@@ -124,16 +124,25 @@ inline int rank_class(int rank) { return rank <= 32 ? 32 : (rank <= 80 ? 80 : 96
 // and all layer inputs after the forward pass, the other derivatives as the backward pass produces them), so that
 // each group's products H, J and its R x R work start as early as possible.
 constexpr int kSideStreams = 3;          // most
-// Without the caller's choice one stream.  A second one (the last layer's derivatives and the layer inputs; the other
-// derivatives after the backward pass) takes the early group out of the chain that the next step waits for, and costs a dozen
-// launches and some events per update, and longer gaps on every queue.  Time per step with two over that with one, fresh
-// minibatches: rank 64 to 96 and 5 to 8 layers 0.96 - 1.08 (49 networks, 1.025 on
-// average), 3 and 4 layers 1.00 - 1.07 (18, 1.03), rank 24 to 60 1.03 - 1.09 (23, 1.06); the
-// speech-shaped network 1.03 (0.369 - 0.373 ms with one, 0.380 with two).  Seven narrow networks of rank 81 to 93, most with
-// thousands of classes, were better off with two, by 0.3 to 4 %.
+// Without the caller's choice one stream, or two (the last layer's derivatives and the layer inputs; the other
+// derivatives after the backward pass).  The second one takes the early group out of the chain that the next step waits
+// for, and costs a dozen launches and some events per update, and longer gaps on every queue.  It pays where the chain is long
+// (ranks above 80, see the tiles of the update) and the early group is most of it: many layers and a last one much wider than the
+// others.  Time per step with two over that with one, 180 networks on fresh minibatches:
+//   rank above 80, five layers or more, ten times as many classes as the widest hidden layer has outputs or more: 0.979
+//   on average (29 networks, 0.92 - 1.03), five to ten times as many 0.996 (12), fewer 1.016 (22), fewer layers 1.005 (17);
+//   rank 64 to 80: 1.030 (82, 0.97 - 1.08), 1.017 with that many layers and classes (24); rank 24 to 60: 1.065 (23);
+//   the speech-shaped network (rank 80) 1.03: 0.369 - 0.373 ms with one, 0.380 with two.
 // A third stream, which starts the upper hidden layers' derivatives in the middle of the backward pass, measured 1 - 2 %
 // slower than two on the speech-shaped network.
-constexpr int kDefaultSideStreams = 1;
+constexpr int kTwoStreamsAboveRank = 80, kTwoStreamsFromLayers = 5, kTwoStreamsClasses = 10;
+inline int default_side_streams(const ngsgd_config& cfg) {
+  const int widest = *std::max_element(cfg.dims + 1, cfg.dims + std::max(cfg.n_layers, 2));
+  return std::max(cfg.rank_in, cfg.rank_out) > kTwoStreamsAboveRank && cfg.n_layers >= kTwoStreamsFromLayers &&
+                 cfg.dims[cfg.n_layers] / kTwoStreamsClasses >= widest
+             ? 2
+             : 1;
+}
 struct SideSync {
   hipStream_t stream = nullptr;
   hipEvent_t inputs_ready = nullptr;   // recorded on the caller's stream: the group's matrices exist
@@ -1556,7 +1565,7 @@ void net_layout(ngsgd_net& net, const ngsgd_config* cfg, Carver& c) {
     din = L.groups;
   }
   net.n_params_padded = n_params;
-  net.n_side = cfg->side_streams > 0 ? cfg->side_streams : kDefaultSideStreams;
+  net.n_side = cfg->side_streams > 0 ? cfg->side_streams : default_side_streams(*cfg);
   net.params = c.take<float>(n_params);
   size_t off = 0;
   for (auto& L : net.layers) {
