@@ -8,7 +8,7 @@
 // the same matrices in a random order 2e-5 and 6e-4.)
 // Its chain has R columns of one barrier and a dozen serial runs of R steps; cyclic Jacobi, which it replaces, goes through
 // R - 1 dependent rounds per sweep and 5 to 10 sweeps.  Factors of 512 x 5000 and 512 x 3001 matrices, fresh data: rank 80 273 us (six
-// sweeps 243, the vectors 30), now 119 (reduction 75, eigenpairs 30, finish 14); rank 20 50, now 35.
+// sweeps 243, the vectors 30), now 121 (reduction 75, eigenpairs 30, finish 15); rank 20 50, now 35.
 // Where the eigenvalues span more than kDirectCondLimit, where a vector's residual is large or where the vectors are too far
 // from orthogonal (eigenvalues that agree to working precision), the finishing kernel runs Jacobi instead.
 #pragma once
