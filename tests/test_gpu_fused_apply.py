@@ -140,3 +140,49 @@ def test_deferred_patches_are_shared_by_the_workgroups(ngsgd):
     finally:
         ngsgd.set_wait_limit_us(2000)
     assert min(times) < 5.0, times
+
+
+@pytest.mark.parametrize("N,D,R", [(300, 1000, 33), (65, 161, 5)])
+def test_captured_call_that_leaves_patches_over(ngsgd, N, D, R):
+    """A captured call whose patches are all deferred, replayed between eager calls that defer none and some that do."""
+    import torch
+    rng = np.random.default_rng(7800 + N)
+    kw = dict(max_batch=N, num_samples_history=600.0, update_period=1 << 30, always_update_first=1)
+    plain, captured = ngsgd.Preconditioner(D, R, **kw), ngsgd.Preconditioner(D, R, **kw)
+    ld = D + (-D) % 4
+    static, gamma, rn2 = torch.zeros(N, ld, device="cuda"), torch.zeros(1, device="cuda"), torch.zeros(N, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+
+    def matrix():
+        return torch.nn.functional.pad(torch.from_numpy(np.ascontiguousarray(data(rng, N, D))), (0, ld - D)).cuda()
+
+    def both(replay, wait_us=2000):
+        m = matrix()
+        static.copy_(m)
+        plain.precondition(m[:, :D])
+        if replay:
+            graph.replay()
+        else:
+            ngsgd.set_wait_limit_us(wait_us)
+            captured.precondition(static[:, :D], gamma, rn2)
+            ngsgd.set_wait_limit_us(2000)
+        torch.cuda.synchronize()
+        want, got = m[:, :D].cpu().numpy(), static[:, :D].cpu().numpy()
+        assert rel(got, want) < 1e-5
+        # squared row norms of what came out: fp32 sums of squares, 1e-5 covers them
+        assert rel(rn2.cpu().numpy(), (got.astype(np.float64) ** 2).sum(1)) < 1e-5
+
+    try:
+        m = matrix()                 # the update, the same for both
+        static.copy_(m)
+        plain.precondition(m[:, :D])
+        captured.precondition(static[:, :D], gamma, rn2)
+        both(False)
+        ngsgd.set_wait_limit_us(0)
+        with torch.cuda.graph(graph):
+            captured.precondition(static[:, :D], gamma, rn2)
+        ngsgd.set_wait_limit_us(2000)
+        for replay, wait_us in ((True, 0), (True, 0), (False, 2000), (True, 0), (False, 0), (False, 2000), (True, 0)):
+            both(replay, wait_us)
+    finally:
+        ngsgd.set_wait_limit_us(2000)

@@ -419,3 +419,14 @@ def test_small_pnorm_net_with_two_side_streams(ngsgd):
     spec = workloads.small_pnorm()
     ora, gpu = make_pair(ngsgd, spec, renorm=True, max_change=0.075, side_streams=2)
     run_and_compare(ngsgd, spec, ora, gpu, 16)
+
+
+def test_small_pnorm_net_that_leaves_patches_over(ngsgd):
+    """The steps without an update leave all patches of all instances to the finishing kernel."""
+    spec = workloads.small_pnorm()
+    ora, gpu = make_pair(ngsgd, spec, renorm=True, max_change=0.075)
+    ngsgd.set_wait_limit_us(0)
+    try:
+        run_and_compare(ngsgd, spec, ora, gpu, 16)
+    finally:
+        ngsgd.set_wait_limit_us(2000)
