@@ -3,22 +3,25 @@
 //
 // The eigenproblem is solved on the smaller of the D x D covariance and the N x N Gram matrix (same
 // non-zero spectrum; an eigenvector u of the Gram matrix gives X_0^T u / sqrt(N lambda)), in fp64 throughout:
-//   1. Householder reduction to a tridiagonal matrix, Q^T A Q = T: one launch per column, each a pass over the
-//      trailing matrix by many workgroups; the last 160 columns in one launch with the matrix in registers;
+//   1. Householder reduction to a tridiagonal matrix, Q^T A Q = T: up to 1024 rows one launch of many workgroups that keep the
+//      matrix in registers and exchange vectors (above, a launch per column, each a pass over the trailing matrix);
+//      the last 160 columns by one workgroup with the matrix in registers;
 //   2. the R largest eigenvalues of T by multisection with Sturm counts, a wavefront each;
 //   3. their eigenvectors by inverse iteration from random vectors, a thread each, then orthonormalised together
 //      (twice, through the inverse Cholesky factor of their Gram matrix): vectors of equal eigenvalues start out
 //      independent and any orthonormal basis of their space serves;
 //   4. back with the reflections, a vector per wavefront.
-// The error is a few eps |A| whatever the spectrum.  Bound: the chain of n - 160 launches.  Ten instances of the
-// speech-shaped network, five of them with n = 512: 3.6 ms, of it 352 launches of 14 us (reading and writing 2 MB per
-// instance) falling to 6 us (latency), the last 160 columns 0.38 ms, eigenvalues 0.14, inverse iteration 0.27,
+// The error is a few eps |A| whatever the spectrum.  Bound: the chain of n columns.  Ten instances of the
+// speech-shaped network, five of them with n = 512: 2.3 ms, of it 352 columns 0.73 (a launch each, 14 us for reading and writing 2 MB per
+// instance, falling to 6 us: 2.6), the last 160 columns 0.38 ms, eigenvalues 0.14, inverse iteration 0.27,
 // orthonormalisation 0.2, back transformation 0.28, rows of W 0.11.  A reduction needs no iteration; block Jacobi took
 // 11 to 18 sweeps of 32 launches and did not settle on softmax derivatives within them (12.8 ms).
 // This runs once per process (and after each parameter-averaging round), never inside the steady-state step.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "gemm.h"
 #include "kernels.h"
@@ -57,6 +60,10 @@ struct InitArgs {
   __device__ double* off() const { return T + np; }
   __device__ double* tau() const { return T + 2 * np; }          // the reflections' factors
   __device__ double* y(const int parity) const { return T + (3 + parity) * (size_t)np; }   // A v of the last two columns
+  // Rows kept on the chip: what column j leaves for the next, A v and the next row, four columns in turn (before sdiag and bounds
+  // are there), the count of workgroups that are running and their dies
+  __device__ double* ring(const int j) const { return T + (3 + 2 * (j & 3)) * (size_t)np; }
+  __device__ int* gate() const { return idx; }
   __device__ double* bounds() const { return T + 5 * (size_t)np; }   // interval that holds T's eigenvalues, largest magnitude in it
   __device__ double* sdiag() const { return T + 6 * (size_t)np; }    // T scaled to unit norm: diagonal, squared off-diagonal
   __device__ double* soff2() const { return T + 7 * (size_t)np; }
@@ -76,11 +83,18 @@ __global__ void init_store_group_kernel(const InitGroup g, InitGroup* __restrict
   for (int i = threadIdx.x; i < (int)(sizeof(InitGroup) / sizeof(uint32_t)); i += blockDim.x) out[i] = src[i];
 }
 
-// The Gram product fills the 64 x 64 tiles on and above the diagonal; this copies them below it.
-// Grid (np/32, np/32, instance), 256 threads.
+constexpr uint64_t kRingEmpty = 0x7ff8dead00c0ffeeULL;   // a NaN that no product leaves (of fp32 operands the low 29 bits are zero)
+
+// The Gram product fills the 64 x 64 tiles on and above the diagonal; this copies them below it.  The first workgroup empties the
+// ring and the gate.  Grid (np/32, np/32, instance), 256 threads.
 __global__ __launch_bounds__(256) void init_mirror_kernel(const InitGroup* __restrict__ gp) {
   const InitArgs& a = gp->a[blockIdx.z];
   const int np = a.np, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+  if (blockIdx.x == 0 && blockIdx.y == 0) {
+    uint64_t* const ring = reinterpret_cast<uint64_t*>(a.ring(0));
+    for (int i = threadIdx.x; i < 8 * np; i += 256) ring[i] = kRingEmpty;
+    if (threadIdx.x < 2) a.gate()[threadIdx.x] = 0;
+  }
   if (i0 >= np || j0 >= np || i0 / kSymGramTile <= j0 / kSymGramTile) return;
   __shared__ double t[32][33];
   const int c = threadIdx.x & 31, r = threadIdx.x >> 5;
@@ -219,6 +233,294 @@ __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __r
   }
 }
 
+// The same columns in one launch: every workgroup keeps its rows in registers (CH 64-column chunks, ROWS rows per wavefront) and the
+// workgroups of an instance exchange A v and the next row, element i of both from the workgroup of row i, through memory.
+// The data are their own signal: a slot is empty (kRingEmpty) until its element is there, and the readers look at the slots themselves.
+// Behind the one barrier of a column every wavefront forms w, the row and its reflection for itself; the product with the row
+// does not wait for the reflection (A v = scale A x + column j + 1).
+// A slot is emptied by its writer two columns later (all of the instance have then read it: the elements of the column between were
+// sent behind that) and written again two columns after that; the wait for the counter of memory operations between makes the
+// emptying visible before the writer's next elements, which a reader of the new ones has seen.
+// Where all of an instance run on one die (matrices of up to 512 rows are dealt to the dies, workgroup b to die b mod 8; the workgroups tell each
+// other where they are before they start) ordinary stores do, which a reader behind the same L2 cache sees after 0.25 us; otherwise
+// stores at device scope, 0.6 to 0.8 us.
+// Progress: a workgroup first waits until all of its instance are running, for at most `limit` ticks.  If they are not, one closes the gate,
+// all leave, and the kernel behind reduces the matrix alone, as if a wait inside takes longer than kTriLost.  The matrix in memory
+// stays as it was until then; the last 160 rows and columns go to the same places of V.
+// Bound: the exchange and the chain of two sums over a wavefront.  One instance of 512 rows 2.07 us a column, ten alike (dealt to the dies; all
+// with stores at device scope 3.9 us in the first version, 3.35 one alone); 1024 rows 3.1 us.
+constexpr int kTriResident = 1024;                    // largest padded size
+constexpr int kTriDies = 8, kTriDieUnits = 2 * 32;    // workgroups of a die: two per compute unit
+constexpr int kTriResidentUnits = kTriDies * kTriDieUnits;
+constexpr long long kTriLost = 100000000;             // ticks (10 ns)
+constexpr int kGateClosed = 1 << 30;
+constexpr bool tri_on_one_die(const int np) { return np <= 512; }
+constexpr int tri_resident_rows(const int np) { return np <= 512 ? 16 : 8; }   // rows of a workgroup
+__host__ __device__ inline int tri_resident_units(const int n, const int rows) { return n > kTriTail ? (n + rows - 1) / rows : 0; }
+
+// 0: not all are; 2: all on one die; 1 otherwise.
+__device__ __forceinline__ int init_all_running(int* const gate, const int units, const long long limit) {
+  const int die = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID
+  const int others = __hip_atomic_fetch_or(gate + 1, 1 << die, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("" : : "v"(others) : "memory");   // it has been performed
+  int seen = __hip_atomic_fetch_add(gate, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+  const long long t0 = wall_clock64();
+  while (seen < units) {
+    if (wall_clock64() - t0 >= limit) {   // closes the gate unless the last one came meanwhile
+      if (__hip_atomic_compare_exchange_strong(gate, &seen, seen | kGateClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        return 0;
+      continue;
+    }
+    __builtin_amdgcn_s_sleep(16);
+    seen = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (seen >= kGateClosed) return 0;
+  const int dies = __hip_atomic_load(gate + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return (dies & (dies - 1)) == 0 ? 2 : 1;
+}
+__device__ __forceinline__ void ring_store(uint64_t* const p, const uint64_t v, const bool near) {
+  if (near)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int CH, int ROWS>
+__global__ __launch_bounds__(256, 2) void init_tri_resident_kernel(const InitGroup* __restrict__ gp, const int first, const int count,
+                                                                   const long long limit) {
+  constexpr int C = 64 * CH, T = CH / 4;
+  constexpr bool kDeal = tri_on_one_die(C);
+  // instance `at` of the launch: one after the other, or every eighth on this die
+  int at = kDeal ? blockIdx.x % kTriDies : 0, unit = kDeal ? blockIdx.x / kTriDies : blockIdx.x, units = 0;
+  for (; at < count; at += kDeal ? kTriDies : 1) {
+    units = tri_resident_units(gp->a[first + at].n, 4 * ROWS);
+    if (unit < units) break;
+    unit -= units;
+  }
+  if (at >= count) return;
+  const InitArgs& a = gp->a[first + at];
+  const int n = a.n, np = a.np, end = n - kTriTail;
+  __shared__ double sy[2][C], sx[2][C], sv[2][C];   // A v, the row and the reflection of the last column, alternately
+  __shared__ int s_run, s_lost;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wg_row = unit * 4 * ROWS, row0 = wg_row + wave * ROWS;
+  const bool last_wg = unit == units - 1;
+  double S[ROWS][CH], v[CH];
+#pragma unroll
+  for (int k = 0; k < CH; ++k) {
+    v[k] = 0.0;
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) S[q][k] = a.A[(size_t)min(row0 + q, n - 1) * np + min(64 * k, np - 64) + lane];
+  }
+#pragma unroll
+  for (int k = 0; k < CH; ++k)
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) S[q][k] = 64 * k < np ? S[q][k] : 0.0;
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int c = tid + 256 * t;
+    sy[0][c] = sv[0][c] = 0.0;
+    sx[0][c] = c < n ? a.A[c] : 0.0;
+  }
+  if (tid == 0) {
+    s_lost = 0;
+    s_run = init_all_running(a.gate(), units, limit);
+  }
+  __syncthreads();
+  if (s_run == 0) return;
+  const bool near = s_run == 2;
+  // this lane's slots: rows row0 .. of A v, then of the next row
+  const int mine = row0 + (lane & (ROWS - 1));
+  const size_t place = (lane < ROWS ? 0 : (size_t)np) + mine;
+  const bool sends = lane < 2 * ROWS && mine < n;
+  double tau = 0.0;
+  int stop = min(end, min(wg_row + 4 * ROWS, n) - 1);   // the columns left of the workgroup's last row
+  // Columns of chunks F to G - 1: the chunks before are done.  (A branch per chunk waits for LDS in each: 2.9 us a column.)
+  auto stage = [&](auto first_chunk) {
+    constexpr int F = decltype(first_chunk)::value, G = F + CH / 4;
+    for (int j = 64 * F; j < min(64 * G, stop); ++j) {
+      const int par = j & 1;
+      if (j > 0) {
+        const uint64_t* const slot = reinterpret_cast<const uint64_t*>(a.ring(j - 1));
+        uint64_t gy[T], gx[T];
+        long long t0 = 0;
+        for (int turn = 0;; ++turn) {
+          bool empty = false;
+#pragma unroll
+          for (int t = 0; t < T; ++t) {
+            const int c = max(min(tid + 256 * t, n - 1), j);
+            gy[t] = __hip_atomic_load(slot + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            gx[t] = __hip_atomic_load(slot + np + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+#pragma unroll
+          for (int t = 0; t < T; ++t) empty |= gy[t] == kRingEmpty || gx[t] == kRingEmpty;
+          if (!empty) break;
+          if ((turn & 63) == 63) {
+            if (turn == 63) t0 = wall_clock64();
+            if (wall_clock64() - t0 > kTriLost) {
+              s_lost = 1;
+              break;
+            }
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+          const int c = tid + 256 * t;
+          const bool in = c >= j && c < n;
+          sy[par][c] = in ? __builtin_bit_cast(double, gy[t]) : 0.0;
+          sx[par][c] = in ? __builtin_bit_cast(double, gx[t]) : 0.0;
+        }
+        __syncthreads();
+      }
+      const int lost = s_lost;
+      asm volatile("s_waitcnt vmcnt(0)" : : : "memory");   // what was emptied a column ago is seen as empty
+      if (j >= 2 && sends) ring_store(reinterpret_cast<uint64_t*>(a.ring(j - 2)) + place, kRingEmpty, near);
+      double w[CH], x[CH], vr[ROWS], wr[ROWS], dot[2] = {0.0, 0.0};
+#pragma unroll
+      for (int k = F; k < CH; ++k) w[k] = sy[par][64 * k + lane];
+#pragma unroll
+      for (int k = F; k < CH; ++k) x[k] = sx[par][64 * k + lane];
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) {
+        vr[q] = sv[par][min(row0 + q, n - 1)];
+        wr[q] = sy[par][min(row0 + q, n - 1)];
+      }
+      const double vj = sv[par][j], yj = sy[par][j], xj = sx[par][j];
+      const double vj1 = sv[par][j + 1], yj1 = sy[par][j + 1], xj1 = sx[par][j + 1];
+#pragma unroll
+      for (int k = F; k < CH; ++k) dot[k & 1] = fma(w[k], v[k], dot[k & 1]);
+      const double half = 0.5 * tau * tau * wave_sum_f64(dot[0] + dot[1]);
+      const double wj = fma(tau, yj, -half * vj), wj1 = fma(tau, yj1, -half * vj1);
+      double sigma[2] = {0.0, 0.0};
+#pragma unroll
+      for (int k = F; k < CH; ++k) {
+        w[k] = fma(tau, w[k], -half * v[k]);
+        x[k] = fma(-wj, v[k], fma(-vj, w[k], x[k]));
+        if (k <= G) x[k] = 64 * k + lane > j + 1 ? x[k] : 0.0;
+        sigma[k & 1] = fma(x[k], x[k], sigma[k & 1]);
+      }
+      const double total = wave_sum_f64(sigma[0] + sigma[1]);
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) wr[q] = fma(tau, wr[q], -half * vr[q]);
+      const double dj = fma(-wj, vj, fma(-vj, wj, xj));
+      double acc[ROWS], next[ROWS];
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) acc[q] = next[q] = 0.0;
+#pragma unroll
+      for (int k = F; k < CH; ++k)
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) {
+          S[q][k] = fma(-wr[q], v[k], fma(-vr[q], w[k], S[q][k]));
+          acc[q] = fma(S[q][k], x[k], acc[q]);
+        }
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) acc[q] = wave_sum_f64(acc[q]);
+#pragma unroll
+      for (int k = F; k <= min(G, CH - 1); ++k) {
+        if (k != (j + 1) >> 6) continue;   // (uniform)
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) next[q] = read_lane_f64(S[q][k], (j + 1) & 63);
+      }
+      const Reflection h = reflection(fma(-wj, vj1, fma(-vj, wj1, xj1)), total);
+      double send = 0.0;
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) {
+        const double p = fma(h.scale, acc[q], next[q]);
+        send = lane == q ? p : (lane == ROWS + q ? next[q] : send);
+      }
+      if (sends && mine > j) {
+        const uint64_t bits = __builtin_bit_cast(uint64_t, send);
+        ring_store(reinterpret_cast<uint64_t*>(a.ring(j)) + place, bits == kRingEmpty ? 0x7ff8000000000000ULL : bits, near);
+      }
+      tau = h.tau;
+#pragma unroll
+      for (int k = F; k < CH; ++k) {
+        v[k] = x[k] * h.scale;
+        if (k <= G) v[k] = 64 * k + lane == j + 1 ? 1.0 : v[k];
+        if (wave == 0) sv[par ^ 1][64 * k + lane] = v[k];
+      }
+      if (last_wg) {
+#pragma unroll
+        for (int k = 0; k < CH; ++k)
+          if ((k & 3) == wave && 64 * k < np) a.V[(size_t)j * np + 64 * k + lane] = k >= F ? v[k] : 0.0;
+        if (tid == 0) {
+          a.diag()[j] = dj;
+          a.off()[j] = h.beta;
+          a.tau()[j] = h.tau;
+        }
+      }
+      if (lost != 0) {   // (uniform) some elements never came
+        if (tid == 0) __hip_atomic_fetch_or(a.gate(), kGateClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stop = 0;
+      }
+    }
+  };
+  stage(std::integral_constant<int, 0>());
+  stage(std::integral_constant<int, CH / 4>());
+  stage(std::integral_constant<int, CH / 2>());
+  if constexpr (64 * CH - kTriTail > 48 * CH) stage(std::integral_constant<int, 3 * CH / 4>());
+#pragma unroll
+  for (int k = 0; k < CH; ++k)
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) {
+      const int i = row0 + q, c = 64 * k + lane;
+      if (i >= end && i < n && c >= end && c < n) a.V[(size_t)i * np + c] = S[q][k];
+    }
+}
+
+// The same columns by one workgroup of 256 threads, for an instance whose gate was closed.  `red`: 8 doubles.
+__device__ void init_tri_alone(const InitArgs& a, const int end, double* const red) {
+  const int n = a.n, np = a.np, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double *const v = a.vec(), *const w = v + np, *const vn = w + np;
+  double tau = 0.0;
+  for (int j = 0; j < end; ++j) {
+    const double* const y = a.y((j & 1) ^ 1);
+    double* const out = a.y(j & 1);
+    const double vj = j > 0 ? vn[j] : 0.0, yj = j > 0 ? y[j] : 0.0;
+    double s = 0.0, sigma = 0.0;
+    if (j > 0)
+      for (int c = j + tid; c < n; c += 256) s = fma(y[c], vn[c], s);
+    const double half = 0.5 * tau * tau * block256_sum_f64(s, red);
+    const double wj = fma(tau, yj, -half * vj);
+    for (int c = j + tid; c < n; c += 256) {
+      const double vc = j > 0 ? vn[c] : 0.0, wc = j > 0 ? fma(tau, y[c], -half * vc) : 0.0;
+      const double x = fma(-wj, vc, fma(-vj, wc, a.A[(size_t)j * np + c]));
+      v[c] = vc;
+      w[c] = wc;
+      vn[c] = x;
+      if (c > j + 1) sigma = fma(x, x, sigma);
+    }
+    sigma = block256_sum_f64(sigma, red + 4);
+    const Reflection h = reflection(vn[j + 1], sigma);
+    tau = h.tau;
+    if (tid == 0) {
+      a.diag()[j] = vn[j];
+      a.off()[j] = h.beta;
+      a.tau()[j] = h.tau;
+    }
+    __syncthreads();
+    for (int c = tid; c < np; c += 256) {
+      const double r = c > j + 1 && c < n ? vn[c] * h.scale : (c == j + 1 ? 1.0 : 0.0);
+      if (c > j && c < n) vn[c] = r;
+      a.V[(size_t)j * np + c] = r;
+    }
+    __syncthreads();
+    for (int i = j + 1 + wave; i < n; i += 4) {
+      double* const row = a.A + (size_t)i * np;
+      const double vr = v[i], wr = w[i];
+      double acc = 0.0;
+      for (int c = j + 1 + lane; c < n; c += 64) {
+        const double t = fma(-wr, v[c], fma(-vr, w[c], row[c]));
+        row[c] = t;
+        acc = fma(t, vn[c], acc);
+      }
+      acc = wave_sum_uniform(acc);
+      if (lane == 0) out[i] = acc;
+    }
+    __syncthreads();
+  }
+}
+
 // The last (at most 160) columns, the matrix in registers: 16 x 16 threads, thread (ti, tj) holds rows ti + 16 a and columns
 // tj + 16 b as a 10 x 10 tile.  Two barriers per column: row j is
 // published, every wavefront forms the reflection for itself; the products are published, every wavefront forms w for
@@ -227,7 +529,7 @@ __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __r
 // with 4 x 4 tiles of 128 columns, 3.9 us with 6 x 6 of 192; a 12 x 12 tile no longer fits into 256 registers: 2.8 us.)  Also divides T by N and scales it for the kernels that
 // follow.  One workgroup of 256 threads per instance.
 constexpr int kTriTile = kTriTail / 16;
-__global__ __launch_bounds__(256) void init_tri_tail_kernel(const InitGroup* __restrict__ gp) {
+__global__ __launch_bounds__(256) void init_tri_tail_kernel(const InitGroup* __restrict__ gp, const int resident) {
   const InitArgs& a = gp->a[blockIdx.x];
   constexpr int T = kTriTail, K = kTriTile;
   constexpr int TP = (T + 63) / 64 * 64;   // the vectors are padded with zeros for a wavefront's lanes
@@ -239,19 +541,22 @@ __global__ __launch_bounds__(256) void init_tri_tail_kernel(const InitGroup* __r
   const double inv_n = 1.0 / (double)a.N;
   double* const v = sv[wave];
   double* const w = sw[wave];
+  const bool alone = resident != 0 && j0 > 0 && *a.gate() >= kGateClosed, kept = resident != 0 && j0 > 0 && !alone;   // (uniform)
+  if (alone) init_tri_alone(a, j0, scratch);
+  const double* const from = kept ? a.V : a.A;
   double S[K][K];
 #pragma unroll
   for (int x = 0; x < K; ++x)
 #pragma unroll
     for (int b = 0; b < K; ++b) {
       const int i = ti + 16 * x, c = tj + 16 * b;
-      S[x][b] = i < m && c < m ? a.A[(size_t)(j0 + i) * np + j0 + c] : 0.0;
+      S[x][b] = i < m && c < m ? from[(size_t)(j0 + i) * np + j0 + c] : 0.0;
     }
   // the last column that the other kernel took (none: a reflection with tau = 0)
   double tau = j0 > 0 ? a.tau()[j0 - 1] : 0.0;
   for (int c = lane; c < TP; c += 64) v[c] = j0 > 0 && c < T ? a.V[(size_t)(j0 - 1) * np + j0 + c] : 0.0;   // j0 > 0: all T columns exist
   if (tid < TP) srow[tid] = 0.0;
-  if (tid < TP) sy[tid] = j0 > 0 && tid < T ? a.y((j0 - 1) & 1)[j0 + tid] : 0.0;
+  if (tid < TP) sy[tid] = j0 > 0 && tid < T ? (kept ? a.ring(j0 - 1) : a.y((j0 - 1) & 1))[j0 + tid] : 0.0;
   for (int i = tid; i < j0; i += 256) {
     a.diag()[i] *= inv_n;
     a.off()[i] *= inv_n;

@@ -460,6 +460,10 @@ struct PrecondCall {
   float* rownorm2_out;
 };
 
+// How long a workgroup of the fused apply kernel waits for the other column chunks of its row block before it
+// forms the H rows itself (microseconds; the kernel's clock runs at 100 MHz).
+std::atomic<long long> g_fused_wait_us{2000};
+
 int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
   ProfScope prof(NGSGD_PROF_INIT, s);
   size_t done = 0;
@@ -524,7 +528,29 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
       hipLaunchKernelGGL(init_mirror_kernel, dim3(np_max / 32, np_max / 32, n), dim3(256), 0, s, gd);
       LAUNCH_CHECK();
     }
-    for (int j = 0; j < n_max - kTriTail; ++j) {
+    const bool resident = np_max <= kTriResident;
+    const int rows = tri_resident_rows(np_max);
+    for (int first = 0; resident && n_max > kTriTail && first < n;) {   // as many instances at a time as can be resident together
+      const bool deal = tri_on_one_die(np_max);
+      int count = 0, units = 0, die_units[kTriDies] = {}, die_max = 0;
+      for (; first + count < n; ++count) {
+        const int u = tri_resident_units(g.a[first + count].n, rows), die = count % kTriDies;
+        if (deal ? die_units[die] + u > kTriDieUnits : units + u > kTriResidentUnits) break;
+        units += u;
+        die_units[die] += u;
+        die_max = std::max(die_max, die_units[die]);
+      }
+      const long long limit = g_fused_wait_us.load() * 100;
+      if (units > 0) {
+        if (deal)
+          hipLaunchKernelGGL((init_tri_resident_kernel<8, 4>), dim3(kTriDies * die_max), dim3(256), 0, s, gd, first, count, limit);
+        else
+          hipLaunchKernelGGL((init_tri_resident_kernel<16, 2>), dim3(units), dim3(256), 0, s, gd, first, count, limit);
+        LAUNCH_CHECK();
+      }
+      first += count;
+    }
+    for (int j = 0; !resident && j < n_max - kTriTail; ++j) {
       const int groups = (n_max - j - 1 + 4 * kTriRows - 1) / (4 * kTriRows);
       if (np_max <= kTriLdsCols) {
         hipLaunchKernelGGL(init_tri_step_kernel, dim3(groups, n), dim3(256), 3 * np_max * sizeof(double), s, gd, j, 3);
@@ -533,7 +559,7 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
         hipLaunchKernelGGL(init_tri_step_kernel, dim3(groups, n), dim3(256), 0, s, gd, j, 2);
       }
     }
-    hipLaunchKernelGGL(init_tri_tail_kernel, dim3(n), dim3(256), 0, s, gd);
+    hipLaunchKernelGGL(init_tri_tail_kernel, dim3(n), dim3(256), 0, s, gd, resident ? 1 : 0);
     LAUNCH_CHECK();
     hipLaunchKernelGGL(init_eigenvalue_kernel, dim3(r_max, n), dim3(64), 0, s, gd);
     LAUNCH_CHECK();
@@ -703,9 +729,6 @@ int launch_j_products(std::vector<PrecondCall>& list, hipStream_t s) {
   return NGSGD_OK;
 }
 
-// How long a workgroup of the fused apply kernel waits for the other column chunks of its row block before it
-// forms the H rows itself (microseconds; the kernel's clock runs at 100 MHz).
-std::atomic<long long> g_fused_wait_us{2000};
 
 inline int fused_chunks(int D, int columns = kFusedChunk) { return (D + columns - 1) / columns; }
 inline int fused_row_blocks(int N) { return (N + kFusedRows - 1) / kFusedRows; }
