@@ -448,11 +448,11 @@ constexpr int kFinishRows = 64, kFinishScaleRows = 2;   // rows of a workgroup, 
 constexpr int kFinishHelpers = 512;            // two per compute unit
 constexpr long long kFinishWait = 100000;      // 1 ms at the clock's 100 MHz
 template <bool SCALE>
-__device__ __forceinline__ void finish_deferred(const FinishArgs& a, const int n_deferred, const int groups, double* red) {
+__device__ __forceinline__ void finish_deferred(const FinishArgs& a, const int block, const int n_deferred, const int groups, double* red) {
   constexpr int ROWS = SCALE ? kFinishScaleRows : kFinishRows, WIDTH = 256 / ROWS;
   __shared__ int s_at;
   const int tid = threadIdx.x, sub = tid & 15;
-  for (int e = blockIdx.x; e < n_deferred; e += groups) {
+  for (int e = block; e < n_deferred; e += groups) {
     const int id = a.deferred[e];
     const int rb = id / a.n_col_tiles, chunk = id % a.n_col_tiles;
     const int c_end = min(a.D, (chunk + 1) * a.chunk_cols);
@@ -548,12 +548,17 @@ __device__ __forceinline__ void finish_deferred(const FinishArgs& a, const int n
 // the workgroup's die holds yet.  With one workgroup per instance, which summed the row norms for the traces and cleared H, and a
 // launch of its own for the scaling: 512 x 5000 10.1 + 7.9 us, 512 x 3001 7.8 + 4.9.
 template <bool SCALE>
+__device__ void finish_rows(const FinishArgs& a, int block);
+template <bool SCALE>
 __global__ __launch_bounds__(256) void finish_apply_kernel(const FinishGroup g) {
+  finish_rows<SCALE>(g.a[blockIdx.y], blockIdx.x);
+}
+template <bool SCALE>
+__device__ __forceinline__ void finish_rows(const FinishArgs& a, const int block) {
   constexpr int ROWS = SCALE ? kFinishScaleRows : kFinishRows;
   __shared__ double red[8], s_row[4][ROWS];
-  const FinishArgs& a = g.a[blockIdx.y];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N, D = a.D;
-  const int row0 = blockIdx.x * ROWS, groups = (N + ROWS - 1) / ROWS;
+  const int row0 = block * ROWS, groups = (N + ROWS - 1) / ROWS;
   if (row0 >= N) return;
   const int n_deferred = a.n_arrive > 0 ? *a.deferred_count() : 0;
   // Everything is requested before the first wait: the row pieces that this wavefront scales (256 / ROWS threads take a row) ...
@@ -583,7 +588,7 @@ __global__ __launch_bounds__(256) void finish_apply_kernel(const FinishGroup g) 
     }
   }
   if (n_deferred > 0) {   // (the same for all wavefronts of the instance: it is cleared when all workgroups have left)
-    finish_deferred<SCALE>(a, n_deferred, groups, red);
+    finish_deferred<SCALE>(a, block, n_deferred, groups, red);
     return;
   }
   double p = (double)part[0] + (double)part[1];
@@ -597,7 +602,7 @@ __global__ __launch_bounds__(256) void finish_apply_kernel(const FinishGroup g) 
     a.prow[r] = p;
     if (a.rownorm2_out != nullptr) a.rownorm2_out[r] = (float)(gamma * gamma * p);
   }
-  if (blockIdx.x == 0 && tid == 0) {
+  if (block == 0 && tid == 0) {
     a.st->gamma = gamma;
     a.st->tr_M = t;
     a.st->tr_Mhat = ph;
@@ -619,7 +624,7 @@ __global__ __launch_bounds__(256) void finish_apply_kernel(const FinishGroup g) 
     const int rows = min(ROWS, N - row0);
     float4* const h = reinterpret_cast<float4*>(a.H + (size_t)row0 * a.ldh);
     for (int i = tid; i < rows * a.ldh / 4; i += 256) h[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (blockIdx.x == 0)
+    if (block == 0)
       for (int i = tid; i < a.n_arrive; i += 256) a.arrive[i] = 0;
   }
 }
@@ -655,14 +660,16 @@ struct BtGroup {
   double num_samples_history;
   BtArgs a[kMaxInstances];
 };
+__device__ __forceinline__ void make_bt_row(const BtArgs& a, const double num_samples_history, const int i, const int first, const int step) {
+  const double eta = 1.0 - exp(-(double)a.N / num_samples_history);
+  const float f = (float)((double)a.N * (1.0 - eta) / eta * (a.st->d[i] + a.st->rho));
+  for (int c = first; c < a.D; c += step) a.J[(size_t)i * a.ld + c] += f * a.W[(size_t)i * a.ld + c];
+}
 __global__ void make_bt_kernel(const BtGroup g) {
   const BtArgs& a = g.a[blockIdx.z];
   const int i = blockIdx.y;
   if (i >= a.R) return;
-  const double eta = 1.0 - exp(-(double)a.N / g.num_samples_history);
-  const float f = (float)((double)a.N * (1.0 - eta) / eta * (a.st->d[i] + a.st->rho));
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < a.D; c += gridDim.x * blockDim.x)
-    a.J[(size_t)i * a.ld + c] += f * a.W[(size_t)i * a.ld + c];
+  make_bt_row(a, g.num_samples_history, i, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
 // W = E^{1/2} R from a state given in definitional form (eq. beta2, etii, wt:def).  One workgroup per row.

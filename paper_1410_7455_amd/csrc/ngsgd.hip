@@ -265,24 +265,31 @@ template <int K>
 constexpr int kEigReduceReserve = kEigLdsReserve - DirectShape<K>::T * DirectShape<K>::T * (int)sizeof(double);
 template <int K, int ITEMS>
 hipError_t eig_attributes() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(eig_reduce_kernel<K>), hipFuncAttributeMaxDynamicSharedMemorySize, kEigReduceReserve<K>);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(eig_reduce_kernel<K, false>), hipFuncAttributeMaxDynamicSharedMemorySize, kEigReduceReserve<K>);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(eig_finish_kernel<K, ITEMS, kEigThreads, false>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(eig_finish_kernel<K, ITEMS, kEigThreads, false, false>),
                              hipFuncAttributeMaxDynamicSharedMemorySize,
                              kEigLdsReserve);
 }
 // The three kernels of an R x R update above rank 32.  A large eigen-problem is a long sequential chain bound by latency, on which
 // the next step waits: its single workgroups ask for most of the compute unit's LDS, so that no workgroup of the layer
 // products (which live on LDS bandwidth) is placed next to them.  That costs the products one compute unit in 256 per instance.
+// With work beside them there are no layer products to keep away.
 template <int K, int ITEMS>
-hipError_t launch_eig(const SmallGroup& g, const int n, const int r_max, hipStream_t s) {
-  const size_t reserve = r_max >= kEigReserveFromRank ? kEigReduceReserve<K> : 0;
-  hipLaunchKernelGGL(eig_reduce_kernel<K>, dim3(n), dim3(kEigReduceThreads), reserve, s, g);
-  hipLaunchKernelGGL(eig_pairs_kernel<K>, dim3(n, (r_max + 3) / 4), dim3(256), 0, s, g);
+hipError_t launch_eig(const SmallGroup& g, const int n, const int r_max, const Beside* beside, hipStream_t s) {
+  if (beside != nullptr) {
+    hipLaunchKernelGGL((eig_reduce_kernel<K, true>), dim3(kBesideFirst + beside->xhat_blocks() + beside->bt.R), dim3(kEigReduceThreads), 0, s, g, *beside);
+    hipLaunchKernelGGL((eig_pairs_kernel<K, true>), dim3(1, (r_max + 3) / 4 + Beside::row_blocks(beside->finish.N)), dim3(256), 0, s, g, *beside);
+  } else {
+    const size_t reserve = r_max >= kEigReserveFromRank ? kEigReduceReserve<K> : 0;
+    hipLaunchKernelGGL((eig_reduce_kernel<K, false>), dim3(n), dim3(kEigReduceThreads), reserve, s, g, Beside());
+    hipLaunchKernelGGL((eig_pairs_kernel<K, false>), dim3(n, (r_max + 3) / 4), dim3(256), 0, s, g, Beside());
+  }
   const int half = (r_max + 1) / 2;
   const size_t jacobi = (size_t)2 * 4 * (half * (half + 1) / 2) * sizeof(double);   // two copies of four planes of 2 x 2 blocks
   const size_t direct = (size_t)(DirectShape<K>::T + 16) * DirectShape<K>::STRIDE * sizeof(double);
-  hipLaunchKernelGGL((eig_finish_kernel<K, ITEMS, kEigThreads, false>), dim3(n, (r_max + 15) / 16), dim3(kEigThreads), std::max(jacobi, direct), s, g);
+  hipLaunchKernelGGL((eig_finish_kernel<K, ITEMS, kEigThreads, false, false>), dim3(n, (r_max + 15) / 16), dim3(kEigThreads), std::max(jacobi, direct), s, g,
+                     Beside());
   return hipGetLastError();
 }
 static_assert((kMaxRank / 2) * (kMaxRank / 2 - 1) / 2 <= 2 * (kEigThreads - 64), "2 x 2 blocks of Jacobi's off-diagonal per thread: two");
@@ -823,6 +830,44 @@ int launch_fused_apply(std::vector<PrecondCall>& list, hipStream_t s) {
   return NGSGD_OK;
 }
 
+// Xhat = X - H W   (eq. hatxt:compute:2), row-norm partials (eq. pi)
+GemmDesc xhat_product(const PrecondCall& c) {
+  ngsgd_precond& p = *c.p;
+  GemmDesc g;
+  g.A = p.H; g.lda = p.ldh;
+  g.B = p.W; g.ldb = p.ldw;
+  g.C = c.M; g.ldc = c.ld;
+  g.M = c.N; g.N = p.dim; g.K = p.rank;
+  g.aux = p.rownorm_part;
+  g.sumsq = p.hat_part;
+  return g;
+}
+// gamma_t, tr(X X^T), tr(Xhat Xhat^T), row norms; gamma Xhat
+FinishArgs finish_args(const PrecondCall& c, const bool fused) {
+  ngsgd_precond& p = *c.p;
+  FinishArgs a;
+  a.st = p.st;
+  a.sumsq_part = p.sumsq_part;
+  a.hat_part = p.hat_part;
+  a.n_sumsq = p.n_sumsq;
+  a.n_hat = fused ? fused_chunks(p.dim, p.fused_columns) * fused_row_blocks(c.N) : ((p.dim + 63) / 64) * ((c.N + 63) / 64);
+  a.rownorm_part = p.rownorm_part;
+  a.n_col_tiles = fused ? fused_chunks(p.dim, p.fused_columns) : (p.dim + 63) / 64;
+  a.N = c.N;
+  a.prow = p.prow;
+  a.gamma_out = c.gamma_out;
+  a.rownorm2_out = c.rownorm2_out;
+  a.X = c.M; a.ldx = c.ld; a.D = p.dim;
+  a.deferred = p.deferred;
+  a.W = p.W; a.ldw = p.ldw;
+  a.H = p.H; a.ldh = p.ldh;
+  a.R = p.rank;
+  a.chunk_cols = p.fused_columns;
+  a.arrive = p.arrive;
+  a.n_arrive = fused ? (int)p.arrive_slots - kFinishSlots : 0;
+  return a;
+}
+
 // With hj_ready the caller has already produced H and J of every instance (all due for an update, none at t = 0)
 // and ordered s behind them; only Xhat and gamma remain.
 // do_products / do_finish select the two halves of the work on the matrices (the products; the reduction of the
@@ -830,7 +875,7 @@ int launch_fused_apply(std::vector<PrecondCall>& list, hipStream_t s) {
 // different times and reduce once.
 int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_t s,
                   std::vector<PrecondCall>& to_update_out, bool hj_ready = false, bool do_products = true,
-                  bool do_finish = true) {
+                  bool do_finish = true, Beside* beside = nullptr) {
   std::vector<PrecondCall> full, to_init, to_update;
   const bool captured = capturing(s);
   for (auto& c : calls) {
@@ -865,24 +910,22 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
     NG_TRY(launch_h_products(full, s));
     NG_TRY(launch_j_products(to_update, s));
   }
-  // Xhat = X - H W   (eq. hatxt:compute:2), row-norm partials (eq. pi)
+  if (beside != nullptr && !to_update.empty()) {   // the rest of this call's output goes with the eigen-problem
+    const GemmDesc d = xhat_product(to_update[0]);
+    plan_tiles<64, 64, Beside::kBk>(d, beside->xhat.p[0]);
+    beside->xhat.p[0].tile_begin = 0;
+    beside->xhat.count = 1;
+    beside->xhat.total_tiles = beside->xhat.p[0].per_split * beside->xhat.p[0].splits;
+    beside->finish = finish_args(to_update[0], false);
+    to_update_out.push_back(to_update[0]);
+    return NGSGD_OK;
+  }
   if (!fused && do_products && !full.empty()) {
     std::vector<GemmDesc> d;
-    for (auto& c : full) {
-      ngsgd_precond& p = *c.p;
-      GemmDesc g;
-      g.A = p.H; g.lda = p.ldh;
-      g.B = p.W; g.ldb = p.ldw;
-      g.C = c.M; g.ldc = c.ld;
-      g.M = c.N; g.N = p.dim; g.K = p.rank;
-      g.aux = p.rownorm_part;
-      g.sumsq = p.hat_part;
-      d.push_back(g);
-    }
+    for (auto& c : full) d.push_back(xhat_product(c));
     ProfScope prof(NGSGD_PROF_PRECOND_XHAT, s);
     HIP_TRY((launch_gemm_group<64, 64, BK, 2, 2, true, false, EPI_SUB_ROWNORM, false>(d.data(), (int)d.size(), s)));
   }
-  // gamma_t, tr(X X^T), tr(Xhat Xhat^T), row norms; gamma Xhat
   for (size_t done = 0; do_finish && done < full.size();) {
     ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
     FinishGroup g;
@@ -891,27 +934,7 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
     int n_max = 0;
     for (int i = 0; i < n; ++i) {
       const PrecondCall& c = full[done + i];
-      ngsgd_precond& p = *c.p;
-      FinishArgs& a = g.a[i];
-      a.st = p.st;
-      a.sumsq_part = p.sumsq_part;
-      a.hat_part = p.hat_part;
-      a.n_sumsq = p.n_sumsq;
-      a.n_hat = fused ? fused_chunks(p.dim, p.fused_columns) * fused_row_blocks(c.N) : ((p.dim + 63) / 64) * ((c.N + 63) / 64);
-      a.rownorm_part = p.rownorm_part;
-      a.n_col_tiles = fused ? fused_chunks(p.dim, p.fused_columns) : (p.dim + 63) / 64;
-      a.N = c.N;
-      a.prow = p.prow;
-      a.gamma_out = c.gamma_out;
-      a.rownorm2_out = c.rownorm2_out;
-      a.X = c.M; a.ldx = c.ld; a.D = p.dim;
-      a.deferred = p.deferred;
-      a.W = p.W; a.ldw = p.ldw;
-      a.H = p.H; a.ldh = p.ldh;
-      a.R = p.rank;
-      a.chunk_cols = p.fused_columns;
-      a.arrive = p.arrive;
-      a.n_arrive = fused ? (int)p.arrive_slots - kFinishSlots : 0;
+      g.a[i] = finish_args(c, fused);
       n_max = std::max(n_max, c.N);
     }
     if (scale_output) {
@@ -943,7 +966,7 @@ int small_chunk(const std::vector<PrecondCall>& list, size_t done) {
 
 // First half of the factor update (App. B.3): K, L, B_t, then Z_t, its eigen-decomposition, rho_{t+1}, D_{t+1}
 // and A_t.  Reads H, J and the partial sums of tr(X X^T); leaves W_t alone.
-int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
+int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s, Beside* beside = nullptr) {
   if (to_update.empty()) return NGSGD_OK;
   {
     // K = J J^T, L = H^T H, fp64 accumulation across the splits
@@ -987,6 +1010,10 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
       ++n;
     }
     bg.count = n;
+    if (beside != nullptr && r_max > kEigSmallRank) {
+      beside->bt = bg.a[0];
+      break;
+    }
     hipLaunchKernelGGL(make_bt_kernel, dim3((d_max + 1023) / 1024, r_max, n), dim3(256), 0, s, bg);
     LAUNCH_CHECK();
     done += n;
@@ -1015,14 +1042,19 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
     prof_place();   // (the eigenvectors' group)
     if (r_max <= kEigSmallRank) {
       using Shape = DirectShape<kEigSmallRank / 16>;
-      hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true>), dim3(n), dim3(kEigSmallThreads), 2 * Shape::T * Shape::STRIDE * sizeof(double), s, g);
+      const size_t dyn = 2 * Shape::T * Shape::STRIDE * sizeof(double);
+      if (beside != nullptr)
+        hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true, true>), dim3(kBesideFirst + beside->xhat_blocks()),
+                           dim3(kEigSmallThreads), dyn, s, g, *beside);
+      else
+        hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true, false>), dim3(n), dim3(kEigSmallThreads), dyn, s, g, Beside());
       LAUNCH_CHECK();
     } else if (r_max <= 48) {
-      HIP_TRY((launch_eig<3, 1>(g, n, r_max, s)));
+      HIP_TRY((launch_eig<3, 1>(g, n, r_max, beside, s)));
     } else if (r_max <= 80) {
-      HIP_TRY((launch_eig<5, 1>(g, n, r_max, s)));
+      HIP_TRY((launch_eig<5, 1>(g, n, r_max, beside, s)));
     } else {
-      HIP_TRY((launch_eig<6, 2>(g, n, r_max, s)));
+      HIP_TRY((launch_eig<6, 2>(g, n, r_max, beside, s)));
     }
     done += n;
   }
@@ -1031,7 +1063,7 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s) {
 
 // Second half: W_{t+1} = A_t B_t (eq. wt1) and the orthogonality check of App. B.3.1.  Overwrites W_t, so the
 // caller orders it behind the last reader of W_t.
-int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s) {
+int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s, const Beside* beside = nullptr) {
   for (size_t done = 0; done < to_update.size();) {
     OrthGroup og;
     const int n = small_chunk(to_update, done);
@@ -1065,6 +1097,17 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s) {
         }
         if (d.empty()) continue;
         ProfScope prof(only_if_reorthogonalised ? NGSGD_PROF_PRECOND_MISC : NGSGD_PROF_PRECOND_WNEW, s);
+        if (beside != nullptr && rc == 32 && !only_if_reorthogonalised) {
+          GemmGroupOf<1> w;
+          plan_tiles<32, 64, Beside::kBk>(d[0], w.p[0]);
+          w.p[0].tile_begin = 0;
+          w.count = 1;
+          w.total_tiles = w.p[0].per_split * w.p[0].splits;
+          const int blocks = (w.total_tiles + kXcds - 1) / kXcds * kXcds + Beside::row_blocks(beside->finish.N);
+          hipLaunchKernelGGL(wnew_finish_kernel, dim3(blocks), dim3(256), 0, s, w, beside->finish);
+          LAUNCH_CHECK();
+          continue;
+        }
         HIP_TRY(by_rank_class(rc, [&] { return launch_wnew<32>(d.data(), (int)d.size(), s); },
                               [&] { return launch_wnew<80>(d.data(), (int)d.size(), s); },
                               [&] { return launch_wnew<96>(d.data(), (int)d.size(), s); }));
@@ -1125,9 +1168,11 @@ int precondition_many(std::vector<PrecondCall>& calls, bool scale_output, hipStr
   NG_TRY(ensure_kernel_attributes());
   NG_TRY(precond_validate(calls));
   std::vector<PrecondCall> to_update;
-  NG_TRY(precond_apply(calls, scale_output, s, to_update));
-  NG_TRY(factor_begin(to_update, s));
-  NG_TRY(factor_finish(to_update, s));
+  Beside beside = {};
+  Beside* const alone = calls.size() == 1 && scale_output ? &beside : nullptr;
+  NG_TRY(precond_apply(calls, scale_output, s, to_update, false, true, true, alone));
+  NG_TRY(factor_begin(to_update, s, alone));
+  NG_TRY(factor_finish(to_update, s, alone));
   for (auto& c : calls) c.p->t += 1;
   return NGSGD_OK;
 }

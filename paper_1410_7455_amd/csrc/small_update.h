@@ -496,9 +496,40 @@ struct ZLoad {
   }
 };
 
+// A call that updates one instance on one stream: what does not wait for the eigen-problem, which leaves the chip idle, runs beside it in
+// the same launches.  Xhat, above rank 32 with B_t, beside the first kernel (which reads D_t and rho_t but leaves them); gamma,
+// row norms and the scaling beside the eigenpairs or, up to rank 32, beside W_(t+1).  The eigen-problem's workgroups come first.
+// 512 x 5000 rank 80: Xhat 9.3, finishing 10.0, B_t 4.4 us and their gaps off the call.
+constexpr int kBesideFirst = kXcds;   // workgroups in front, so that a die's units stay a contiguous share
+struct Beside {
+  GemmGroupOf<1> xhat;
+  BtArgs bt;                    // R = 0: none
+  FinishArgs finish;
+  static constexpr int kBk = 16;
+  static int row_blocks(const int N) { return (N + kFinishScaleRows - 1) / kFinishScaleRows; }
+  int xhat_blocks() const { return (xhat.total_tiles + kXcds - 1) / kXcds * kXcds; }
+};
+// 256 threads; block counts from the first workgroup beside.
+__device__ __forceinline__ void beside_products(const Beside& b, const double num_samples_history, const int block) {
+  const int per = (b.xhat.total_tiles + kXcds - 1) / kXcds;
+  if (block >= per * kXcds) {
+    if (block - per * kXcds < b.bt.R) make_bt_row(b.bt, num_samples_history, block - per * kXcds, threadIdx.x, 256);
+    return;
+  }
+  const int unit = block % kXcds * per + block / kXcds;
+  if (unit < b.xhat.total_tiles) gemm_unit<64, 64, Beside::kBk, 2, 2, true, false, EPI_SUB_ROWNORM, false, 0, false, kPrefetch>(b.xhat, 0, unit);
+}
+
 // Above rank 32, first kernel: Z_t and its reduction.  A workgroup per instance.
-template <int K>
-__global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const SmallGroup g) {
+template <int K, bool BESIDE>
+__global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const SmallGroup g, const Beside beside) {
+  if constexpr (BESIDE) {
+    if ((int)blockIdx.x >= kBesideFirst) {
+      beside_products(beside, g.num_samples_history, (int)blockIdx.x - kBesideFirst);
+      return;
+    }
+    if ((int)blockIdx.x >= g.count) return;
+  }
   using Shape = DirectShape<K>;
   constexpr int NT = kEigReduceThreads;
   constexpr int T = Shape::T;
@@ -531,8 +562,15 @@ __global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const Sma
 }
 
 // Second kernel: four eigenpairs per workgroup of 256 threads.  Grid (instance, ceil(R / 4)).
-template <int K>
-__global__ __launch_bounds__(256) void eig_pairs_kernel(const SmallGroup g) {
+template <int K, bool BESIDE>
+__global__ __launch_bounds__(256) void eig_pairs_kernel(const SmallGroup g, const Beside beside) {
+  if constexpr (BESIDE) {
+    const int pairs = (g.a[0].R + 3) / 4;
+    if ((int)blockIdx.y >= pairs) {
+      finish_rows<true>(beside.finish, (int)blockIdx.y - pairs);
+      return;
+    }
+  }
   using Shape = DirectShape<K>;
   constexpr int T = Shape::T;
   __shared__ DirectTridiagonal<K> t;
@@ -583,8 +621,15 @@ struct FusedLds<K, NT, false> {};
 // (eq. rhodash2, dt1, rhot1, beta2, etii) and A_t (eq. wt1).  Above rank 32 a workgroup per 16 rows of A_t: each checks all
 // vectors, by the same arithmetic so that all decide alike, and takes its rows' share of the second product; the first one does what is left.
 // Grid (instance, FUSED ? 1 : ceil(R / 16)).
-template <int K, int ITEMS, int NT, bool FUSED>
-__global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g) {
+template <int K, int ITEMS, int NT, bool FUSED, bool BESIDE>
+__global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g, const Beside beside) {
+  if constexpr (BESIDE) {
+    if ((int)blockIdx.x >= kBesideFirst) {
+      if (threadIdx.x < 256) beside_products(beside, g.num_samples_history, (int)blockIdx.x - kBesideFirst);
+      return;
+    }
+    if ((int)blockIdx.x >= g.count) return;
+  }
   using Shape = DirectShape<K>;
   constexpr int T = Shape::T, SU = Shape::STRIDE, NW = NT / 64;
   typedef double doublex4 __attribute__((ext_vector_type(4)));
@@ -1032,6 +1077,17 @@ __global__ __launch_bounds__(kSmallThreads) void orth_fix_kernel(const OrthGroup
     }
   }
   if (tid == 0) st->flags = (st->flags & ~kFlagOrthCheck) | kFlagReorth;
+}
+
+// Up to rank 32: W_{t+1} = A_t B_t of one instance, and beside it what finishes the call's output.  256 threads.
+__global__ __launch_bounds__(256) void wnew_finish_kernel(const GemmGroupOf<1> w, const FinishArgs finish) {
+  const int per = (w.total_tiles + kXcds - 1) / kXcds, block = blockIdx.x;
+  if (block >= per * kXcds) {
+    finish_rows<true>(finish, block - per * kXcds);
+    return;
+  }
+  const int unit = block % kXcds * per + block / kXcds;
+  if (unit < w.total_tiles) gemm_unit<32, 64, Beside::kBk, 2, 2, true, false, EPI_STORE, false, 0, false, kPrefetch>(w, 0, unit);
 }
 
 }  // namespace ngsgd
