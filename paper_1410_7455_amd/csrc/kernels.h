@@ -647,31 +647,6 @@ __global__ __launch_bounds__(256) void rownorm_kernel(const float* __restrict__ 
   }
 }
 
-// B_t = J_t + (N (1 - eta) / eta) (D_t + rho_t I) W_t, written over J (eq. wt1).  Grid (col blocks, R, instance).
-// Must run while st still holds D_t and rho_t, i.e. before the R x R update kernel.
-struct BtArgs {
-  float* J;
-  const float* W;
-  const PrecondScalars* st;
-  int ld, D, R, N;
-};
-struct BtGroup {
-  int count;
-  double num_samples_history;
-  BtArgs a[kMaxInstances];
-};
-__device__ __forceinline__ void make_bt_row(const BtArgs& a, const double num_samples_history, const int i, const int first, const int step) {
-  const double eta = 1.0 - exp(-(double)a.N / num_samples_history);
-  const float f = (float)((double)a.N * (1.0 - eta) / eta * (a.st->d[i] + a.st->rho));
-  for (int c = first; c < a.D; c += step) a.J[(size_t)i * a.ld + c] += f * a.W[(size_t)i * a.ld + c];
-}
-__global__ void make_bt_kernel(const BtGroup g) {
-  const BtArgs& a = g.a[blockIdx.z];
-  const int i = blockIdx.y;
-  if (i >= a.R) return;
-  make_bt_row(a, g.num_samples_history, i, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
-}
-
 // W = E^{1/2} R from a state given in definitional form (eq. beta2, etii, wt:def).  One workgroup per row.
 __global__ __launch_bounds__(256) void set_state_kernel(const double* __restrict__ Rm, const double* __restrict__ d,
                                                         double rho, double alpha, int R, int D,

@@ -278,7 +278,7 @@ hipError_t eig_attributes() {
 template <int K, int ITEMS>
 hipError_t launch_eig(const SmallGroup& g, const int n, const int r_max, const Beside* beside, hipStream_t s) {
   if (beside != nullptr) {
-    hipLaunchKernelGGL((eig_reduce_kernel<K, true>), dim3(kBesideFirst + beside->xhat_blocks() + beside->bt.R), dim3(kEigReduceThreads), 0, s, g, *beside);
+    hipLaunchKernelGGL((eig_reduce_kernel<K, true>), dim3(kBesideFirst + beside->xhat_blocks()), dim3(kEigReduceThreads), 0, s, g, *beside);
     hipLaunchKernelGGL((eig_pairs_kernel<K, true>), dim3(1, (r_max + 3) / 4 + Beside::row_blocks(beside->finish.N)), dim3(256), 0, s, g, *beside);
   } else {
     const size_t reserve = r_max >= kEigReserveFromRank ? kEigReduceReserve<K> : 0;
@@ -917,6 +917,8 @@ int precond_apply(std::vector<PrecondCall>& calls, bool scale_output, hipStream_
     beside->xhat.count = 1;
     beside->xhat.total_tiles = beside->xhat.p[0].per_split * beside->xhat.p[0].splits;
     beside->finish = finish_args(to_update[0], false);
+    prof_place();   // (the groups of Xhat and of the finishing kernel)
+    prof_place();
     to_update_out.push_back(to_update[0]);
     return NGSGD_OK;
   }
@@ -964,7 +966,7 @@ int small_chunk(const std::vector<PrecondCall>& list, size_t done) {
   return n;
 }
 
-// First half of the factor update (App. B.3): K, L, B_t, then Z_t, its eigen-decomposition, rho_{t+1}, D_{t+1}
+// First half of the factor update (App. B.3): K, L, then Z_t, its eigen-decomposition, rho_{t+1}, D_{t+1}
 // and A_t.  Reads H, J and the partial sums of tr(X X^T); leaves W_t alone.
 int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s, Beside* beside = nullptr) {
   if (to_update.empty()) return NGSGD_OK;
@@ -994,30 +996,6 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s, Beside* bes
     ProfScope prof(NGSGD_PROF_PRECOND_KL, s);
     HIP_TRY(launch_small_gram(rc, d.data(), (int)d.size(), s));
   }
-  // B_t over J (needs D_t, rho_t: before the R x R update)
-  for (size_t done = 0; done < to_update.size();) {
-    ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
-    BtGroup bg;
-    bg.num_samples_history = to_update[done].p->num_samples_history;
-    int n = 0, r_max = 0, d_max = 0;
-    while (n < kMaxInstances && done + n < to_update.size()) {
-      const PrecondCall& c = to_update[done + n];
-      ngsgd_precond& p = *c.p;
-      if (p.num_samples_history != bg.num_samples_history) break;
-      bg.a[n] = BtArgs{p.J, p.W, p.st, p.ldw, p.dim, p.rank, p.last_N};
-      r_max = std::max(r_max, p.rank);
-      d_max = std::max(d_max, p.dim);
-      ++n;
-    }
-    bg.count = n;
-    if (beside != nullptr && r_max > kEigSmallRank) {
-      beside->bt = bg.a[0];
-      break;
-    }
-    hipLaunchKernelGGL(make_bt_kernel, dim3((d_max + 1023) / 1024, r_max, n), dim3(256), 0, s, bg);
-    LAUNCH_CHECK();
-    done += n;
-  }
   // Z_t, eigen-decomposition, rho_{t+1}, D_{t+1}, A_t
   for (size_t done = 0; done < to_update.size();) {
     SmallGroup g;
@@ -1033,13 +1011,15 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s, Beside* bes
       a.st = p.st; a.K = p.K; a.L = p.L; a.At = p.At; a.ldat = p.ldh;
       a.R = p.rank; a.D = p.dim; a.N = p.last_N;
       a.direct = p.direct;
+      a.bt = reinterpret_cast<float*>(p.idx);   // (the initialisation is done with it)
       a.sumsq_part = p.sumsq_part;
       a.n_sumsq = p.n_sumsq;
       r_max = std::max(r_max, p.rank);
     }
     g.count = n;
     ProfScope prof(NGSGD_PROF_PRECOND_SMALL, s);
-    prof_place();   // (the eigenvectors' group)
+    prof_place();   // (the eigenvectors' group and B_t's)
+    prof_place();
     if (r_max <= kEigSmallRank) {
       using Shape = DirectShape<kEigSmallRank / 16>;
       const size_t dyn = 2 * Shape::T * Shape::STRIDE * sizeof(double);
@@ -1078,7 +1058,31 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s, const Besi
     }
     og.count = n;
     const bool clears = n == 1 || r_max <= kOrthClearRank, counts = clears && !capturing(s);
-    auto launch_new_factor = [&](const bool only_if_reorthogonalised) -> int {
+    // W_{t+1} = A_t B_t; App. B.3.1: W W^T of the new factor, accumulated into K (cleared by the R x R kernel) only for the
+    // instances whose update asked for the check
+    for (int rc : {32, 80, 96}) {
+      NewFactorGroup f;
+      f.count = f.total = 0;
+      for (int i = 0; i < n; ++i) {
+        const ngsgd_precond& p = *to_update[done + i].p;
+        if (p.ldh != rc) continue;
+        f.a[f.count++] = NewFactorArgs{p.st, p.At, reinterpret_cast<const float*>(p.idx), p.J, p.W, p.K, p.ldh, p.ldw, p.rank, p.dim, f.total};
+        f.total += (p.dim + 63) / 64;
+      }
+      if (f.count == 0) continue;
+      ProfScope prof(NGSGD_PROF_PRECOND_WNEW, s);
+      const dim3 grid(f.total), block(256);
+      if (rc == 32 && beside != nullptr)
+        hipLaunchKernelGGL(new_factor_finish_kernel, dim3(f.total + Beside::row_blocks(beside->finish.N)), block, 0, s, f.a[0], f.total, beside->finish);
+      else if (rc == 32)
+        hipLaunchKernelGGL(new_factor_kernel<32>, grid, block, 0, s, f);
+      else if (rc == 80)
+        hipLaunchKernelGGL(new_factor_kernel<80>, grid, block, 0, s, f);
+      else
+        hipLaunchKernelGGL(new_factor_kernel<96>, grid, block, 0, s, f);
+      LAUNCH_CHECK();
+    }
+    auto launch_product_again = [&]() -> int {
       for (int rc : {32, 80, 96}) {
         std::vector<GemmDesc> d;
         for (int i = 0; i < n; ++i) {
@@ -1089,53 +1093,20 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s, const Besi
           w.B = p.J; w.ldb = p.ldw;
           w.C = p.W; w.ldc = p.ldw;
           w.M = p.rank; w.N = p.dim; w.K = p.rank;
-          if (only_if_reorthogonalised) {
-            w.gate = &p.st->flags;
-            w.gate_mask = kFlagReorth;
-          }
+          w.gate = &p.st->flags;
+          w.gate_mask = kFlagReorth;
           d.push_back(w);
         }
         if (d.empty()) continue;
-        ProfScope prof(only_if_reorthogonalised ? NGSGD_PROF_PRECOND_MISC : NGSGD_PROF_PRECOND_WNEW, s);
-        if (beside != nullptr && rc == 32 && !only_if_reorthogonalised) {
-          GemmGroupOf<1> w;
-          plan_tiles<32, 64, Beside::kBk>(d[0], w.p[0]);
-          w.p[0].tile_begin = 0;
-          w.count = 1;
-          w.total_tiles = w.p[0].per_split * w.p[0].splits;
-          const int blocks = (w.total_tiles + kXcds - 1) / kXcds * kXcds + Beside::row_blocks(beside->finish.N);
-          hipLaunchKernelGGL(wnew_finish_kernel, dim3(blocks), dim3(256), 0, s, w, beside->finish);
-          LAUNCH_CHECK();
-          continue;
-        }
+        ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
         HIP_TRY(by_rank_class(rc, [&] { return launch_wnew<32>(d.data(), (int)d.size(), s); },
                               [&] { return launch_wnew<80>(d.data(), (int)d.size(), s); },
                               [&] { return launch_wnew<96>(d.data(), (int)d.size(), s); }));
       }
       return NGSGD_OK;
     };
-    NG_TRY(launch_new_factor(false));
-    {
-      // App. B.3.1: W W^T of the new factor, accumulated into K (cleared by the R x R kernel) only for the
-      // instances whose update asked for the check, then the check itself and, if needed, the Cholesky fix
-      std::vector<GemmDesc> dg;
-      for (int i = 0; i < n; ++i) {
-        ngsgd_precond& p = *to_update[done + i].p;
-        GemmDesc w;
-        w.A = p.W; w.lda = p.ldw;
-        w.B = p.W; w.ldb = p.ldw;
-        w.C = p.K; w.ldc = p.rank;
-        w.M = p.rank; w.N = p.rank; w.K = p.dim;
-        w.splits = gram_splits(rank_class(r_max), p.rank, n, p.dim);
-        w.kc = 1;
-        w.gate = &p.st->flags;
-        w.gate_mask = kFlagOrthCheck;
-        dg.push_back(w);
-      }
-      {
-        ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
-        HIP_TRY(launch_small_gram(rank_class(r_max), dg.data(), (int)dg.size(), s));
-      }
+    prof_place();   // (the group of W W^T)
+    {   // the check itself and, if needed, the Cholesky fix
       ProfScope prof(NGSGD_PROF_PRECOND_MISC, s);
       const size_t dyn = (size_t)r_max * (r_max + 1) * sizeof(double);   // W W^T of an instance
       const int ct = orth_columns_per_thread(r_max);   // 2 R / 32 rounded up: 1 .. 6
@@ -1151,7 +1122,7 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s, const Besi
       LAUNCH_CHECK();
     }
     // where the check failed the kernel has folded the fix into A_t: W_{t+1} = A_t B_t once more for those
-    NG_TRY(launch_new_factor(true));
+    NG_TRY(launch_product_again());
     for (int i = 0; i < n; ++i) {
       ngsgd_precond& p = *to_update[done + i].p;
       if (!counts) continue;

@@ -44,6 +44,7 @@ struct SmallArgs {
   float* At;         // out: A_t (eq. wt1), R x ldat
   int ldat;
   int R, D, N;
+  float* bt;                  // out: R factors of W_t's rows in B_t
   const double* sumsq_part;   // partial sums of tr(X X^T) left by the H product
   int n_sumsq;
   // What the kernels of the direct method hand on: R rows of `ldv` doubles of reflections and of eigenvectors, seven vectors, rho_t; and
@@ -497,27 +498,25 @@ struct ZLoad {
 };
 
 // A call that updates one instance on one stream: what does not wait for the eigen-problem, which leaves the chip idle, runs beside it in
-// the same launches.  Xhat, above rank 32 with B_t, beside the first kernel (which reads D_t and rho_t but leaves them); gamma,
-// row norms and the scaling beside the eigenpairs or, up to rank 32, beside W_(t+1).  The eigen-problem's workgroups come first.
-// 512 x 5000 rank 80: Xhat 9.3, finishing 10.0, B_t 4.4 us and their gaps off the call.
+// the same launches.  Xhat beside the first kernel; gamma, row norms and the scaling beside the eigenpairs or, up to rank 32, beside
+// W_(t+1).  The eigen-problem's workgroups come first.  512 x 5000 rank 80: Xhat 9.3, finishing 10.0 us and their gaps off the call.
 constexpr int kBesideFirst = kXcds;   // workgroups in front, so that a die's units stay a contiguous share
 struct Beside {
   GemmGroupOf<1> xhat;
-  BtArgs bt;                    // R = 0: none
   FinishArgs finish;
   static constexpr int kBk = 16;
   static int row_blocks(const int N) { return (N + kFinishScaleRows - 1) / kFinishScaleRows; }
   int xhat_blocks() const { return (xhat.total_tiles + kXcds - 1) / kXcds * kXcds; }
 };
 // 256 threads; block counts from the first workgroup beside.
-__device__ __forceinline__ void beside_products(const Beside& b, const double num_samples_history, const int block) {
-  const int per = (b.xhat.total_tiles + kXcds - 1) / kXcds;
-  if (block >= per * kXcds) {
-    if (block - per * kXcds < b.bt.R) make_bt_row(b.bt, num_samples_history, block - per * kXcds, threadIdx.x, 256);
-    return;
-  }
-  const int unit = block % kXcds * per + block / kXcds;
+__device__ __forceinline__ void beside_products(const Beside& b, const int block) {
+  const int per = (b.xhat.total_tiles + kXcds - 1) / kXcds, unit = block % kXcds * per + block / kXcds;
   if (unit < b.xhat.total_tiles) gemm_unit<64, 64, Beside::kBk, 2, 2, true, false, EPI_SUB_ROWNORM, false, 0, false, kPrefetch>(b.xhat, 0, unit);
+}
+
+// Factors of B_t = J_t + (N (1 - eta) / eta) (D_t + rho_t I) W_t (eq. wt1), while D_t and rho_t are there.
+__device__ __forceinline__ void store_bt_factors(const SmallArgs& a, const UpdateFactors& f, const double* s_dr) {
+  if ((int)threadIdx.x < a.R) a.bt[threadIdx.x] = (float)((double)a.N * (1.0 - f.eta) / f.eta * s_dr[threadIdx.x]);
 }
 
 // Above rank 32, first kernel: Z_t and its reduction.  A workgroup per instance.
@@ -525,7 +524,7 @@ template <int K, bool BESIDE>
 __global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const SmallGroup g, const Beside beside) {
   if constexpr (BESIDE) {
     if ((int)blockIdx.x >= kBesideFirst) {
-      beside_products(beside, g.num_samples_history, (int)blockIdx.x - kBesideFirst);
+      beside_products(beside, (int)blockIdx.x - kBesideFirst);
       return;
     }
     if ((int)blockIdx.x >= g.count) return;
@@ -544,6 +543,7 @@ __global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const Sma
   load.request(a, [](const int i) { return i; });
   const double rho = a.st->rho;
   const UpdateFactors f = update_factors(a, g, a.st->d, rho, s_ise, s_dr, T);
+  store_bt_factors(a, f, s_dr);
   // handed on: the last kernel's workgroups cannot read what one of them replaces
   for (int i = tid; i <= R; i += NT) a.d_rho(T)[i] = i < R ? a.st->d[i] : rho;
   if (tid == 0) *a.k_tickets(T) = 0;
@@ -625,7 +625,7 @@ template <int K, int ITEMS, int NT, bool FUSED, bool BESIDE>
 __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g, const Beside beside) {
   if constexpr (BESIDE) {
     if ((int)blockIdx.x >= kBesideFirst) {
-      if (threadIdx.x < 256) beside_products(beside, g.num_samples_history, (int)blockIdx.x - kBesideFirst);
+      if (threadIdx.x < 256) beside_products(beside, (int)blockIdx.x - kBesideFirst);
       return;
     }
     if ((int)blockIdx.x >= g.count) return;
@@ -669,6 +669,7 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g, cons
   if constexpr (FUSED) load.request(a, [](const int i) { return i; });   // (the upper half of the threads as well, and drops it)
   const UpdateFactors f = update_factors(a, g, FUSED ? st->d : a.d_rho(T), FUSED ? st->rho : a.d_rho(T)[R], s_ise, s_dr, T);
   if constexpr (FUSED) {
+    store_bt_factors(a, f, s_dr);
     static_assert(NT >= 256 && NT >= 16 * T, "all pairs at once");
     typename DirectTile<K, 256>::Regs S;
     load.ordered(a, f, s_ise, s_dr, S, s_fused.t.diag, s_order);
@@ -1079,15 +1080,118 @@ __global__ __launch_bounds__(kSmallThreads) void orth_fix_kernel(const OrthGroup
   if (tid == 0) st->flags = (st->flags & ~kFlagOrthCheck) | kFlagReorth;
 }
 
-// Up to rank 32: W_{t+1} = A_t B_t of one instance, and beside it what finishes the call's output.  256 threads.
-__global__ __launch_bounds__(256) void wnew_finish_kernel(const GemmGroupOf<1> w, const FinishArgs finish) {
-  const int per = (w.total_tiles + kXcds - 1) / kXcds, block = blockIdx.x;
-  if (block >= per * kXcds) {
-    finish_rows<true>(finish, block - per * kXcds);
-    return;
+// W_{t+1} = A_t B_t with B_t = J_t + (its factors) W_t (eq. wt1), and for the instances whose update asked for the orthogonality check
+// (App. B.3.1) W W^T of the new factor, added to K in fp64, and B_t over J, for the second product if the check fails.  A workgroup
+// takes all rows of 64 columns, so it alone reads the columns of W_t that it replaces; a wavefront has 16 of them in registers.
+// Bound: latency.  As three launches (B_t, the product, the gated Gram matrix of its own) the chain behind the eigen-problem was
+// two launches longer.
+struct NewFactorArgs {
+  const PrecondScalars* st;
+  const float* At;
+  const float* bt;
+  float* J;
+  float* W;
+  double* K;
+  int ldat, ld, R, D;
+  int begin;             // first workgroup
+};
+struct NewFactorGroup {
+  int count, total;
+  NewFactorArgs a[kMaxInstances];
+};
+template <int RC>
+__device__ __forceinline__ void new_factor_unit(const NewFactorArgs& a, const int chunk) {
+  constexpr int TJ = RC / 16, LDA = RC + 4, LDT = 68;
+  __shared__ __attribute__((aligned(16))) float lds[RC * (LDA > LDT ? LDA : LDT)];   // A_t, then the workgroup's part of W_(t+1)
+  __shared__ float s_f[RC];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int R = a.R, D = a.D, col = chunk * 64 + wave * 16 + l16, cc = min(col, D - 1);
+  // lane group g takes k = 16 b + 4 g + q in step (b, q), of both operands
+  float jv[TJ][4], wv[TJ][4];
+#pragma unroll
+  for (int b = 0; b < TJ; ++b)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const size_t at = (size_t)min(16 * b + 4 * g4 + q, R - 1) * a.ld + cc;
+      jv[b][q] = a.J[at];
+      wv[b][q] = a.W[at];
+    }
+  for (int e = tid; e < RC * RC / 4; e += 256) {
+    const int i = e / (RC / 4), k = e % (RC / 4) * 4;
+    float4 v = *reinterpret_cast<const float4*>(a.At + (size_t)min(i, R - 1) * a.ldat + k);
+    const int left = i < R ? R - k : 0;
+    v.x = left > 0 ? v.x : 0.f;
+    v.y = left > 1 ? v.y : 0.f;
+    v.z = left > 2 ? v.z : 0.f;
+    v.w = left > 3 ? v.w : 0.f;
+    *reinterpret_cast<float4*>(&lds[i * LDA + k]) = v;
   }
-  const int unit = block % kXcds * per + block / kXcds;
-  if (unit < w.total_tiles) gemm_unit<32, 64, Beside::kBk, 2, 2, true, false, EPI_STORE, false, 0, false, kPrefetch>(w, 0, unit);
+  if (tid < RC) s_f[tid] = tid < R ? a.bt[tid] : 0.f;
+  const bool check = (a.st->flags & kFlagOrthCheck) != 0;   // (uniform)
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < TJ; ++b)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = 16 * b + 4 * g4 + q;
+      const float v = fmaf(s_f[k], wv[b][q], jv[b][q]);
+      jv[b][q] = k < R ? v : 0.f;
+      if (check && k < R && col < D) a.J[(size_t)k * a.ld + col] = v;
+    }
+  floatx4 acc[TJ];
+#pragma unroll
+  for (int t = 0; t < TJ; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int b = 0; b < TJ; ++b) {
+    float4 af[TJ];
+#pragma unroll
+    for (int t = 0; t < TJ; ++t) af[t] = *reinterpret_cast<const float4*>(&lds[(16 * t + l16) * LDA + 16 * b + 4 * g4]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int t = 0; t < TJ; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(pick4(af[t], q), jv[b][q], acc[t], 0, 0, 0);
+  }
+#pragma unroll
+  for (int t = 0; t < TJ; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 16 * t + 4 * g4 + q;
+      if (i < R && col < D) a.W[(size_t)i * a.ld + col] = acc[t][q];
+    }
+  if (!check) return;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < TJ; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) lds[(16 * t + 4 * g4 + q) * LDT + wave * 16 + l16] = col < D ? acc[t][q] : 0.f;
+  __syncthreads();
+  for (int tile = wave; tile < TJ * TJ; tile += 4) {
+    const int i0 = tile / TJ * 16, j0 = tile % TJ * 16;
+    doublex4 c = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 64; k += 4)
+      c = __builtin_amdgcn_mfma_f64_16x16x4f64((double)lds[(i0 + l16) * LDT + k + g4], (double)lds[(j0 + l16) * LDT + k + g4], c, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 4 * r + g4, j = j0 + l16;
+      if (i < R && j < R) unsafeAtomicAdd(a.K + (size_t)i * R + j, c[r]);
+    }
+  }
+}
+// Grid: 64-column blocks of all instances; 256 threads.
+template <int RC>
+__global__ __launch_bounds__(256) void new_factor_kernel(const NewFactorGroup g) {
+  int pi = 0;
+  for (int i = 1; i < g.count; ++i)
+    if ((int)blockIdx.x >= g.a[i].begin) pi = i;
+  new_factor_unit<RC>(g.a[pi], (int)blockIdx.x - g.a[pi].begin);
+}
+// Up to rank 32, one instance: beside it what finishes the call's output.
+__global__ __launch_bounds__(256) void new_factor_finish_kernel(const NewFactorArgs a, const int chunks, const FinishArgs finish) {
+  if ((int)blockIdx.x >= chunks)
+    finish_rows<true>(finish, (int)blockIdx.x - chunks);
+  else
+    new_factor_unit<32>(a, blockIdx.x);
 }
 
 }  // namespace ngsgd

@@ -91,6 +91,29 @@ def test_from_shared_state_matches_oracle(ngsgd, N, D, R, period):
     compare_states(torch, pre, ora, rng)
 
 
+@pytest.mark.parametrize("N,D,R", [(30, 2, 1), (50, 63, 16), (50, 64, 17), (40, 65, 32), (70, 127, 33), (90, 128, 48), (90, 129, 80), (100, 191, 81), (99, 321, 96)])
+def test_updates_at_the_edges_of_the_new_factor(ngsgd, N, D, R):
+    """A single matrix, every call updating: the output goes beside the eigen-problem (above rank 32 and below), the new factor is formed
+    64 columns at a time for rank classes of 32, 80 and 96, with the orthogonality check's products in the same launch; the factor
+    that the calls leave is compared too."""
+    import torch
+    rng = np.random.default_rng(3000 + N + D)
+    kw = dict(num_samples_history=400.0, update_period=1)
+    ora = OnlineNaturalGradient(D, R, **kw)
+    for _ in range(2):
+        ora.precondition(data(rng, N, D))
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, **kw)
+    upload_state(torch, pre, ora)
+    for step in range(4):
+        M = data(rng, N - (step == 2), D)
+        expect, g_o, rn_o = ora.precondition(M)
+        got, g_g, rn_g = gpu_call(torch, pre, M)
+        assert rel(got, expect) < TOL, f"step {step}"
+        assert g_g == pytest.approx(g_o, rel=1e-4)
+        assert rel(rn_g, rn_o) < 2e-4      # the square of a quantity held to 1e-4
+    compare_states(torch, pre, ora, rng)
+
+
 @pytest.mark.parametrize("N,D,R", [(128, 301, 20), (96, 700, 40), (257, 64, 8), (80, 80, 12)])
 def test_free_running_from_device_initialisation(ngsgd, N, D, R):
     """Both sides build their state from the first minibatch (App. B.3.2) and then run the paper's schedule."""
