@@ -12,9 +12,9 @@
 //      independent and any orthonormal basis of their space serves;
 //   4. back with the reflections, a vector per wavefront.
 // The error is a few eps |A| whatever the spectrum.  Bound: the chain of n columns.  Ten instances of the
-// speech-shaped network, five of them with n = 512: 2.3 ms, of it 352 columns 0.73 (a launch each, 14 us for reading and writing 2 MB per
+// speech-shaped network, five of them with n = 512: 2.2 ms, of it 352 columns 0.73 (a launch each, 14 us for reading and writing 2 MB per
 // instance, falling to 6 us: 2.6), the last 160 columns 0.38 ms, eigenvalues 0.14, inverse iteration 0.27,
-// orthonormalisation 0.2, back transformation 0.28, rows of W 0.11.  A reduction needs no iteration; block Jacobi took
+// orthonormalisation 0.2, back transformation 0.15, rows of W 0.11.  A reduction needs no iteration; block Jacobi took
 // 11 to 18 sweeps of 32 launches and did not settle on softmax derivatives within them (12.8 ms).
 // This runs once per process (and after each parameter-averaging round), never inside the steady-state step.
 #pragma once
@@ -935,48 +935,99 @@ __global__ __launch_bounds__(256) void init_ortho_apply_kernel(const InitGroup* 
   }
 }
 
+// Inner products between the reflections of four neighbouring columns, 4 m + p with 4 m + q, p < q, in the order 01 02 03 12 13 23, for
+// the back transformation; to X, which is free by then.  A wavefront per four.  Grid (ceil(n / 16), instance), 256 threads.
+__global__ __launch_bounds__(256) void init_back_products_kernel(const InitGroup* __restrict__ gp) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, n = a.n, np = a.np;
+  if (4 * m > n - 2) return;
+  const double* V[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) V[p] = a.V + (size_t)min(4 * m + p, n - 2) * np;
+  double g[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int c = (4 * m & ~63) + lane; c < np; c += 64) {
+    const double v0 = V[0][c], v1 = V[1][c], v2 = V[2][c], v3 = V[3][c];
+    g[0] = fma(v0, v1, g[0]);
+    g[1] = fma(v0, v2, g[1]);
+    g[2] = fma(v0, v3, g[2]);
+    g[3] = fma(v1, v2, g[3]);
+    g[4] = fma(v1, v3, g[4]);
+    g[5] = fma(v2, v3, g[5]);
+  }
+#pragma unroll
+  for (int p = 0; p < 6; ++p) g[p] = wave_sum_f64(g[p]);
+#pragma unroll
+  for (int p = 0; p < 6; ++p)
+    if (lane == p) a.X[6 * m + p] = g[p];
+}
+
 // Eigenvectors of T -> of A: the reflections, last to first, on a vector per wavefront, which it holds in registers
-// (NC 64-element chunks; chunks where the reflection is zero are neither read nor touched).  Bound: the latency of n
-// dependent inner products, with the reflections requested four steps ahead.  Grid (ceil(R/4), instance), 256 threads.
-constexpr int kBackAhead = 4;
-template <int NC>
+// (NC 64-element chunks).  B reflections at a time: their inner products with the vector as it is, corrected by the ones before through
+// the products between them, so that a chain of two sums serves B; those of the next two blocks are on their way.  Only the
+// loads leave out chunks where a reflection is zero: a branch around work waits for loads in each chunk.
+// n = 512: 148 us and 5 for the products, one reflection at a time 278 (n = 1024, two at a time: 533 and 807; three blocks in flight 173,
+// all chunks without a branch 150 and 642).  Grid (ceil(R/4), instance), 256 threads.
+template <int NC, int B>
 __device__ __forceinline__ void init_back_registers(const InitArgs& a, double* __restrict__ xk, const int lane) {
+  static_assert(B == 2 || B == 4, "pairs within the products of four");
   const int n = a.n, np = a.np;
   const double* __restrict__ V = a.V + lane;
   const double* __restrict__ tau = a.tau();
-  double x[NC], v[kBackAhead][NC];
+  const double* __restrict__ products = a.X;
+  double x[NC], v[2][B][NC], f[2][B], g[2][6];
 #pragma unroll
   for (int c = 0; c < NC; ++c) x[c] = 64 * c < np ? xk[64 * c + lane] : 0.0;
-  auto live = [&](const int c, const int j) { return 64 * c < np && 64 * c + 63 > j; };
-  auto fetch = [&](const int j, const int set) {
-    if (j < 0) return;
+  auto fetch = [&](const int m, const int set) {   // reflections B m .. B m + B - 1; beyond the last one tau is zero
+    if (m < 0) return;
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (live(c, j)) v[set][c] = V[(size_t)j * np + 64 * c];
-  };
-  auto step = [&](const int j, const int set) {
-    if (j < 0) return;
-    double dot[2] = {0.0, 0.0};
+    for (int p = 0; p < B; ++p) {
+      const int j = min(B * m + p, n - 2);
+      f[set][p] = B * m + p <= n - 2 ? tau[j] : 0.0;
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (live(c, j)) dot[c & 1] = fma(v[set][c], x[c], dot[c & 1]);
-    const double f = tau[j] * wave_sum_uniform(dot[0] + dot[1]);
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (live(c, j)) x[c] = fma(-f, v[set][c], x[c]);
-  };
-#pragma unroll
-  for (int t = 0; t < kBackAhead; ++t) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) v[t][c] = 0.0;
-    fetch(n - 2 - t, t);
-  }
-  for (int j = n - 2; j >= 0; j -= kBackAhead) {
-#pragma unroll
-    for (int t = 0; t < kBackAhead; ++t) {
-      step(j - t, t);
-      fetch(j - t - kBackAhead, t);
+      for (int c = 0; c < NC; ++c) {
+        v[set][p][c] = 0.0;
+        if (64 * c < np && 64 * c + 63 > j) v[set][p][c] = V[(size_t)j * np + 64 * c];
+      }
     }
+#pragma unroll
+    for (int p = 0; p < (B == 4 ? 6 : 1); ++p) g[set][p] = products[B == 4 ? 6 * m + p : 6 * (m >> 1) + 5 * (m & 1)];
+  };
+  auto step = [&](const int m, const int set) {
+    if (m < 0) return;
+    double dot[B];
+#pragma unroll
+    for (int p = 0; p < B; ++p) dot[p] = 0.0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int p = 0; p < B; ++p) dot[p] = fma(v[set][p][c], x[c], dot[p]);
+#pragma unroll
+    for (int p = 0; p < B; ++p) dot[p] = wave_sum_f64(dot[p]);
+    double* const t = f[set];
+    if constexpr (B == 4) {
+      const double* const q = g[set];
+      t[3] *= dot[3];
+      t[2] *= fma(-t[3], q[5], dot[2]);
+      t[1] *= fma(-t[2], q[3], fma(-t[3], q[4], dot[1]));
+      t[0] *= fma(-t[1], q[0], fma(-t[2], q[1], fma(-t[3], q[2], dot[0])));
+    } else {
+      t[1] *= dot[1];
+      t[0] *= fma(-t[1], g[set][0], dot[0]);
+    }
+#pragma unroll
+    for (int p = B - 1; p >= 0; --p)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) x[c] = fma(-t[p], v[set][p][c], x[c]);
+  };
+  int m = (n - 2) / B;   // n = 1: nothing
+  if (n < 2) return;
+  fetch(m, 0);
+  fetch(m - 1, 1);
+  for (; m >= 0; m -= 2) {
+    step(m, 0);
+    fetch(m - 2, 0);
+    step(m - 1, 1);
+    fetch(m - 3, 1);
   }
 #pragma unroll
   for (int c = 0; c < NC; ++c)
@@ -988,11 +1039,13 @@ __global__ __launch_bounds__(256) void init_back_kernel(const InitGroup* __restr
   if (k >= a.R) return;
   double* const x = a.A + (size_t)k * np;
   if (np <= 128) {
-    init_back_registers<2>(a, x, lane);
+    init_back_registers<2, 4>(a, x, lane);
+  } else if (np <= 256) {
+    init_back_registers<4, 4>(a, x, lane);
   } else if (np <= 512) {
-    init_back_registers<8>(a, x, lane);
+    init_back_registers<8, 4>(a, x, lane);
   } else if (np <= 1024) {
-    init_back_registers<16>(a, x, lane);
+    init_back_registers<16, 2>(a, x, lane);
   } else {
     for (int j = n - 2; j >= 0; --j) {   // a lane reads and writes only its own elements of x
       const double* const v = a.V + (size_t)j * np;

@@ -584,6 +584,7 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
       hipLaunchKernelGGL(init_ortho_apply_kernel, dim3(np_max / 64, n), dim3(256), 0, s, gd, second);
     }
     LAUNCH_CHECK();
+    hipLaunchKernelGGL(init_back_products_kernel, dim3((n_max + 15) / 16, n), dim3(256), 0, s, gd);
     hipLaunchKernelGGL(init_back_kernel, dim3((r_max + 3) / 4, n), dim3(256), 0, s, gd);
     LAUNCH_CHECK();
     hipLaunchKernelGGL(init_select_kernel, dim3(n), dim3(256), 0, s, gd);
