@@ -1280,7 +1280,18 @@ int simple_many(const std::vector<SimpleCall>& calls, bool scale_output, hipStre
       }
       if (!rows.empty()) NG_TRY(launch_layer_gemms(GEMM_BWD, rows.data(), (int)rows.size(), s));
       if (!cols.empty()) NG_TRY(launch_layer_gemms(GEMM_FWD, cols.data(), (int)cols.size(), s));
-      hipLaunchKernelGGL(simple_rows_kernel, dim3(n_max, cnt), dim3(256), 0, s, g);
+      // the scaled output in one go where the elimination's buffer holds a number per row (of a tall, very narrow matrix it does not)
+      bool late = scale_output;
+      for (int i = 0; i < cnt; ++i) late = late && (size_t)g.a[i].N <= (size_t)g.a[i].np * g.a[i].np;
+      if (late) {
+        hipLaunchKernelGGL(simple_rows_kernel<true>, dim3(n_max, cnt), dim3(256), 0, s, g);
+        LAUNCH_CHECK();
+        hipLaunchKernelGGL(simple_scale_kernel, dim3((n_max + kSimpleScaleRows - 1) / kSimpleScaleRows, cnt), dim3(256), 0, s, g);
+        LAUNCH_CHECK();
+        done += cnt;
+        continue;
+      }
+      hipLaunchKernelGGL(simple_rows_kernel<false>, dim3(n_max, cnt), dim3(256), 0, s, g);
       LAUNCH_CHECK();
       hipLaunchKernelGGL(simple_gamma_kernel, dim3(cnt), dim3(256), 0, s, g);
       LAUNCH_CHECK();

@@ -322,23 +322,37 @@ __global__ __launch_bounds__(256) void simple_sweep_kernel(const SimpleGroup g, 
   }
 }
 
-// a_i = x_i . q_i, b_i = 1 + a_i / (N - 1 - a_i), xhat_i = b_i q_i (App. A.3), ||xhat_i||^2.  Grid (N_max, count).
+// a_i = x_i . q_i, b_i = 1 + a_i / (N - 1 - a_i), xhat_i = b_i q_i (App. A.3), ||xhat_i||^2.  With LATE b_i goes to the elimination's
+// first buffer (done with by then) and xhat_i is left to the kernel that scales.  A row's first 5120 columns are requested at once and stay in
+// registers.  Grid (N_max, count).
+template <bool LATE>
 __global__ __launch_bounds__(256) void simple_rows_kernel(const SimpleGroup g) {
   const SimpleArgs& a = g.a[blockIdx.y];
   const int i = blockIdx.x;
   if (i >= a.N) return;
+  constexpr int AHEAD = 5;
   __shared__ double scratch[16];
   const int tid = threadIdx.x, D = a.D, D4 = D >> 2;
   float* __restrict__ x = a.M + (size_t)i * a.ld;           // rows start on 16-byte boundaries
   const float* __restrict__ q = a.Q + (size_t)i * a.ldq;
   float4* __restrict__ x4 = reinterpret_cast<float4*>(x);
   const float4* __restrict__ q4 = reinterpret_cast<const float4*>(q);
+  float4 xr[AHEAD], qr[AHEAD];
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) {
+    const int c = min(tid + 256 * u, max(D4 - 1, 0));
+    xr[u] = D4 > 0 ? x4[c] : q4[c];   // (a last row shorter than a piece may end the caller's memory)
+    qr[u] = q4[c];
+  }
   double dot = 0.0, qq = 0.0;
-  for (int c = tid; c < D4; c += 256) {
-    const float4 xv = x4[c], qv = q4[c];
+  auto piece = [&](const float4& xv, const float4& qv) {
     dot += (double)xv.x * qv.x + (double)xv.y * qv.y + (double)xv.z * qv.z + (double)xv.w * qv.w;
     qq += (double)qv.x * qv.x + (double)qv.y * qv.y + (double)qv.z * qv.z + (double)qv.w * qv.w;
-  }
+  };
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u)
+    if (tid + 256 * u < D4) piece(xr[u], qr[u]);
+  for (int c = tid + 256 * AHEAD; c < D4; c += 256) piece(x4[c], q4[c]);
   for (int c = 4 * D4 + tid; c < D; c += 256) {
     const double xv = x[c], qv = q[c];
     dot += xv * qv;
@@ -347,12 +361,56 @@ __global__ __launch_bounds__(256) void simple_rows_kernel(const SimpleGroup g) {
   dot = block_sum(dot, scratch);
   qq = block_sum(qq, scratch);
   const double b = 1.0 + dot / ((double)(a.N - 1) - dot);
-  for (int c = tid; c < D4; c += 256) {
-    const float4 qv = q4[c];
-    x4[c] = make_float4((float)(b * qv.x), (float)(b * qv.y), (float)(b * qv.z), (float)(b * qv.w));
+  if (tid == 0) {
+    a.prow[i] = b * b * qq;
+    if (LATE) a.buf[0][i] = b;
   }
+  if (LATE) return;
+  auto scaled = [&](const float4& v) { return make_float4((float)(b * v.x), (float)(b * v.y), (float)(b * v.z), (float)(b * v.w)); };
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u)
+    if (tid + 256 * u < D4) x4[tid + 256 * u] = scaled(qr[u]);
+  for (int c = tid + 256 * AHEAD; c < D4; c += 256) x4[c] = scaled(q4[c]);
   for (int c = 4 * D4 + tid; c < D; c += 256) x[c] = (float)(b * (double)q[c]);
-  if (tid == 0) a.prow[i] = b * b * qq;
+}
+
+// gamma as below by every workgroup, and gamma Xhat from Q and what simple_rows_kernel<true> left: X is written once (a launch each for
+// Xhat, gamma and the scaling, 512 x 5000: 9.4 + 4.0 + 6.8 us; now 5.5 + 9.4).  Grid (ceil(N_max / 2), count), 256 threads, two rows.
+constexpr int kSimpleScaleRows = 2;
+__global__ __launch_bounds__(256) void simple_scale_kernel(const SimpleGroup g) {
+  const SimpleArgs& a = g.a[blockIdx.y];
+  constexpr int WIDTH = 256 / kSimpleScaleRows, AHEAD = 10;
+  __shared__ double scratch[16];
+  const int tid = threadIdx.x, D = a.D, D4 = D >> 2, row0 = blockIdx.x * kSimpleScaleRows, i = row0 + tid / WIDTH, c0 = tid % WIDTH;
+  if (row0 >= a.N) return;
+  const int ic = min(i, a.N - 1);
+  const float* __restrict__ q = a.Q + (size_t)ic * a.ldq;
+  const float4* __restrict__ q4 = reinterpret_cast<const float4*>(q);
+  float* __restrict__ x = a.M + (size_t)ic * a.ld;
+  float4* __restrict__ x4 = reinterpret_cast<float4*>(x);
+  float4 qr[AHEAD];
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) qr[u] = q4[min(c0 + WIDTH * u, max(D4 - 1, 0))];
+  const double b = a.buf[0][ic], p = a.prow[ic];
+  double den = 0.0;
+  for (int r = tid; r < a.N; r += 256) den += a.prow[r];
+  den = block_sum(den, scratch);
+  const double gamma = den > 0.0 ? sqrt(a.scal[0] / den) : 1.0;
+  if (blockIdx.x == 0 && tid == 0) {
+    *a.gamma = gamma;
+    if (a.gamma_out != nullptr) *a.gamma_out = (float)gamma;
+  }
+  if (i >= a.N) return;
+  if (c0 == 0 && a.rownorm2_out != nullptr) a.rownorm2_out[i] = (float)(gamma * gamma * p);
+  const float s = (float)gamma;
+  auto scaled = [&](const float4& v) {
+    return make_float4(s * (float)(b * v.x), s * (float)(b * v.y), s * (float)(b * v.z), s * (float)(b * v.w));
+  };
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u)
+    if (c0 + WIDTH * u < D4) x4[c0 + WIDTH * u] = scaled(qr[u]);
+  for (int c = c0 + WIDTH * AHEAD; c < D4; c += WIDTH) x4[c] = scaled(q4[c]);
+  if (c0 < D - 4 * D4) x[4 * D4 + c0] = s * (float)(b * (double)q[4 * D4 + c0]);
 }
 
 // gamma = sqrt(tr(X^T X) / tr(Xhat^T Xhat)), 1 if the denominator is 0 (App. A.2).  Grid (count), 256 threads.

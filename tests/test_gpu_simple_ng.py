@@ -57,6 +57,20 @@ def test_small_shapes_match_the_definition(ngsgd, N, D):
     assert abs(np.linalg.norm(got.astype(np.float64)) / np.linalg.norm(M.astype(np.float64)) - 1.0) < 1e-5
 
 
+@pytest.mark.parametrize("N,D", [(5, 1), (6, 3), (1024, 2), (1025, 2), (33, 5119), (34, 5121), (7, 5130)])
+def test_scaled_output_at_the_edges_of_its_pieces(ngsgd, N, D):
+    """Rows shorter than a piece of four, rows of what a workgroup keeps in registers and a little more, an odd last row; the most
+    rows of a narrow matrix whose elimination buffer (32 x 32) still holds a number per row, and one more."""
+    import torch
+    rng = np.random.default_rng(1500 + N + D)
+    M = data(rng, N, D, decay=0.9995)
+    got, g_g, rn_g = gpu_call(torch, ngsgd.SimplePreconditioner(N, D), M)
+    want, g_o, rn_o = simple_ng(M.astype(np.float64))
+    assert rel(got, want) < TOL
+    assert g_g == pytest.approx(g_o, rel=1e-4)
+    assert rel(rn_g, rn_o) < 2e-4      # the square of a quantity held to 1e-4
+
+
 @pytest.mark.parametrize("N,D", [(200, 301), (333, 77), (130, 520), (257, 1000)])
 def test_medium_shapes_and_reuse(ngsgd, N, D):
     """Several tiles and pivot blocks; the same workspace serves calls with fewer rows and a padded ld."""
