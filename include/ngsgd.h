@@ -266,7 +266,9 @@ const char* ngsgd_strerror(int code);
  * is bounded: after this many microseconds (default 2000) a workgroup stops waiting and leaves its part
  * of the matrix to the (slow) completion step of the following kernel, so the kernel ends whatever else
  * occupies the GPU.  0 makes every workgroup take that route at once unless its partners have already
- * finished (used by the tests of that route).  Process-wide. */
+ * finished (used by the tests of that route).  The workgroups that share a matrix while a first factor is
+ * built wait as long for each other to be running; then the following kernel reduces that matrix alone
+ * (512 rows: some milliseconds instead of 0.7).  Process-wide. */
 int ngsgd_set_wait_limit_us(int64_t microseconds);
 /* hipError_t value of the most recent failed HIP call on this thread (0 if none). */
 int ngsgd_last_hip_error(void);

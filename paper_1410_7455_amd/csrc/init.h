@@ -12,7 +12,7 @@
 //      independent and any orthonormal basis of their space serves;
 //   4. back with the reflections, a vector per wavefront.
 // The error is a few eps |A| whatever the spectrum.  Bound: the chain of n columns.  Ten instances of the
-// speech-shaped network, five of them with n = 512: 2.2 ms, of it 352 columns 0.73 (a launch each, 14 us for reading and writing 2 MB per
+// speech-shaped network, five of them with n = 512: 2.0 ms, of it 352 columns 0.73 (a launch each, 14 us for reading and writing 2 MB per
 // instance, falling to 6 us: 2.6), the last 160 columns 0.38 ms, eigenvalues 0.14, inverse iteration 0.27,
 // orthonormalisation 0.2, back transformation 0.15, rows of W 0.11.  A reduction needs no iteration; block Jacobi took
 // 11 to 18 sweeps of 32 launches and did not settle on softmax derivatives within them (12.8 ms).
@@ -52,6 +52,7 @@ struct InitArgs {
   int* idx;            // R: row of the eigenvector matrix for each kept eigenpair, -1 if the direction is null
   float* W;            // R x ldw
   int ldw;
+  int place;           // rows kept on the chip: launch x kTriDies + die, -1: not
   double* vwork;       // kMaxRank + D doubles
 
   __device__ double* G() const { return X + (size_t)np * rq; }   // rq x rq: Gram matrix of X, then the inverse of its Cholesky factor
@@ -241,14 +242,15 @@ __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __r
 // A slot is emptied by its writer two columns later (all of the instance have then read it: the elements of the column between were
 // sent behind that) and written again two columns after that; the wait for the counter of memory operations between makes the
 // emptying visible before the writer's next elements, which a reader of the new ones has seen.
-// Where all of an instance run on one die (matrices of up to 512 rows are dealt to the dies, workgroup b to die b mod 8; the workgroups tell each
+// Where all of an instance run on one die (matrices of up to 512 rows are dealt to the dies, the largest first to the one with the
+// fewest workgroups, workgroup b to die b mod 8; the workgroups tell each
 // other where they are before they start) ordinary stores do, which a reader behind the same L2 cache sees after 0.25 us; otherwise
 // stores at device scope, 0.6 to 0.8 us.
 // Progress: a workgroup first waits until all of its instance are running, for at most `limit` ticks.  If they are not, one closes the gate,
 // all leave, and the kernel behind reduces the matrix alone, as if a wait inside takes longer than kTriLost.  The matrix in memory
 // stays as it was until then; the last 160 rows and columns go to the same places of V.
-// Bound: the exchange and the chain of two sums over a wavefront.  One instance of 512 rows 2.07 us a column, ten alike (dealt to the dies; all
-// with stores at device scope 3.9 us in the first version, 3.35 one alone); 1024 rows 3.1 us.
+// Bound: the exchange and the chain of two sums over a wavefront.  One instance of 512 rows 2.07 us a column, the ten of a speech-shaped network 2.09 (with stores at
+// device scope 3.9 us in the first version, 3.35 one alone; dealt in turn, two dies with two large ones, 2.5); 1024 rows 3.1 us.
 constexpr int kTriResident = 1024;                    // largest padded size
 constexpr int kTriDies = 8, kTriDieUnits = 2 * 32;    // workgroups of a die: two per compute unit
 constexpr int kTriResidentUnits = kTriDies * kTriDieUnits;
@@ -286,19 +288,21 @@ __device__ __forceinline__ void ring_store(uint64_t* const p, const uint64_t v, 
 }
 
 template <int CH, int ROWS>
-__global__ __launch_bounds__(256, 2) void init_tri_resident_kernel(const InitGroup* __restrict__ gp, const int first, const int count,
+__global__ __launch_bounds__(256, 2) void init_tri_resident_kernel(const InitGroup* __restrict__ gp, const int launch,
                                                                    const long long limit) {
   constexpr int C = 64 * CH, T = CH / 4;
   constexpr bool kDeal = tri_on_one_die(C);
-  // instance `at` of the launch: one after the other, or every eighth on this die
-  int at = kDeal ? blockIdx.x % kTriDies : 0, unit = kDeal ? blockIdx.x / kTriDies : blockIdx.x, units = 0;
-  for (; at < count; at += kDeal ? kTriDies : 1) {
-    units = tri_resident_units(gp->a[first + at].n, 4 * ROWS);
+  // the instance: those of this launch one after the other, or those of this launch and die
+  const int bin = launch * kTriDies + (kDeal ? (int)blockIdx.x % kTriDies : 0), count = gp->count;
+  int at = 0, unit = kDeal ? blockIdx.x / kTriDies : blockIdx.x, units = 0;
+  for (; at < count; ++at) {
+    if (gp->a[at].place != bin) continue;
+    units = tri_resident_units(gp->a[at].n, 4 * ROWS);
     if (unit < units) break;
     unit -= units;
   }
   if (at >= count) return;
-  const InitArgs& a = gp->a[first + at];
+  const InitArgs& a = gp->a[at];
   const int n = a.n, np = a.np, end = n - kTriTail;
   __shared__ double sy[2][C], sx[2][C], sv[2][C];   // A v, the row and the reflection of the last column, alternately
   __shared__ int s_run, s_lost;

@@ -468,8 +468,34 @@ struct PrecondCall {
 };
 
 // How long a workgroup of the fused apply kernel waits for the other column chunks of its row block before it
-// forms the H rows itself (microseconds; the kernel's clock runs at 100 MHz).
+// leaves its patch to the finishing kernel, and one of the initialisation's reduction for the others of its matrix to be running
+// (microseconds; the kernels' clock runs at 100 MHz).
 std::atomic<long long> g_fused_wait_us{2000};
+
+// Deals the instances to launches of as many workgroups as can be resident together, and to the dies where an instance fits one: the
+// largest first, each to the die with the fewest workgroups.
+void plan_resident(InitGroup& g, const int np_max, std::vector<int>& launch_units) {
+  const bool deal = tri_on_one_die(np_max);
+  const int bins = deal ? kTriDies : 1, room = deal ? kTriDieUnits : kTriResidentUnits;
+  int order[kMaxInstances], load[kTriDies] = {};
+  for (int i = 0; i < g.count; ++i) order[i] = i;
+  std::stable_sort(order, order + g.count, [&](const int x, const int y) { return g.a[x].n > g.a[y].n; });
+  for (int o = 0; o < g.count; ++o) {
+    InitArgs& a = g.a[order[o]];
+    const int u = tri_resident_units(a.n, tri_resident_rows(np_max));
+    a.place = -1;
+    if (u == 0) continue;
+    int* bin = std::min_element(load, load + bins);
+    if (launch_units.empty() || *bin + u > room) {
+      launch_units.push_back(0);
+      std::fill(load, load + bins, 0);
+      bin = load;
+    }
+    a.place = ((int)launch_units.size() - 1) * kTriDies + (int)(bin - load);
+    *bin += u;
+    launch_units.back() = bins * *std::max_element(load, load + bins);
+  }
+}
 
 int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
   ProfScope prof(NGSGD_PROF_INIT, s);
@@ -508,6 +534,9 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
       g.epsilon = p.epsilon;
     }
     const int np_max = (int)align_up(n_max, kInitPad), rq_max = (int)align_up(r_max, 16);
+    const bool resident = np_max <= kTriResident;
+    std::vector<int> launch_units;   // workgroups of each launch of the reduction that keeps the rows on the chip
+    if (resident) plan_resident(g, np_max, launch_units);
     InitGroup* gd = calls[done].p->init_group;
     static_assert(sizeof(InitGroup) % sizeof(uint32_t) == 0 && sizeof(InitGroup) <= 4096, "copied word by word");
     hipLaunchKernelGGL(init_store_group_kernel, dim3(1), dim3(256), 0, s, g, gd);
@@ -535,27 +564,13 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
       hipLaunchKernelGGL(init_mirror_kernel, dim3(np_max / 32, np_max / 32, n), dim3(256), 0, s, gd);
       LAUNCH_CHECK();
     }
-    const bool resident = np_max <= kTriResident;
-    const int rows = tri_resident_rows(np_max);
-    for (int first = 0; resident && n_max > kTriTail && first < n;) {   // as many instances at a time as can be resident together
-      const bool deal = tri_on_one_die(np_max);
-      int count = 0, units = 0, die_units[kTriDies] = {}, die_max = 0;
-      for (; first + count < n; ++count) {
-        const int u = tri_resident_units(g.a[first + count].n, rows), die = count % kTriDies;
-        if (deal ? die_units[die] + u > kTriDieUnits : units + u > kTriResidentUnits) break;
-        units += u;
-        die_units[die] += u;
-        die_max = std::max(die_max, die_units[die]);
-      }
-      const long long limit = g_fused_wait_us.load() * 100;
-      if (units > 0) {
-        if (deal)
-          hipLaunchKernelGGL((init_tri_resident_kernel<8, 4>), dim3(kTriDies * die_max), dim3(256), 0, s, gd, first, count, limit);
-        else
-          hipLaunchKernelGGL((init_tri_resident_kernel<16, 2>), dim3(units), dim3(256), 0, s, gd, first, count, limit);
-        LAUNCH_CHECK();
-      }
-      first += count;
+    const long long limit = g_fused_wait_us.load() * 100;
+    for (size_t l = 0; l < launch_units.size(); ++l) {
+      if (tri_on_one_die(np_max))
+        hipLaunchKernelGGL((init_tri_resident_kernel<8, 4>), dim3(launch_units[l]), dim3(256), 0, s, gd, (int)l, limit);
+      else
+        hipLaunchKernelGGL((init_tri_resident_kernel<16, 2>), dim3(launch_units[l]), dim3(256), 0, s, gd, (int)l, limit);
+      LAUNCH_CHECK();
     }
     for (int j = 0; !resident && j < n_max - kTriTail; ++j) {
       const int groups = (n_max - j - 1 + 4 * kTriRows - 1) / (4 * kTriRows);
