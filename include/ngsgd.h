@@ -137,8 +137,8 @@ int ngsgd_precond_get_state(const ngsgd_precond* p, float* dev_W, double* dev_d,
 
 /* Diagnostics of the latest factor update, copied to HOST memory after waiting for the stream:
  * flags (bit 0: orthogonality check still pending, 1: an eigenvalue of Z_t was floored, 2: the factor was
- * re-orthogonalised (App. B.3.1), 3: the eigen-solver hit its sweep limit) and the Jacobi sweeps it used (1 where the
- * direct solver served). */
+ * re-orthogonalised (App. B.3.1), 3: the eigen-solver hit its sweep limit; 4, of the latest first factor: its matrix was
+ * reduced from memory, see ngsgd_set_wait_limit_us) and the Jacobi sweeps it used (1 where the direct solver served). */
 int ngsgd_precond_diagnostics(const ngsgd_precond* p, int32_t* flags_host, int32_t* sweeps_host,
                               void* hip_stream);
 
@@ -266,9 +266,10 @@ const char* ngsgd_strerror(int code);
  * is bounded: after this many microseconds (default 2000) a workgroup stops waiting and leaves its part
  * of the matrix to the (slow) completion step of the following kernel, so the kernel ends whatever else
  * occupies the GPU.  0 makes every workgroup take that route at once unless its partners have already
- * finished (used by the tests of that route).  The workgroups that share a matrix while a first factor is
- * built wait as long for each other to be running; then the following kernel reduces that matrix alone
- * (512 rows: some milliseconds instead of 0.7).  Process-wide. */
+ * finished (used by the tests of that route).  The workgroups that share a matrix of 161 to 1024 rows while a
+ * first factor is built wait for each other to be running: twice as long up to 512 rows, six times above.  Then they
+ * leave, and the following kernel reduces that matrix from memory (a call with a first factor of 512 rows takes
+ * 3.3 ms instead of 1.9, of 1024 rows 11.0 instead of 5.2).  0 sends every such matrix there.  Process-wide. */
 int ngsgd_set_wait_limit_us(int64_t microseconds);
 /* hipError_t value of the most recent failed HIP call on this thread (0 if none). */
 int ngsgd_last_hip_error(void);

@@ -182,7 +182,7 @@ class Preconditioner:
         return W, d, float(rho.item()), t.value
 
     def diagnostics(self):
-        """(flags, Jacobi sweeps) of the latest factor update; waits for the stream."""
+        """(flags, Jacobi sweeps) of the latest factor update (flag 16: of the latest first factor); waits for the stream."""
         flags, sweeps = c_int32(0), c_int32(0)
         _check(self.lib.ngsgd_precond_diagnostics(self.handle, byref(flags), byref(sweeps), _stream_ptr()),
                "ngsgd_precond_diagnostics")
@@ -346,7 +346,7 @@ def profile_read():
 
 
 def set_wait_limit_us(microseconds: int) -> None:
-    """ngsgd_set_wait_limit_us: bound of the fused apply kernel's wait between workgroups."""
+    """ngsgd_set_wait_limit_us: bound of the waits between workgroups (fused apply kernel, first factors)."""
     _check(load_library().ngsgd_set_wait_limit_us(int(microseconds)), "ngsgd_set_wait_limit_us")
 
 

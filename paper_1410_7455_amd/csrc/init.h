@@ -62,9 +62,9 @@ struct InitArgs {
   __device__ double* tau() const { return T + 2 * np; }          // the reflections' factors
   __device__ double* y(const int parity) const { return T + (3 + parity) * (size_t)np; }   // A v of the last two columns
   // Rows kept on the chip: what column j leaves for the next, A v and the next row, four columns in turn (before sdiag and bounds
-  // are there), the count of workgroups that are running and their dies
+  // are there); the count of workgroups that are running and their dies, and behind a closed gate the units taken and done
   __device__ double* ring(const int j) const { return T + (3 + 2 * (j & 3)) * (size_t)np; }
-  __device__ int* gate() const { return idx; }
+  __device__ int* gate() const { return st->gate; }
   __device__ double* bounds() const { return T + 5 * (size_t)np; }   // interval that holds T's eigenvalues, largest magnitude in it
   __device__ double* sdiag() const { return T + 6 * (size_t)np; }    // T scaled to unit norm: diagonal, squared off-diagonal
   __device__ double* soff2() const { return T + 7 * (size_t)np; }
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void init_mirror_kernel(const InitGroup* __res
   if (blockIdx.x == 0 && blockIdx.y == 0) {
     uint64_t* const ring = reinterpret_cast<uint64_t*>(a.ring(0));
     for (int i = threadIdx.x; i < 8 * np; i += 256) ring[i] = kRingEmpty;
-    if (threadIdx.x < 2) a.gate()[threadIdx.x] = 0;
+    if (threadIdx.x < kGateWords) a.gate()[threadIdx.x] = 0;
   }
   if (i0 >= np || j0 >= np || i0 / kSymGramTile <= j0 / kSymGramTile) return;
   __shared__ double t[32][33];
@@ -118,13 +118,9 @@ constexpr int kTriRows = 4;                   // rows per wavefront
 constexpr int kTriChunks = 8;                 // 64-column chunks held in registers
 constexpr int kTriCols = 2;                   // columns per thread requested together in the vector phase
 constexpr int kTriLdsCols = 2048;
-__global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __restrict__ gp, const int j, const int phases) {
-  const InitArgs& a = gp->a[blockIdx.y];
-  const int n = a.n, np = a.np;
-  if (j >= n - kTriTail) return;   // uniform over the workgroup, as below
-  const int wg_row = j + 1 + (int)blockIdx.x * 4 * kTriRows;
-  if (phases == 1 ? blockIdx.x != 0 : wg_row >= n) return;
-  extern __shared__ double dyn_tri[];
+__host__ __device__ inline int tri_step_units(const int n, const int j) { return (n - j - 1 + 4 * kTriRows - 1) / (4 * kTriRows); }
+__device__ __forceinline__ void tri_step(const InitArgs& a, const int j, const int phases, const int unit, double* const dyn_tri) {
+  const int n = a.n, np = a.np, wg_row = j + 1 + unit * 4 * kTriRows;
   __shared__ double red[2][4];
   double* const vo = phases == 3 ? dyn_tri : a.vec();   // the last column's v and w, and the new v
   double* const wo = vo + np;
@@ -195,13 +191,13 @@ __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __r
     const double dj = vn[j];
     __syncthreads();
     for (int c = b0 + tid; c < np; c += 256) vn[c] = c > j + 1 ? vn[c] * h.scale : (c == j + 1 ? 1.0 : 0.0);
-    if (blockIdx.x == 0 && tid == 0) {
+    if (unit == 0 && tid == 0) {
       a.diag()[j] = dj;
       a.off()[j] = h.beta;
       a.tau()[j] = h.tau;
     }
     __syncthreads();
-    if (blockIdx.x == 0)
+    if (unit == 0)
       for (int c = tid; c < np; c += 256) a.V[(size_t)j * np + c] = c > j ? vn[c] : 0.0;
   }
   if (!(phases & 2)) return;
@@ -233,6 +229,13 @@ __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __r
     if (lane == 0 && row0 + q < n) a.y(j & 1)[row0 + q] = acc[q];
   }
 }
+__global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __restrict__ gp, const int j, const int phases) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  if (j >= a.n - kTriTail) return;   // uniform over the workgroup, as below
+  if ((int)blockIdx.x >= (phases == 1 ? 1 : tri_step_units(a.n, j))) return;
+  extern __shared__ double dyn_tri[];
+  tri_step(a, j, phases, blockIdx.x, dyn_tri);
+}
 
 // The same columns in one launch: every workgroup keeps its rows in registers (CH 64-column chunks, ROWS rows per wavefront) and the
 // workgroups of an instance exchange A v and the next row, element i of both from the workgroup of row i, through memory.
@@ -247,21 +250,26 @@ __global__ __launch_bounds__(256) void init_tri_step_kernel(const InitGroup* __r
 // other where they are before they start) ordinary stores do, which a reader behind the same L2 cache sees after 0.25 us; otherwise
 // stores at device scope, 0.6 to 0.8 us.
 // Progress: a workgroup first waits until all of its instance are running, for at most `limit` ticks.  If they are not, one closes the gate,
-// all leave, and the kernel behind reduces the matrix alone, as if a wait inside takes longer than kTriLost.  The matrix in memory
+// all leave, and the kernel behind reduces the matrix from memory, as if a wait inside takes longer than kTriLost.  The matrix in memory
 // stays as it was until then; the last 160 rows and columns go to the same places of V.
+// Launches of several streams fill the chip together: an instance whose last workgroups are not placed yet waits for another one's
+// reduction to end.
 // Bound: the exchange and the chain of two sums over a wavefront.  One instance of 512 rows 2.07 us a column, the ten of a speech-shaped network 2.09 (with stores at
 // device scope 3.9 us in the first version, 3.35 one alone; dealt in turn, two dies with two large ones, 2.5); 1024 rows 3.1 us.
 constexpr int kTriResident = 1024;                    // largest padded size
 constexpr int kTriDies = 8, kTriDieUnits = 2 * 32;    // workgroups of a die: two per compute unit
 constexpr int kTriResidentUnits = kTriDies * kTriDieUnits;
 constexpr long long kTriLost = 100000000;             // ticks (10 ns)
-constexpr int kGateClosed = 1 << 30;
 constexpr bool tri_on_one_die(const int np) { return np <= 512; }
 constexpr int tri_resident_rows(const int np) { return np <= 512 ? 16 : 8; }   // rows of a workgroup
 __host__ __device__ inline int tri_resident_units(const int n, const int rows) { return n > kTriTail ? (n + rows - 1) / rows : 0; }
 
 // 0: not all are; 2: all on one die; 1 otherwise.
 __device__ __forceinline__ int init_all_running(int* const gate, const int units, const long long limit) {
+  if (limit == 0) {   // no time to wait
+    __hip_atomic_fetch_or(gate, kGateClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return 0;
+  }
   const int die = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID
   const int others = __hip_atomic_fetch_or(gate + 1, 1 << die, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("" : : "v"(others) : "memory");   // it has been performed
@@ -472,56 +480,40 @@ __global__ __launch_bounds__(256, 2) void init_tri_resident_kernel(const InitGro
     }
 }
 
-// The same columns by one workgroup of 256 threads, for an instance whose gate was closed.  `red`: 8 doubles.
-__device__ void init_tri_alone(const InitArgs& a, const int end, double* const red) {
-  const int n = a.n, np = a.np, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double *const v = a.vec(), *const w = v + np, *const vn = w + np;
-  double tau = 0.0;
-  for (int j = 0; j < end; ++j) {
-    const double* const y = a.y((j & 1) ^ 1);
-    double* const out = a.y(j & 1);
-    const double vj = j > 0 ? vn[j] : 0.0, yj = j > 0 ? y[j] : 0.0;
-    double s = 0.0, sigma = 0.0;
-    if (j > 0)
-      for (int c = j + tid; c < n; c += 256) s = fma(y[c], vn[c], s);
-    const double half = 0.5 * tau * tau * block256_sum_f64(s, red);
-    const double wj = fma(tau, yj, -half * vj);
-    for (int c = j + tid; c < n; c += 256) {
-      const double vc = j > 0 ? vn[c] : 0.0, wc = j > 0 ? fma(tau, y[c], -half * vc) : 0.0;
-      const double x = fma(-wj, vc, fma(-vj, wc, a.A[(size_t)j * np + c]));
-      v[c] = vc;
-      w[c] = wc;
-      vn[c] = x;
-      if (c > j + 1) sigma = fma(x, x, sigma);
-    }
-    sigma = block256_sum_f64(sigma, red + 4);
-    const Reflection h = reflection(vn[j + 1], sigma);
-    tau = h.tau;
+// The same columns from memory, for the instances whose gate was closed: whatever workgroups are running take the units of
+// init_tri_step_kernel's launches one after the other, column by column.  A unit begins when all of the columns before its own are
+// done; the workgroups that hold those are running, so every wait ends, however few there are and whenever the others come.
+// Order across the dies as at the boundaries of launches: a workgroup's stores are written back before its unit counts as done, what
+// its die holds of the others' is dropped before it begins the next.
+// Bound: that exchange, as for the launches: 512 rows 3.27 ms a call, 1024 rows 10.97 (a launch per column 3.37 and 10.2, rows kept
+// on the chip 1.86 and 5.2).  By one workgroup a network's first factors of 1024 rows took 0.65 s.
+// Grid (units, instance), 256 threads, 3 np doubles of LDS.
+constexpr int kTriSharedUnits = 64;   // workgroups of an instance
+__global__ __launch_bounds__(256) void init_tri_shared_kernel(const InitGroup* __restrict__ gp) {
+  const InitArgs& a = gp->a[blockIdx.y];
+  const int n = a.n, end = n - kTriTail, tid = threadIdx.x;
+  if (end <= 0 || *a.gate() < kGateClosed) return;
+  extern __shared__ double dyn_tri[];
+  __shared__ int s_unit;
+  int j = 0, before = 0;   // units of the columns before j
+  for (;;) {
+    if (tid == 0) s_unit = __hip_atomic_fetch_add(a.gate() + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int unit = s_unit;
+    for (; j < end && unit - before >= tri_step_units(n, j); ++j) before += tri_step_units(n, j);
+    if (j >= end) return;   // (uniform)
     if (tid == 0) {
-      a.diag()[j] = vn[j];
-      a.off()[j] = h.beta;
-      a.tau()[j] = h.tau;
+      while (__hip_atomic_load(a.gate() + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < before) __builtin_amdgcn_s_sleep(4);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
-    for (int c = tid; c < np; c += 256) {
-      const double r = c > j + 1 && c < n ? vn[c] * h.scale : (c == j + 1 ? 1.0 : 0.0);
-      if (c > j && c < n) vn[c] = r;
-      a.V[(size_t)j * np + c] = r;
-    }
+    tri_step(a, j, 3, unit - before, dyn_tri);
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");   // every wavefront's stores are in the die's L2 cache
     __syncthreads();
-    for (int i = j + 1 + wave; i < n; i += 4) {
-      double* const row = a.A + (size_t)i * np;
-      const double vr = v[i], wr = w[i];
-      double acc = 0.0;
-      for (int c = j + 1 + lane; c < n; c += 64) {
-        const double t = fma(-wr, v[c], fma(-vr, w[c], row[c]));
-        row[c] = t;
-        acc = fma(t, vn[c], acc);
-      }
-      acc = wave_sum_uniform(acc);
-      if (lane == 0) out[i] = acc;
+    if (tid == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(a.gate() + 3, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
   }
 }
 
@@ -545,8 +537,7 @@ __global__ __launch_bounds__(256) void init_tri_tail_kernel(const InitGroup* __r
   const double inv_n = 1.0 / (double)a.N;
   double* const v = sv[wave];
   double* const w = sw[wave];
-  const bool alone = resident != 0 && j0 > 0 && *a.gate() >= kGateClosed, kept = resident != 0 && j0 > 0 && !alone;   // (uniform)
-  if (alone) init_tri_alone(a, j0, scratch);
+  const bool kept = resident != 0 && j0 > 0 && *a.gate() < kGateClosed;   // (uniform) the columns before have left their rest in V
   const double* const from = kept ? a.V : a.A;
   double S[K][K];
 #pragma unroll

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <cstring>
 #include <new>
@@ -468,9 +469,12 @@ struct PrecondCall {
 };
 
 // How long a workgroup of the fused apply kernel waits for the other column chunks of its row block before it
-// leaves its patch to the finishing kernel, and one of the initialisation's reduction for the others of its matrix to be running
-// (microseconds; the kernels' clock runs at 100 MHz).
+// leaves its patch to the finishing kernel (microseconds; the kernels' clock runs at 100 MHz).
 std::atomic<long long> g_fused_wait_us{2000};
+// One of the initialisation's reduction waits so many times as long for the others of its matrix to be running: what other streams
+// have in front of them are reductions like its own, of up to 0.74 and 2.7 ms.  Three and four replicas on streams, 13 matrices of
+// 1024 rows each: with 2 ms up to 7 of them went through memory (52 -> 68 ms, 65 -> 73), from 4 ms on none.
+constexpr int tri_wait_factor(const int np_max) { return tri_on_one_die(np_max) ? 2 : 6; }
 
 // Deals the instances to launches of as many workgroups as can be resident together, and to the dies where an instance fits one: the
 // largest first, each to the die with the fewest workgroups.
@@ -564,7 +568,7 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
       hipLaunchKernelGGL(init_mirror_kernel, dim3(np_max / 32, np_max / 32, n), dim3(256), 0, s, gd);
       LAUNCH_CHECK();
     }
-    const long long limit = g_fused_wait_us.load() * 100;
+    const long long limit = g_fused_wait_us.load() * 100 * tri_wait_factor(np_max);
     for (size_t l = 0; l < launch_units.size(); ++l) {
       if (tri_on_one_die(np_max))
         hipLaunchKernelGGL((init_tri_resident_kernel<8, 4>), dim3(launch_units[l]), dim3(256), 0, s, gd, (int)l, limit);
@@ -572,8 +576,12 @@ int run_init(const std::vector<PrecondCall>& calls, hipStream_t s) {
         hipLaunchKernelGGL((init_tri_resident_kernel<16, 2>), dim3(launch_units[l]), dim3(256), 0, s, gd, (int)l, limit);
       LAUNCH_CHECK();
     }
+    if (!launch_units.empty()) {   // what of it could not run at once
+      hipLaunchKernelGGL(init_tri_shared_kernel, dim3(std::min(kTriSharedUnits, tri_step_units(n_max, 0)), n), dim3(256), 3 * np_max * sizeof(double), s, gd);
+      LAUNCH_CHECK();
+    }
     for (int j = 0; !resident && j < n_max - kTriTail; ++j) {
-      const int groups = (n_max - j - 1 + 4 * kTriRows - 1) / (4 * kTriRows);
+      const int groups = tri_step_units(n_max, j);
       if (np_max <= kTriLdsCols) {
         hipLaunchKernelGGL(init_tri_step_kernel, dim3(groups, n), dim3(256), 3 * np_max * sizeof(double), s, gd, j, 3);
       } else {
@@ -1487,12 +1495,13 @@ extern "C" int ngsgd_precond_diagnostics(const ngsgd_precond* p, int32_t* flags_
   if (p == nullptr) return NGSGD_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   NG_TRY(join_side(p->sync, s));
-  int v[2] = {0, 0};
+  int v[3] = {0, 0, 0};
+  static_assert(offsetof(PrecondScalars, gate) == offsetof(PrecondScalars, flags) + 2 * sizeof(int), "copied together");
   if (p->rank > 0) {
     HIP_TRY(hipMemcpyAsync(v, &p->st->flags, sizeof(v), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
   }
-  if (flags_host != nullptr) *flags_host = v[0];
+  if (flags_host != nullptr) *flags_host = v[0] | (v[2] >= kGateClosed ? kFlagInitFromMemory : 0);
   if (sweeps_host != nullptr) *sweeps_host = v[1];
   return NGSGD_OK;
 }

@@ -14,6 +14,9 @@ constexpr int kFlagOrthCheck = 1;   // App. B.3.1: C_t was floored or ill-condit
 constexpr int kFlagFloored = 2;     // some eigenvalue of Z_t was floored
 constexpr int kFlagReorth = 4;      // the latest update re-orthogonalised W
 constexpr int kFlagNoConverge = 8;  // Jacobi hit its sweep limit
+constexpr int kFlagInitFromMemory = 16;   // (diagnostics only)
+
+constexpr int kGateWords = 4, kGateClosed = 1 << 30;   // see PrecondScalars::gate
 
 // Scalars of the factorisation F_t = R_t^T D_t R_t + rho_t I (eq. low:rank), kept in fp64 on the device.
 struct PrecondScalars {
@@ -25,6 +28,7 @@ struct PrecondScalars {
   double trace_S0;        // tr(S_0), initialisation only
   int flags;
   int sweeps;             // Jacobi sweeps used by the latest update
+  int gate[kGateWords];   // counters of the latest first factor's reduction, the first one with kGateClosed if it went through memory
   double d[kMaxRank];     // diag(D_t)
   double e[kMaxRank];     // diag(E_t) (eq. etii) for the current d, rho
 };

@@ -374,6 +374,34 @@ def test_average_replicas_on_their_own_streams(ngsgd):
             assert rel(gpu.get_params(l).cpu().numpy(), ora.W[l]) < TOL
 
 
+@pytest.mark.parametrize("rows", [200, 600])
+def test_first_factors_of_several_replicas_at_once(ngsgd, rows):
+    """Three replicas build their first factors on streams of their own: matrices that many workgroups share, of up to 512 rows
+    and above.  The weights after three steps are those of replicas stepped one after the other."""
+    import torch
+    spec = workloads.NetSpec("rows", 9, [60, 700, 640, 650], [workloads.TANH, workloads.TANH], 10, rows, 6, 20, 0.002, 3, softmax_zero_init=False,
+                             label_law="uniform", splice=1, base_dim=60)
+    finals = []
+    for at_once in (False, True):
+        nets = [make_pair(ngsgd, spec, max_change=0.075, side_streams=1)[1] for _ in range(3)]
+        streams = [torch.cuda.Stream() for _ in nets]
+        data = [[tuple(torch.from_numpy(a).cuda() for a in workloads.minibatch(spec, t, replica=r)) for t in range(3)] for r in range(3)]
+        torch.cuda.synchronize()
+        for t in range(3):
+            for r, net in enumerate(nets):
+                net.step(*data[r][t], spec.lr, stream=streams[r])
+                if not at_once:
+                    torch.cuda.synchronize()
+        for net, s in zip(nets, streams):
+            net.join(s)
+        torch.cuda.synchronize()
+        finals.append([net.get_params(l).cpu().numpy() for net in nets for l in range(spec.n_layers)])
+    start = workloads.initial_weights(spec)
+    for i, (a, b) in enumerate(zip(*finals)):
+        moved = np.linalg.norm(np.asarray(b, np.float64) - start[i % spec.n_layers])
+        assert np.linalg.norm(a.astype(np.float64) - b) < TOL * moved
+
+
 def back_to_back_equals_synchronised(ngsgd, side_streams):
     import torch
     spec = workloads.small_pnorm()

@@ -6,6 +6,8 @@ action X -> X - X W^T W on a probe.
 """
 import math
 
+import time
+
 import numpy as np
 import pytest
 
@@ -153,25 +155,34 @@ def test_initial_factor(ngsgd, N, D, R):
 
 @pytest.mark.parametrize("N,D,R", [(161, 160, 33), (161, 170, 9), (192, 500, 80), (513, 520, 20), (700, 600, 90), (1024, 1030, 16)])
 def test_initial_factor_without_waiting(ngsgd, N, D, R):
-    """With no time to wait, the workgroups that share a matrix leave it as it is, and the kernel behind reduces it alone (no
-    column, one column, and more; matrices of up to and above 512 rows).  The same once more with time."""
+    """With no time to wait, the workgroups that share a matrix leave it as it is, and the kernel behind reduces it from memory (no
+    column, one column, and more; matrices of up to and above 512 rows).  The same once more with time.  A flag tells which way
+    a matrix went: up to 160 rows there is but one.  And it is quick: with one workgroup for a matrix it took some
+    hundred milliseconds."""
     import torch
     rng = np.random.default_rng(78 + N + 3 * D)
     ora = OnlineNaturalGradient(D, R, num_samples_history=500.0, update_period=1)
     M = data(rng, N, D, decay=0.985)
     expect, g_o, rn_o = ora.precondition(M)
     pre = ngsgd.Preconditioner(D, R, max_batch=N, num_samples_history=500.0, update_period=1)
-    for wait_us in (0, 2000):
+    for wait_us in (0, 2000, 0):
         pre.reset()
         ngsgd.set_wait_limit_us(wait_us)
         try:
             print(f"initial factor N={N} D={D} R={R} wait_us={wait_us}", flush=True)
+            torch.cuda.synchronize()
+            begin = time.perf_counter()
             got, g_g, rn_g = gpu_call(torch, pre, M)
+            torch.cuda.synchronize()
+            took = time.perf_counter() - begin
         finally:
             ngsgd.set_wait_limit_us(2000)
         assert rel(got, expect) < 1e-5      # as test_initial_factor
         assert g_g == pytest.approx(g_o, rel=1e-5)
         assert rel(rn_g, rn_o) < 2e-5
+        assert bool(pre.diagnostics()[0] & 16) == (wait_us == 0 and min(N, D) > 160)
+        print(f"took {took * 1e3:.1f} ms", flush=True)
+    assert took < 0.1      # 1024 rows take 12 ms, the transfers of M among them
 
 
 @pytest.mark.parametrize("first,second", [(300, 201), (201, 300), (130, 70), (161, 159)])
