@@ -323,21 +323,23 @@ __global__ __launch_bounds__(256) void simple_sweep_kernel(const SimpleGroup g, 
 }
 
 // a_i = x_i . q_i, b_i = 1 + a_i / (N - 1 - a_i), xhat_i = b_i q_i (App. A.3), ||xhat_i||^2.  With LATE b_i goes to the elimination's
-// first buffer (done with by then) and xhat_i is left to the kernel that scales.  A row's first 5120 columns are requested at once and stay in
-// registers.  Grid (N_max, count).
+// first buffer (done with by then) and xhat_i is left to the kernel that scales; a row's first 5120 columns are then requested at once
+// (512 x 5000: 9.4 -> 5.5 us).  The matrices of a network fill the chip with rows, and the registers of that would cost them more wavefronts than
+// it gives: eight matrices of 512 rows and 60 to 901 columns 14.6 instead of 11.7 us, twelve of 700 rows and 200 to 1000 columns 21.5 instead of
+// 17.1 (the speech-shaped network's ten 22 either way).  Grid (N_max, count).
 template <bool LATE>
 __global__ __launch_bounds__(256) void simple_rows_kernel(const SimpleGroup g) {
   const SimpleArgs& a = g.a[blockIdx.y];
   const int i = blockIdx.x;
   if (i >= a.N) return;
-  constexpr int AHEAD = 5;
+  constexpr int AHEAD = LATE ? 5 : 0;
   __shared__ double scratch[16];
   const int tid = threadIdx.x, D = a.D, D4 = D >> 2;
   float* __restrict__ x = a.M + (size_t)i * a.ld;           // rows start on 16-byte boundaries
   const float* __restrict__ q = a.Q + (size_t)i * a.ldq;
   float4* __restrict__ x4 = reinterpret_cast<float4*>(x);
   const float4* __restrict__ q4 = reinterpret_cast<const float4*>(q);
-  float4 xr[AHEAD], qr[AHEAD];
+  float4 xr[LATE ? AHEAD : 1], qr[LATE ? AHEAD : 1];
 #pragma unroll
   for (int u = 0; u < AHEAD; ++u) {
     const int c = min(tid + 256 * u, max(D4 - 1, 0));
@@ -361,17 +363,17 @@ __global__ __launch_bounds__(256) void simple_rows_kernel(const SimpleGroup g) {
   dot = block_sum(dot, scratch);
   qq = block_sum(qq, scratch);
   const double b = 1.0 + dot / ((double)(a.N - 1) - dot);
+  if (!LATE) {
+    for (int c = tid; c < D4; c += 256) {
+      const float4 qv = q4[c];
+      x4[c] = make_float4((float)(b * qv.x), (float)(b * qv.y), (float)(b * qv.z), (float)(b * qv.w));
+    }
+    for (int c = 4 * D4 + tid; c < D; c += 256) x[c] = (float)(b * (double)q[c]);
+  }
   if (tid == 0) {
     a.prow[i] = b * b * qq;
     if (LATE) a.buf[0][i] = b;
   }
-  if (LATE) return;
-  auto scaled = [&](const float4& v) { return make_float4((float)(b * v.x), (float)(b * v.y), (float)(b * v.z), (float)(b * v.w)); };
-#pragma unroll
-  for (int u = 0; u < AHEAD; ++u)
-    if (tid + 256 * u < D4) x4[tid + 256 * u] = scaled(qr[u]);
-  for (int c = tid + 256 * AHEAD; c < D4; c += 256) x4[c] = scaled(q4[c]);
-  for (int c = 4 * D4 + tid; c < D; c += 256) x[c] = (float)(b * (double)q[c]);
 }
 
 // gamma as below by every workgroup, and gamma Xhat from Q and what simple_rows_kernel<true> left: X is written once (a launch each for
