@@ -111,7 +111,7 @@ void prof_place() {
     g_prof.used += 2;
 }
 
-constexpr int kSumsqMax = 1024;   // partial sums of squares per preconditioner call
+constexpr int kSumsqMax = 1024;   // partial sums of squares per preconditioner call of up to 65536 rows
 constexpr int kWideRow = 2048;    // rows at least this wide get 512-thread workgroups in the row-wise kernels
 constexpr int kTargetBlocks = 512;
 
@@ -224,7 +224,7 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.max_col_tiles = (D + 63) / 64;
   p.rownorm_part = c.take<float>((size_t)p.max_col_tiles * NB);
   p.hat_part = c.take<double>((size_t)p.max_col_tiles * ((NB + 63) / 64));   // (the fused kernel's patches are larger than 64 x 64)
-  p.sumsq_part = c.take<double>(kSumsqMax);
+  p.sumsq_part = c.take<double>(std::max(kSumsqMax, (NB + 63) / 64));   // (the H product leaves one per 64 rows at least)
   p.deferred = c.take<int>(kSumsqMax);
   p.n_init_max = NB < D ? NB : D;
   const size_t np_init = align_up(p.n_init_max, kInitPad), rq = align_up(R, 16);

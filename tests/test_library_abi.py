@@ -61,6 +61,19 @@ def test_precond_workspace_sizing_and_argument_errors(lib):
     assert lib.ngsgd_precondition(None, None, 1, 4, None, None, None) == ng.NGSGD_EINVAL
 
 
+def test_precond_workspace_of_very_many_rows(lib):
+    """What grows with the rows, each piece rounded up to 256 bytes: per row a double, H and a float per 64 columns; per 64 rows a
+    double for every 64 columns, one for the sum of squares (1024 of them at least) and a counter."""
+    dim, rank, rank_class, rows = 40, 33, 80, (65536, 131328, 262144)
+    n = c_size_t(0)
+    sizes = []
+    for r in rows:
+        assert lib.ngsgd_precond_workspace_bytes(dim, rank, r, byref(n)) == 0
+        sizes.append(n.value)
+    for a, b, more in zip(sizes, sizes[1:], [y - x for x, y in zip(rows, rows[1:])]):
+        assert b - a >= more * (8 + 4 * rank_class + 4) + more // 64 * (8 + 8 + 4) - 6 * 256
+
+
 def test_simple_method_sizing_and_argument_errors(lib):
     n = c_size_t(0)
     assert lib.ngsgd_simple_workspace_bytes(512, 5000, byref(n)) == 0
