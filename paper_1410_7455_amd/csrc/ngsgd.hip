@@ -280,7 +280,7 @@ template <int K, int ITEMS>
 hipError_t launch_eig(const SmallGroup& g, const int n, const int r_max, const Beside* beside, hipStream_t s) {
   if (beside != nullptr) {
     hipLaunchKernelGGL((eig_reduce_kernel<K, true>), dim3(kBesideFirst + beside->xhat_blocks()), dim3(kEigReduceThreads), 0, s, g, *beside);
-    hipLaunchKernelGGL((eig_pairs_kernel<K, true>), dim3(1, (r_max + 3) / 4 + Beside::row_blocks(beside->finish.N)), dim3(256), 0, s, g, *beside);
+    hipLaunchKernelGGL((eig_pairs_kernel<K, true>), dim3((r_max + 3) / 4 + Beside::row_blocks(beside->finish.N)), dim3(256), 0, s, g, *beside);
   } else {
     const size_t reserve = r_max >= kEigReserveFromRank ? kEigReduceReserve<K> : 0;
     hipLaunchKernelGGL((eig_reduce_kernel<K, false>), dim3(n), dim3(kEigReduceThreads), reserve, s, g, Beside());

@@ -561,13 +561,15 @@ __global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const Sma
   }
 }
 
-// Second kernel: four eigenpairs per workgroup of 256 threads.  Grid (instance, ceil(R / 4)).
+// Second kernel: four eigenpairs per workgroup of 256 threads.  Grid (instance, ceil(R / 4)); beside them, of the one instance, all in the
+// first extent, which holds any number of rows.
 template <int K, bool BESIDE>
 __global__ __launch_bounds__(256) void eig_pairs_kernel(const SmallGroup g, const Beside beside) {
+  const int instance = BESIDE ? 0 : blockIdx.x, block = BESIDE ? blockIdx.x : blockIdx.y;
   if constexpr (BESIDE) {
     const int pairs = (g.a[0].R + 3) / 4;
-    if ((int)blockIdx.y >= pairs) {
-      finish_rows<true>(beside.finish, (int)blockIdx.y - pairs);
+    if (block >= pairs) {
+      finish_rows<true>(beside.finish, block - pairs);
       return;
     }
   }
@@ -576,9 +578,9 @@ __global__ __launch_bounds__(256) void eig_pairs_kernel(const SmallGroup g, cons
   __shared__ DirectTridiagonal<K> t;
   __shared__ double s_tau[T], s_work[4][kDirectWork<K>], s_g[T / 4][6];
   __shared__ __attribute__((aligned(16))) double s_V[T * T];
-  const SmallArgs& a = g.a[blockIdx.x];
+  const SmallArgs& a = g.a[instance];
   const int R = a.R, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if ((int)blockIdx.y * 4 >= R) return;
+  if (block * 4 >= R) return;
   if (tid < T) {
     t.diag[tid] = tid < R ? a.diag(T)[tid] : 0.0;
     t.off[tid] = tid < R - 1 ? a.off(T)[tid] : 0.0;
@@ -592,7 +594,7 @@ __global__ __launch_bounds__(256) void eig_pairs_kernel(const SmallGroup g, cons
   direct_block_products<K, 256>(s_V, T, R, s_g);
   double lo, hi, norm, x[K], lambda, residual;
   direct_scale<K>(t, R, lo, hi, norm);   // ends with a barrier
-  const int k = blockIdx.y * 4 + wave;
+  const int k = block * 4 + wave;
   if (k >= R) return;   // uniform over the wavefront
   direct_pair<K, 64>(t, R, k, lo, hi, s_V, T, s_tau, s_g, s_work[wave], x, lambda, residual);
   if (group16_index() == 0) {

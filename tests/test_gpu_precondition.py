@@ -116,6 +116,27 @@ def test_updates_at_the_edges_of_the_new_factor(ngsgd, N, D, R):
     compare_states(torch, pre, ora, rng)
 
 
+@pytest.mark.parametrize("R", [20, 33])
+def test_updates_with_very_many_rows(ngsgd, R):
+    """More workgroups for the output's rows than a grid's second and third extent hold (65535), beside the eigenpairs and the new factor."""
+    import torch
+    N, D = 131200, 40
+    rng = np.random.default_rng(4000 + R)
+    kw = dict(num_samples_history=400000.0, update_period=1)
+    ora = OnlineNaturalGradient(D, R, **kw)
+    ora.precondition(data(rng, 200, D))
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, **kw)
+    upload_state(torch, pre, ora)
+    for step in range(2):
+        M = data(rng, N, D)
+        expect, g_o, rn_o = ora.precondition(M)
+        got, g_g, rn_g = gpu_call(torch, pre, M)
+        assert rel(got, expect) < TOL, f"step {step}"
+        assert g_g == pytest.approx(g_o, rel=1e-4)
+        assert rel(rn_g, rn_o) < 2e-4      # the square of a quantity held to 1e-4
+    compare_states(torch, pre, ora, rng)
+
+
 @pytest.mark.parametrize("N,D,R", [(128, 301, 20), (96, 700, 40), (257, 64, 8), (80, 80, 12)])
 def test_free_running_from_device_initialisation(ngsgd, N, D, R):
     """Both sides build their state from the first minibatch (App. B.3.2) and then run the paper's schedule."""
