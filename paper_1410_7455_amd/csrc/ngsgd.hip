@@ -1496,9 +1496,9 @@ extern "C" int ngsgd_precond_diagnostics(const ngsgd_precond* p, int32_t* flags_
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   NG_TRY(join_side(p->sync, s));
   int v[3] = {0, 0, 0};
-  static_assert(offsetof(PrecondScalars, gate) == offsetof(PrecondScalars, flags) + 2 * sizeof(int), "copied together");
   if (p->rank > 0) {
-    HIP_TRY(hipMemcpyAsync(v, &p->st->flags, sizeof(v), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(v, &p->st->flags, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(v + 2, p->st->gate, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
   }
   if (flags_host != nullptr) *flags_host = v[0] | (v[2] >= kGateClosed ? kFlagInitFromMemory : 0);

@@ -28,9 +28,9 @@ struct PrecondScalars {
   double trace_S0;        // tr(S_0), initialisation only
   int flags;
   int sweeps;             // Jacobi sweeps used by the latest update
-  int gate[kGateWords];   // counters of the latest first factor's reduction, the first one with kGateClosed if it went through memory
   double d[kMaxRank];     // diag(D_t)
   double e[kMaxRank];     // diag(E_t) (eq. etii) for the current d, rho
+  int gate[kGateWords];   // counters of the latest first factor's reduction, the first one with kGateClosed if it went through memory
 };
 
 }  // namespace ngsgd
