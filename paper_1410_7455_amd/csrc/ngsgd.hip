@@ -7,7 +7,6 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
-#include <cstddef>
 #include <cstdint>
 #include <cstring>
 #include <new>
@@ -283,14 +282,14 @@ hipError_t launch_eig(const SmallGroup& g, const int n, const int r_max, const B
     hipLaunchKernelGGL((eig_pairs_kernel<K, true>), dim3((r_max + 3) / 4 + Beside::row_blocks(beside->finish.N)), dim3(256), 0, s, g, *beside);
   } else {
     const size_t reserve = r_max >= kEigReserveFromRank ? kEigReduceReserve<K> : 0;
-    hipLaunchKernelGGL((eig_reduce_kernel<K, false>), dim3(n), dim3(kEigReduceThreads), reserve, s, g, Beside());
-    hipLaunchKernelGGL((eig_pairs_kernel<K, false>), dim3(n, (r_max + 3) / 4), dim3(256), 0, s, g, Beside());
+    hipLaunchKernelGGL((eig_reduce_kernel<K, false>), dim3(n), dim3(kEigReduceThreads), reserve, s, g, NothingBeside());
+    hipLaunchKernelGGL((eig_pairs_kernel<K, false>), dim3(n, (r_max + 3) / 4), dim3(256), 0, s, g, NothingBeside());
   }
   const int half = (r_max + 1) / 2;
   const size_t jacobi = (size_t)2 * 4 * (half * (half + 1) / 2) * sizeof(double);   // two copies of four planes of 2 x 2 blocks
   const size_t direct = (size_t)(DirectShape<K>::T + 16) * DirectShape<K>::STRIDE * sizeof(double);
   hipLaunchKernelGGL((eig_finish_kernel<K, ITEMS, kEigThreads, false, false>), dim3(n, (r_max + 15) / 16), dim3(kEigThreads), std::max(jacobi, direct), s, g,
-                     Beside());
+                     NothingBeside());
   return hipGetLastError();
 }
 static_assert((kMaxRank / 2) * (kMaxRank / 2 - 1) / 2 <= 2 * (kEigThreads - 64), "2 x 2 blocks of Jacobi's off-diagonal per thread: two");
@@ -1051,7 +1050,7 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s, Beside* bes
         hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true, true>), dim3(kBesideFirst + beside->xhat_blocks()),
                            dim3(kEigSmallThreads), dyn, s, g, *beside);
       else
-        hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true, false>), dim3(n), dim3(kEigSmallThreads), dyn, s, g, Beside());
+        hipLaunchKernelGGL((eig_finish_kernel<kEigSmallRank / 16, 1, kEigSmallThreads, true, false>), dim3(n), dim3(kEigSmallThreads), dyn, s, g, NothingBeside());
       LAUNCH_CHECK();
     } else if (r_max <= 48) {
       HIP_TRY((launch_eig<3, 1>(g, n, r_max, beside, s)));

@@ -12,6 +12,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "eig_direct.h"
 #include "gemm.h"
 #include "kernels.h"
@@ -508,6 +510,9 @@ struct Beside {
   static int row_blocks(const int N) { return (N + kFinishScaleRows - 1) / kFinishScaleRows; }
   int xhat_blocks() const { return (xhat.total_tiles + kXcds - 1) / kXcds * kXcds; }
 };
+struct NothingBeside {};   // (what the other launches carry)
+template <bool BESIDE>
+using BesideArg = std::conditional_t<BESIDE, Beside, NothingBeside>;
 // 256 threads; block counts from the first workgroup beside.
 __device__ __forceinline__ void beside_products(const Beside& b, const int block) {
   const int per = (b.xhat.total_tiles + kXcds - 1) / kXcds, unit = block % kXcds * per + block / kXcds;
@@ -521,7 +526,7 @@ __device__ __forceinline__ void store_bt_factors(const SmallArgs& a, const Updat
 
 // Above rank 32, first kernel: Z_t and its reduction.  A workgroup per instance.
 template <int K, bool BESIDE>
-__global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const SmallGroup g, const Beside beside) {
+__global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const SmallGroup g, const BesideArg<BESIDE> beside) {
   if constexpr (BESIDE) {
     if ((int)blockIdx.x >= kBesideFirst) {
       beside_products(beside, (int)blockIdx.x - kBesideFirst);
@@ -564,7 +569,7 @@ __global__ __launch_bounds__(kEigReduceThreads) void eig_reduce_kernel(const Sma
 // Second kernel: four eigenpairs per workgroup of 256 threads.  Grid (instance, ceil(R / 4)); beside them, of the one instance, all in the
 // first extent, which holds any number of rows.
 template <int K, bool BESIDE>
-__global__ __launch_bounds__(256) void eig_pairs_kernel(const SmallGroup g, const Beside beside) {
+__global__ __launch_bounds__(256) void eig_pairs_kernel(const SmallGroup g, const BesideArg<BESIDE> beside) {
   const int instance = BESIDE ? 0 : blockIdx.x, block = BESIDE ? blockIdx.x : blockIdx.y;
   if constexpr (BESIDE) {
     const int pairs = (g.a[0].R + 3) / 4;
@@ -624,7 +629,7 @@ struct FusedLds<K, NT, false> {};
 // vectors, by the same arithmetic so that all decide alike, and takes its rows' share of the second product; the first one does what is left.
 // Grid (instance, FUSED ? 1 : ceil(R / 16)).
 template <int K, int ITEMS, int NT, bool FUSED, bool BESIDE>
-__global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g, const Beside beside) {
+__global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g, const BesideArg<BESIDE> beside) {
   if constexpr (BESIDE) {
     if ((int)blockIdx.x >= kBesideFirst) {
       if (threadIdx.x < 256) beside_products(beside, (int)blockIdx.x - kBesideFirst);
