@@ -191,6 +191,7 @@ struct ngsgd_precond {
   int* idx = nullptr;
   double* vwork = nullptr;
   double* direct = nullptr;       // scratch of a factor update's eigen-problem
+  float* bt = nullptr;            // factors of W_t's rows in B_t, from the eigen-problem to the new factor
   bool owned_by_net = false;
   SideSync* sync = nullptr;   // set for instances of a network
   int last_N = 0;             // rows of the latest call
@@ -235,6 +236,7 @@ void precond_layout(ngsgd_precond& p, Carver& c) {
   p.idx = c.take<int>(kMaxRank);
   p.vwork = c.take<double>((size_t)kMaxRank + D);
   p.direct = c.take<double>(direct_scratch_doubles(R));
+  p.bt = c.take<float>(R);
 }
 
 int precond_check_config(int dim, int rank, int max_batch, float alpha, float S, float eps, int period, int first) {
@@ -1034,7 +1036,7 @@ int factor_begin(std::vector<PrecondCall>& to_update, hipStream_t s, Beside* bes
       a.st = p.st; a.K = p.K; a.L = p.L; a.At = p.At; a.ldat = p.ldh;
       a.R = p.rank; a.D = p.dim; a.N = p.last_N;
       a.direct = p.direct;
-      a.bt = reinterpret_cast<float*>(p.idx);   // (the initialisation is done with it)
+      a.bt = p.bt;
       a.sumsq_part = p.sumsq_part;
       a.n_sumsq = p.n_sumsq;
       r_max = std::max(r_max, p.rank);
@@ -1089,7 +1091,7 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s, const Besi
       for (int i = 0; i < n; ++i) {
         const ngsgd_precond& p = *to_update[done + i].p;
         if (p.ldh != rc) continue;
-        f.a[f.count++] = NewFactorArgs{p.st, p.At, reinterpret_cast<const float*>(p.idx), p.J, p.W, p.K, p.ldh, p.ldw, p.rank, p.dim, f.total};
+        f.a[f.count++] = NewFactorArgs{p.st, p.At, p.bt, p.J, p.W, p.K, p.ldh, p.ldw, p.rank, p.dim, f.total};
         f.total += (p.dim + 63) / 64;
       }
       if (f.count == 0) continue;
