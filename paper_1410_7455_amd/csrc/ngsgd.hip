@@ -1159,13 +1159,25 @@ int factor_finish(std::vector<PrecondCall>& to_update, hipStream_t s, const Besi
   return NGSGD_OK;
 }
 
+// Largest Xhat, in tiles of 64 x 64, that goes beside the eigen-problem.  The LDS of the eigen-problem's kernels leaves a compute unit three
+// workgroups for it above rank 48 and two above 80, and the eigen-problem is soon the shorter part.  Time of an updating call without / with:
+//   above 48: 2048 x 6000 (3008 tiles) 1.15 - 1.18, 4096 x 5000 (5056) 1.04 - 1.11, 2048 x 12000 (6016) 1.00 - 1.07, 15000 x 2000 (7520) 0.94 - 1.01,
+//             30000 x 1000 (7504) 0.88 - 0.97, 8192 x 5000 (10112) 0.91 - 0.97, 65000 x 5000 (80264) 0.66 - 0.70;
+//   up to 32: 12000 x 5000 (14852) 1.01 - 1.04, 16384 x 5000 (20224) 1.00 - 1.02, 65000 x 5000 0.97; 33 to 48: 1.01 - 1.02 there.
+int beside_tiles(const int rank) { return rank <= kEigSmallRank ? 16384 : (rank <= 48 ? INT32_MAX : 6144); }
+
 // Both phases for one list of instances on one stream.
 int precondition_many(std::vector<PrecondCall>& calls, bool scale_output, hipStream_t s) {
   NG_TRY(ensure_kernel_attributes());
   NG_TRY(precond_validate(calls));
   std::vector<PrecondCall> to_update;
   Beside beside = {};
-  Beside* const alone = calls.size() == 1 && scale_output ? &beside : nullptr;
+  Beside* alone = nullptr;
+  if (calls.size() == 1 && scale_output) {
+    const ngsgd_precond& p = *calls[0].p;
+    const long long tiles = (long long)((calls[0].N + 63) / 64) * ((p.dim + 63) / 64);
+    if (tiles <= beside_tiles(p.rank)) alone = &beside;
+  }
   NG_TRY(precond_apply(calls, scale_output, s, to_update, false, true, true, alone));
   NG_TRY(factor_begin(to_update, s, alone));
   NG_TRY(factor_finish(to_update, s, alone));

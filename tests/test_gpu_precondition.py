@@ -137,6 +137,33 @@ def test_updates_with_very_many_rows(ngsgd, R):
     compare_states(torch, pre, ora, rng)
 
 
+@pytest.mark.parametrize("N,D,R,beside", [(4096, 6144, 49, True), (4100, 6144, 49, False), (4100, 6144, 48, True)])
+def test_updates_of_large_matrices(ngsgd, N, D, R, beside):
+    """Above rank 48 the output of more than 6144 tiles is not formed beside the eigen-problem, which would hold it up.  A launch of
+    its own is a group of its own in the profile."""
+    import torch
+    rng = np.random.default_rng(5000 + N + R)
+    kw = dict(num_samples_history=20000.0, update_period=1)
+    ora = OnlineNaturalGradient(D, R, **kw)
+    ora.precondition(data(rng, 200, D))
+    pre = ngsgd.Preconditioner(D, R, max_batch=N, **kw)
+    upload_state(torch, pre, ora)
+    M = data(rng, N, D)
+    expect, g_o, rn_o = ora.precondition(M)
+    ngsgd.profile_enable(True)
+    try:
+        ngsgd.profile_read()
+        got, g_g, rn_g = gpu_call(torch, pre, M)
+        groups = ngsgd.profile_read()["precond_xhat"][1]
+    finally:
+        ngsgd.profile_enable(False)
+    assert groups == (0 if beside else 1)
+    assert rel(got, expect) < TOL
+    assert g_g == pytest.approx(g_o, rel=1e-4)
+    assert rel(rn_g, rn_o) < 2e-4      # the square of a quantity held to 1e-4
+    compare_states(torch, pre, ora, rng)
+
+
 @pytest.mark.parametrize("N,D,R", [(128, 301, 20), (96, 700, 40), (257, 64, 8), (80, 80, 12)])
 def test_free_running_from_device_initialisation(ngsgd, N, D, R):
     """Both sides build their state from the first minibatch (App. B.3.2) and then run the paper's schedule."""
