@@ -908,7 +908,8 @@ __global__ __launch_bounds__(NT) void eig_finish_kernel(const SmallGroup g, cons
 // 1e-3, W <- E^{1/2} L^{-1} E^{-1/2} W with O = L L^T.  Runs only when the update asked for the check.
 struct OrthArgs {
   PrecondScalars* st;
-  double* G;         // R x R, W W^T of the new factor (accumulated only when the check was requested); cleared on exit
+  double* G;         // R x R, W W^T of the new factor (accumulated only when the check was requested), its 16 x 16 tiles on and
+                     // above the diagonal; cleared on exit
   float* At;         // R x R (ldat): A_t on entry; when the fix is needed, E^{1/2} L^{-1} E^{-1/2} A_t on return
   int ldat;
   int R;
@@ -967,7 +968,13 @@ __global__ __launch_bounds__(kSmallThreads) void orth_fix_kernel(const OrthGroup
   // the check: G and E through LDS (coalesced reads), O symmetrised from there
   double* const Gs = dyn;   // R x (R + 1)
   const int SG = R + 1;
-  for (int idx = tid; idx < R * R; idx += nt) Gs[(idx / R) * SG + idx % R] = a.G[idx];
+  for (int idx = tid; idx < R * R; idx += nt) {
+    const int r = idx / R, c = idx % R;
+    if (r / 16 > c / 16) continue;
+    const double v = a.G[idx];
+    Gs[r * SG + c] = v;
+    if (r / 16 < c / 16) Gs[c * SG + r] = v;
+  }
   for (int k = tid; k < R; k += nt) s_ise[k] = rsqrt(st->e[k]);
   __syncthreads();
   double dev = 0.0;
@@ -1090,8 +1097,9 @@ __global__ __launch_bounds__(kSmallThreads) void orth_fix_kernel(const OrthGroup
 // W_{t+1} = A_t B_t with B_t = J_t + (its factors) W_t (eq. wt1), and for the instances whose update asked for the orthogonality check
 // (App. B.3.1) W W^T of the new factor, added to K in fp64, and B_t over J, for the second product if the check fails.  A workgroup
 // takes all rows of 64 columns, so it alone reads the columns of W_t that it replaces; a wavefront has 16 of them in registers.
-// Bound: latency.  As three launches (B_t, the product, the gated Gram matrix of its own) the chain behind the eigen-problem was
-// two launches longer.
+// Bound: latency, above rank 80 with many columns the atomic additions of W W^T (all its tiles instead of those on and above the diagonal:
+// 5000 columns rank 80 / 96 15.2 / 19.4 us instead of 13.6 / 17.1, 50000 columns 63.6 / 86.9 instead of 55.8 / 75.6).  As three launches
+// (B_t, the product, the gated Gram matrix of its own) 22 / 25 and 64 / 72 us and two gaps of some 2 us.
 struct NewFactorArgs {
   const PrecondScalars* st;
   const float* At;
@@ -1174,6 +1182,7 @@ __device__ __forceinline__ void new_factor_unit(const NewFactorArgs& a, const in
   __syncthreads();
   for (int tile = wave; tile < TJ * TJ; tile += 4) {
     const int i0 = tile / TJ * 16, j0 = tile % TJ * 16;
+    if (i0 > j0) continue;   // (uniform)
     doublex4 c = {0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 64; k += 4)
