@@ -1226,6 +1226,8 @@ struct SimpleCall {
   float* rownorm2_out;   // optional
 };
 
+constexpr long long kSimpleLateColumns = 8192, kSimpleLatePerRow = 160;   // longest rows whose scaled output is written once
+
 // Enqueues the simple method for a list of independent matrices; every stage is one grouped launch.  With
 // scale_output the matrices are left as gamma * Xhat, without it as Xhat with gamma in *gamma.
 int simple_many(const std::vector<SimpleCall>& calls, bool scale_output, hipStream_t s) {
@@ -1316,9 +1318,13 @@ int simple_many(const std::vector<SimpleCall>& calls, bool scale_output, hipStre
       }
       if (!rows.empty()) NG_TRY(launch_layer_gemms(GEMM_BWD, rows.data(), (int)rows.size(), s));
       if (!cols.empty()) NG_TRY(launch_layer_gemms(GEMM_FWD, cols.data(), (int)cols.size(), s));
-      // the scaled output in one go where the elimination's buffer holds a number per row (of a tall, very narrow matrix it does not)
+      // The scaled output in one go where the elimination's buffer holds a number per row (of a tall, very narrow matrix it does not) and
+      // the rows are not few and long, which leaves most of the chip to the one launch that scales with a workgroup per two rows.
+      // Written twice / once: 16 x 8000 49.2 / 47.8 us a call, 12000 50.7 / 51.7, 80000 100 / 130; 64 x 8000 62.1 / 60.3, 20000 76.3 / 78.6;
+      // 128 x 20000 109.7 / 108.9, 40000 141 / 146; 256 x 40000 246.1 / 244.3, 80000 417 / 420; 512 x 80000 1155 / 1149.
       bool late = scale_output;
-      for (int i = 0; i < cnt; ++i) late = late && (size_t)g.a[i].N <= (size_t)g.a[i].np * g.a[i].np;
+      for (int i = 0; i < cnt; ++i)
+        late = late && (size_t)g.a[i].N <= (size_t)g.a[i].np * g.a[i].np && g.a[i].D <= std::max(kSimpleLateColumns, kSimpleLatePerRow * (long long)g.a[i].N);
       if (late) {
         hipLaunchKernelGGL(simple_rows_kernel<true>, dim3(n_max, cnt), dim3(256), 0, s, g);
         LAUNCH_CHECK();

@@ -57,10 +57,12 @@ def test_small_shapes_match_the_definition(ngsgd, N, D):
     assert abs(np.linalg.norm(got.astype(np.float64)) / np.linalg.norm(M.astype(np.float64)) - 1.0) < 1e-5
 
 
-@pytest.mark.parametrize("N,D", [(5, 1), (6, 3), (1024, 2), (1025, 2), (33, 5119), (34, 5121), (7, 5130)])
+@pytest.mark.parametrize("N,D", [(5, 1), (6, 3), (1024, 2), (1025, 2), (33, 5119), (34, 5121), (7, 5130), (9, 8191), (9, 8193),
+                                 (52, 8320), (52, 8321)])
 def test_scaled_output_at_the_edges_of_its_pieces(ngsgd, N, D):
     """Rows shorter than a piece of four, rows of what a workgroup keeps in registers and a little more, an odd last row; the most
-    rows of a narrow matrix whose elimination buffer (32 x 32) still holds a number per row, and one more."""
+    rows of a narrow matrix whose elimination buffer (32 x 32) still holds a number per row, and one more; the longest rows that are written
+    once, 8192 columns or 160 per row, and longer ones."""
     import torch
     rng = np.random.default_rng(1500 + N + D)
     M = data(rng, N, D, decay=0.9995)
