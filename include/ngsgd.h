@@ -238,7 +238,10 @@ int ngsgd_last_max_change_scale(ngsgd_net* net, int32_t layer, double* dev_out, 
  * n_categories >= NGSGD_PROF_CATEGORIES entries, host memory) and clears the record.  Process-wide,
  * not thread-safe; at most 32768 groups are kept between reads (one whose work another group's kernel does is
  * not counted, but takes a place): if more were launched the call still
- * fills the arrays with what was kept and returns NGSGD_ENOMEM. */
+ * fills the arrays with what was kept and returns NGSGD_ENOMEM.
+ * An updating ngsgd_precondition forms Xhat and finishes its output beside the R x R update and, up to rank 32,
+ * the new factor: both are then in the time of those groups, and PRECOND_XHAT stays empty (large matrices aside).
+ * So is B_t, and the check's W W^T, in that of W_{t+1}. */
 #define NGSGD_PROF_GEMM_FWD 0        /* A_l = [X_l, 1] W_l^T, tanh                               */
 #define NGSGD_PROF_GEMM_BWD 1        /* dX_l = O_l W_l, mostly with the derivative of tanh       */
 #define NGSGD_PROF_GEMM_UPD 2        /* W_l += lr a_l Obar_l^T Xbar_l, max-change (one launch)   */
@@ -247,9 +250,9 @@ int ngsgd_last_max_change_scale(ngsgd_net* net, int32_t layer, double* dev_out, 
 #define NGSGD_PROF_PRECOND_XHAT 5    /* Xhat = X - H W and row norms                             */
 #define NGSGD_PROF_PRECOND_KL 6      /* K = J J^T, L = H^T H                                     */
 #define NGSGD_PROF_PRECOND_SMALL 7   /* R x R update: Z_t, eigen-decomposition, A_t              */
-#define NGSGD_PROF_PRECOND_WNEW 8    /* W_{t+1} = A_t B_t                                        */
+#define NGSGD_PROF_PRECOND_WNEW 8    /* B_t, W_{t+1} = A_t B_t                                   */
 #define NGSGD_PROF_ELEMENTWISE 9     /* nonlinearities behind no product, log-softmax            */
-#define NGSGD_PROF_PRECOND_MISC 10   /* clears, gamma, B_t, orthogonality check, rescale         */
+#define NGSGD_PROF_PRECOND_MISC 10   /* clears, gamma, orthogonality check, rescale              */
 #define NGSGD_PROF_INIT 11           /* state initialisation from the first minibatch            */
 #define NGSGD_PROF_SIMPLE_GRAM 12    /* simple method: X^T X or X X^T                            */
 #define NGSGD_PROF_SIMPLE_INVERSE 13 /* simple method: (beta I + Gram / (N-1))^{-1}              */
