@@ -374,10 +374,11 @@ def test_average_replicas_on_their_own_streams(ngsgd):
             assert rel(gpu.get_params(l).cpu().numpy(), ora.W[l]) < TOL
 
 
-@pytest.mark.parametrize("rows", [200, 600])
-def test_first_factors_of_several_replicas_at_once(ngsgd, rows):
+@pytest.mark.parametrize("rows,wait_us", [(200, 2000), (600, 2000), (200, 0), (600, 0)])
+def test_first_factors_of_several_replicas_at_once(ngsgd, rows, wait_us):
     """Three replicas build their first factors on streams of their own: matrices that many workgroups share, of up to 512 rows
-    and above.  The weights after three steps are those of replicas stepped one after the other."""
+    and above; without time to wait, all of them from memory.  The weights after three steps are those of replicas stepped one after the
+    other."""
     import torch
     spec = workloads.NetSpec("rows", 9, [60, 700, 640, 650], [workloads.TANH, workloads.TANH], 10, rows, 6, 20, 0.002, 3, softmax_zero_init=False,
                              label_law="uniform", splice=1, base_dim=60)
@@ -387,14 +388,22 @@ def test_first_factors_of_several_replicas_at_once(ngsgd, rows):
         streams = [torch.cuda.Stream() for _ in nets]
         data = [[tuple(torch.from_numpy(a).cuda() for a in workloads.minibatch(spec, t, replica=r)) for t in range(3)] for r in range(3)]
         torch.cuda.synchronize()
-        for t in range(3):
-            for r, net in enumerate(nets):
-                net.step(*data[r][t], spec.lr, stream=streams[r])
-                if not at_once:
-                    torch.cuda.synchronize()
-        for net, s in zip(nets, streams):
-            net.join(s)
-        torch.cuda.synchronize()
+        ngsgd.set_wait_limit_us(wait_us if at_once else 2000)
+        try:
+            for t in range(3):
+                for r, net in enumerate(nets):
+                    net.step(*data[r][t], spec.lr, stream=streams[r])
+                    if not at_once:
+                        torch.cuda.synchronize()
+            for net, s in zip(nets, streams):
+                net.join(s)
+            torch.cuda.synchronize()
+        finally:
+            ngsgd.set_wait_limit_us(2000)
+        if at_once and wait_us == 0:
+            for net in nets:   # (the first layer's input has 61 columns)
+                ways = [bool(net.precond(l, side).diagnostics()[0] & 16) for l in range(spec.n_layers) for side in (0, 1)]
+                assert ways == [False] + [True] * (len(ways) - 1)
         finals.append([net.get_params(l).cpu().numpy() for net in nets for l in range(spec.n_layers)])
     start = workloads.initial_weights(spec)
     for i, (a, b) in enumerate(zip(*finals)):
