@@ -487,6 +487,8 @@ __global__ __launch_bounds__(256, 2) void init_tri_resident_kernel(const InitGro
 // its die holds of the others' is dropped before it begins the next.
 // Bound: that exchange, as for the launches: 512 rows 3.27 ms a call, 1024 rows 10.97 (a launch per column 3.37 and 10.2, rows kept
 // on the chip 1.86 and 5.2).  By one workgroup a network's first factors of 1024 rows took 0.65 s.  With all gates open 4.5 us.
+// All 13 of them and the smaller ones from memory: 44.8 ms a step that restarts, instead of 21.4 (launches 23.9).  With 32 workgroups for a matrix 36 ms,
+// but one matrix of 1024 rows then 13.9; few go this way at a time.
 // Grid (units, instance), 256 threads, 3 np doubles of LDS.
 constexpr int kTriSharedUnits = 64;   // workgroups of an instance
 __global__ __launch_bounds__(256) void init_tri_shared_kernel(const InitGroup* __restrict__ gp) {
